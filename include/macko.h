@@ -256,13 +256,13 @@ MACKO_API int macko_spmv(macko_handle_t h, const void* x_dev, void* y_dev, void*
 MACKO_API int macko_dense_gemv(const void* W_dev, int64_t rows, int64_t cols, int64_t ld,
                                const void* x_dev, void* y_dev, void* stream);
 
-/* Small-batch product with one matrix (the matrix is streamed and decoded once per piece of
- * up to 8 vectors, for every code width and both value widths; rows shorter than 384
- * stored entries on average, and batches whose interleaved vectors do not fit LDS, run
- * as independent matrix-vector products instead).  From batch 8 on the kernel is bound
- * by vector arithmetic, not by memory: on the Llama2-7B shapes at 50 % sparsity the
- * vendor library's dense fp16 GEMM on the decoded matrix (macko_decode_device) is as
- * fast at batch 8 and faster beyond; this call is meant for batch 2 to 8.
+/* Small-batch product with one matrix: the matrix is streamed and decoded once for the whole
+ * batch on the matrix cores (more than 8 vectors, or 5 to 8 where the vector kernel would need
+ * several pieces; codes of up to 4 bits, ldx < 2^24), else once per piece of up to 8 vectors, for every
+ * code width and both value widths (rows shorter than 384 stored entries on average, and batches whose
+ * interleaved vectors do not fit LDS, then run as independent matrix-vector products).
+ * An infinity or a NaN in a vector reaches only the results of rows that store an entry at its column
+ * (such results are computed apart, entry by entry, which is slow).
  * Y[b][r] = sum_k values[k] * X[b][column(k)] for b < batch, 0 <= batch <= MACKO_MAX_BATCH.
  * X_dev: fp16, batch vectors of `cols` elements, vector b at X_dev + b*ldx
  * (ldx >= cols); Y_dev: fp16, vector b at Y_dev + b*ldy (ldy >= rows).  fp32

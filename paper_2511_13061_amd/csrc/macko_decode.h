@@ -174,6 +174,8 @@ struct LaneValues<16> {
   __device__ __forceinline__ float get() const {
     return f16_bits_to_f32((uint16_t)bits<K>());
   }
+  template <int K>
+  __device__ __forceinline__ uint32_t half() const { return bits<K>(); }    // fp16 bit pattern of entry K
 };
 template <>
 struct LaneValues<8> {
@@ -201,6 +203,8 @@ struct LaneValues<8> {
     const float2v p = __builtin_amdgcn_cvt_pk_f32_fp8((int)(K < 4 ? v.x : v.y), (K & 2) != 0);
     return (K & 1) ? p.y : p.x;
   }
+  template <int K>
+  __device__ __forceinline__ uint32_t half() const { return f32_to_f16_bits(get<K>()); }   // exact: E4M3 is a subset of fp16
 };
 
 

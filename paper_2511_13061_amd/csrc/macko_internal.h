@@ -78,6 +78,10 @@ constexpr int chain_error_word() { return 25 * 64; }
 // batch products with one matrix: Y[b] = W X[b], vectors ldx / ldy elements apart (p.x, p.y unused)
 int launch_spmm(const SpmvProblem& p, const void* X, int64_t ldx, void* Y, int64_t ldy, int batch,
                 hipStream_t stream);
+// the same on the matrix cores: which calls it can serve (any batch up to 64), and the launch
+bool spmm_tile_serves(const SpmvProblem& p, const void* X, int64_t ldx, int batch);
+int launch_spmm_tile(const SpmvProblem& p, const uint16_t* X, int64_t ldx, uint16_t* Y, int64_t ldy, int batch,
+                     hipStream_t stream);
 // device-side expansion: column index of every stored entry; the dense matrix back
 int launch_columns(const SpmvProblem& p, int32_t* cols_out, hipStream_t stream);
 // structural check of bound device arrays; *first_bad (device) must hold `rows` beforehand

@@ -310,7 +310,8 @@ int launch_bt(const SpmvProblem& p, const uint16_t* X, int64_t ldx, uint16_t* Y,
 
 // Y[b][r] = sum over row r of W * X[b][column], b < batch.  The batch is cut into
 // pieces of 8, 4, 2 or 1 vectors, each the largest that fits LDS; single vectors
-// (and matrices with short rows) go through the matrix-vector path.
+// (and matrices with short rows) go through the matrix-vector path; larger batches go to the
+// matrix cores in one piece (macko_spmm_tile.hip).
 int launch_spmm(const SpmvProblem& p, const void* X, int64_t ldx, void* Y, int64_t ldy, int batch,
                 hipStream_t stream) {
   if (p.pad_nnz > (int64_t{1} << 32) - 4096) return MACKO_E_UNSUPPORTED;   // 32-bit entry indices in the kernel
@@ -326,6 +327,15 @@ int launch_spmm(const SpmvProblem& p, const void* X, int64_t ldx, void* Y, int64
   const int64_t one = lds_bytes_for(p.cols, p.b_delta);
   const int64_t limit = 160 * 1024 - 64;
   const bool long_rows = p.pad_nnz / p.rows >= 384;
+  // The matrix cores serve the whole batch at one price, about that of 8 vectors here.  From 9 vectors on they
+  // win everywhere (us here -> there: 512 x 512 at 50 %, 9 vectors: 7.2 -> 5.1; 4096 x 4096: 17.8 -> 10.5; 11008 x 4096 at
+  // 90 %: 19.0 -> 15.8; 14336 x 3584 at 70 %: 29.8 -> 22.3).  From 5 to 8 one piece of 8 here is as fast or faster (2048 x 4096:
+  // 8.8 and 9.8; 11008 x 4096: 21.5 and 21.7, at 90 % 12.3 and 15.9), except where 8 vectors do not fit LDS (4096 x 11008:
+  // 27.4 -> 19.6, at 90 % 13.4 -> 13.3) and where the rows are short and there are enough of them to fill the chip with
+  // tiles (14336 x 512 at 50 %: 21.2 -> 11.8, 4096 x 4096 at 96 %: 9.0 -> 7.4; but 512 x 512: 4.1 -> 5.1).
+  if (spmm_tile_serves(p, X, ldx, batch) &&
+      (batch > 8 || (batch > 4 && (long_rows ? 8 * one > limit : p.rows >= (int64_t)device_cu_count() * 16))))
+    return launch_spmm_tile(p, Xp, ldx, Yp, ldy, batch, stream);
   int done = 0;
   while (done < batch) {
     const int left = batch - done;

@@ -1432,3 +1432,80 @@ def test_chain_under_graph_capture_replays_like_eager():
             # eager work between replays: an ordinary product and another eager chain
             assert torch.equal(eager(x)[3], want[3])
         assert M.chain_status(None) == (0, -1)
+
+
+# ------------------------------------------------------------------ batches on the matrix cores
+
+def _batch_reference(W64, X64):
+    """Y and the sums of magnitudes in 64 bits, [batch, rows]."""
+    return X64 @ W64.T, np.abs(X64) @ np.abs(W64).T
+
+
+@pytest.mark.parametrize("kind", ["b1", "b2", "b4", "fp8"])
+@pytest.mark.parametrize("rows,cols,batch", [
+    (1, 8, 9), (15, 63, 16), (16, 64, 17), (17, 65, 32), (33, 127, 33), (40, 129, 48), (31, 1000, 49), (48, 2047, 64),
+    (20, 2048, 9), (19, 2049, 16), (18, 4095, 10), (16, 4096, 15), (35, 4097, 12), (23, 4097, 64), (9, 8193, 20), (7, 12000, 7),
+    (4099, 77, 5), (4100, 300, 11), (4200, 130, 50)])
+def test_spmm_tile_edges(kind, rows, cols, batch):
+    """Tiles of 16 rows, windows of 2048 or 4096 columns, groups of 128 columns, 16 vectors per instruction: the sizes
+    around them, with empty rows, rows that start inside a chunk, values below 2^-14, strided and 2-byte aligned
+    vectors whose surroundings hold NaN."""
+    b_delta = {"b1": 1, "b2": 2, "b4": 4, "fp8": 4}[kind]
+    rng = np.random.default_rng(rows * 131 + cols * 7 + batch)
+    density = rng.choice([0.03, 0.3, 0.5, 0.9])
+    W = (rng.standard_normal((rows, cols)) * 0.02 * (rng.random((rows, cols)) < density)).astype(np.float16)
+    W[rng.random((rows, cols)) < 0.01] = np.float16(3e-6)                 # a subnormal number
+    if rows > 4:
+        W[3] = 0
+        W[-1] = 0
+    X = rng.standard_normal((batch, cols)).astype(np.float16)
+    if kind == "fp8":
+        W8 = wl.fp8_values_of(W.view(np.uint16))
+        W64 = oracle.fp8_to_double(np.arange(256, dtype=np.uint8))[W8]
+        m = M.encode_fp8(W8).to_device()
+    else:
+        W64 = W.astype(np.float64)
+        m = M.encode(W, b_delta).to_device()
+    Xbuf = torch.full((batch, cols + 3), float("nan"), dtype=torch.float16, device="cuda")
+    Xbuf[:, 1:cols + 1] = torch.from_numpy(X).cuda()
+    Ybuf = torch.full((batch, rows + 3), 7.0, dtype=torch.float16, device="cuda")
+    m.spmm(Xbuf[:, 1:cols + 1], Ybuf[:, 1:rows + 1])
+    torch.cuda.synchronize()
+    Y = Ybuf[:, 1:rows + 1].cpu().numpy().astype(np.float64)
+    ref, mag = _batch_reference(W64, X.astype(np.float64))
+    # one rounding to fp16 (relative 2^-11, or half of the smallest fp16 number) of a 32-bit sum of `cols` terms
+    bound = np.abs(ref) * 2.0 ** -11 + 2.0 ** -25 + mag * cols * 2.0 ** -24
+    worst = np.max(np.abs(Y - ref) / bound)
+    assert worst <= 1.01, (kind, rows, cols, batch, worst)
+    assert (Ybuf[:, 0] == 7).all() and (Ybuf[:, rows + 1:] == 7).all()
+
+
+@pytest.mark.parametrize("kind", ["b1", "b4", "fp8"])
+def test_spmm_tile_leaves_out_what_is_not_stored(kind):
+    """An infinity or a NaN of a vector reaches the rows that store an entry at its column and no others; one of the
+    matrix stays in its row.  Reference: the stored entries (padding included) one by one in 64 bits."""
+    rng = np.random.default_rng(5)
+    rows, cols, batch = 50, 2300, 34
+    W = (rng.standard_normal((rows, cols)) * (rng.random((rows, cols)) < 0.5)).astype(np.float16)
+    X = rng.standard_normal((batch, cols)).astype(np.float16)
+    X[2, 100] = np.inf
+    X[17, 2299] = np.nan
+    X[33, 0] = -np.inf
+    if kind == "fp8":
+        m = M.encode_fp8(wl.fp8_values_of(W.view(np.uint16))).to_device()
+        values, _, row_ptr = m.host_buffers()
+        values = oracle.fp8_to_double(np.arange(256, dtype=np.uint8))[values]
+    else:
+        W[20, 2299] = np.inf
+        m = M.encode(W, {"b1": 1, "b4": 4}[kind]).to_device()
+        values, _, row_ptr = m.host_buffers()
+        values = values.view(np.float16).astype(np.float64)
+    Y = m.spmm(torch.from_numpy(X).cuda()).cpu().numpy().astype(np.float64)
+    n = int(row_ptr[-1])
+    columns = m.columns_device().cpu().numpy()[:n]
+    with np.errstate(invalid="ignore"):
+        ref = np.add.reduceat(values[:n] * X.astype(np.float64)[:, columns], row_ptr[:-1].astype(np.int64), axis=1)
+    fine = np.isfinite(ref)
+    assert not fine[2].all() and fine[2].any() and not fine[17].all() and fine[17].any() and fine[0, :20].all()
+    assert np.array_equal(Y[~fine], ref[~fine], equal_nan=True)
+    assert np.allclose(Y[fine], ref[fine], atol=2e-3, rtol=2e-3)

@@ -96,9 +96,8 @@ MACKO_API int macko_encode(const uint16_t* dense_host, int64_t rows, int64_t col
  * is bound on return and keeps no host copy.  Synchronises `stream` (the sizes
  * of the outputs are only known after a counting pass).  The result is
  * bit-identical to macko_encode on the same input.  The encoder keeps one scratch
- * buffer per device between calls as long as it is at most 64 MiB (matrices of up
- * to about 100 M cells then encode without any allocation but the output's); a
- * larger one is released before the call returns.  One call at a time per process. */
+ * buffer per device between calls (about 8 bytes per row) as long as it is at most
+ * 64 MiB; a larger one is released before the call returns.  One call at a time per process. */
 MACKO_API int macko_encode_device(const void* dense_dev, int64_t rows, int64_t cols, int64_t ld,
                                   void* stream, macko_handle_t* out, macko_report_t* report);
 
@@ -180,8 +179,7 @@ MACKO_API int macko_bind_device(macko_handle_t h, void* values_dev, void* deltas
 MACKO_API int macko_encode_fp8(const uint8_t* dense_host, int64_t rows, int64_t cols, int64_t ld,
                                macko_handle_t* out, macko_report_t* report);
 /* macko_encode_device for a dense matrix of 8-bit values in device memory (uint8 [rows x ld]);
- * same contract, bit-identical to macko_encode_fp8; the encoder's scratch holds 3 bytes per
- * stored entry for such a call. */
+ * same contract, bit-identical to macko_encode_fp8. */
 MACKO_API int macko_encode_device_fp8(const void* dense_dev, int64_t rows, int64_t cols, int64_t ld, void* stream,
                                       macko_handle_t* out, macko_report_t* report);
 /* macko_wrap_device for arrays that hold 8-bit values (values_dev: alloc_nnz bytes,

@@ -1,14 +1,17 @@
 // Dense fp16 -> MACKO conversion on the GPU (format of Section 4.1, tail
 // padding of Section 4.5).  Passes: count the stored entries of every row,
-// prefix-sum the counts into row_ptr, write values and one code byte per entry,
-// pack the code bytes.  The output is bit-identical to the host encoder's.
+// prefix-sum the counts into row_ptr, write values and packed codes.  The output is
+// bit-identical to the host encoder's.
 //
 // One wavefront works on one row; per step a lane looks at 8 consecutive
-// columns (one 16-byte load, issued one step ahead).  The position of the
-// previous stored entry is carried across lanes with a DPP max-scan and across
-// steps in a register, so each lane can price its own non-zeros: a non-zero at
+// columns (one load, issued ahead).  The position of the
+// previous stored entry is carried across lanes and steps, so each lane can price its own non-zeros: a non-zero at
 // distance g from the previously stored column costs (g-1) / 2^b_delta padding
-// entries plus itself.  Per-row counts go to arrays that the scan kernel totals (no atomics).
+// entries plus itself.  Per-row counts go to arrays that the scan kernels total (no atomics).
+//
+// Roofline: HBM (2 x the dense matrix read, the second time mostly from the last-level cache, and the encoding
+// written once); what the passes are short of in practice is vector issue, hence the packed zero test, the table of
+// what a mask of 8 columns stores, and padding entries that cost no instruction (see encode_fill_kernel).
 #include "macko_device.h"
 #include "macko_internal.h"
 
@@ -24,108 +27,116 @@ struct EncodeStats {
   unsigned int max_row_entries;
 };
 
-// 8 consecutive columns as loaded (4 x 2 fp16), and the same with the non-zero mask.
-struct RawChunk {
-  uint32_t u[4];
-};
-struct Chunk {
-  uint16_t h[8];
-  unsigned mask;   // bit k set iff h[k] is neither +0 nor -0
-};
-
-// Loads only; columns at or beyond `cols` read as +0.  The caller decodes the
-// result one loop iteration later, so the load is in flight behind the work on
-// the current chunk.
-//
-// 8-bit values (IN8) are widened on the way in, sign to bit 15 and the other seven bits in
-// place, so that "neither +0 nor -0" is the same test for both widths; the fill pass then
-// writes 16-bit values to scratch and a last pass narrows them again.
-__device__ __forceinline__ uint32_t widen8(uint32_t b) { return (b & 0x7Fu) | ((b & 0x80u) << 8); }
-
+// 8 consecutive columns of one row as loaded: fp16 values, or bytes (8-bit values).
 template <bool IN8>
-__device__ __forceinline__ RawChunk load_raw(const void* __restrict__ row_v, int col0, int cols, bool vec_ok) {
-  RawChunk r;
+struct Chunk {
+  static constexpr int kWords = IN8 ? 2 : 4;
+  uint32_t u[kWords];
+};
+
+// Loads only; columns at or beyond `cols` read as +0.  The caller looks at the
+// result two loop iterations later, so the load is in flight behind the work on
+// earlier chunks.  Rows may start at any element: the wide load is an unaligned one where they do (one instruction as well).
+template <bool IN8>
+__device__ __forceinline__ Chunk<IN8> load_chunk(const void* __restrict__ row_v, int col0, int cols) {
+  Chunk<IN8> c;
+#pragma unroll
+  for (int k = 0; k < Chunk<IN8>::kWords; ++k) c.u[k] = 0u;
   if (IN8) {
     const uint8_t* row = static_cast<const uint8_t*>(row_v);
-    uint32_t b[8];
-    if (vec_ok && col0 + 8 <= cols) {
-      const uint2 q = *reinterpret_cast<const uint2*>(row + col0);
-#pragma unroll
-      for (int k = 0; k < 8; ++k) b[k] = ((k < 4 ? q.x : q.y) >> (8 * (k & 3))) & 0xFFu;
+    if (col0 + 8 <= cols) {
+      __builtin_memcpy(c.u, row + col0, 8);
     } else {
 #pragma unroll
-      for (int k = 0; k < 8; ++k) b[k] = (col0 + k < cols) ? row[col0 + k] : 0u;
+      for (int k = 0; k < 8; ++k)
+        if (col0 + k < cols) c.u[(k >> 2) % Chunk<IN8>::kWords] |= (uint32_t)row[col0 + k] << (8 * (k & 3));
     }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) r.u[k] = widen8(b[2 * k]) | (widen8(b[2 * k + 1]) << 16);
-    return r;
-  }
-  const uint16_t* row = static_cast<const uint16_t*>(row_v);
-  if (vec_ok && col0 + 8 <= cols) {
-    const uint4 q = *reinterpret_cast<const uint4*>(row + col0);
-    r.u[0] = q.x; r.u[1] = q.y; r.u[2] = q.z; r.u[3] = q.w;
   } else {
+    const uint16_t* row = static_cast<const uint16_t*>(row_v);
+    if (col0 + 8 <= cols) {
+      __builtin_memcpy(c.u, row + col0, 16);
+    } else {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const uint32_t lo = (col0 + 2 * k < cols) ? row[col0 + 2 * k] : 0u;
-      const uint32_t hi = (col0 + 2 * k + 1 < cols) ? row[col0 + 2 * k + 1] : 0u;
-      r.u[k] = lo | (hi << 16);
+      for (int k = 0; k < 8; ++k)
+        if (col0 + k < cols) c.u[(k >> 1) % Chunk<IN8>::kWords] |= (uint32_t)row[col0 + k] << (16 * (k & 1));
     }
-  }
-  return r;
-}
-
-__device__ __forceinline__ Chunk decode_chunk(const RawChunk& r) {
-  Chunk c;
-  c.mask = 0;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    c.h[k] = (uint16_t)(r.u[k >> 1] >> (16 * (k & 1)));
-    c.mask |= ((c.h[k] & 0x7FFFu) != 0 ? 1u : 0u) << k;
   }
   return c;
 }
 
-// What a lane needs to know about its 8 columns.  Two non-zeros inside one
-// chunk are at most 7 columns apart, so with deltas of up to 8 or more only the
-// first non-zero of a chunk can need padding entries in front of it; for 1- and
-// 2-bit codes the gaps inside the chunk are priced one by one.
-struct LaneView {
-  unsigned entries;   // stored entries this chunk contributes (non-zeros + padding)
-  unsigned nnz;       // non-zeros in the chunk
-  int lead;           // (gap - 1) of the chunk's first non-zero: column - previous stored column - 1
-};
+// Bit k set iff column k is neither +0 nor -0.  Packed: adding 0x7FFF (0x7F) to the bits other than the sign carries
+// into the sign position exactly when one of them is set, and never further.
+template <bool IN8>
+__device__ __forceinline__ unsigned nonzero_mask(const Chunk<IN8>& c) {
+  if (IN8) {
+    const uint32_t a = ((c.u[0] & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) & 0x80808080u;
+    const uint32_t b = ((c.u[1] & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) & 0x80808080u;
+    uint32_t x = (a >> 7) | (b >> 3);                   // bits 0, 8, 16, 24 and 4, 12, 20, 28
+    x |= x >> 7;
+    return (x | (x >> 14)) & 0xFFu;
+  }
+  uint32_t x = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {                         // columns 2j and 2j + 1 at bits 2j and 16 + 2j
+    const uint32_t t = ((c.u[j % Chunk<IN8>::kWords] & 0x7FFF7FFFu) + 0x7FFF7FFFu) & 0x80008000u;
+    x |= t >> (15 - 2 * j);
+  }
+  return (x | (x >> 15)) & 0xFFu;
+}
 
-// `carry` is the position (column + 1, 0 = none) of the last stored entry of the
-// steps already consumed; it is advanced over this step.
-__device__ __forceinline__ LaneView view_chunk(unsigned mask, int col0, int lane, int b_delta, uint32_t* carry) {
+// What 8 columns store from their first non-zero on, for every mask of non-zeros.  Gaps inside the 8 columns need padding
+// entries with 1- and 2-bit codes only; with wider ones only the first non-zero can have padding in front of it.
+struct MaskInfo {
+  uint64_t codes;          // 2^b_delta - 1 - code of entry e at bits e * b_delta (0 for the first, and for padding)
+  uint32_t pos;            // entry number of column k at bits 4k (non-zeros only)
+  uint32_t count;          // entries
+};
+template <int BD>
+__device__ __forceinline__ MaskInfo mask_info(unsigned mask) {
+  constexpr int kFull = (1 << BD) - 1;
+  MaskInfo m{0, 0u, 0u};
+  int e = 0, prev = -1;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    if (!((mask >> k) & 1u)) continue;
+    if (prev >= 0) {
+      const int g1 = k - prev - 1;                      // columns skipped
+      e += 1 + (g1 >> BD);
+      m.codes |= (uint64_t)(kFull - (g1 & kFull)) << (BD * e);
+    }
+    m.pos |= (uint32_t)e << (4 * k);
+    m.count = (uint32_t)e + 1u;
+    prev = k;
+  }
+  return m;
+}
+
+// Columns skipped in front of the chunk's first non-zero (0 without one).  `carry` is the position (column + 1, 0 = none) of
+// the last stored entry of the steps already consumed; it is advanced over this step.
+__device__ __forceinline__ int lead_of_chunk(unsigned mask, int col0, int lane, uint32_t* carry) {
   const uint32_t lastpos = mask ? (uint32_t)(col0 + 32 - __clz((int)mask)) : 0u;
-  const uint32_t incl = wave_incl_scan_max_u32(lastpos);
+  uint32_t incl = lastpos;
+  // where every lane has a non-zero the lane before holds the previous one: no scan
+  if (!__all(mask != 0u)) incl = wave_incl_scan_max_u32(lastpos);
   uint32_t prevpos = (uint32_t)__shfl_up((int)incl, 1);
   if (lane == 0) prevpos = 0;
   prevpos = max(prevpos, *carry);
   *carry = max(*carry, (uint32_t)__builtin_amdgcn_readlane((int)incl, 63));
-  LaneView v;
-  v.nnz = (unsigned)__popc(mask);
-  v.lead = mask ? col0 + (__ffs((int)mask) - 1) - (int)prevpos : 0;
-  v.entries = mask ? v.nnz + (unsigned)(v.lead >> b_delta) : 0u;
-  if (b_delta < 3) {               // deltas of at most 2 or 4: gaps inside the chunk can need padding too
-    unsigned m = mask & (mask - 1);                      // every non-zero but the first
-    int prevk = mask ? __ffs((int)mask) - 1 : 0;
-    while (m) {
-      const int k = __ffs((int)m) - 1;
-      m &= m - 1;
-      v.entries += (unsigned)((k - prevk - 1) >> b_delta);
-      prevk = k;
-    }
-  }
-  return v;
+  return mask ? col0 + (__ffs((int)mask) - 1) - (int)prevpos : 0;
 }
 
-template <bool IN8>
+// steps of 512 columns loaded ahead
+constexpr int kEncodeAhead = 2;
+
+template <bool IN8, int BD>
 __global__ void __launch_bounds__(256)
-encode_count_kernel(const void* __restrict__ dense, int rows, int cols, int64_t ld, bool vec_ok, int b_delta,
+encode_count_kernel(const void* __restrict__ dense, int rows, int cols, int64_t ld,
                     uint32_t* __restrict__ row_entries, uint32_t* __restrict__ row_nnz) {
+  __shared__ uint32_t counts[256];                      // entries from the first non-zero on, by mask (narrow codes)
+  if (BD < 3) {
+    counts[threadIdx.x] = mask_info<BD>(threadIdx.x).count;
+    __syncthreads();
+  }
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int nwaves = blockDim.x >> 6;
@@ -133,14 +144,20 @@ encode_count_kernel(const void* __restrict__ dense, int rows, int cols, int64_t 
     const void* src = static_cast<const unsigned char*>(dense) + (int64_t)row * ld * (IN8 ? 1 : 2);
     uint32_t carry = 0;
     unsigned entries = 0, nnz = 0;
-    RawChunk nxt = load_raw<IN8>(src, lane * 8, cols, vec_ok);
-    for (int base = 0; base < cols; base += 512) {
-      const int col0 = base + lane * 8;
-      const Chunk c = decode_chunk(nxt);
-      nxt = load_raw<IN8>(src, col0 + 512, cols, vec_ok);            // next step's columns, in flight
-      const LaneView v = view_chunk(c.mask, col0, lane, b_delta, &carry);
-      entries += v.entries;
-      nnz += v.nnz;
+    Chunk<IN8> ring[kEncodeAhead];
+#pragma unroll
+    for (int j = 0; j < kEncodeAhead; ++j) ring[j] = load_chunk<IN8>(src, 512 * j + lane * 8, cols);
+    for (int base = 0; base < cols; base += 512 * kEncodeAhead) {
+#pragma unroll
+      for (int j = 0; j < kEncodeAhead; ++j) {
+        const int col0 = base + 512 * j + lane * 8;     // steps behind the last column count nothing
+        const unsigned mask = nonzero_mask<IN8>(ring[j]);
+        ring[j] = load_chunk<IN8>(src, col0 + 512 * kEncodeAhead, cols);
+        const int lead = lead_of_chunk(mask, col0, lane, &carry);
+        const unsigned n = (unsigned)__popc(mask);
+        nnz += n;
+        entries += (BD < 3 ? counts[mask] : n) + (unsigned)(lead >> BD);
+      }
     }
     entries = wave_incl_scan_u32(entries);
     nnz = wave_incl_scan_u32(nnz);
@@ -151,10 +168,11 @@ encode_count_kernel(const void* __restrict__ dense, int rows, int cols, int64_t 
   }
 }
 
-// Row pointers from the per-row counts in three small launches: every block of
+// Row pointers from the per-row counts in small launches: every block of
 // 1024 rows totals its counts, one workgroup turns the block totals into block
-// offsets (and totals the statistics of the storage report), every block then
-// prefix-sums its own rows.  The entry total is kept as a 64-bit number so that
+// offsets (and totals the statistics of the storage report, which it writes to pinned host memory: no copy to wait
+// for), every block then prefix-sums its own rows.  Up to kFusedBlocks blocks the one workgroup does the first of
+// these as well, a wavefront per block (11008 rows: 4.8 + 4.9 us and a launch -> one launch).  The entry total is kept as a 64-bit number so that
 // the host can detect overflow of the 32-bit row pointers before anything is
 // written through them.
 struct BlockSums {
@@ -203,10 +221,47 @@ encode_block_sums_kernel(const uint32_t* __restrict__ row_entries, const uint32_
   }
 }
 
-// one workgroup: block_off[b] = entries of the blocks in front of b; totals to *stats
+constexpr int kFusedBlocks = 64;
+
+// one workgroup: block_off[b] = entries of the blocks in front of b; totals to *stats.  FUSED: from the rows' counts,
+// at most kFusedBlocks blocks; else from the block totals.
+template <bool FUSED>
 __global__ void __launch_bounds__(1024)
-encode_block_offsets_kernel(const BlockSums* __restrict__ sums, int nblocks, unsigned long long* __restrict__ block_off,
-                            uint32_t* __restrict__ row_ptr_last, EncodeStats* __restrict__ stats) {
+encode_block_offsets_kernel(const BlockSums* __restrict__ sums, const uint32_t* __restrict__ row_entries,
+                            const uint32_t* __restrict__ row_nnz, int rows, int nblocks,
+                            unsigned long long* __restrict__ block_off, EncodeStats* __restrict__ stats) {
+  __shared__ BlockSums fused[FUSED ? kFusedBlocks : 1];
+  if (FUSED) {
+    const int lane = threadIdx.x & 63;
+    for (int b = threadIdx.x >> 6; b < nblocks; b += 16) {
+      uint32_t e[16], z[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int r = 1024 * b + 64 * i + lane;
+        e[i] = r < rows ? row_entries[r] : 0u;
+        z[i] = r < rows ? row_nnz[r] : 0u;
+      }
+      unsigned long long se = 0, sn = 0;
+      unsigned int empty = 0, longest = 0;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        se += e[i];
+        sn += z[i];
+        empty += (1024 * b + 64 * i + lane < rows && e[i] == 0) ? 1u : 0u;
+        longest = max(longest, e[i]);
+      }
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) {
+        se += __shfl_xor(se, off);
+        sn += __shfl_xor(sn, off);
+        empty += __shfl_xor(empty, off);
+        longest = max(longest, __shfl_xor(longest, off));
+      }
+      if (lane == 0) fused[b] = BlockSums{se, sn, empty, longest};
+    }
+    __syncthreads();
+    sums = fused;
+  }
   __shared__ unsigned long long wave_tot[16];
   __shared__ unsigned long long carry_s;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -257,13 +312,12 @@ encode_block_offsets_kernel(const BlockSums* __restrict__ sums, int nblocks, uns
     stats->nnz = nn;
     stats->empty_rows = em;
     stats->max_row_entries = mx;
-    *row_ptr_last = (uint32_t)carry_s;
   }
 }
 
 __global__ void __launch_bounds__(1024)
 encode_row_ptr_kernel(const uint32_t* __restrict__ row_entries, int rows, const unsigned long long* __restrict__ block_off,
-                      uint32_t* __restrict__ row_ptr, uint32_t total) {
+                      uint32_t* __restrict__ row_ptr, uint32_t total, int b_delta, uint32_t* __restrict__ deltas) {
   __shared__ unsigned long long wave_tot[16];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int r = blockIdx.x * 1024 + t;
@@ -273,165 +327,179 @@ encode_row_ptr_kernel(const uint32_t* __restrict__ row_entries, int rows, const 
   __syncthreads();
   unsigned long long before = block_off[blockIdx.x];
   for (int i = 0; i < wave; ++i) before += wave_tot[i];
-  if (r < rows) row_ptr[r] = (uint32_t)(before + incl - e);
-  if (r == rows - 1) row_ptr[rows] = total;
+  // a 32-bit word of codes that two rows share is put together with atomic ORs by the fill kernel: it has to be zero
+  auto clear_shared_word = [&](uint64_t entry) {
+    if ((entry * (unsigned)b_delta) & 31u) deltas[(entry * (unsigned)b_delta) >> 5] = 0u;
+  };
+  if (r < rows) {
+    const uint32_t p = (uint32_t)(before + incl - e);
+    row_ptr[r] = p;
+    clear_shared_word(p);
+  }
+  if (r == rows - 1) {
+    row_ptr[rows] = total;
+    clear_shared_word(total);
+  }
 }
 
-// Second pass: values and one code byte per entry.  A wavefront's entries of one step are
-// contiguous in the output (from `cursor` on), but every lane holds a different number of them;
-// they are first put in order in LDS (index = position in the output modulo 16, so that aligned
-// 16-byte pieces of LDS are aligned 16-byte pieces of the arrays) and then written out with
-// 16-byte stores, the ragged first and last piece element by element.  A step with more than
-// kStage entries (long runs of padding) writes straight to memory instead.
-constexpr int kStage = 1024;
+// Second pass: values and packed codes.  A wavefront collects its row's entries in LDS, a window of kFillWindow entries
+// at a time (numbered from a multiple of 32 entries at or before the row's start, so that 16-byte pieces of values and
+// 32-bit words of codes are aligned in LDS as in memory), and writes full windows out in full-width stores.
+//  - Codes are ORed into the window as 2^b_delta - 1 - code and inverted on the way out: a padding entry is then all
+//    zeros, value and code, and costs nothing but its place.
+//  - What a lane stores follows from the mask of its 8 columns, looked up in a table (MaskInfo); only the code of its
+//    first non-zero depends on the columns before.
+//  - An entry in front of the window or behind it lands in a margin that is never read (a lane's entries, without the padding
+//    in front of them, span at most 8); a step that reaches behind the window is put into it once more when
+//    the window has moved on.
+//  - The words of codes that two rows share are ORed into memory (cleared beforehand by encode_row_ptr_kernel).
+// The previous version wrote a code byte per entry to scratch, packed by another kernel, and visited a lane's columns with two
+// predicated stores each: 11008 x 4096 at 50 % took 55.8 us + 6.0 us to pack, 36864 x 12288 411 us.
+constexpr int kFillWindow = 1024;
 constexpr int kFillWaves = 4;
+constexpr int kFillMargin = 8;                          // entries
 
-template <bool IN8>
+template <bool IN8, int BD>
 __global__ void __launch_bounds__(64 * kFillWaves)
-encode_fill_kernel(const void* __restrict__ dense, int rows, int cols, int64_t ld, bool vec_ok, int b_delta,
-                   const uint32_t* __restrict__ row_ptr, uint16_t* __restrict__ values,
-                   uint8_t* __restrict__ codes8, uint32_t pad_nnz, uint32_t alloc_nnz) {
+encode_fill_kernel(const void* __restrict__ dense, int rows, int cols, int64_t ld,
+                   const uint32_t* __restrict__ row_ptr, void* __restrict__ values_v,
+                   uint32_t* __restrict__ deltas, uint32_t pad_nnz, uint32_t alloc_nnz) {
+  constexpr uint32_t kFull = (1u << BD) - 1u;
+  constexpr int kValueBytes = IN8 ? 1 : 2;
+  constexpr int kPiece = 16 / kValueBytes;              // entries per 16-byte piece of values
+  constexpr int kWordEntries = 32 / BD;                 // entries per word of codes
+  constexpr int kWords = kFillWindow / kWordEntries;    // of a window; one margin of 4 words on either side
+  __shared__ __align__(16) unsigned char stage_v[kFillWaves][(kFillWindow + 2 * kPiece) * kValueBytes];   // margins of a piece
+  __shared__ uint32_t stage_c[kFillWaves][kWords + 8];
+  __shared__ uint32_t table_pos[256];
+  __shared__ uint32_t table_codes[256];
+  __shared__ uint32_t table_high[BD == 8 ? 256 : (BD < 3 ? 256 : 1)];     // codes 4 ... 7 of 8-bit codes; counts of narrow ones
+  static_assert(kPiece >= kFillMargin && 4 * 32 >= BD * kFillMargin, "margins");
+  uint16_t* values16 = static_cast<uint16_t*>(values_v);
+  uint8_t* values8 = static_cast<uint8_t*>(values_v);
   // the zero tail of both arrays (fewer than 128 entries): the first workgroup writes it
-  if (blockIdx.x == 0)
+  if (blockIdx.x == 0) {
     for (uint32_t k = pad_nnz + threadIdx.x; k < alloc_nnz; k += blockDim.x) {
-      values[k] = 0;
-      codes8[k] = 0;
+      if (IN8) values8[k] = 0;
+      else values16[k] = 0;
     }
-  __shared__ __align__(16) uint16_t stage_v[kFillWaves][kStage + 16];
-  __shared__ __align__(16) uint8_t stage_c[kFillWaves][kStage + 16];
-  const int full = (1 << b_delta) - 1;             // code of the largest delta
+    const uint64_t first = ((uint64_t)pad_nnz * BD + 31) >> 5, last = ((uint64_t)alloc_nnz * BD) >> 5;
+    for (uint64_t k = first + threadIdx.x; k < last; k += blockDim.x) deltas[k] = 0u;
+  }
+  {
+    const MaskInfo m = mask_info<BD>(threadIdx.x);      // 256 threads, 256 masks
+    table_pos[threadIdx.x] = m.pos;
+    table_codes[threadIdx.x] = (uint32_t)m.codes;
+    if (BD == 8) table_high[threadIdx.x] = (uint32_t)(m.codes >> 32);
+    if (BD < 3) table_high[threadIdx.x] = m.count;
+  }
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
-  const int nwaves = blockDim.x >> 6;
-  uint16_t* sv = stage_v[wave];
-  uint8_t* sc = stage_c[wave];
-  for (int row = blockIdx.x * nwaves + wave; row < rows; row += gridDim.x * nwaves) {
-    const void* src = static_cast<const unsigned char*>(dense) + (int64_t)row * ld * (IN8 ? 1 : 2);
+  unsigned char* sv = stage_v[wave] + 16;               // entry 0 of the window
+  uint32_t* sc = stage_c[wave] + 4;
+  for (int i = lane; i < (kFillWindow + 2 * kPiece) * kValueBytes / 16; i += 64)
+    reinterpret_cast<uint4*>(stage_v[wave])[i] = make_uint4(0, 0, 0, 0);
+  for (int i = lane; i < kWords + 8; i += 64) stage_c[wave][i] = 0u;
+  __syncthreads();
+
+  for (int row = blockIdx.x * kFillWaves + wave; row < rows; row += gridDim.x * kFillWaves) {
+    const uint32_t begin = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_ptr[row]);
+    const uint32_t end = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_ptr[row + 1]);
+    const void* src = static_cast<const unsigned char*>(dense) + (int64_t)row * ld * kValueBytes;
     uint32_t carry = 0;
-    uint32_t cursor = row_ptr[row];              // first entry of this step
-    RawChunk nxt = load_raw<IN8>(src, lane * 8, cols, vec_ok);
-    for (int base = 0; base < cols; base += 512) {
-      const int col0 = base + lane * 8;
-      const Chunk c = decode_chunk(nxt);
-      nxt = load_raw<IN8>(src, col0 + 512, cols, vec_ok);            // next step's columns, in flight
-      const LaneView v = view_chunk(c.mask, col0, lane, b_delta, &carry);
-      const uint32_t incl = wave_incl_scan_u32(v.entries);
-      const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-      const bool staged = total <= (uint32_t)kStage;                 // wavefront-uniform
-      const uint32_t align = cursor & 15u;
-      // where this lane's first entry goes: LDS index (staged) or output index (direct)
-      size_t o = staged ? (size_t)(align + (incl - v.entries)) : (size_t)cursor + (incl - v.entries);
-      if (c.mask && staged && b_delta >= 3) {
-        // Common case.  Only the chunk's first non-zero can have padding in front of it; the
-        // eight columns are then visited in a fixed order, so that no register is picked with a
-        // run-time index and every lane runs the same eight predicated stores.
-        for (int pads = v.lead >> b_delta; pads > 0; --pads) {       // padding entries, greedy
-          sv[o] = 0;
-          sc[o] = (uint8_t)full;
-          ++o;
-        }
-        int g1 = v.lead & full;                  // code of the next stored non-zero
-        bool seen = false;                       // zeros in front of the first non-zero are part of v.lead
+    uint32_t cursor = begin;                            // first entry of this step
+    uint32_t window = begin & ~31u;                     // first entry of the window
+    // entries [max(begin, window), min(end, window + kFillWindow)) to memory, the window zero again
+    auto flush = [&]() {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");     // a wavefront's LDS operations complete in order
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      const uint32_t lo = begin > window ? begin - window : 0u;             // in entries of the window
+      const uint32_t hi = min(end - window, (uint32_t)kFillWindow);
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          if ((c.mask >> k) & 1u) {
-            sv[o] = c.h[k];
-            sc[o] = (uint8_t)g1;
-            ++o;
-            g1 = 0;                              // the next non-zero is g1 + 1 columns further
-            seen = true;
-          } else if (seen) {
-            ++g1;
-          }
-        }
-      } else if (c.mask) {
-        unsigned m = c.mask;
-        int g1 = v.lead;                         // (gap - 1) in front of the next stored non-zero
-        int prevk = -1;
-        while (m) {
-          const int k = __ffs((int)m) - 1;
-          m &= m - 1;
-          if (prevk >= 0) g1 = k - prevk - 1;
-          for (int pads = g1 >> b_delta; pads > 0; --pads) {        // padding entries, greedy
-            if (staged) {
-              sv[o] = 0;
-              sc[o] = (uint8_t)full;
-            } else {
-              values[o] = 0;
-              codes8[o] = (uint8_t)full;
+      for (int j = 0; j < kFillWindow / kPiece / 64; ++j) {
+        const uint32_t p = (uint32_t)(lane + 64 * j), first = kPiece * p, last = first + kPiece;
+        if (last > lo && first < hi) {
+          uint4* q = reinterpret_cast<uint4*>(sv) + p;
+          const uint4 v = *q;
+          const size_t at = (size_t)window + first;
+          if (first >= lo && last <= hi) {
+            *reinterpret_cast<uint4*>(static_cast<unsigned char*>(values_v) + at * kValueBytes) = v;
+          } else {                                      // the row's first or last entries
+            for (uint32_t k = max(first, lo); k < min(last, hi); ++k) {
+              if (IN8) values8[window + k] = sv[k];
+              else values16[window + k] = reinterpret_cast<const uint16_t*>(sv)[k];
             }
-            ++o;
           }
-          if (staged) {
-            sv[o] = c.h[k];
-            sc[o] = (uint8_t)(g1 & full);
-          } else {
-            values[o] = c.h[k];
-            codes8[o] = (uint8_t)(g1 & full);
-          }
-          ++o;
-          prevk = k;
+          *q = make_uint4(0, 0, 0, 0);
         }
       }
-      if (staged && total > 0) {
-        __builtin_amdgcn_wave_barrier();
-        const uint32_t first = align, last = align + total;         // staged entries [first, last)
-        const size_t out0 = (size_t)cursor - align;                  // output index of staged index 0 (multiple of 16)
-        // values: pieces of 8 entries
-        for (uint32_t p = lane; 8u * p < last; p += 64) {
-          const uint32_t lo = 8u * p, hi = lo + 8u;
-          if (hi <= first) continue;
-          if (lo >= first && hi <= last) {
-            *reinterpret_cast<uint4*>(values + out0 + lo) = *reinterpret_cast<const uint4*>(sv + lo);
+#pragma unroll
+      for (int j = 0; j < (kWords + 63) / 64; ++j) {
+        const uint32_t p = (uint32_t)(lane + 64 * j), first = kWordEntries * p, last = first + kWordEntries;
+        if ((kWords % 64 == 0 || p < (uint32_t)kWords) && last > lo && first < hi) {
+          const uint32_t c = ~sc[p];
+          sc[p] = 0u;
+          uint32_t* out = deltas + (((uint64_t)window * BD) >> 5) + p;
+          if (first >= lo && last <= hi) {
+            *out = c;
           } else {
-            for (uint32_t k = max(lo, first); k < min(hi, last); ++k) values[out0 + k] = sv[k];
+            const uint32_t from = first < lo ? BD * (lo - first) : 0u, to = last > hi ? BD * (hi - first) : 32u;
+            atomicOr(out, c & (0xFFFFFFFFu << from) & (0xFFFFFFFFu >> (32u - to)));
           }
         }
-        // code bytes: pieces of 16 entries
-        for (uint32_t p = lane; 16u * p < last; p += 64) {
-          const uint32_t lo = 16u * p, hi = lo + 16u;
-          if (hi <= first) continue;
-          if (lo >= first && hi <= last) {
-            *reinterpret_cast<uint4*>(codes8 + out0 + lo) = *reinterpret_cast<const uint4*>(sc + lo);
-          } else {
-            for (uint32_t k = max(lo, first); k < min(hi, last); ++k) codes8[out0 + k] = sc[k];
-          }
-        }
-        __builtin_amdgcn_wave_barrier();
       }
-      cursor += total;
-    }
-  }
-}
-
-// Packed word i holds the codes of entries (32 / b_delta) i ..., entry k in bits
-// b_delta (k mod (32 / b_delta)) upwards; one code byte per entry comes in.
-__global__ void __launch_bounds__(256)
-encode_pack_kernel(const uint8_t* __restrict__ codes8, int64_t words, int b_delta, uint32_t* __restrict__ deltas) {
-  const int per_word = 32 / b_delta;                 // 32, 16, 8 or 4 entries: a multiple of 4 bytes of input
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < words;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const uint32_t* src = reinterpret_cast<const uint32_t*>(codes8 + (int64_t)per_word * i);
-    uint32_t w = 0;
-    for (int q = 0; q < per_word / 4; ++q) {
-      const uint32_t c = src[q];
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    Chunk<IN8> ring[kEncodeAhead];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) w |= ((c >> (8 * k)) & 0xFFu) << (b_delta * (4 * q + k));
-    }
-    deltas[i] = w;
-  }
-}
-
-// 8-bit values: the widened 16-bit values of the fill pass back to bytes (4 entries per thread and step)
-__global__ void __launch_bounds__(256)
-encode_narrow_kernel(const uint16_t* __restrict__ wide, int64_t quads, uint32_t* __restrict__ values8) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < quads; i += (int64_t)gridDim.x * blockDim.x) {
-    const uint2 q = reinterpret_cast<const uint2*>(wide)[i];
-    const uint32_t h[4] = {q.x & 0xFFFFu, q.x >> 16, q.y & 0xFFFFu, q.y >> 16};
-    uint32_t w = 0;
+    for (int j = 0; j < kEncodeAhead; ++j) ring[j] = load_chunk<IN8>(src, 512 * j + lane * 8, cols);
+    for (int base = 0; base < cols; base += 512 * kEncodeAhead) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) w |= ((h[k] & 0x7Fu) | ((h[k] >> 8) & 0x80u)) << (8 * k);
-    values8[i] = w;
+      for (int j = 0; j < kEncodeAhead; ++j) {
+        const int col0 = base + 512 * j + lane * 8;     // steps behind the last column store nothing
+        const Chunk<IN8> c = ring[j];
+        ring[j] = load_chunk<IN8>(src, col0 + 512 * kEncodeAhead, cols);
+        const unsigned mask = nonzero_mask<IN8>(c);
+        const uint32_t pos = table_pos[mask];
+        const uint32_t low = table_codes[mask];
+        const int lead = lead_of_chunk(mask, col0, lane, &carry);
+        const uint32_t count = BD < 3 ? table_high[mask] : (uint32_t)__popc(mask);
+        const uint32_t pads = (uint32_t)lead >> BD;     // padding entries in front, greedy
+        const uint32_t incl = wave_incl_scan_u32(pads + count);
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        const uint32_t first = cursor + incl - count;   // the lane's first non-zero
+        // its code, and the others', from bit 0 on
+        uint64_t codes = low | (mask ? kFull - ((uint32_t)lead & kFull) : 0u);
+        if (BD == 8) codes |= (uint64_t)table_high[mask] << 32;
+        for (;;) {
+          const int rel = (int)(first - window);
+          if (mask != 0u && (uint32_t)(rel + kFillMargin) < (uint32_t)(kFillWindow + kFillMargin)) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+              if ((mask >> k) & 1u) {
+                const int at = rel + (int)((pos >> (4 * k)) & 15u);
+                if (IN8) sv[at] = (uint8_t)(c.u[(k >> 2) % Chunk<IN8>::kWords] >> (8 * (k & 3)));
+                else reinterpret_cast<uint16_t*>(sv)[at] = (uint16_t)(c.u[(k >> 1) % Chunk<IN8>::kWords] >> (16 * (k & 1)));
+              }
+            }
+            const uint32_t bit = (uint32_t)(BD * rel + 128);         // the margin in front is 4 words
+            uint32_t* w = sc - 4 + (bit >> 5);
+            const uint64_t shifted = codes << (bit & 31u);
+            atomicOr(w, (uint32_t)shifted);
+            atomicOr(w + 1, (uint32_t)(shifted >> 32));
+            if (BD == 8) atomicOr(w + 2, (uint32_t)((codes >> 1) >> (63u - (bit & 31u))));
+          }
+          if (cursor + total - window <= (uint32_t)kFillWindow) break;
+          flush();
+          window += kFillWindow;
+        }
+        cursor += total;
+      }
+    }
+    if (end > window && end > begin) flush();
   }
 }
 
@@ -448,8 +516,8 @@ struct DeviceBuf {
   }
 };
 
-// Scratch memory of the encoder (per-row counts, block sums, the code bytes), kept per
-// device and reused from call to call; it only grows.  One encoder call at a time uses it.
+// Scratch memory of the encoder (per-row counts and block sums: about 8 bytes per row), kept per
+// device and reused from call to call.  One encoder call at a time uses it.
 struct Workspace {
   void* p = nullptr;
   size_t cap = 0;
@@ -483,8 +551,6 @@ int encode_on_device(const void* dense, int64_t rows, int64_t cols, int64_t ld, 
                      int64_t* max_row_entries) {
   const int cus = device_cu_count();
   const bool in8 = b_val == 8;
-  // 8 columns per load: 16 bytes of fp16, 8 bytes of 8-bit values
-  const bool vec_ok = (ld % 8 == 0) && (reinterpret_cast<uintptr_t>(dense) & (in8 ? 7 : 15)) == 0;
   int dev = 0;
   MACKO_HIP_TRY(hipGetDevice(&dev));
   if (dev < 0 || dev >= 64) return MACKO_E_UNSUPPORTED;
@@ -502,40 +568,34 @@ int encode_on_device(const void* dense, int64_t rows, int64_t cols, int64_t ld, 
   const int64_t nblocks = (rows + 1023) / 1024;
   const size_t o_counts = 0;
   const size_t o_nnz = align_up(o_counts + 4 * (size_t)rows, 256);
-  const size_t o_rowptr = align_up(o_nnz + 4 * (size_t)rows, 256);
-  const size_t o_sums = align_up(o_rowptr + 256, 256);
+  const size_t o_sums = align_up(o_nnz + 4 * (size_t)rows, 256);
   const size_t o_boff = align_up(o_sums + sizeof(BlockSums) * (size_t)std::max<int64_t>(nblocks, 1), 256);
-  const size_t o_stats = align_up(o_boff + 8 * (size_t)std::max<int64_t>(nblocks, 1), 256);
-  const size_t o_codes = align_up(o_stats + sizeof(EncodeStats), 256);
-  // room for the code bytes is reserved for the expected case right away (half the cells), so
-  // that the common call does not have to grow the scratch after the counting pass
-  if (workspace_reserve(ws, o_codes + (size_t)rows * (size_t)cols / 2 + 4096) != hipSuccess) {
+  const size_t scratch_bytes = o_boff + 8 * (size_t)std::max<int64_t>(nblocks, 1);
+  if (workspace_reserve(ws, scratch_bytes) != hipSuccess) {
     (void)hipGetLastError();
     return MACKO_E_OUT_OF_MEMORY;
   }
   auto at = [&](size_t off) { return static_cast<unsigned char*>(ws.p) + off; };
   uint32_t* counts = reinterpret_cast<uint32_t*>(at(o_counts));
   uint32_t* nnzs = reinterpret_cast<uint32_t*>(at(o_nnz));
-  uint32_t* rp_last = reinterpret_cast<uint32_t*>(at(o_rowptr));   // scratch word for the 32-bit total
   BlockSums* sums = reinterpret_cast<BlockSums*>(at(o_sums));
   unsigned long long* boff = reinterpret_cast<unsigned long long*>(at(o_boff));
-  EncodeStats* stats_d = reinterpret_cast<EncodeStats*>(at(o_stats));
 
   const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((rows + 3) / 4, (int64_t)cus * 16));
   if (rows > 0) {
-    if (in8)
-      hipLaunchKernelGGL(encode_count_kernel<true>, dim3(grid), dim3(256), 0, stream, dense, (int)rows,
-                         (int)cols, ld, vec_ok, b_delta, counts, nnzs);
-    else
-      hipLaunchKernelGGL(encode_count_kernel<false>, dim3(grid), dim3(256), 0, stream, dense, (int)rows,
-                         (int)cols, ld, vec_ok, b_delta, counts, nnzs);
-    hipLaunchKernelGGL(encode_block_sums_kernel, dim3((unsigned)nblocks), dim3(1024), 0, stream, counts, nnzs,
-                       (int)rows, sums);
+    auto kcount = in8 ? encode_count_kernel<true, 4> : b_delta == 4 ? encode_count_kernel<false, 4>
+                  : b_delta == 2 ? encode_count_kernel<false, 2> : b_delta == 8 ? encode_count_kernel<false, 8>
+                                                                                : encode_count_kernel<false, 1>;
+    hipLaunchKernelGGL(kcount, dim3(grid), dim3(256), 0, stream, dense, (int)rows, (int)cols, ld, counts, nnzs);
+    if (nblocks > kFusedBlocks)
+      hipLaunchKernelGGL(encode_block_sums_kernel, dim3((unsigned)nblocks), dim3(1024), 0, stream, counts, nnzs,
+                         (int)rows, sums);
   }
-  hipLaunchKernelGGL(encode_block_offsets_kernel, dim3(1), dim3(1024), 0, stream, sums, (int)nblocks, boff,
-                     rp_last, stats_d);
+  hipLaunchKernelGGL(nblocks > kFusedBlocks ? encode_block_offsets_kernel<false> : encode_block_offsets_kernel<true>,
+                     dim3(1), dim3(1024), 0, stream, static_cast<const BlockSums*>(sums),
+                     static_cast<const uint32_t*>(counts), static_cast<const uint32_t*>(nnzs), (int)rows, (int)nblocks,
+                     boff, ws.pinned_stats);
   MACKO_HIP_TRY(hipGetLastError());
-  MACKO_HIP_TRY(hipMemcpyAsync(ws.pinned_stats, stats_d, sizeof(EncodeStats), hipMemcpyDeviceToHost, stream));
   MACKO_HIP_TRY(hipStreamSynchronize(stream));
   const EncodeStats st = *ws.pinned_stats;
   if (st.pad_nnz >= (1ull << 32)) return MACKO_E_OVERFLOW;
@@ -544,9 +604,7 @@ int encode_on_device(const void* dense, int64_t rows, int64_t cols, int64_t ld, 
   const int64_t alloc = (pad + granule - 1) / granule * granule;
   if (alloc >= (int64_t{1} << 32)) return MACKO_E_OVERFLOW;
 
-  // the output block; the code bytes get more scratch if the guess above was too small
-  // (nothing in the old scratch but the per-row counts is needed any more, so they are
-  // turned into row pointers before the scratch moves)
+  // the output block
   const size_t b_values = 0;
   const size_t b_deltas = align_up(b_values + (size_t)alloc * (in8 ? 1 : 2), 256);
   const size_t b_rowptr = align_up(b_deltas + (size_t)alloc * b_delta / 8, 256);
@@ -562,44 +620,19 @@ int encode_on_device(const void* dense, int64_t rows, int64_t cols, int64_t ld, 
   uint32_t* rp = reinterpret_cast<uint32_t*>(ob + b_rowptr);
   if (rows > 0)
     hipLaunchKernelGGL(encode_row_ptr_kernel, dim3((unsigned)nblocks), dim3(1024), 0, stream, counts, (int)rows,
-                       boff, rp, (uint32_t)pad);
+                       boff, rp, (uint32_t)pad, b_delta, dels);
   else
     MACKO_HIP_TRY(hipMemsetAsync(rp, 0, 4, stream));
-  // scratch after the counts: one code byte per entry, and for 8-bit values the widened values
-  const size_t o_wide = align_up(o_codes + (size_t)alloc + 256, 256);
-  const size_t scratch_needed = in8 ? o_wide + 2 * (size_t)alloc + 256 : o_codes + (size_t)alloc + 256;
-  if (scratch_needed > ws.cap) {
-    MACKO_HIP_TRY(hipStreamSynchronize(stream));       // the launch above reads the old scratch
-    if (workspace_reserve(ws, scratch_needed) != hipSuccess) {
-      (void)hipGetLastError();
-      return MACKO_E_OUT_OF_MEMORY;
-    }
-  }
-  uint8_t* codes = static_cast<unsigned char*>(ws.p) + o_codes;
-
   if (rows > 0 && alloc > 0) {
-    if (in8) {
-      uint16_t* wide = reinterpret_cast<uint16_t*>(static_cast<unsigned char*>(ws.p) + o_wide);
-      hipLaunchKernelGGL(encode_fill_kernel<true>, dim3(grid), dim3(64 * kFillWaves), 0, stream, dense, (int)rows,
-                         (int)cols, ld, vec_ok, b_delta, static_cast<const uint32_t*>(rp), wide, codes,
-                         (uint32_t)pad, (uint32_t)alloc);
-      const int64_t quads = alloc / 4;                   // alloc is a multiple of 16
-      const unsigned ngrid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((quads + 255) / 256, (int64_t)cus * 16));
-      hipLaunchKernelGGL(encode_narrow_kernel, dim3(ngrid), dim3(256), 0, stream, static_cast<const uint16_t*>(wide),
-                         quads, static_cast<uint32_t*>(vals));
-    } else {
-      hipLaunchKernelGGL(encode_fill_kernel<false>, dim3(grid), dim3(64 * kFillWaves), 0, stream, dense, (int)rows,
-                         (int)cols, ld, vec_ok, b_delta, static_cast<const uint32_t*>(rp),
-                         static_cast<uint16_t*>(vals), codes, (uint32_t)pad, (uint32_t)alloc);
-    }
-    const int64_t words = alloc * b_delta / 32;
-    const unsigned pgrid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((words + 255) / 256, (int64_t)cus * 16));
-    hipLaunchKernelGGL(encode_pack_kernel, dim3(pgrid), dim3(256), 0, stream, static_cast<const uint8_t*>(codes),
-                       words, b_delta, dels);
+    auto kfill = in8 ? encode_fill_kernel<true, 4> : b_delta == 4 ? encode_fill_kernel<false, 4>
+                 : b_delta == 2 ? encode_fill_kernel<false, 2> : b_delta == 8 ? encode_fill_kernel<false, 8>
+                                                                              : encode_fill_kernel<false, 1>;
+    hipLaunchKernelGGL(kfill, dim3(grid), dim3(64 * kFillWaves), 0, stream, dense, (int)rows, (int)cols, ld,
+                       static_cast<const uint32_t*>(rp), vals, dels, (uint32_t)pad, (uint32_t)alloc);
   }
   MACKO_HIP_TRY(hipGetLastError());
   MACKO_HIP_TRY(hipStreamSynchronize(stream));
-  // a large scratch buffer is not kept: after a 36864 x 12288 matrix it would hold 280 MB until the process ends
+  // a large scratch buffer (more than 8 M rows) is not kept
   if (ws.cap > kKeepScratchBytes) {
     (void)hipFree(ws.p);
     ws.p = nullptr;

@@ -1509,3 +1509,33 @@ def test_spmm_tile_leaves_out_what_is_not_stored(kind):
     assert not fine[2].all() and fine[2].any() and not fine[17].all() and fine[17].any() and fine[0, :20].all()
     assert np.array_equal(Y[~fine], ref[~fine], equal_nan=True)
     assert np.allclose(Y[fine], ref[fine], atol=2e-3, rtol=2e-3)
+
+
+# ------------------------------------------------------------------ GPU encoder: windows, shared words, unaligned rows
+
+@pytest.mark.parametrize("kind", ["b1", "b2", "b4", "b8", "fp8"])
+@pytest.mark.parametrize("rows,cols,density,shift", [
+    (70001, 3, 0.5, 0), (1000, 3, 0.5, 0), (257, 8, 1.0, 1), (300, 9, 0.1, 3), (64, 511, 0.9, 0), (65, 513, 0.5, 1), (40, 1024, 1.0, 0),
+    (33, 1031, 0.97, 5), (30, 2055, 0.02, 7), (9, 40000, 0.0005, 0), (5, 70000, 0.0, 2), (12, 5000, 0.6, 0)])
+def test_gpu_encoder_window_edges(kind, rows, cols, density, shift):
+    """Rows of a few entries (many rows in one word of codes), rows that end at and around a full window of 1024 entries,
+    gaps of more padding than a window holds, rows that begin at any element."""
+    rng = np.random.default_rng(rows + 17 * cols)
+    W = ((rng.standard_normal((rows, cols)) + 3) * (rng.random((rows, cols)) < density)).astype(np.float16)
+    W[::3, 0] = 1.5
+    W[1::3, -1] = -2.0
+    W[rng.random((rows, cols)) < 0.01] = np.float16(-0.0)
+    big = torch.full((rows, cols + shift + 1), 9.0, dtype=torch.float16, device="cuda")
+    if kind == "fp8":
+        W8 = wl.fp8_values_of(W.view(np.uint16))
+        enc = oracle.encode8(W8)
+        big = torch.full((rows, cols + shift + 1), 9, dtype=torch.uint8, device="cuda")
+        big[:, shift:shift + cols] = torch.from_numpy(W8).cuda()
+        g = M.encode_device_fp8(big[:, shift:shift + cols])
+    else:
+        b_delta = int(kind[1])
+        enc = oracle.encode(W.view(np.uint16), b_delta)
+        big[:, shift:shift + cols] = torch.from_numpy(W).cuda()
+        g = M.encode_device(big[:, shift:shift + cols], b_delta=b_delta)
+    assert_same_encoding(g.fetch_device(), enc)
+    assert (g.report.nnz, g.report.pad_nnz, g.report.alloc_nnz) == (enc.nnz, enc.pad_nnz, enc.alloc_nnz)

@@ -232,11 +232,9 @@ MACKO_API int macko_columns_device(macko_handle_t h, int32_t* cols_dev, void* st
  * is lossless, Section 5.2; -0 inputs come back as +0).
  * dense_dev: fp16 [rows x ld] on the device (uint8 [rows x ld] for a matrix
  * with 8-bit values, at most 163840 columns), ld >= cols elements, aligned to
- * its element size (16-byte aligned with rows of a multiple of 16 bytes for
- * full-width stores), caller owned, must not overlap the format arrays.  Cells [r][0, cols)
+ * its element size, caller owned, must not overlap the format arrays.  Cells [r][0, cols)
  * are overwritten, cells between cols and ld are left untouched.  Enqueues one
- * kernel on `stream` (two for rows of more than 81920 columns) and does not
- * synchronise. */
+ * kernel on `stream` and does not synchronise. */
 MACKO_API int macko_decode_device(macko_handle_t h, void* dense_dev, int64_t ld, void* stream);
 
 /* ---- the product (Section 4.4; Y = M V of Appendix A) --------------------- */

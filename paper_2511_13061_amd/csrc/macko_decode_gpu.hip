@@ -10,7 +10,7 @@
 // One wavefront per row and 512 entries per step, as in the product.  Expanding
 // a matrix is a conversion, not a per-token operation.  Roofline: HBM; the dense
 // expansion reads 2.5 n bytes and writes 2 R C bytes once (rows are assembled in
-// LDS); rows too long for LDS are cleared in HBM first and then scattered into.
+// LDS, whole or a window at a time).
 #include "macko_decode.h"
 #include "macko_device.h"
 #include "macko_internal.h"
@@ -20,11 +20,10 @@ namespace {
 
 constexpr int kExpandBlock = 256;
 
-template <int BD, bool DENSE>
+template <int BD>
 __global__ void __launch_bounds__(kExpandBlock)
-expand_kernel(const uint4* __restrict__ values, const uint32_t* __restrict__ deltas,
-              const uint32_t* __restrict__ row_ptr, const int rows, const int cols,
-              int32_t* __restrict__ cols_out, uint16_t* __restrict__ dense, const int64_t ld) {
+expand_kernel(const uint32_t* __restrict__ deltas, const uint32_t* __restrict__ row_ptr, const int rows,
+              int32_t* __restrict__ cols_out) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (kExpandBlock / 64) + (threadIdx.x >> 6)));
   const int nwaves = (int)gridDim.x * (kExpandBlock / 64);
@@ -40,8 +39,6 @@ expand_kernel(const uint4* __restrict__ values, const uint32_t* __restrict__ del
       const uint32_t chunk = min(e0, end - 1u) >> 3;         // lanes past the row end re-read its last chunk
       LaneCodes<BD> w;
       w.load(deltas, chunk);
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (DENSE) v = load_stream(values + chunk);
       w.keep_if(e0 < end);
       w.decode();
       const uint32_t tot = w.total();
@@ -51,18 +48,10 @@ expand_kernel(const uint4* __restrict__ values, const uint32_t* __restrict__ del
         if (before > 0) base2 = -(int)w.through(before - 1);
       }
       const int lanebase = base2 + (int)(incl - tot);
-      const uint32_t vv[4] = {v.x, v.y, v.z, v.w};
 #define MACKO_ENTRY(k)                                                                  \
   {                                                                                     \
     const uint32_t e = e0 + k;                                                          \
-    if (e >= start && e < end) {                                                        \
-      const int col = (lanebase + w.template offset<k>()) >> 1;                         \
-      if (DENSE) {                                                                      \
-        if (col < cols) dense[(int64_t)row * ld + col] = (uint16_t)(vv[k >> 1] >> (16 * (k & 1))); \
-      } else {                                                                          \
-        cols_out[e] = col;                                                              \
-      }                                                                                 \
-    }                                                                                   \
+    if (e >= start && e < end) cols_out[e] = (lanebase + w.template offset<k>()) >> 1;  \
   }
       MACKO_ENTRY(0) MACKO_ENTRY(1) MACKO_ENTRY(2) MACKO_ENTRY(3)
       MACKO_ENTRY(4) MACKO_ENTRY(5) MACKO_ENTRY(6) MACKO_ENTRY(7)
@@ -123,20 +112,6 @@ check_kernel(const uint32_t* __restrict__ deltas, const uint32_t* __restrict__ r
       bad = __any(lane_bad);
     }
     if (bad && lane == 0) atomicMin(first_bad, (unsigned int)row);
-  }
-}
-
-// dense[r][0 .. cols) = +0 for every row (cells between cols and ld are left alone)
-template <bool VEC>
-__global__ void __launch_bounds__(256) zero_rows_kernel(uint16_t* __restrict__ dense, const int rows, const int cols,
-                                                         const int64_t ld) {
-  const int per_row = VEC ? cols / 8 : cols;                 // stores per row
-  const int64_t total = (int64_t)rows * per_row;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-    const int64_t r = i / per_row;
-    const int c = (int)(i - r * per_row);
-    if (VEC) reinterpret_cast<uint4*>(dense + r * ld)[c] = make_uint4(0, 0, 0, 0);
-    else dense[r * ld + c] = 0;
   }
 }
 
@@ -232,9 +207,154 @@ decode_rows_kernel(const void* __restrict__ values, const uint32_t* __restrict__
   }
 }
 
+// The same for rows that leave too few row buffers in LDS, or that do not lie on 16 bytes: the wavefront assembles its row
+// a window at a time.  The window is aligned to 16 bytes as the row lies in memory: full-width
+// stores whatever the alignment of dense and ld, value by value only at the row's two ends.  A step (512 stored entries)
+// that reaches behind the window is put into it in parts, out of registers; what a lane's entries leave outside
+// the window lands in a margin in front of it or behind it.
+//
+// Bound by HBM and by the wavefronts in flight (16 per compute unit; seven row buffers of 22 KB left 7): 4096 x 11008 at
+// 50 % 38.5 -> 34.5 us (4.3 TB/s), 1000 x 4093: 7.1 -> 6.1.  Short aligned rows stay with the kernel above (11008 x 4096 at 90 %:
+// 20.9 there, 21.5-24 here; 9000 x 300: 4.6 and 5.3: they run each part of the code once or twice, and here is more of it).
+// Windows of 2, 4 and 8 KB, and 1 or 2 steps loaded ahead are within 3 % of each other on long rows.
+constexpr int kWindowBytes = 8192;
+constexpr int kWindowWaves = 4;
+constexpr int window_margin(int b_delta, int b_val) { return b_delta == 8 ? 16 : 8 * (1 << b_delta) * (b_val / 8); }
+
 template <int BD, int VB>
-int launch_decode_rows_bd(const SpmvProblem& p, void* dense, int64_t ld, bool vec, int waves_per_wg,
-                          int64_t lds_bytes, hipStream_t stream) {
+__global__ void __launch_bounds__(64 * kWindowWaves)
+decode_windows_kernel(const void* __restrict__ values, const uint32_t* __restrict__ deltas,
+                      const uint32_t* __restrict__ row_ptr, const int rows, const int cols,
+                      unsigned char* __restrict__ dense, const int64_t ld) {
+  constexpr int EB = VB / 8;                                  // bytes per value
+  // a lane's 8 entries span at most 8 * 2^BD columns; with 8-bit codes they are checked one by one instead
+  constexpr int kMargin = window_margin(BD, VB);
+  static_assert(kMargin % 16 == 0, "the window starts on a 16-byte boundary");
+  constexpr int RING = 2;
+  __shared__ __align__(16) unsigned char lds[kWindowWaves * (kMargin + kWindowBytes) + kMargin];   // margin, window, ..., margin
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  const int lane = threadIdx.x & 63;
+  const int wave_in_wg = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int wave = (int)blockIdx.x * kWindowWaves + wave_in_wg;
+  const int nwaves = (int)gridDim.x * kWindowWaves;
+  unsigned char* win = lds + wave_in_wg * (kWindowBytes + kMargin) + kMargin;
+  u32x4* win4 = reinterpret_cast<u32x4*>(win);
+  for (int c = lane; c < kWindowBytes / 16; c += 64) win4[c] = u32x4{0, 0, 0, 0};
+  for (int row = wave; row < rows; row += nwaves) {          // wavefront-uniform
+    const uint32_t start = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_ptr[row]);
+    const uint32_t end = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_ptr[row + 1]);
+    unsigned char* out = static_cast<unsigned char*>(dense) + (int64_t)row * ld * EB;
+    const int skew = (int)(reinterpret_cast<uintptr_t>(out) & 15);          // bytes of the first 16 that are not the row's
+    out -= skew;
+    const int64_t row_end = skew + (int64_t)cols * EB;       // in bytes from the aligned start
+    int64_t at = 0;                                          // first byte of the window
+    auto flush = [&]() {
+      // the window is private to the wavefront, whose LDS operations complete in order
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      const int from = at == 0 ? skew : 0, to = (int)min(row_end - at, (int64_t)kWindowBytes);       // the row's bytes
+      unsigned char* to_mem = out + at;
+      if ((from | to) & 15) {                                // values of the row in a 16-byte piece that is not all its own
+        constexpr int kPiece = 16 / EB;
+        const int p = lane < kPiece ? (from & ~15) + EB * lane : (to & ~15) + EB * (lane - kPiece);
+        if (lane < 2 * kPiece && p >= from && p < to) {
+          if (VB == 16) *reinterpret_cast<uint16_t*>(to_mem + p) = *reinterpret_cast<const uint16_t*>(win + p);
+          else to_mem[p] = win[p];
+        }
+      }
+      for (int lo = 16 * lane; lo < to; lo += 1024) {        // behind the row's end the window holds zeros
+        const u32x4 t = win4[lo >> 4];
+        win4[lo >> 4] = u32x4{0, 0, 0, 0};
+        if (lo >= from && lo + 16 <= to) __builtin_nontemporal_store(t, reinterpret_cast<u32x4*>(to_mem + lo));
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      at += kWindowBytes;
+    };
+    if (end > start) {
+      const uint32_t a0 = start & ~7u;
+      const int nsteps = (int)((end - a0 + 511u) >> 9);
+      LaneCodes<BD> wq[RING];
+      LaneValues<VB> vq[RING];
+      auto issue = [&](int j, int step) {                    // lanes past the row end re-read its last chunk
+        const uint32_t chunk = min(a0 + 512u * (uint32_t)step + 8u * (uint32_t)lane, end - 1u) >> 3;
+        wq[j].load(deltas, chunk);
+        vq[j].load(values, chunk);
+      };
+#pragma unroll
+      for (int j = 0; j < RING; ++j) issue(j, min(j, nsteps - 1));
+      int base2 = 0;                                         // doubled position behind the steps so far
+      for (int step0 = 0; step0 < nsteps; step0 += RING) {
+#pragma unroll
+        for (int j = 0; j < RING; ++j) {
+          const int step = step0 + j;
+          if (step >= nsteps) break;
+          const uint32_t e0 = a0 + 512u * (uint32_t)step + 8u * (uint32_t)lane;
+          LaneCodes<BD> w = wq[j];
+          LaneValues<VB> v = vq[j];
+          issue(j, min(step + RING, nsteps - 1));
+          if (step == nsteps - 1) {                          // what lies behind the row's end is put as zeros
+            const uint32_t nv = e0 < end ? end - e0 : 0u;
+            w.keep_if(nv != 0);
+            v.keep_first(nv);
+          }
+          w.decode();
+          const uint32_t tot = w.total();
+          const uint32_t incl = wave_incl_scan_u32(tot);
+          if (step == 0) {                                   // entries of the previous row land in front of column 0
+            const int before = (int)(start - a0);
+            if (before > 0) base2 = -(int)w.through(before - 1);
+          }
+          const int lanebase = base2 + (int)(incl - tot);
+          base2 += (int)__builtin_amdgcn_readlane((int)incl, 63);
+          for (;;) {
+            const int rel = skew + (lanebase >> (VB == 8 ? 1 : 0)) - (int)at;    // the lane's first column in the window
+            if (BD != 8) {
+              // Lanes entirely outside write to the margin.  What is put behind the row's end is zero, and what the
+              // previous row's entries put in front of a row that does not start on 16 bytes is not written out.
+              unsigned char* p = win + ((uint32_t)(rel + kMargin) < (uint32_t)(kWindowBytes + kMargin) ? rel : -kMargin);
+#define MACKO_PUT(K)                                                                                          \
+  if (VB == 16) *reinterpret_cast<uint16_t*>(p + w.template offset<K>()) = (uint16_t)v.template bits<K>();      \
+  else p[w.template offset<K>() >> 1] = (unsigned char)v.template bits<K>();
+              MACKO_PUT(0) MACKO_PUT(1) MACKO_PUT(2) MACKO_PUT(3) MACKO_PUT(4) MACKO_PUT(5) MACKO_PUT(6) MACKO_PUT(7)
+#undef MACKO_PUT
+            } else {
+#define MACKO_PUT(K)                                                                                          \
+  {                                                                                                           \
+    const int q = rel + w.template offset<K>();                                                                \
+    if (e0 + K >= start && e0 + K < end && q >= 0 && q < kWindowBytes)                                         \
+      *reinterpret_cast<uint16_t*>(win + q) = (uint16_t)v.template bits<K>();                                  \
+  }
+              MACKO_PUT(0) MACKO_PUT(1) MACKO_PUT(2) MACKO_PUT(3) MACKO_PUT(4) MACKO_PUT(5) MACKO_PUT(6) MACKO_PUT(7)
+#undef MACKO_PUT
+            }
+            if (at + kWindowBytes >= row_end || skew + (base2 >> (VB == 8 ? 1 : 0)) <= at + kWindowBytes) break;
+            flush();
+          }
+        }
+      }
+    }
+    while (at < row_end) flush();
+  }
+}
+
+template <int BD, int VB>
+int launch_decode_windows_bd(const SpmvProblem& p, void* dense, int64_t ld, hipStream_t stream) {
+  const int64_t waves_wanted = std::min<int64_t>(p.rows, (int64_t)device_cu_count() * 32);
+  const dim3 grid((unsigned)((waves_wanted + kWindowWaves - 1) / kWindowWaves));
+  hipLaunchKernelGGL((decode_windows_kernel<BD, VB>), grid, dim3(64 * kWindowWaves), 0, stream,
+                     static_cast<const void*>(p.values), reinterpret_cast<const uint32_t*>(p.deltas), p.row_ptr,
+                     (int)p.rows, (int)p.cols, static_cast<unsigned char*>(dense), ld);
+  hipError_t e = hipGetLastError();
+  return e == hipSuccess ? MACKO_OK : hip_fail(e);
+}
+
+template <int BD, int VB>
+int launch_decode_rows_bd(const SpmvProblem& p, void* dense, int64_t ld, bool vec, int64_t lds_bytes,
+                          hipStream_t stream) {
+  constexpr int waves_per_wg = 4;
   const int block = 64 * waves_per_wg;
   const int64_t waves_wanted = std::min<int64_t>(p.rows, (int64_t)device_cu_count() * 32);
   const dim3 grid((unsigned)((waves_wanted + waves_per_wg - 1) / waves_per_wg));
@@ -251,32 +371,14 @@ int launch_decode_rows_bd(const SpmvProblem& p, void* dense, int64_t ld, bool ve
   return e == hipSuccess ? MACKO_OK : hip_fail(e);
 }
 
-template <bool DENSE>
-int launch_expand(const SpmvProblem& p, int32_t* cols_out, uint16_t* dense, int64_t ld, hipStream_t stream) {
+int launch_expand(const SpmvProblem& p, int32_t* cols_out, hipStream_t stream) {
   const int64_t waves_wanted = std::min<int64_t>(p.rows, (int64_t)device_cu_count() * 64);
   const dim3 grid((unsigned)((waves_wanted + kExpandBlock / 64 - 1) / (kExpandBlock / 64))), block(kExpandBlock);
-  const uint4* values = reinterpret_cast<const uint4*>(p.values);
   const uint32_t* deltas = reinterpret_cast<const uint32_t*>(p.deltas);
-  switch (p.b_delta) {
-    case 1:
-      hipLaunchKernelGGL((expand_kernel<1, DENSE>), grid, block, 0, stream, values, deltas, p.row_ptr, (int)p.rows,
-                         (int)p.cols, cols_out, dense, ld);
-      break;
-    case 2:
-      hipLaunchKernelGGL((expand_kernel<2, DENSE>), grid, block, 0, stream, values, deltas, p.row_ptr, (int)p.rows,
-                         (int)p.cols, cols_out, dense, ld);
-      break;
-    case 4:
-      hipLaunchKernelGGL((expand_kernel<4, DENSE>), grid, block, 0, stream, values, deltas, p.row_ptr, (int)p.rows,
-                         (int)p.cols, cols_out, dense, ld);
-      break;
-    case 8:
-      hipLaunchKernelGGL((expand_kernel<8, DENSE>), grid, block, 0, stream, values, deltas, p.row_ptr, (int)p.rows,
-                         (int)p.cols, cols_out, dense, ld);
-      break;
-    default:
-      return MACKO_E_UNSUPPORTED;
-  }
+  auto kfn = p.b_delta == 1 ? expand_kernel<1> : p.b_delta == 2 ? expand_kernel<2>
+             : p.b_delta == 4 ? expand_kernel<4> : p.b_delta == 8 ? expand_kernel<8> : nullptr;
+  if (!kfn) return MACKO_E_UNSUPPORTED;
+  hipLaunchKernelGGL(kfn, grid, block, 0, stream, deltas, p.row_ptr, (int)p.rows, cols_out);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? MACKO_OK : hip_fail(e);
 }
@@ -313,48 +415,40 @@ int launch_check(const SpmvProblem& p, unsigned int* first_bad, hipStream_t stre
 
 int launch_columns(const SpmvProblem& p, int32_t* cols_out, hipStream_t stream) {
   if (p.rows == 0 || p.pad_nnz == 0) return MACKO_OK;
-  return launch_expand<false>(p, cols_out, nullptr, 0, stream);
+  return launch_expand(p, cols_out, stream);
 }
 
 int launch_decode(const SpmvProblem& p, void* dense_any, int64_t ld, hipStream_t stream) {
   if (p.rows == 0 || p.cols == 0) return MACKO_OK;
   const int eb = p.b_val / 8;                                // bytes per value
   const bool vec = (p.cols * eb) % 16 == 0 && (ld * eb) % 16 == 0 && (reinterpret_cast<uintptr_t>(dense_any) & 15) == 0;
-  // one pass through a row buffer in LDS per wavefront
   const int64_t row_bytes = 16 * ((p.cols * eb + 15) / 16);
   constexpr int64_t kLdsLimit = 160 * 1024;
-  if (row_bytes <= kLdsLimit) {
-    // row buffers per compute unit: workgroups of 4 wavefronts while 8 or more fit, else one workgroup of 1..7
-    const int per_cu = (int)(kLdsLimit / row_bytes);
-    const int waves_per_wg = per_cu >= 8 ? 4 : per_cu;
-    const int64_t lds_bytes = row_bytes * waves_per_wg;
-    if (p.b_val == 8) {                                      // 8-bit values come with 4-bit codes
-      if (p.b_delta != 4) return MACKO_E_UNSUPPORTED;
-      return launch_decode_rows_bd<4, 8>(p, dense_any, ld, vec, waves_per_wg, lds_bytes, stream);
-    }
+  if (p.b_val == 8 && row_bytes > kLdsLimit) return MACKO_E_UNSUPPORTED;    // 8-bit rows of more than 163840 columns
+  if (p.b_val == 8 && p.b_delta != 4) return MACKO_E_UNSUPPORTED;           // 8-bit values come with 4-bit codes
+  // Row buffers per compute unit: at least 8 (4096 x 11008 has 7: 38.5 us, in windows 34.5; 9000 columns have 8: 9.8 us for 2000
+  // rows, in windows 10.3), and rows on 16 bytes unless they are short (1000 x 4093: 7.1 and 6.1; 9000 x 300: 4.6 and 5.3).
+  const int64_t per_cu = kLdsLimit / row_bytes;
+  if (per_cu < 8 || (!vec && row_bytes >= 2048)) {
+    if (p.b_val == 8) return launch_decode_windows_bd<4, 8>(p, dense_any, ld, stream);
     switch (p.b_delta) {
-      case 1: return launch_decode_rows_bd<1, 16>(p, dense_any, ld, vec, waves_per_wg, lds_bytes, stream);
-      case 2: return launch_decode_rows_bd<2, 16>(p, dense_any, ld, vec, waves_per_wg, lds_bytes, stream);
-      case 4: return launch_decode_rows_bd<4, 16>(p, dense_any, ld, vec, waves_per_wg, lds_bytes, stream);
-      case 8: return launch_decode_rows_bd<8, 16>(p, dense_any, ld, vec, waves_per_wg, lds_bytes, stream);
+      case 1: return launch_decode_windows_bd<1, 16>(p, dense_any, ld, stream);
+      case 2: return launch_decode_windows_bd<2, 16>(p, dense_any, ld, stream);
+      case 4: return launch_decode_windows_bd<4, 16>(p, dense_any, ld, stream);
+      case 8: return launch_decode_windows_bd<8, 16>(p, dense_any, ld, stream);
       default: return MACKO_E_UNSUPPORTED;
     }
   }
-  if (p.b_val != 16) return MACKO_E_UNSUPPORTED;             // 8-bit rows of more than 163840 columns
-  uint16_t* dense = static_cast<uint16_t*>(dense_any);
-  // rows too long for LDS: clear the matrix, then scatter the stored values (two kernels in stream order)
-  const int64_t stores = p.rows * (vec ? p.cols / 8 : p.cols);
-  const int64_t wgs = std::min<int64_t>((stores + 255) / 256, (int64_t)device_cu_count() * 32);
-  if (vec)
-    hipLaunchKernelGGL(zero_rows_kernel<true>, dim3((unsigned)wgs), dim3(256), 0, stream, dense, (int)p.rows,
-                       (int)p.cols, ld);
-  else
-    hipLaunchKernelGGL(zero_rows_kernel<false>, dim3((unsigned)wgs), dim3(256), 0, stream, dense, (int)p.rows,
-                       (int)p.cols, ld);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return hip_fail(e);
-  if (p.pad_nnz == 0) return MACKO_OK;
-  return launch_expand<true>(p, nullptr, dense, ld, stream);
+  // one pass through a row buffer in LDS per wavefront, in workgroups of 4 wavefronts
+  const int64_t lds_bytes = row_bytes * 4;
+  if (p.b_val == 8) return launch_decode_rows_bd<4, 8>(p, dense_any, ld, vec, lds_bytes, stream);
+  switch (p.b_delta) {
+    case 1: return launch_decode_rows_bd<1, 16>(p, dense_any, ld, vec, lds_bytes, stream);
+    case 2: return launch_decode_rows_bd<2, 16>(p, dense_any, ld, vec, lds_bytes, stream);
+    case 4: return launch_decode_rows_bd<4, 16>(p, dense_any, ld, vec, lds_bytes, stream);
+    case 8: return launch_decode_rows_bd<8, 16>(p, dense_any, ld, vec, lds_bytes, stream);
+    default: return MACKO_E_UNSUPPORTED;
+  }
 }
 
 }  // namespace macko

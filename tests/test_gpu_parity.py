@@ -1539,3 +1539,30 @@ def test_gpu_encoder_window_edges(kind, rows, cols, density, shift):
         g = M.encode_device(big[:, shift:shift + cols], b_delta=b_delta)
     assert_same_encoding(g.fetch_device(), enc)
     assert (g.report.nnz, g.report.pad_nnz, g.report.alloc_nnz) == (enc.nnz, enc.pad_nnz, enc.alloc_nnz)
+
+
+@pytest.mark.parametrize("kind", ["b1", "b2", "b4", "b8", "fp8"])
+@pytest.mark.parametrize("rows,cols,density,shift", [
+    (70, 1, 0.5, 0), (50, 7, 0.9, 1), (33, 2047, 0.5, 3), (20, 2048, 0.5, 0), (20, 2049, 0.4, 5), (12, 4096, 0.9, 8),
+    (11, 4103, 0.03, 2), (7, 40001, 0.0003, 7), (3, 100000, 0.3, 0), (40, 300, 0.0, 4)])
+def test_decode_device_windows(kind, rows, cols, density, shift):
+    """Rows around a window of 4096 bytes, rows that begin at any element, steps that reach over several windows; the
+    cells around the matrix keep what they hold."""
+    rng = np.random.default_rng(rows + 13 * cols)
+    W = ((rng.standard_normal((rows, cols)) + 3) * (rng.random((rows, cols)) < density)).astype(np.float16)
+    W[::2, -1] = -2.0
+    W[1::4] = 0
+    W[W == 0] = 0                                                          # no -0
+    if kind == "fp8":
+        W = wl.fp8_values_of(W.view(np.uint16))
+        W[W == 0x80] = 0                                                   # -0 comes back as +0
+        m = M.encode_fp8(W).to_device()
+        buf = torch.full((rows, cols + shift + 3), 9, dtype=torch.uint8, device="cuda")
+    else:
+        m = M.encode(W, int(kind[1])).to_device()
+        buf = torch.full((rows, cols + shift + 3), 9.0, dtype=torch.float16, device="cuda")
+    m.decode_device(buf[:, shift:shift + cols])
+    torch.cuda.synchronize()
+    got = buf.cpu().numpy()
+    assert np.array_equal(got[:, shift:shift + cols].view(W.dtype), W)
+    assert (got[:, :shift] == 9).all() and (got[:, shift + cols:] == 9).all()

@@ -11,8 +11,8 @@
 // about 6 (65 vector instructions per step of 512 entries), memory latency 4 (one 16-wavefront
 // workgroup per compute unit), scattering into LDS 2, and the window products 4, half of that the
 // transposes of the B operand (times found by leaving one part out).  Measured against the vector kernel
-// at 50 % (us, batch 8 / 16 / 64): 4096 x 11008: 29.6 / 59 / 239 -> 19.9 / 20.5 / 37.4, 11008 x 4096:
-// 23.6 / 46 / 183 -> 21.7 / 22.3 / 41.7, 4096 x 4096: 12.1 / 24 / 96 -> 10.3 / 11.1 / 18.5.
+// at 50 % (us, batch 8 / 16 / 64): 4096 x 11008: 29.6 / 59 / 239 -> 20.5 / 21.2 / 38.7, 11008 x 4096:
+// 23.6 / 46 / 183 -> 22.7 / 23.2 / 43.6, 4096 x 4096: 12.1 / 24 / 96 -> 11.5 / 11.7 / 19.0.
 //
 // Tried: 8 rows per workgroup and two workgroups per compute unit (28-40 us where 16 rows take 21: half
 // of the matrix instruction is idle and every B element is fetched twice); 3 and 4 steps loaded ahead
@@ -61,6 +61,12 @@ __device__ __forceinline__ void move_regs(T& dst, const T& src) {
   for (int i = 0; i < n; ++i) asm volatile("v_mov_b32 %0, %1" : "=v"(b[i]) : "v"(a[i]));
   __builtin_memcpy(&dst, b, sizeof(T));
 }
+
+// The compiler takes these as changed here: what is computed from them afterwards cannot have been computed earlier.
+__device__ __forceinline__ void keep_opaque(uint32_t& w, LaneValues<16>& v) {
+  asm volatile("" : "+v"(w), "+v"(v.v.x), "+v"(v.v.y), "+v"(v.v.z), "+v"(v.v.w));
+}
+__device__ __forceinline__ void keep_opaque(uint32_t& w, LaneValues<8>& v) { asm volatile("" : "+v"(w), "+v"(v.v.x), "+v"(v.v.y)); }
 
 template <int CTRL>
 __device__ __forceinline__ uint32_t quad_dpp(uint32_t v) {
@@ -174,6 +180,8 @@ spmm_tile_kernel(const TileArgs a) {
   u32x4 b[G][NT][4];
   int k0 = 0, tile = 0;                                // first column of the window, tile
   auto load_b = [&]() {
+    uint32_t xo = xoff;
+    if (NT > 2) asm volatile("" : "+v"(xo));           // no offsets computed in front of the loop and kept in registers
 #pragma unroll
     for (int g = 0; g < G; ++g)
 #pragma unroll
@@ -181,7 +189,7 @@ spmm_tile_kernel(const TileArgs a) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const auto q = __builtin_amdgcn_raw_buffer_load_b128(
-              xrsrc, (int)(xoff + 2u * (uint32_t)(k0 + 128 * g) + (uint32_t)(16 * t + r) * ldx2), 0, 0);
+              xrsrc, (int)(xo + 2u * (uint32_t)(k0 + 128 * g) + (uint32_t)(16 * t + r) * ldx2), 0, 0);
           b[g][t][r] = u32x4{(uint32_t)q[0], (uint32_t)q[1], (uint32_t)q[2], (uint32_t)q[3]};
         }
   };
@@ -276,7 +284,10 @@ spmm_tile_kernel(const TileArgs a) {
             sum += *p;
             *p = float4v{0.f, 0.f, 0.f, 0.f};
           }
-          const int m0 = 4 * (lane >> 4), left = wg_rows - kTileRows * tile - m0;     // lane holds rows m0 ... m0 + 3
+          int l = lane;
+          if (NT > 2) asm volatile("" : "+v"(l));      // nor pointers into Y
+          const int n = l & 15;
+          const int m0 = 4 * (l >> 4), left = wg_rows - kTileRows * tile - m0;     // lane holds rows m0 ... m0 + 3
           if (16 * t + n < a.batch) {
             uint16_t* y = a.Y + (int64_t)(16 * t + n) * a.ldy + (row0 + kTileRows * tile + m0);
 #pragma unroll
@@ -293,6 +304,8 @@ spmm_tile_kernel(const TileArgs a) {
         }
         acc[t] = float4v{0.f, 0.f, 0.f, 0.f};
       }
+      __builtin_amdgcn_sched_barrier(0);
+      load_b();
       __syncthreads();
       ++tile;
     }
@@ -353,6 +366,8 @@ spmm_tile_kernel(const TileArgs a) {
     for (;;) {
       if (tile == target) {
         if (!live) goto out;
+        // with many vectors every register counts: nothing about the entries is computed in front of this loop and kept
+        if (NT > 1) keep_opaque(w.w, v);
         // lanes without an entry in the window write to the pad; so do a lane's entries in front of the window or
         // behind it.  What is behind the row's end is zero, and so is the tile there.
         int rel = lanebase - 2 * k0;
@@ -401,7 +416,7 @@ int launch_tile_as(TileArgs a, hipStream_t stream) {
 // Windows of 4096 columns where the registers allow it (up to 16 vectors) and the row is longer than 2048: fewer
 // products of windows to wait for (4096 x 4096, 8 vectors: 11.3 -> 10.6 us; 14336 x 1024 would lose, 14.0 -> 15.9,
 // its tile being cleared and read twice as wide as needed).  One step ahead instead of two from 33 vectors on: two
-// would spill registers in the loop (42 -> 60 us).
+// would spill registers in the loop (44 -> 60 us).
 template <int BD, int VB>
 int launch_tile_bd(const TileArgs& a, hipStream_t stream) {
   const int nt = (a.batch + 15) / 16;

@@ -281,16 +281,16 @@ MACKO_API int macko_spmv_group(int n, const macko_handle_t* handles, const void*
                                void* const* y_dev, void* stream);
 
 /* Any number of independent products (the linear layers of a whole stack, one
- * x and one y each): grouped launches of up to MACKO_MAX_GROUP consecutive
- * products, dealt in turn to three side streams that the library keeps per
+ * x and one y each).  Products that all take the wavefront-per-row kernel with one
+ * code width and value width go up to 32 to a launch, on `stream`.  Others are dealt out as grouped launches of up to
+ * MACKO_MAX_GROUP consecutive products to three side streams that the library keeps per
  * device, so that the end of one launch overlaps the start of the next (a
- * launch costs about 3 us whatever its size; on one stream 128 launches of a
- * 13B-shaped stack take 2.54 ms, dealt out like this 2.1 ms).  The side
+ * launch costs about 3 us whatever its size).  The side
  * streams start after the work already enqueued on `stream`, and `stream`
  * continues after all of them (event fork / join, no host synchronisation, so
  * the call can be captured into a graph).  No ordering among the products; the
  * y vectors must not alias each other or any x.  n <= MACKO_MAX_GROUP is
- * macko_spmv_group.  Calls are serialised by a mutex while they enqueue. */
+ * macko_spmv_group.  Calls that use the side streams are serialised by a mutex while they enqueue. */
 MACKO_API int macko_spmv_many(int64_t n, const macko_handle_t* handles, const void* const* x_dev,
                               void* const* y_dev, void* stream);
 /* A chain of dependent products in ONE kernel launch (the linear layers of a decoder

@@ -625,6 +625,36 @@ int macko_spmv_many(int64_t n, const macko_handle_t* handles, const void* const*
     if (st != MACKO_OK) return st;
   }
   if (n <= MACKO_MAX_GROUP) return n == 0 ? MACKO_OK : macko_spmv_group((int)n, handles, x_dev, y_dev, stream);
+  // Products that all take the wave-per-row kernel with one code width go kMaxWide to a launch, others as
+  // macko_spmv_group takes them.
+  auto problem = [&](int64_t i) {
+    macko_handle_t h = handles[i];
+    return macko::SpmvProblem{h->d_values, h->d_deltas, h->d_row_ptr, h->rows, h->cols, h->pad_nnz,
+                              x_dev[i], y_dev[i], h->b_delta, h->b_val};
+  };
+  int launch_class = -1;
+  for (int64_t i = 0; i < n && launch_class != 0; ++i) {
+    if (handles[i]->rows == 0) continue;
+    const int c = macko::spmv_launch_class(problem(i));
+    launch_class = launch_class < 0 || launch_class == c ? c : 0;
+  }
+  const bool uniform = launch_class > 0;
+  auto launch = [&](int64_t at, int count, hipStream_t s) -> int {
+    macko::SpmvProblem p[macko::kMaxWide];
+    int m = 0;
+    for (int i = 0; i < count; ++i)
+      if (handles[at + i]->rows != 0) p[m++] = problem(at + i);
+    return m == 0 ? MACKO_OK : macko::launch_spmv_group(m, p, s);
+  };
+  // Wide launches follow each other on the caller's stream: the seam between two is 1 % of them, while the fork and join
+  // below take some 20 us of the device and two of them at a time are no faster (56 products: 505 us over two side streams).
+  if (uniform) {
+    for (int64_t at = 0; at < n; at += macko::kMaxWide) {
+      const int st = launch(at, (int)std::min<int64_t>(macko::kMaxWide, n - at), static_cast<hipStream_t>(stream));
+      if (st != MACKO_OK) return st;
+    }
+    return MACKO_OK;
+  }
   int dev = 0;
   MACKO_HIP_TRY(hipGetDevice(&dev));
   std::lock_guard<std::mutex> lock(g_many_mutex);

@@ -47,6 +47,7 @@ int device_cu_count();
 
 // launchers implemented in the .hip files; all return a macko_status
 constexpr int kMaxGroup = 8;            // MACKO_MAX_GROUP
+constexpr int kMaxWide = 32;            // products in one launch of macko_spmv_many
 
 struct SpmvProblem {
   const uint16_t* values;
@@ -64,8 +65,10 @@ struct GemvProblem {
   const void* x;
   void* y;
 };
-// n independent products, as few kernel launches as the shapes allow (1 <= n <= kMaxGroup)
+// n independent products, as few kernel launches as the shapes allow (1 <= n <= kMaxGroup; kMaxWide for the sparse product)
 int launch_spmv_group(int n, const SpmvProblem* problems, hipStream_t stream);
+// 0: the product does not take the wave-per-row kernel; products with the same other number fit one launch
+int spmv_launch_class(const SpmvProblem& p);
 int launch_gemv_group(int n, const GemvProblem* problems, hipStream_t stream);
 // phases of products in one launch, phase p + 1 after phase p: sizes[p] products in phase p, listed in
 // phase order; `scratch` is chain_scratch_bytes() of zeroed device memory that the launch leaves zeroed

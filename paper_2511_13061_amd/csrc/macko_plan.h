@@ -42,7 +42,7 @@ struct PlanMat {
 struct Plan {
   int block = 0;           // threads per workgroup
   int64_t total_wgs = 0;
-  PlanMat m[kMaxGroup] = {};
+  PlanMat m[kMaxWide] = {};
 };
 
 constexpr int64_t kPlanLdsPerCu = 160 * 1024;
@@ -82,7 +82,7 @@ inline bool plan_resident(Plan& plan, int n, const PlanInput* in, int cus, int f
   if (total_rows < (int64_t)cus * 4) return false;
   double best_cost = 0;
   int best_k = 0, best_nw = 0;
-  PlanMat best_m[kMaxGroup] = {};
+  PlanMat best_m[kMaxWide] = {};
   for (int k = 1; k <= 4; ++k) {
     if (k != (forced_k ? forced_k : 2)) continue;
     if (k * max_lds > kPlanLdsPerCu) continue;
@@ -93,7 +93,7 @@ inline bool plan_resident(Plan& plan, int n, const PlanInput* in, int cus, int f
       const int64_t wgs = (int64_t)cus * k;
       if (waves < 12 && total_rows >= (int64_t)cus * 12) continue;  // too few loads in flight
       // deal the workgroups out in proportion to the work, every matrix at least one
-      PlanMat pm[kMaxGroup];
+      PlanMat pm[kMaxWide];
       int64_t given = 0;
       int largest = 0;
       bool ok = true;

@@ -368,6 +368,32 @@ spmv_wave_row_kernel(const int wb1, const int wb2, const int wb3, const int wb4,
                                        nwaves, inv_nwaves, (uint32_t)g.m[mi].amask, 64 * nwaves);
 }
 
+// More than kMaxGroup matrices: the workgroup's matrix is looked up in the descriptors' own list of first workgroups
+// (unused slots hold INT_MAX), two wide scalar loads in front of everything else.  That costs a workgroup some 0.2 us against
+// the list in registers above, and a launch of many products has workgroups enough to hide it; what it saves is launches, and
+// the fork and join of side streams around them (14 products of two 13B-shaped layers with 2-bit codes, 762 MB:
+// two launches on two streams 164 us, one launch 120).
+struct SpmvWideArgs {
+  int wg_begin[kMaxWide];
+  SpmvMat m[kMaxWide];
+};
+template <bool SIMPLE, int BD, int VB>
+__global__ void __launch_bounds__(1024)
+spmv_wave_row_wide_kernel(const uint32_t waves, const SpmvWideArgs g) {
+  const int inv_nwaves = (int)(waves & 0x1FFFFu), nwaves = (int)(waves >> 17);
+  int mi = 0, wg0 = 0;
+#pragma unroll
+  for (int i = 1; i < kMaxWide; ++i) {
+    const int first = g.wg_begin[i];
+    const bool in = (int)blockIdx.x >= first;
+    mi = in ? i : mi;
+    wg0 = in ? first : wg0;
+  }
+  const SpmvMat& m = g.m[mi];
+  spmv_wave_row_body<2, SIMPLE, BD, VB>(m.values, m.deltas, m.row_ptr, m.x, m.y, m.rows, m.cols, m.q, m.r,
+                                        (int)blockIdx.x - wg0, nwaves, inv_nwaves, (uint32_t)m.amask, 64 * nwaves);
+}
+
 // One matrix: the 14 leading arguments, which a starting wavefront finds in registers, hold
 // everything it needs to request its row pointers and x at once, without any argument load before:
 //   shape    floor(65536 / wavefronts per workgroup) + 1 in bits 0..16, wavefronts per workgroup in
@@ -568,6 +594,10 @@ constexpr int64_t kMaxLdsBytes = 160 * 1024 - 64;   // 160 KB per CU minus the s
 constexpr int64_t kResidentStepsPerCu = 448;
 // many-workgroup regime: steps of work per wavefront (whole rows; at least one row)
 constexpr int64_t kStepsPerWave = 8;
+// launches of more than kMaxGroup matrices: a workgroup takes longer to start (see spmv_wave_row_wide_kernel) and the launch
+// is long enough for larger ones (14 products of two 13B-shaped layers, us for 8 / 12 / 16 / 24 steps: 2-bit codes
+// 157 / 121 / 120 / 121, 4-bit codes 132 / 126 / 126 / 128)
+constexpr int64_t kStepsPerWaveWide = 16;
 // rows of at least this many stored entries on average take the wave-per-row kernel (a step
 // covers 512 entries; below about 40 % use of a step the sub-wave kernel wins: measured
 // crossover between 133 and 247 entries per row on 36864 x 12288 at 98-99 % sparsity)
@@ -707,7 +737,7 @@ int launch_wave_row_bd(const SpmvGroupArgs& args, const SpmvGroupHeader& head, i
 int launch_wave_row_group(int nwr, const SpmvProblem* const* wr, int b_delta, int b_val, hipStream_t stream) {
   const Tuning& t = tuning();
   const int cus = device_cu_count();
-  PlanInput in[kMaxGroup];
+  PlanInput in[kMaxWide];
   int64_t max_lds = 0, total_steps = 0;
   for (int i = 0; i < nwr; ++i) {
     const SpmvProblem& p = *wr[i];
@@ -762,11 +792,11 @@ int launch_wave_row_group(int nwr, const SpmvProblem* const* wr, int b_delta, in
     const int nwaves = block / 64;
     int64_t group_rows = 0;
     for (int i = 0; i < nwr; ++i) group_rows += in[i].rows;
-    int64_t rpw[kMaxGroup];
+    int64_t rpw[kMaxWide];
     for (int i = 0; i < nwr; ++i) {
       rpw[i] = t.spmv_rows_per_wg;
       if (rpw[i] == 0) {
-        const int64_t target = t.spmv_steps_per_wave ? t.spmv_steps_per_wave : kStepsPerWave;
+        const int64_t target = t.spmv_steps_per_wave ? t.spmv_steps_per_wave : nwr > kMaxGroup ? kStepsPerWaveWide : kStepsPerWave;
         const int64_t want = std::max<int64_t>(1, (2 * target + in[i].steps_per_row) / (2 * in[i].steps_per_row));  // nearest
         const int64_t cap = std::max<int64_t>(1, group_rows / ((int64_t)cus * 16));
         rpw[i] = std::min(want, cap) * nwaves;
@@ -776,6 +806,7 @@ int launch_wave_row_group(int nwr, const SpmvProblem* const* wr, int b_delta, in
   }
   if (plan.total_wgs >= (int64_t{1} << 31)) return MACKO_E_UNSUPPORTED;
 
+  SpmvWideArgs wide_args{};
   SpmvGroupArgs args{};
   SpmvGroupHeader head{};
   const int nwaves = plan.block / 64;
@@ -783,9 +814,10 @@ int launch_wave_row_group(int nwr, const SpmvProblem* const* wr, int b_delta, in
   int64_t wg_begin = 0;
   bool simple = true;
   for (int i = 0; i < kMaxGroup; ++i) head.wg_begin[i] = INT32_MAX;
+  for (int i = 0; i < kMaxWide; ++i) wide_args.wg_begin[i] = INT32_MAX;
   for (int i = 0; i < nwr; ++i) {
     const SpmvProblem& p = *wr[i];
-    SpmvMat& m = args.m[i];
+    SpmvMat& m = nwr > kMaxGroup ? wide_args.m[i] : args.m[i];
     m.values = p.values;
     m.deltas = reinterpret_cast<const uint32_t*>(p.deltas);
     m.row_ptr = p.row_ptr;
@@ -799,10 +831,26 @@ int launch_wave_row_group(int nwr, const SpmvProblem* const* wr, int b_delta, in
     const int align = align_knob ? (int)align_knob : (p.pad_nnz / p.rows >= kAlignMinEntries ? kStepAlign : 8);
     m.amask = std::min(std::max(align, 8), kMaxStepAlign) - 1;
     m.pad = 0;
-    head.wg_begin[i] = (int)wg_begin;
+    (nwr > kMaxGroup ? wide_args.wg_begin : head.wg_begin)[i] = (int)wg_begin;
     wg_begin += plan.m[i].nwg;
     // the lean start-up path needs an aligned x whose length is a multiple of 8 and fits the staging registers
     simple = simple && stage_x_is_simple(m.x, m.cols, plan.block);
+  }
+  if (nwr > kMaxGroup) {
+    using KW = void (*)(uint32_t, SpmvWideArgs);
+    KW kfn = nullptr;
+    if (b_val == 8) kfn = simple ? (KW)spmv_wave_row_wide_kernel<true, 4, 8> : (KW)spmv_wave_row_wide_kernel<false, 4, 8>;
+    else if (b_delta == 1) kfn = simple ? (KW)spmv_wave_row_wide_kernel<true, 1, 16> : (KW)spmv_wave_row_wide_kernel<false, 1, 16>;
+    else if (b_delta == 2) kfn = simple ? (KW)spmv_wave_row_wide_kernel<true, 2, 16> : (KW)spmv_wave_row_wide_kernel<false, 2, 16>;
+    else if (b_delta == 4) kfn = simple ? (KW)spmv_wave_row_wide_kernel<true, 4, 16> : (KW)spmv_wave_row_wide_kernel<false, 4, 16>;
+    else if (b_delta == 8) kfn = simple ? (KW)spmv_wave_row_wide_kernel<true, 8, 16> : (KW)spmv_wave_row_wide_kernel<false, 8, 16>;
+    if (!kfn) return MACKO_E_UNSUPPORTED;
+    int st = set_lds_limit(kfn, max_lds);
+    if (st != MACKO_OK) return st;
+    hipLaunchKernelGGL(kfn, dim3((unsigned)plan.total_wgs), dim3(plan.block), (size_t)max_lds, stream,
+                       (uint32_t)head.inv_nwaves | ((uint32_t)nwaves << 17), wide_args);
+    hipError_t e = hipGetLastError();
+    return e == hipSuccess ? MACKO_OK : hip_fail(e);
   }
   // Two steps of loads in flight per wavefront are enough at 16+ wavefronts per
   // compute unit, and the smaller loop body matters when a wavefront runs it only
@@ -979,15 +1027,26 @@ int launch_spmv_chain(int n_phases, const int* sizes, const SpmvProblem* problem
   return e == hipSuccess ? MACKO_OK : hip_fail(e);
 }
 
-int launch_spmv_group(int n, const SpmvProblem* problems, hipStream_t stream) {
-  if (n < 1 || n > kMaxGroup) return MACKO_E_INVALID_ARG;
+namespace {
+
+bool wants_wave_row(const SpmvProblem& p) {
   const Tuning& t = tuning();
-  auto wants_wave_row = [&](const SpmvProblem& p) {
-    if (p.rows == 0 || p.pad_nnz == 0) return false;
-    if (spmv_lds_bytes(p.cols, p.b_delta) > kMaxLdsBytes) return false;
-    if (t.spmv_kernel != 0) return t.spmv_kernel == 2;
-    return p.pad_nnz / p.rows >= kWaveRowMinEntries;
-  };
+  if (p.rows == 0 || p.pad_nnz == 0) return false;
+  if (spmv_lds_bytes(p.cols, p.b_delta) > kMaxLdsBytes) return false;
+  if (t.spmv_kernel != 0) return t.spmv_kernel == 2;
+  return p.pad_nnz / p.rows >= kWaveRowMinEntries;
+}
+
+}  // namespace
+
+int spmv_launch_class(const SpmvProblem& p) {
+  if (p.b_val == 8) return p.pad_nnz > 0 && p.b_delta == 4 && spmv_lds_bytes(p.cols, 4) <= kMaxLdsBytes ? 8 * 16 : 0;
+  return wants_wave_row(p) ? p.b_delta : 0;
+}
+
+int launch_spmv_group(int n, const SpmvProblem* problems, hipStream_t stream) {
+  if (n < 1 || n > kMaxWide) return MACKO_E_INVALID_ARG;
+  const Tuning& t = tuning();
   // matrices that do not go into a grouped wave-per-row launch
   for (int i = 0; i < n; ++i) {
     const SpmvProblem& p = problems[i];
@@ -1008,7 +1067,7 @@ int launch_spmv_group(int n, const SpmvProblem* problems, hipStream_t stream) {
   }
   // one grouped launch per code width
   for (int bd : {4, 2, 8, 1}) {
-    const SpmvProblem* wr[kMaxGroup];
+    const SpmvProblem* wr[kMaxWide];
     int nwr = 0;
     for (int i = 0; i < n; ++i)
       if (problems[i].b_delta == bd && problems[i].b_val == 16 && wants_wave_row(problems[i])) wr[nwr++] = &problems[i];
@@ -1018,7 +1077,7 @@ int launch_spmv_group(int n, const SpmvProblem* problems, hipStream_t stream) {
   }
   // and one for the matrices with 8-bit values
   {
-    const SpmvProblem* wr[kMaxGroup];
+    const SpmvProblem* wr[kMaxWide];
     int nwr = 0;
     for (int i = 0; i < n; ++i)
       if (problems[i].b_val == 8 && problems[i].rows > 0 && problems[i].pad_nnz > 0) wr[nwr++] = &problems[i];

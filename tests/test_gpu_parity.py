@@ -1566,3 +1566,27 @@ def test_decode_device_windows(kind, rows, cols, density, shift):
     got = buf.cpu().numpy()
     assert np.array_equal(got[:, shift:shift + cols].view(W.dtype), W)
     assert (got[:, :shift] == 9).all() and (got[:, shift + cols:] == 9).all()
+
+
+@pytest.mark.parametrize("kind", ["b1", "b2", "b4", "b8", "fp8"])
+@pytest.mark.parametrize("n", [9, 17, 32, 33, 65])
+def test_spmv_many_wide_launches(kind, n):
+    """More than 8 products of one code width: up to 32 in one launch, over ragged shapes (column counts that the lean
+    staging of x does not take among them) and a matrix without rows; the arithmetic per row is that of a single launch."""
+    rng = np.random.default_rng(n)
+    mats, xs = [], []
+    for i in range(n):
+        rows, cols = (0, 700) if i == 4 else (int(rng.integers(1, 90)), int(rng.integers(700, 3000)))
+        cols = cols // 8 * 8 if kind == "b4" else cols
+        W = (rng.standard_normal((rows, cols)) * (rng.random((rows, cols)) < 0.6)).astype(np.float16)
+        if kind == "fp8":
+            mats.append(M.encode_fp8(wl.fp8_values_of(W.view(np.uint16)) if rows else W.astype(np.uint8)).to_device())
+        else:
+            mats.append(M.encode(W, int(kind[1])).to_device())
+        xs.append(torch.from_numpy(rng.standard_normal(cols).astype(np.float16)).cuda())
+    ys = [torch.full((m.rows,), 7.0, dtype=torch.float16, device="cuda") for m in mats]
+    M.SpmvMany(mats, xs, ys).launch()
+    want = [m.spmv(x) for m, x in zip(mats, xs)]
+    torch.cuda.synchronize()
+    for i in range(n):
+        assert torch.equal(ys[i], want[i]), (kind, n, i)

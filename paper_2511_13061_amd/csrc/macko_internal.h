@@ -67,8 +67,17 @@ struct GemvProblem {
 };
 // n independent products, as few kernel launches as the shapes allow (1 <= n <= kMaxGroup; kMaxWide for the sparse product)
 int launch_spmv_group(int n, const SpmvProblem* problems, hipStream_t stream);
-// 0: the product does not take the wave-per-row kernel; products with the same other number fit one launch
-int spmv_launch_class(const SpmvProblem& p);
+// Rows of at least this many stored entries on average take the wave-per-row kernel (a step
+// covers 512 entries; below about 40 % use of a step the sub-wave kernel wins: measured
+// crossover between 133 and 247 entries per row on 36864 x 12288 at 98-99 % sparsity).
+constexpr int64_t kWaveRowMinEntries = 192;
+// 0: the product may need a launch of its own; products with the same other number fit one launch of the wave-per-row kernel
+// (an x of up to 64 K columns fits LDS with every code width)
+inline int spmv_launch_class(const SpmvProblem& p) {
+  if (p.rows == 0 || p.pad_nnz == 0 || p.cols > 65536 || tuning().spmv_kernel != 0) return 0;
+  if (p.b_val == 8) return p.b_delta == 4 ? 8 * 16 : 0;
+  return p.pad_nnz / p.rows >= kWaveRowMinEntries ? p.b_delta : 0;
+}
 int launch_gemv_group(int n, const GemvProblem* problems, hipStream_t stream);
 // phases of products in one launch, phase p + 1 after phase p: sizes[p] products in phase p, listed in
 // phase order; `scratch` is chain_scratch_bytes() of zeroed device memory that the launch leaves zeroed

@@ -598,10 +598,6 @@ constexpr int64_t kStepsPerWave = 8;
 // is long enough for larger ones (14 products of two 13B-shaped layers, us for 8 / 12 / 16 / 24 steps: 2-bit codes
 // 157 / 121 / 120 / 121, 4-bit codes 132 / 126 / 126 / 128)
 constexpr int64_t kStepsPerWaveWide = 16;
-// rows of at least this many stored entries on average take the wave-per-row kernel (a step
-// covers 512 entries; below about 40 % use of a step the sub-wave kernel wins: measured
-// crossover between 133 and 247 entries per row on 36864 x 12288 at 98-99 % sparsity)
-constexpr int64_t kWaveRowMinEntries = 192;
 // x copies of at least this many bytes make a matrix "wide" for the launch planner
 constexpr int64_t kWideLdsBytes = 36 * 1024;
 // widest x that is staged once per 256-thread workgroup (see the row-length rule in launch_wave_row_group)
@@ -1027,26 +1023,15 @@ int launch_spmv_chain(int n_phases, const int* sizes, const SpmvProblem* problem
   return e == hipSuccess ? MACKO_OK : hip_fail(e);
 }
 
-namespace {
-
-bool wants_wave_row(const SpmvProblem& p) {
-  const Tuning& t = tuning();
-  if (p.rows == 0 || p.pad_nnz == 0) return false;
-  if (spmv_lds_bytes(p.cols, p.b_delta) > kMaxLdsBytes) return false;
-  if (t.spmv_kernel != 0) return t.spmv_kernel == 2;
-  return p.pad_nnz / p.rows >= kWaveRowMinEntries;
-}
-
-}  // namespace
-
-int spmv_launch_class(const SpmvProblem& p) {
-  if (p.b_val == 8) return p.pad_nnz > 0 && p.b_delta == 4 && spmv_lds_bytes(p.cols, 4) <= kMaxLdsBytes ? 8 * 16 : 0;
-  return wants_wave_row(p) ? p.b_delta : 0;
-}
-
 int launch_spmv_group(int n, const SpmvProblem* problems, hipStream_t stream) {
   if (n < 1 || n > kMaxWide) return MACKO_E_INVALID_ARG;
   const Tuning& t = tuning();
+  auto wants_wave_row = [&](const SpmvProblem& p) {
+    if (p.rows == 0 || p.pad_nnz == 0) return false;
+    if (spmv_lds_bytes(p.cols, p.b_delta) > kMaxLdsBytes) return false;
+    if (t.spmv_kernel != 0) return t.spmv_kernel == 2;
+    return p.pad_nnz / p.rows >= kWaveRowMinEntries;
+  };
   // matrices that do not go into a grouped wave-per-row launch
   for (int i = 0; i < n; ++i) {
     const SpmvProblem& p = problems[i];

@@ -175,9 +175,28 @@ def _host_u16_matrix(dense) -> np.ndarray:
     return a
 
 
+# torch, once it has been needed, and its way to the current stream's handle without a Stream object: that object takes
+# 2.7 us to make, as long as the launch itself (None where this torch does not have it)
+_torch = None
+_raw_stream = None
+_current_device = None
+
+
+def _need_torch():
+    global _torch, _raw_stream, _current_device
+    if _torch is None:
+        import torch
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        _current_device = getattr(torch._C, "_cuda_getDevice", None)
+        _torch = torch
+    return _torch
+
+
 def _stream_ptr(stream) -> int:
     if stream is None:
-        import torch
+        torch = _torch or _need_torch()
+        if _raw_stream is not None and _current_device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_current_device())
         return int(torch.cuda.current_stream().cuda_stream)
     if isinstance(stream, int):
         return stream
@@ -195,6 +214,7 @@ class MackoMatrix:
         self._h = ctypes.c_void_p(handle)
         self.report = report
         self._keep = []          # torch tensors that back the device arrays
+        self._shape = None       # (rows, cols, bits per value), asked for once: a handle never changes them
 
     # -- lifetime ---------------------------------------------------------
     def destroy(self) -> None:
@@ -202,6 +222,13 @@ class MackoMatrix:
             load_library().macko_destroy(self._h)
             self._h = ctypes.c_void_p(None)
             self._keep = []
+            self._shape = None
+
+    def _dims(self):
+        if self._shape is None:
+            rep = self.get_report()
+            self._shape = (rep.rows, rep.cols, rep.b_val)
+        return self._shape
 
     def __del__(self):
         try:
@@ -309,10 +336,10 @@ class MackoMatrix:
     def decode_device(self, dense_dev=None, stream=None):
         """macko_decode_device: the dense matrix back, as a torch CUDA tensor [rows, cols] (float16, or
         uint8 bit patterns for a matrix with 8-bit values)."""
-        import torch
+        torch = _need_torch()
         if dense_dev is None:
-            dt = torch.uint8 if self.get_report().b_val == 8 else torch.float16
-            dense_dev = torch.empty((self.rows, self.cols), dtype=dt, device="cuda")
+            rows, cols, b_val = self._dims()
+            dense_dev = torch.empty((rows, cols), dtype=torch.uint8 if b_val == 8 else torch.float16, device="cuda")
         if dense_dev.dim() != 2 or (dense_dev.shape[1] > 1 and dense_dev.stride(1) != 1):
             raise ValueError("dense_dev must be a row-major [rows, >= cols] tensor")
         ld = dense_dev.stride(0) if dense_dev.shape[0] > 1 else max(dense_dev.shape[1], 1)
@@ -322,21 +349,22 @@ class MackoMatrix:
 
     def spmv(self, x_dev, y_dev=None, stream=None):
         """y = W x.  x_dev: torch float16 CUDA tensor [cols]; returns y_dev [rows]."""
-        import torch
         if y_dev is None:
-            y_dev = torch.empty(self.rows, dtype=torch.float16, device=x_dev.device)
-        _check(load_library().macko_spmv(self._h, _dev_ptr(x_dev), _dev_ptr(y_dev), _stream_ptr(stream)),
-               "macko_spmv")
+            torch = _torch or _need_torch()
+            y_dev = torch.empty((self._shape or self._dims())[0], dtype=torch.float16, device=x_dev.device)
+        st = (_lib or load_library()).macko_spmv(self._h, x_dev.data_ptr(), y_dev.data_ptr(), _stream_ptr(stream))
+        if st != 0:
+            _check(st, "macko_spmv")
         return y_dev
 
     def spmm(self, X_dev, Y_dev=None, stream=None):
         """Y[b] = W X[b] for a torch float16 CUDA matrix X_dev [batch, cols]; returns [batch, rows]."""
-        import torch
+        torch = _need_torch()
         if X_dev.dim() != 2 or X_dev.stride(1) != 1:
             raise ValueError("X_dev must be a row-major [batch, cols] tensor")
         batch = X_dev.shape[0]
         if Y_dev is None:
-            Y_dev = torch.empty((batch, self.rows), dtype=torch.float16, device=X_dev.device)
+            Y_dev = torch.empty((batch, self._dims()[0]), dtype=torch.float16, device=X_dev.device)
         _check(load_library().macko_spmm(self._h, batch, _dev_ptr(X_dev), X_dev.stride(0) if batch > 1 else max(X_dev.shape[1], 1),
                                          _dev_ptr(Y_dev), Y_dev.stride(0) if batch > 1 else max(Y_dev.shape[1], 1),
                                          _stream_ptr(stream)), "macko_spmm")

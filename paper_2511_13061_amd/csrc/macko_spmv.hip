@@ -13,6 +13,7 @@
 #include "macko_plan.h"
 
 #include <climits>
+#include <cstring>
 #include <mutex>
 
 namespace macko {
@@ -802,7 +803,7 @@ int launch_wave_row_group(int nwr, const SpmvProblem* const* wr, int b_delta, in
   }
   if (plan.total_wgs >= (int64_t{1} << 31)) return MACKO_E_UNSUPPORTED;
 
-  SpmvWideArgs wide_args{};
+  SpmvWideArgs wide_args;                              // filled in for more than kMaxGroup matrices only
   SpmvGroupArgs args{};
   SpmvGroupHeader head{};
   const int nwaves = plan.block / 64;
@@ -810,7 +811,10 @@ int launch_wave_row_group(int nwr, const SpmvProblem* const* wr, int b_delta, in
   int64_t wg_begin = 0;
   bool simple = true;
   for (int i = 0; i < kMaxGroup; ++i) head.wg_begin[i] = INT32_MAX;
-  for (int i = 0; i < kMaxWide; ++i) wide_args.wg_begin[i] = INT32_MAX;
+  if (nwr > kMaxGroup) {
+    std::memset(&wide_args, 0, sizeof(wide_args));
+    for (int i = 0; i < kMaxWide; ++i) wide_args.wg_begin[i] = INT32_MAX;
+  }
   for (int i = 0; i < nwr; ++i) {
     const SpmvProblem& p = *wr[i];
     SpmvMat& m = nwr > kMaxGroup ? wide_args.m[i] : args.m[i];

@@ -80,7 +80,8 @@ inline bool plan_resident(Plan& plan, int n, const PlanInput* in, int cus, int f
     max_lds = std::max(max_lds, in[i].lds_bytes);
   }
   if (total_rows < (int64_t)cus * 4) return false;
-  const int middle = total_work <= 4 * total_rows && total_work >= (int64_t)cus * 128 ? 22 : 20;
+  const bool enough = total_work >= (int64_t)cus * 128 || total_rows >= (int64_t)cus * 64;
+  const int middle = total_work <= 4 * total_rows && enough ? 22 : 20;
   double best_cost = 0;
   int best_k = 0, best_nw = 0;
   PlanMat best_m[kMaxWide] = {};
@@ -120,10 +121,11 @@ inline bool plan_resident(Plan& plan, int n, const PlanInput* in, int cus, int f
       // all resident wavefronts share the memory system: time ~ slowest share x wavefronts;
       // a mild preference for 16..24 wavefronts per compute unit and for fewer, larger workgroups.
       // Where 16 and 24 split the rows equally well: rows of up to 4 steps take 24, since each row ends in a reduction
-      // that only other wavefronts can cover (microseconds for 16 / 24: 12288x12288, 95 % pruned, 9.7 / 8.9; 24576x2048,
-      // 70 %, 11.6 / 11.0; 12288x4096, 70 %, 9.6 / 9.3).  Longer rows take 16 (12288x4096, 30 %, 16.3 / 16.5), and so do
-      // launches of fewer than 128 steps per compute unit, where the start of 24 wavefronts shows (12288x12288, 95 %,
-      // 8-bit codes, 7.9 / 8.0; 12288x2048, 60 %, 7.38 / 7.41)
+      // that only other wavefronts can cover (microseconds for 16 / 24: 12288x12288, 95 % pruned, 9.7 / 8.9, with 8-bit
+      // values 9.1 / 8.2; 24576x2048, 70 %, 11.6 / 11.0; 12288x4096, 70 %, 9.6 / 9.3; 24576x4096, 90 %, 10.7 / 10.5, with
+      // 8-bit values 10.5 / 10.0).  Longer rows take 16 (12288x4096, 30 %, 16.3 / 16.5), and so do launches of few rows
+      // of one or two steps, where the start of 24 wavefronts shows (12288x12288, 95 %, 8-bit codes, 7.9 / 8.0;
+      // 12288x2048, 60 %, 7.38 / 7.41)
       double cost = (double)worst * waves;
       cost *= 1.0 + 0.002 * std::abs(waves - middle) + 0.001 * k;
       if (best_k == 0 || cost < best_cost) {

@@ -1592,10 +1592,10 @@ def test_spmv_many_wide_launches(kind, n):
         assert torch.equal(ys[i], want[i]), (kind, n, i)
 
 
-@pytest.mark.parametrize("rows,cols", [(12287, 1500), (12288, 1500), (12289, 1500), (12288, 900), (12288, 2600)])
+@pytest.mark.parametrize("rows,cols", [(12287, 1500), (12288, 1500), (12289, 1500), (12288, 900), (12288, 2600), (24576, 700)])
 def test_spmv_wavefronts_per_compute_unit_do_not_change_the_result(rows, cols):
     """Shapes on both sides of the rule that takes 24 instead of 16 wavefronts per compute unit (rows of up to 4 steps of
-    512 entries, at least 128 steps per compute unit): a row is one wavefront's, whichever split is taken."""
+    512 entries, at least 128 steps or 64 rows per compute unit): a row is one wavefront's, whichever split is taken."""
     x = wl.x_vector(cols, 5, 1)
     W = wl.bernoulli(rows, cols, 0.1, 0.02, 5, rows)
     y = spmv_case(W, x)

@@ -91,7 +91,7 @@ constexpr int chain_error_word() { return 25 * 64; }
 int launch_spmm(const SpmvProblem& p, const void* X, int64_t ldx, void* Y, int64_t ldy, int batch,
                 hipStream_t stream);
 // the same on the matrix cores: which calls it can serve (any batch up to 64), and the launch
-bool spmm_tile_serves(const SpmvProblem& p, const void* X, int64_t ldx, int batch);
+bool spmm_tile_serves(const SpmvProblem& p, int64_t ldx);
 int launch_spmm_tile(const SpmvProblem& p, const uint16_t* X, int64_t ldx, uint16_t* Y, int64_t ldy, int batch,
                      hipStream_t stream);
 // device-side expansion: column index of every stored entry; the dense matrix back

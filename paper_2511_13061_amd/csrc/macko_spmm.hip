@@ -333,7 +333,7 @@ int launch_spmm(const SpmvProblem& p, const void* X, int64_t ldx, void* Y, int64
   // 8.8 and 9.8; 11008 x 4096: 21.5 and 21.7, at 90 % 12.3 and 15.9), except where 8 vectors do not fit LDS (4096 x 11008:
   // 27.4 -> 19.6, at 90 % 13.4 -> 13.3) and where the rows are short and there are enough of them to fill the chip with
   // tiles (14336 x 512 at 50 %: 21.2 -> 11.8, 4096 x 4096 at 96 %: 9.0 -> 7.4; but 512 x 512: 4.1 -> 5.1).
-  if (spmm_tile_serves(p, X, ldx, batch) &&
+  if (spmm_tile_serves(p, ldx) &&
       (batch > 8 || (batch > 4 && (long_rows ? 8 * one > limit : p.rows >= (int64_t)device_cu_count() * 16))))
     return launch_spmm_tile(p, Xp, ldx, Yp, ldy, batch, stream);
   int done = 0;

@@ -170,10 +170,14 @@ spmm_tile_kernel(const TileArgs a) {
   // bytes of one vector, load r from vector 4 (lane / 4 % 4) + r, and exchange 16-byte blocks afterwards.
   const bool odd_lane = lane & 1, high_lane = lane & 2;
   // The vectors are one buffer (base rounded down to 4 bytes): what lies behind its end, vectors past the batch among
-  // it, reads as zero; what lies between two vectors is cleared where it is used.  The end is checked per 4 bytes, and
-  // the last element of an odd number of columns is the first half of such a piece: 2 bytes more (spmm_tile_serves).
+  // it, reads as zero; what lies between two vectors is cleared where it is used.  The end is checked per 4 bytes, so
+  // the buffer ends in front of the last element of an odd number of columns, which would be half of such a piece: the
+  // last vector's is loaded by itself and put in its place where the vectors end.  (The other vectors' are inside: the
+  // element behind them is the next vector's, or lies between the two; a single column is not served.)
   const uint32_t xmis = (uint32_t)(reinterpret_cast<uintptr_t>(a.X) & 2);
-  const uint32_t xbytes = (uint32_t)(((int64_t)(a.batch - 1) * a.ldx + cols) * 2) + xmis + 2u * (cols & 1);
+  const uint32_t xbytes = (uint32_t)(((int64_t)(a.batch - 1) * a.ldx + (cols & ~1)) * 2) + xmis;
+  uint32_t last_x = 0u;
+  if (cols & 1) last_x = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.X[(int64_t)(a.batch - 1) * a.ldx + cols - 1]);
   const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<unsigned char*>(reinterpret_cast<const unsigned char*>(a.X) - xmis), 0, (int)xbytes, 0x00020000);
   const uint32_t ldx2 = 2u * (uint32_t)a.ldx;
@@ -245,6 +249,17 @@ spmm_tile_kernel(const TileArgs a) {
             for (int t = 0; t < NT; ++t)
 #pragma unroll
               for (int r = 0; r < 4; ++r) b[g][t][r][i] &= mask;
+          }
+          if (cols & 1) {                              // the last element of the last vector (left is odd here)
+            const int last = a.batch - 1 - 4 * ((lane >> 2) & 3);        // load r of tile t is vector `last` if 16 t + r is
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const uint32_t e = left == 2 * i + 1 ? last_x : 0u;
+#pragma unroll
+              for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) b[g][t][r][i] |= last == 16 * t + r ? e : 0u;
+            }
           }
         }
 #pragma unroll
@@ -430,12 +445,10 @@ int launch_tile_bd(const TileArgs& a, hipStream_t stream) {
 
 }  // namespace
 
-bool spmm_tile_serves(const SpmvProblem& p, const void* X, int64_t ldx, int batch) {
+bool spmm_tile_serves(const SpmvProblem& p, int64_t ldx) {
   if (p.b_delta > 4 || p.pad_nnz == 0 || p.rows == 0) return false;   // the pad of the tile holds 4-bit deltas
-  if (ldx >= (int64_t{1} << 24)) return false;         // vectors are addressed with 32-bit byte offsets
-  // with an odd number of columns the kernel reads 2 bytes behind the last vector: not across a page
-  const uintptr_t x_end = reinterpret_cast<uintptr_t>(X) + 2 * (uintptr_t)((batch - 1) * ldx + p.cols);
-  return p.cols % 2 == 0 || x_end % 4096 != 0;
+  if (p.cols < 2) return false;                        // see the end of the vectors' buffer in the kernel
+  return ldx < (int64_t{1} << 24);                     // vectors are addressed with 32-bit byte offsets
 }
 
 int launch_spmm_tile(const SpmvProblem& p, const uint16_t* X, int64_t ldx, uint16_t* Y, int64_t ldy, int batch,

@@ -1602,3 +1602,38 @@ def test_spmv_wavefronts_per_compute_unit_do_not_change_the_result(rows, cols):
     check_y(y, W, x, f"{rows}x{cols}")
     for block in (512, 768):
         assert torch.equal(y, spmv_case(W, x, spmv_resident=2, spmv_block=block)), (rows, cols, block)
+
+
+@pytest.mark.parametrize("kind", ["b1", "b2", "b4", "fp8"])
+@pytest.mark.parametrize("rows,cols,batch,skip", [(70, 1, 9, 0), (40, 3, 9, 0), (33, 127, 64, 0), (50, 129, 33, 2), (20, 2047, 12, 0),
+                                                  (20, 2049, 17, 0), (37, 4097, 16, 0), (37, 4099, 50, 6), (16, 511, 7, 0)])
+def test_spmm_odd_columns_wherever_the_vectors_end(kind, rows, cols, batch, skip):
+    """The vectors of an odd number of columns end in the middle of 4 bytes.  Whether they end at a page (4096 bytes), one
+    element in front of or behind it, and whatever lies behind them, the result is the same bit for bit."""
+    rng = np.random.default_rng(rows + cols)
+    W = (rng.standard_normal((rows, cols)) * (rng.random((rows, cols)) < 0.6)).astype(np.float16)
+    W[:, -1] = rng.standard_normal(rows).astype(np.float16)                # every row stores the last column
+    if kind == "fp8":
+        W8 = wl.fp8_values_of(W.view(np.uint16))
+        W64 = oracle.fp8_to_double(np.arange(256, dtype=np.uint8))[W8]
+        m = M.encode_fp8(W8).to_device()
+    else:
+        W64 = W.astype(np.float64)
+        m = M.encode(W, int(kind[1])).to_device()
+    X = rng.standard_normal((batch, cols)).astype(np.float16)
+    ldx = cols + skip
+    length = (batch - 1) * ldx + cols
+    got = []
+    for end in (0, 1, 2, -1, 1000):                                        # elements behind a page
+        buf = torch.full((length + 6144,), float("nan"), dtype=torch.float16, device="cuda")
+        at = ((length + 2047) // 2048 * 2048 + 2048 - length + end) - (buf.data_ptr() % 4096) // 2
+        assert 0 <= at and (buf.data_ptr() + 2 * (at + length - end)) % 4096 == 0
+        Xd = buf[at:at + length].as_strided((batch, cols), (ldx, 1))
+        Xd.copy_(torch.from_numpy(X))
+        got.append(m.spmm(Xd))
+    torch.cuda.synchronize()
+    ref, mag = _batch_reference(W64, X.astype(np.float64))
+    bound = np.abs(ref) * 2.0 ** -11 + 2.0 ** -25 + mag * cols * 2.0 ** -24        # as in test_spmm_tile_edges
+    assert np.max(np.abs(got[0].cpu().numpy().astype(np.float64) - ref) / bound) <= 1.01
+    for y in got[1:]:
+        assert torch.equal(y, got[0])

@@ -93,6 +93,7 @@ __device__ __forceinline__ void quad_transpose(u32x4 (&b)[4], bool odd, bool hig
 // The results of one row for the vectors of `vectors` (bit b: vector b), entry by entry.  The product with the expanded
 // row multiplies zeros with every element of x; where that gives something else than leaving them out, i.e. where
 // x holds an infinity or a NaN, the result of the product is not finite and this takes its place.  Rare and slow.
+// An entry at or beyond the last column (a wrong encoding) counts for nothing, as in the product.
 template <int BD, int VB>
 __device__ __forceinline__ void tile_row_by_entries(const TileArgs& a, int row, uint32_t start, uint32_t end, uint64_t vectors) {
   const int lane = threadIdx.x & 63;
@@ -116,8 +117,11 @@ __device__ __forceinline__ void tile_row_by_entries(const TileArgs& a, int row, 
       if (e0 < start) base2 = -(int)w.through((int)(start - e0) - 1);
       const int lanebase = base2 + (int)(incl - tot);
 #define MACKO_ENTRY(K)                                                              \
-  if (e + K >= start && e + K < end)                                                \
-    acc = fmaf(v.template get<K>(), f16_bits_to_f32(x[(lanebase + w.template offset<K>()) >> 1]), acc);
+  {                                                                                 \
+    const int col = (lanebase + w.template offset<K>()) >> 1;                       \
+    if (e + K >= start && e + K < end && (uint32_t)col < (uint32_t)a.cols)          \
+      acc = fmaf(v.template get<K>(), f16_bits_to_f32(x[col]), acc);                \
+  }
       MACKO_ENTRY(0) MACKO_ENTRY(1) MACKO_ENTRY(2) MACKO_ENTRY(3) MACKO_ENTRY(4) MACKO_ENTRY(5) MACKO_ENTRY(6) MACKO_ENTRY(7)
 #undef MACKO_ENTRY
       base2 += (int)__builtin_amdgcn_readlane((int)incl, 63);
@@ -277,6 +281,11 @@ spmm_tile_kernel(const TileArgs a) {
             acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, __builtin_bit_cast(half8, b[g][t][r]), acc[t], 0, 0, 0);
           if (NT > 2) __builtin_amdgcn_sched_barrier(0);
         }
+      } else {
+        // Groups behind the last column are not multiplied.  What a wrong encoding's row puts there would be part of the
+        // next tile's row: a right one's leaves zeros.
+#pragma unroll
+        for (int r = 0; r < 4; ++r) *reinterpret_cast<half8*>(arow + 256 * g + 16 * r) = half8{0, 0, 0, 0, 0, 0, 0, 0};
       }
     }
     k0 += kWindow;

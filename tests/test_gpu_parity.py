@@ -1637,3 +1637,37 @@ def test_spmm_odd_columns_wherever_the_vectors_end(kind, rows, cols, batch, skip
     assert np.max(np.abs(got[0].cpu().numpy().astype(np.float64) - ref) / bound) <= 1.01
     for y in got[1:]:
         assert torch.equal(y, got[0])
+
+
+def _wrap_with_fewer_columns(W, cols, b_delta):
+    """W on the device, encoded, and its arrays adopted again as a matrix of `cols` columns: the entries behind them
+    are an encoding's that macko_check_device rejects."""
+    m = M.encode_device(W, b_delta=b_delta)
+    bufs = [torch.from_numpy(a.copy()).cuda() for a in m.fetch_device()]
+    return M.wrap_device(W.shape[0], cols, m.report.pad_nnz, *bufs, b_delta=b_delta)
+
+
+@pytest.mark.parametrize("b_delta", [1, 4])
+@pytest.mark.parametrize("cols,beyond,batch", [(2112, 500, 20), (4200, 300, 9), (300, 900, 40)])
+def test_spmm_tile_entries_beyond_the_last_column_stay_in_their_row(b_delta, cols, beyond, batch):
+    """Rows that run past the last column (columns between the last one and the end of the tile's window) count there for
+    nothing, also where a vector holds an infinity, and spoil no row of the next tile (4200 rows: two tiles a workgroup)."""
+    rows = 4200
+    g = torch.Generator(device="cuda").manual_seed(cols + batch)
+    W = torch.empty((rows, cols + beyond), dtype=torch.float16, device="cuda").normal_(0.0, 0.02, generator=g)
+    W.mul_(torch.rand(W.shape, generator=g, device="cuda") < 0.5)
+    W[1::3, cols:] = 0
+    w = _wrap_with_fewer_columns(W, cols, b_delta)
+    X = torch.empty((batch, cols), dtype=torch.float16, device="cuda").normal_(0.0, 1.0, generator=g)
+    X[2, 5] = float("inf")
+    Y = w.spmm(X)
+    torch.cuda.synchronize()
+    Wc, Y = W[:, :cols].double().cpu().numpy(), Y.cpu().numpy().astype(np.float64)
+    X = X.double().cpu().numpy()
+    stored = Wc[:, 5] != 0
+    # rows that store nothing at column 5 are as if it held 0 (padding entries of value 0 may lie there with 1-bit codes)
+    ref = np.where(np.isfinite(X), X, 0.0) @ Wc.T
+    fine = np.ones(Y.shape, dtype=bool)
+    fine[2] = ~stored if b_delta == 4 else np.isfinite(Y[2])
+    assert np.allclose(Y[fine], ref[fine], atol=2e-3, rtol=2e-3)
+    assert not np.isfinite(Y[2][stored]).any()

@@ -248,12 +248,14 @@ decode_windows_kernel(const void* __restrict__ values, const uint32_t* __restric
     out -= skew;
     const int64_t row_end = skew + (int64_t)cols * EB;       // in bytes from the aligned start
     int64_t at = 0;                                          // first byte of the window
+    bool beyond = false;                                     // entries may lie behind the row's end (a wrong encoding)
     auto flush = [&]() {
       // the window is private to the wavefront, whose LDS operations complete in order
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       const int from = at == 0 ? skew : 0, to = (int)min(row_end - at, (int64_t)kWindowBytes);       // the row's bytes
+      const int clear_to = beyond ? kWindowBytes : to;       // what was put behind a right row's end is zeros
       unsigned char* to_mem = out + at;
       if ((from | to) & 15) {                                // values of the row in a 16-byte piece that is not all its own
         constexpr int kPiece = 16 / EB;
@@ -263,7 +265,7 @@ decode_windows_kernel(const void* __restrict__ values, const uint32_t* __restric
           else to_mem[p] = win[p];
         }
       }
-      for (int lo = 16 * lane; lo < to; lo += 1024) {        // behind the row's end the window holds zeros
+      for (int lo = 16 * lane; lo < clear_to; lo += 1024) {
         const u32x4 t = win4[lo >> 4];
         win4[lo >> 4] = u32x4{0, 0, 0, 0};
         if (lo >= from && lo + 16 <= to) __builtin_nontemporal_store(t, reinterpret_cast<u32x4*>(to_mem + lo));
@@ -309,6 +311,9 @@ decode_windows_kernel(const void* __restrict__ values, const uint32_t* __restric
           }
           const int lanebase = base2 + (int)(incl - tot);
           base2 += (int)__builtin_amdgcn_readlane((int)incl, 63);
+          // positions only grow, so a row that runs past its end does so by its last step; the lane that holds its last
+          // entry counts the codes behind it as well, which costs a right row that ends there a clearing too many
+          if (step == nsteps - 1) beyond = __any(e0 < end && skew + ((lanebase + (int)tot) >> (VB == 8 ? 1 : 0)) > row_end);
           for (;;) {
             const int rel = skew + (lanebase >> (VB == 8 ? 1 : 0)) - (int)at;    // the lane's first column in the window
             if (BD != 8) {

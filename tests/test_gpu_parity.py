@@ -1671,3 +1671,17 @@ def test_spmm_tile_entries_beyond_the_last_column_stay_in_their_row(b_delta, col
     fine[2] = ~stored if b_delta == 4 else np.isfinite(Y[2])
     assert np.allclose(Y[fine], ref[fine], atol=2e-3, rtol=2e-3)
     assert not np.isfinite(Y[2][stored]).any()
+
+
+@pytest.mark.parametrize("b_delta", [1, 4, 8])
+@pytest.mark.parametrize("rows,cols,beyond", [(9000, 10300, 1500), (9000, 5001, 700), (300, 777, 90)])
+def test_decode_device_entries_beyond_the_last_column_are_left_out(rows, cols, beyond, b_delta):
+    """Rows that run past the last column lose what lies there and spoil no other row (9000 rows: a wavefront assembles
+    several rows in the same window)."""
+    g = torch.Generator(device="cuda").manual_seed(cols)
+    W = torch.empty((rows, cols + beyond), dtype=torch.float16, device="cuda").normal_(0.0, 0.02, generator=g)
+    W.mul_(torch.rand(W.shape, generator=g, device="cuda") < 0.06)
+    W += 0.0                                                               # no -0
+    W[1::3, cols:] = 0
+    w = _wrap_with_fewer_columns(W, cols, b_delta)
+    assert torch.equal(w.decode_device(), W[:, :cols])

@@ -27,7 +27,7 @@ expand_kernel(const uint32_t* __restrict__ deltas, const uint32_t* __restrict__ 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (kExpandBlock / 64) + (threadIdx.x >> 6)));
   const int nwaves = (int)gridDim.x * (kExpandBlock / 64);
-  for (int row = wave; row < rows; row += nwaves) {          // wavefront-uniform
+  for (uint32_t row = wave; row < (uint32_t)rows; row += nwaves) {          // wavefront-uniform
     const uint32_t start = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_ptr[row]);
     const uint32_t end = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_ptr[row + 1]);
     if (end <= start) continue;
@@ -74,10 +74,10 @@ check_kernel(const uint32_t* __restrict__ deltas, const uint32_t* __restrict__ r
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (kExpandBlock / 64) + (threadIdx.x >> 6)));
   const int nwaves = (int)gridDim.x * (kExpandBlock / 64);
-  for (int row = wave; row < rows; row += nwaves) {          // wavefront-uniform
+  for (uint32_t row = wave; row < (uint32_t)rows; row += nwaves) {          // wavefront-uniform
     const uint32_t start = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_ptr[row]);
     const uint32_t end = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_ptr[row + 1]);
-    bool bad = end < start || end > pad_nnz || (row == 0 && start != 0u) || (row == rows - 1 && end != pad_nnz);
+    bool bad = end < start || end > pad_nnz || (row == 0u && start != 0u) || (row == (uint32_t)rows - 1u && end != pad_nnz);
     if (!bad && end > start) {
       const uint32_t a0 = start & ~7u;
       const int nsteps = (int)((end - a0 + 511u) >> 9);
@@ -111,7 +111,7 @@ check_kernel(const uint32_t* __restrict__ deltas, const uint32_t* __restrict__ r
       }
       bad = __any(lane_bad);
     }
-    if (bad && lane == 0) atomicMin(first_bad, (unsigned int)row);
+    if (bad && lane == 0) atomicMin(first_bad, row);
   }
 }
 
@@ -135,7 +135,7 @@ decode_rows_kernel(const void* __restrict__ values, const uint32_t* __restrict__
   const int chunks = (cols * EB + 15) >> 4;                   // 16-byte chunks of the row buffer
   unsigned char* rowbuf = lds + (size_t)wave_in_wg * chunks * 16;
   uint4* rowbuf4 = reinterpret_cast<uint4*>(rowbuf);
-  for (int row = wave; row < rows; row += nwaves) {          // wavefront-uniform
+  for (uint32_t row = wave; row < (uint32_t)rows; row += nwaves) {          // wavefront-uniform
     const uint32_t start = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_ptr[row]);
     const uint32_t end = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_ptr[row + 1]);
     for (int c = lane; c < chunks; c += 64) rowbuf4[c] = make_uint4(0, 0, 0, 0);
@@ -240,7 +240,7 @@ decode_windows_kernel(const void* __restrict__ values, const uint32_t* __restric
   unsigned char* win = lds + wave_in_wg * (kWindowBytes + kMargin) + kMargin;
   u32x4* win4 = reinterpret_cast<u32x4*>(win);
   for (int c = lane; c < kWindowBytes / 16; c += 64) win4[c] = u32x4{0, 0, 0, 0};
-  for (int row = wave; row < rows; row += nwaves) {          // wavefront-uniform
+  for (uint32_t row = wave; row < (uint32_t)rows; row += nwaves) {          // wavefront-uniform
     const uint32_t start = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_ptr[row]);
     const uint32_t end = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_ptr[row + 1]);
     unsigned char* out = static_cast<unsigned char*>(dense) + (int64_t)row * ld * EB;

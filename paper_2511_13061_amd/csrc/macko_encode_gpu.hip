@@ -37,8 +37,10 @@ struct Chunk {
 // Loads only; columns at or beyond `cols` read as +0.  The caller looks at the
 // result two loop iterations later, so the load is in flight behind the work on
 // earlier chunks.  Rows may start at any element: the wide load is an unaligned one where they do (one instruction as well).
+// Rows and columns are counted without a sign: the steps loaded ahead reach 2048 columns behind the last one, whose number
+// may be all but 2^31, and a wavefront's next row may lie as far behind the last row.
 template <bool IN8>
-__device__ __forceinline__ Chunk<IN8> load_chunk(const void* __restrict__ row_v, int col0, int cols) {
+__device__ __forceinline__ Chunk<IN8> load_chunk(const void* __restrict__ row_v, uint32_t col0, uint32_t cols) {
   Chunk<IN8> c;
 #pragma unroll
   for (int k = 0; k < Chunk<IN8>::kWords; ++k) c.u[k] = 0u;
@@ -113,8 +115,8 @@ __device__ __forceinline__ MaskInfo mask_info(unsigned mask) {
 
 // Columns skipped in front of the chunk's first non-zero (0 without one).  `carry` is the position (column + 1, 0 = none) of
 // the last stored entry of the steps already consumed; it is advanced over this step.
-__device__ __forceinline__ int lead_of_chunk(unsigned mask, int col0, int lane, uint32_t* carry) {
-  const uint32_t lastpos = mask ? (uint32_t)(col0 + 32 - __clz((int)mask)) : 0u;
+__device__ __forceinline__ int lead_of_chunk(unsigned mask, uint32_t col0, int lane, uint32_t* carry) {
+  const uint32_t lastpos = mask ? col0 + 32u - (uint32_t)__clz((int)mask) : 0u;
   uint32_t incl = lastpos;
   // where every lane has a non-zero the lane before holds the previous one: no scan
   if (!__all(mask != 0u)) incl = wave_incl_scan_max_u32(lastpos);
@@ -122,7 +124,7 @@ __device__ __forceinline__ int lead_of_chunk(unsigned mask, int col0, int lane, 
   if (lane == 0) prevpos = 0;
   prevpos = max(prevpos, *carry);
   *carry = max(*carry, (uint32_t)__builtin_amdgcn_readlane((int)incl, 63));
-  return mask ? col0 + (__ffs((int)mask) - 1) - (int)prevpos : 0;
+  return mask ? (int)(col0 + (uint32_t)(__ffs((int)mask) - 1) - prevpos) : 0;
 }
 
 // steps of 512 columns loaded ahead
@@ -130,7 +132,7 @@ constexpr int kEncodeAhead = 2;
 
 template <bool IN8, int BD>
 __global__ void __launch_bounds__(256)
-encode_count_kernel(const void* __restrict__ dense, int rows, int cols, int64_t ld,
+encode_count_kernel(const void* __restrict__ dense, uint32_t rows, uint32_t cols, int64_t ld,
                     uint32_t* __restrict__ row_entries, uint32_t* __restrict__ row_nnz) {
   __shared__ uint32_t counts[256];                      // entries from the first non-zero on, by mask (narrow codes)
   if (BD < 3) {
@@ -140,19 +142,19 @@ encode_count_kernel(const void* __restrict__ dense, int rows, int cols, int64_t 
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int nwaves = blockDim.x >> 6;
-  for (int row = blockIdx.x * nwaves + wave; row < rows; row += gridDim.x * nwaves) {
+  for (uint32_t row = blockIdx.x * nwaves + wave; row < rows; row += gridDim.x * nwaves) {
     const void* src = static_cast<const unsigned char*>(dense) + (int64_t)row * ld * (IN8 ? 1 : 2);
     uint32_t carry = 0;
     unsigned entries = 0, nnz = 0;
     Chunk<IN8> ring[kEncodeAhead];
 #pragma unroll
-    for (int j = 0; j < kEncodeAhead; ++j) ring[j] = load_chunk<IN8>(src, 512 * j + lane * 8, cols);
-    for (int base = 0; base < cols; base += 512 * kEncodeAhead) {
+    for (int j = 0; j < kEncodeAhead; ++j) ring[j] = load_chunk<IN8>(src, 512u * j + 8u * lane, cols);
+    for (uint32_t base = 0; base < cols; base += 512u * kEncodeAhead) {
 #pragma unroll
       for (int j = 0; j < kEncodeAhead; ++j) {
-        const int col0 = base + 512 * j + lane * 8;     // steps behind the last column count nothing
+        const uint32_t col0 = base + 512u * j + 8u * lane;     // steps behind the last column count nothing
         const unsigned mask = nonzero_mask<IN8>(ring[j]);
-        ring[j] = load_chunk<IN8>(src, col0 + 512 * kEncodeAhead, cols);
+        ring[j] = load_chunk<IN8>(src, col0 + 512u * kEncodeAhead, cols);
         const int lead = lead_of_chunk(mask, col0, lane, &carry);
         const unsigned n = (unsigned)__popc(mask);
         nnz += n;
@@ -192,11 +194,11 @@ __device__ __forceinline__ unsigned long long wave_incl_scan_u64(unsigned long l
 }
 
 __global__ void __launch_bounds__(1024)
-encode_block_sums_kernel(const uint32_t* __restrict__ row_entries, const uint32_t* __restrict__ row_nnz, int rows,
+encode_block_sums_kernel(const uint32_t* __restrict__ row_entries, const uint32_t* __restrict__ row_nnz, uint32_t rows,
                          BlockSums* __restrict__ sums) {
   __shared__ BlockSums part[16];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int r = blockIdx.x * 1024 + t;
+  const uint32_t r = blockIdx.x * 1024u + t;
   const uint32_t e = r < rows ? row_entries[r] : 0u;
   unsigned long long se = e, sn = r < rows ? row_nnz[r] : 0u;
   unsigned int empty = (r < rows && e == 0) ? 1u : 0u, longest = e;
@@ -316,11 +318,11 @@ encode_block_offsets_kernel(const BlockSums* __restrict__ sums, const uint32_t* 
 }
 
 __global__ void __launch_bounds__(1024)
-encode_row_ptr_kernel(const uint32_t* __restrict__ row_entries, int rows, const unsigned long long* __restrict__ block_off,
+encode_row_ptr_kernel(const uint32_t* __restrict__ row_entries, uint32_t rows, const unsigned long long* __restrict__ block_off,
                       uint32_t* __restrict__ row_ptr, uint32_t total, int b_delta, uint32_t* __restrict__ deltas) {
   __shared__ unsigned long long wave_tot[16];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int r = blockIdx.x * 1024 + t;
+  const uint32_t r = blockIdx.x * 1024u + t;
   const unsigned long long e = r < rows ? row_entries[r] : 0u;
   const unsigned long long incl = wave_incl_scan_u64(e, lane);
   if (lane == 63) wave_tot[wave] = incl;
@@ -361,7 +363,7 @@ constexpr int kFillMargin = 8;                          // entries
 
 template <bool IN8, int BD>
 __global__ void __launch_bounds__(64 * kFillWaves)
-encode_fill_kernel(const void* __restrict__ dense, int rows, int cols, int64_t ld,
+encode_fill_kernel(const void* __restrict__ dense, uint32_t rows, uint32_t cols, int64_t ld,
                    const uint32_t* __restrict__ row_ptr, void* __restrict__ values_v,
                    uint32_t* __restrict__ deltas, uint32_t pad_nnz, uint32_t alloc_nnz) {
   constexpr uint32_t kFull = (1u << BD) - 1u;
@@ -402,7 +404,7 @@ encode_fill_kernel(const void* __restrict__ dense, int rows, int cols, int64_t l
   for (int i = lane; i < kWords + 8; i += 64) stage_c[wave][i] = 0u;
   __syncthreads();
 
-  for (int row = blockIdx.x * kFillWaves + wave; row < rows; row += gridDim.x * kFillWaves) {
+  for (uint32_t row = blockIdx.x * kFillWaves + wave; row < rows; row += gridDim.x * kFillWaves) {
     const uint32_t begin = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_ptr[row]);
     const uint32_t end = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_ptr[row + 1]);
     const void* src = static_cast<const unsigned char*>(dense) + (int64_t)row * ld * kValueBytes;
@@ -455,13 +457,13 @@ encode_fill_kernel(const void* __restrict__ dense, int rows, int cols, int64_t l
     };
     Chunk<IN8> ring[kEncodeAhead];
 #pragma unroll
-    for (int j = 0; j < kEncodeAhead; ++j) ring[j] = load_chunk<IN8>(src, 512 * j + lane * 8, cols);
-    for (int base = 0; base < cols; base += 512 * kEncodeAhead) {
+    for (int j = 0; j < kEncodeAhead; ++j) ring[j] = load_chunk<IN8>(src, 512u * j + 8u * lane, cols);
+    for (uint32_t base = 0; base < cols; base += 512u * kEncodeAhead) {
 #pragma unroll
       for (int j = 0; j < kEncodeAhead; ++j) {
-        const int col0 = base + 512 * j + lane * 8;     // steps behind the last column store nothing
+        const uint32_t col0 = base + 512u * j + 8u * lane;     // steps behind the last column store nothing
         const Chunk<IN8> c = ring[j];
-        ring[j] = load_chunk<IN8>(src, col0 + 512 * kEncodeAhead, cols);
+        ring[j] = load_chunk<IN8>(src, col0 + 512u * kEncodeAhead, cols);
         const unsigned mask = nonzero_mask<IN8>(c);
         const uint32_t pos = table_pos[mask];
         const uint32_t low = table_codes[mask];
@@ -586,10 +588,10 @@ int encode_on_device(const void* dense, int64_t rows, int64_t cols, int64_t ld, 
     auto kcount = in8 ? encode_count_kernel<true, 4> : b_delta == 4 ? encode_count_kernel<false, 4>
                   : b_delta == 2 ? encode_count_kernel<false, 2> : b_delta == 8 ? encode_count_kernel<false, 8>
                                                                                 : encode_count_kernel<false, 1>;
-    hipLaunchKernelGGL(kcount, dim3(grid), dim3(256), 0, stream, dense, (int)rows, (int)cols, ld, counts, nnzs);
+    hipLaunchKernelGGL(kcount, dim3(grid), dim3(256), 0, stream, dense, (uint32_t)rows, (uint32_t)cols, ld, counts, nnzs);
     if (nblocks > kFusedBlocks)
       hipLaunchKernelGGL(encode_block_sums_kernel, dim3((unsigned)nblocks), dim3(1024), 0, stream, counts, nnzs,
-                         (int)rows, sums);
+                         (uint32_t)rows, sums);
   }
   hipLaunchKernelGGL(nblocks > kFusedBlocks ? encode_block_offsets_kernel<false> : encode_block_offsets_kernel<true>,
                      dim3(1), dim3(1024), 0, stream, static_cast<const BlockSums*>(sums),
@@ -619,7 +621,7 @@ int encode_on_device(const void* dense, int64_t rows, int64_t cols, int64_t ld, 
   uint32_t* dels = reinterpret_cast<uint32_t*>(ob + b_deltas);
   uint32_t* rp = reinterpret_cast<uint32_t*>(ob + b_rowptr);
   if (rows > 0)
-    hipLaunchKernelGGL(encode_row_ptr_kernel, dim3((unsigned)nblocks), dim3(1024), 0, stream, counts, (int)rows,
+    hipLaunchKernelGGL(encode_row_ptr_kernel, dim3((unsigned)nblocks), dim3(1024), 0, stream, counts, (uint32_t)rows,
                        boff, rp, (uint32_t)pad, b_delta, dels);
   else
     MACKO_HIP_TRY(hipMemsetAsync(rp, 0, 4, stream));
@@ -627,7 +629,7 @@ int encode_on_device(const void* dense, int64_t rows, int64_t cols, int64_t ld, 
     auto kfill = in8 ? encode_fill_kernel<true, 4> : b_delta == 4 ? encode_fill_kernel<false, 4>
                  : b_delta == 2 ? encode_fill_kernel<false, 2> : b_delta == 8 ? encode_fill_kernel<false, 8>
                                                                               : encode_fill_kernel<false, 1>;
-    hipLaunchKernelGGL(kfill, dim3(grid), dim3(64 * kFillWaves), 0, stream, dense, (int)rows, (int)cols, ld,
+    hipLaunchKernelGGL(kfill, dim3(grid), dim3(64 * kFillWaves), 0, stream, dense, (uint32_t)rows, (uint32_t)cols, ld,
                        static_cast<const uint32_t*>(rp), vals, dels, (uint32_t)pad, (uint32_t)alloc);
   }
   MACKO_HIP_TRY(hipGetLastError());

@@ -1685,3 +1685,25 @@ def test_decode_device_entries_beyond_the_last_column_are_left_out(rows, cols, b
     W[1::3, cols:] = 0
     w = _wrap_with_fewer_columns(W, cols, b_delta)
     assert torch.equal(w.decode_device(), W[:, :cols])
+
+
+def test_gpu_encoder_row_of_all_but_2_31_columns():
+    """The widest row there is (2^31 - 1 columns, 4 GB): the loads ahead of its end stay in front of it.  Expected arrays by
+    the format's rule: a gap of g columns takes (g - 1) / 256 padding entries of code 255 and a code of (g - 1) % 256."""
+    cols = 2 ** 31 - 1
+    W = torch.zeros((1, cols), dtype=torch.float16, device="cuda")
+    at = [5, 6, 2 ** 30 + 3, cols - 1500, cols - 1]
+    values, codes, prev = [], [], -1
+    for i, c in enumerate(at):
+        W[0, c] = i + 1.0
+        pads, code = divmod(c - prev - 1, 256)
+        values += [np.zeros(pads, np.float16), np.array([i + 1.0], np.float16)]
+        codes += [np.full(pads, 255, np.uint8), np.array([code], np.uint8)]
+        prev = c
+    values, codes = np.concatenate(values), np.concatenate(codes)
+    m = M.encode_device(W, b_delta=8)
+    v, d, r = m.fetch_device()
+    n = len(values)
+    assert list(r) == [0, n] and m.report.nnz == len(at) and m.report.pad_nnz == n
+    assert np.array_equal(v[:n].view(np.float16), values) and np.array_equal(d[:n], codes)
+    assert not v[n:].any() and not d[n:].any()

@@ -248,14 +248,13 @@ decode_windows_kernel(const void* __restrict__ values, const uint32_t* __restric
     out -= skew;
     const int64_t row_end = skew + (int64_t)cols * EB;       // in bytes from the aligned start
     int64_t at = 0;                                          // first byte of the window
-    bool beyond = false;                                     // entries may lie behind the row's end (a wrong encoding)
+    int put_end = 0;                                         // no entry was put at this byte or behind it
     auto flush = [&]() {
       // the window is private to the wavefront, whose LDS operations complete in order
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       const int from = at == 0 ? skew : 0, to = (int)min(row_end - at, (int64_t)kWindowBytes);       // the row's bytes
-      const int clear_to = beyond ? kWindowBytes : to;       // what was put behind a right row's end is zeros
       unsigned char* to_mem = out + at;
       if ((from | to) & 15) {                                // values of the row in a 16-byte piece that is not all its own
         constexpr int kPiece = 16 / EB;
@@ -265,6 +264,9 @@ decode_windows_kernel(const void* __restrict__ values, const uint32_t* __restric
           else to_mem[p] = win[p];
         }
       }
+      // Behind a right row's end the window holds zeros.  An entry at or beyond the last column (a wrong encoding) goes no
+      // further than this row.
+      const int clear_to = max(to, min(put_end - (int)at, kWindowBytes));
       for (int lo = 16 * lane; lo < clear_to; lo += 1024) {
         const u32x4 t = win4[lo >> 4];
         win4[lo >> 4] = u32x4{0, 0, 0, 0};
@@ -311,9 +313,6 @@ decode_windows_kernel(const void* __restrict__ values, const uint32_t* __restric
           }
           const int lanebase = base2 + (int)(incl - tot);
           base2 += (int)__builtin_amdgcn_readlane((int)incl, 63);
-          // positions only grow, so a row that runs past its end does so by its last step; the lane that holds its last
-          // entry counts the codes behind it as well, which costs a right row that ends there a clearing too many
-          if (step == nsteps - 1) beyond = __any(e0 < end && skew + ((lanebase + (int)tot) >> (VB == 8 ? 1 : 0)) > row_end);
           for (;;) {
             const int rel = skew + (lanebase >> (VB == 8 ? 1 : 0)) - (int)at;    // the lane's first column in the window
             if (BD != 8) {
@@ -340,6 +339,9 @@ decode_windows_kernel(const void* __restrict__ values, const uint32_t* __restric
           }
         }
       }
+      // the lanes behind the row's last entry went on by 8 columns each; that entry's own lane by the codes behind it as well
+      const int idle = 63 - (int)((end - 1u - (a0 + 512u * (uint32_t)(nsteps - 1))) >> 3);
+      put_end = skew + ((base2 - 16 * idle) >> (VB == 8 ? 1 : 0));
     }
     while (at < row_end) flush();
   }

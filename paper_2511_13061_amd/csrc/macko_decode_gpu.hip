@@ -10,7 +10,7 @@
 // One wavefront per row and 512 entries per step, as in the product.  Expanding
 // a matrix is a conversion, not a per-token operation.  Roofline: HBM; the dense
 // expansion reads 2.5 n bytes and writes 2 R C bytes once (rows are assembled in
-// LDS, whole or a window at a time).
+// LDS, whole or a window at a time; a few rows longer than LDS are cleared and scattered into).
 #include "macko_decode.h"
 #include "macko_device.h"
 #include "macko_internal.h"
@@ -20,10 +20,11 @@ namespace {
 
 constexpr int kExpandBlock = 256;
 
-template <int BD>
+// DENSE: the stored values to their places in a cleared fp16 matrix; else every entry's column to cols_out.
+template <int BD, bool DENSE>
 __global__ void __launch_bounds__(kExpandBlock)
-expand_kernel(const uint32_t* __restrict__ deltas, const uint32_t* __restrict__ row_ptr, const int rows,
-              int32_t* __restrict__ cols_out) {
+expand_kernel(const void* __restrict__ values, const uint32_t* __restrict__ deltas, const uint32_t* __restrict__ row_ptr,
+              const int rows, const int cols, int32_t* __restrict__ cols_out, uint16_t* __restrict__ dense, const int64_t ld) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (kExpandBlock / 64) + (threadIdx.x >> 6)));
   const int nwaves = (int)gridDim.x * (kExpandBlock / 64);
@@ -38,7 +39,9 @@ expand_kernel(const uint32_t* __restrict__ deltas, const uint32_t* __restrict__ 
       const uint32_t e0 = a0 + 512u * (uint32_t)step + 8u * (uint32_t)lane;
       const uint32_t chunk = min(e0, end - 1u) >> 3;         // lanes past the row end re-read its last chunk
       LaneCodes<BD> w;
+      LaneValues<16> v;
       w.load(deltas, chunk);
+      if (DENSE) v.load(values, chunk);
       w.keep_if(e0 < end);
       w.decode();
       const uint32_t tot = w.total();
@@ -51,13 +54,31 @@ expand_kernel(const uint32_t* __restrict__ deltas, const uint32_t* __restrict__ 
 #define MACKO_ENTRY(k)                                                                  \
   {                                                                                     \
     const uint32_t e = e0 + k;                                                          \
-    if (e >= start && e < end) cols_out[e] = (lanebase + w.template offset<k>()) >> 1;  \
+    const int col = (lanebase + w.template offset<k>()) >> 1;                           \
+    if (e >= start && e < end) {                                                        \
+      if (!DENSE) cols_out[e] = col;                                                    \
+      else if (col < cols) dense[(int64_t)row * ld + col] = (uint16_t)v.template bits<k>(); \
+    }                                                                                   \
   }
       MACKO_ENTRY(0) MACKO_ENTRY(1) MACKO_ENTRY(2) MACKO_ENTRY(3)
       MACKO_ENTRY(4) MACKO_ENTRY(5) MACKO_ENTRY(6) MACKO_ENTRY(7)
 #undef MACKO_ENTRY
       base2 += (int)__builtin_amdgcn_readlane((int)incl, 63);
     }
+  }
+}
+
+// dense[r][0 .. cols) = +0 for every row (cells between cols and ld are left alone)
+template <bool VEC>
+__global__ void __launch_bounds__(256) zero_rows_kernel(uint16_t* __restrict__ dense, const int rows, const int cols,
+                                                         const int64_t ld) {
+  const int per_row = VEC ? cols / 8 : cols;                 // stores per row
+  const int64_t total = (int64_t)rows * per_row;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
+    const int64_t r = i / per_row;
+    const int c = (int)(i - r * per_row);
+    if (VEC) reinterpret_cast<uint4*>(dense + r * ld)[c] = make_uint4(0, 0, 0, 0);
+    else dense[r * ld + c] = 0;
   }
 }
 
@@ -207,7 +228,7 @@ decode_rows_kernel(const void* __restrict__ values, const uint32_t* __restrict__
   }
 }
 
-// The same for rows that leave too few row buffers in LDS, or that do not lie on 16 bytes: the wavefront assembles its row
+// The same for rows that leave too few row buffers in LDS (see long_rows_way), or that do not lie on 16 bytes: the wavefront assembles its row
 // a window at a time.  The window is aligned to 16 bytes as the row lies in memory: full-width
 // stores whatever the alignment of dense and ld, value by value only at the row's two ends.  A step (512 stored entries)
 // that reaches behind the window is put into it in parts, out of registers; what a lane's entries leave outside
@@ -359,9 +380,8 @@ int launch_decode_windows_bd(const SpmvProblem& p, void* dense, int64_t ld, hipS
 }
 
 template <int BD, int VB>
-int launch_decode_rows_bd(const SpmvProblem& p, void* dense, int64_t ld, bool vec, int64_t lds_bytes,
+int launch_decode_rows_bd(const SpmvProblem& p, void* dense, int64_t ld, bool vec, int waves_per_wg, int64_t lds_bytes,
                           hipStream_t stream) {
-  constexpr int waves_per_wg = 4;
   const int block = 64 * waves_per_wg;
   const int64_t waves_wanted = std::min<int64_t>(p.rows, (int64_t)device_cu_count() * 32);
   const dim3 grid((unsigned)((waves_wanted + waves_per_wg - 1) / waves_per_wg));
@@ -378,16 +398,51 @@ int launch_decode_rows_bd(const SpmvProblem& p, void* dense, int64_t ld, bool ve
   return e == hipSuccess ? MACKO_OK : hip_fail(e);
 }
 
-int launch_expand(const SpmvProblem& p, int32_t* cols_out, hipStream_t stream) {
+template <bool DENSE>
+int launch_expand(const SpmvProblem& p, int32_t* cols_out, uint16_t* dense, int64_t ld, hipStream_t stream) {
   const int64_t waves_wanted = std::min<int64_t>(p.rows, (int64_t)device_cu_count() * 64);
   const dim3 grid((unsigned)((waves_wanted + kExpandBlock / 64 - 1) / (kExpandBlock / 64))), block(kExpandBlock);
-  const uint32_t* deltas = reinterpret_cast<const uint32_t*>(p.deltas);
-  auto kfn = p.b_delta == 1 ? expand_kernel<1> : p.b_delta == 2 ? expand_kernel<2>
-             : p.b_delta == 4 ? expand_kernel<4> : p.b_delta == 8 ? expand_kernel<8> : nullptr;
+  auto kfn = p.b_delta == 1 ? expand_kernel<1, DENSE> : p.b_delta == 2 ? expand_kernel<2, DENSE>
+             : p.b_delta == 4 ? expand_kernel<4, DENSE> : p.b_delta == 8 ? expand_kernel<8, DENSE> : nullptr;
   if (!kfn) return MACKO_E_UNSUPPORTED;
-  hipLaunchKernelGGL(kfn, grid, block, 0, stream, deltas, p.row_ptr, (int)p.rows, cols_out);
+  hipLaunchKernelGGL(kfn, grid, block, 0, stream, static_cast<const void*>(p.values),
+                     reinterpret_cast<const uint32_t*>(p.deltas), p.row_ptr, (int)p.rows, (int)p.cols, cols_out, dense, ld);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? MACKO_OK : hip_fail(e);
+}
+
+// Clears the matrix, then scatters the stored values (two kernels in stream order).
+int launch_clear_and_scatter(const SpmvProblem& p, uint16_t* dense, int64_t ld, bool vec, hipStream_t stream) {
+  const int64_t stores = p.rows * (vec ? p.cols / 8 : p.cols);
+  const int64_t wgs = std::min<int64_t>((stores + 255) / 256, (int64_t)device_cu_count() * 32);
+  hipLaunchKernelGGL(vec ? zero_rows_kernel<true> : zero_rows_kernel<false>, dim3((unsigned)wgs), dim3(256), 0, stream, dense,
+                     (int)p.rows, (int)p.cols, ld);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return hip_fail(e);
+  return p.pad_nnz == 0 ? MACKO_OK : launch_expand<true>(p, nullptr, dense, ld, stream);
+}
+
+// How a matrix whose rows leave fewer than 8 row buffers per compute unit is decoded.  The windows have 16 wavefronts in
+// flight per compute unit whatever the row's length, but visit every window of the row one after the other, and with 8-bit codes check
+// each entry against it.  All times are in windows over the other way, rows on 16 bytes, 16-bit values (8-bit values are
+// within 10 % either way and take the windows).
+enum class LongRows { kWindows, kBuffers, kScatter };
+LongRows long_rows_way(const SpmvProblem& p, int64_t per_cu, bool vec) {
+  if (p.b_val != 16) return LongRows::kWindows;
+  const int64_t room = (int64_t)device_cu_count() * per_cu;
+  const double density = (double)p.pad_nnz / (double)p.rows / (double)p.cols;
+  if (per_cu > 0) {
+    // row buffers, all rows at once (4096 x 11008 at 50 %: 0.83; otherwise 0.53 ... 0.98)
+    if (!vec || p.rows > room) return LongRows::kWindows;
+    if (p.b_delta == 8) return LongRows::kBuffers;                           // 1.02 ... 1.42, 16 x 40000: 1.37
+    if (p.b_delta < 4) return 2 * p.rows >= room ? LongRows::kBuffers : LongRows::kWindows;   // 1500 x 11008: 1.21; 256 x 11008: 0.88
+    if (density < 0.08 && per_cu <= 5) return LongRows::kBuffers;            // hardly more than padding: 1.00 ... 1.17
+    return per_cu <= 4 && 4 * p.rows >= 3 * room ? LongRows::kBuffers : LongRows::kWindows;   // 512 x 40000 at 93 %: 1.20; 256: 1.00
+  }
+  // rows longer than LDS: a few sparse ones are sooner cleared by the whole chip and scattered into
+  const double most = p.b_delta == 8 ? (p.rows <= 2 ? 0.25 : p.rows <= 64 ? 0.11 : p.rows <= 128 ? 0.06 : p.rows <= 256 ? 0.025 : 0.0)
+                                     : (p.rows <= 2 ? 0.13 : p.rows <= 16 ? 0.07 : 0.0);
+  return density < most ? LongRows::kScatter : LongRows::kWindows;           // 4 x 100000, 98 %, 8-bit codes: 2.54; 256 x 100000: 1.05
 }
 
 }  // namespace
@@ -422,7 +477,7 @@ int launch_check(const SpmvProblem& p, unsigned int* first_bad, hipStream_t stre
 
 int launch_columns(const SpmvProblem& p, int32_t* cols_out, hipStream_t stream) {
   if (p.rows == 0 || p.pad_nnz == 0) return MACKO_OK;
-  return launch_expand(p, cols_out, stream);
+  return launch_expand<false>(p, cols_out, nullptr, 0, stream);
 }
 
 int launch_decode(const SpmvProblem& p, void* dense_any, int64_t ld, hipStream_t stream) {
@@ -436,7 +491,11 @@ int launch_decode(const SpmvProblem& p, void* dense_any, int64_t ld, hipStream_t
   // Row buffers per compute unit: at least 8 (4096 x 11008 has 7: 38.5 us, in windows 34.5; 9000 columns have 8: 9.8 us for 2000
   // rows, in windows 10.3), and rows on 16 bytes unless they are short (1000 x 4093: 7.1 and 6.1; 9000 x 300: 4.6 and 5.3).
   const int64_t per_cu = kLdsLimit / row_bytes;
-  if (per_cu < 8 || (!vec && row_bytes >= 2048)) {
+  LongRows way = LongRows::kBuffers;
+  if (per_cu < 8) way = long_rows_way(p, per_cu, vec);
+  else if (!vec && row_bytes >= 2048) way = LongRows::kWindows;
+  if (way == LongRows::kScatter) return launch_clear_and_scatter(p, static_cast<uint16_t*>(dense_any), ld, vec, stream);
+  if (way == LongRows::kWindows) {
     if (p.b_val == 8) return launch_decode_windows_bd<4, 8>(p, dense_any, ld, stream);
     switch (p.b_delta) {
       case 1: return launch_decode_windows_bd<1, 16>(p, dense_any, ld, stream);
@@ -446,14 +505,15 @@ int launch_decode(const SpmvProblem& p, void* dense_any, int64_t ld, hipStream_t
       default: return MACKO_E_UNSUPPORTED;
     }
   }
-  // one pass through a row buffer in LDS per wavefront, in workgroups of 4 wavefronts
-  const int64_t lds_bytes = row_bytes * 4;
-  if (p.b_val == 8) return launch_decode_rows_bd<4, 8>(p, dense_any, ld, vec, lds_bytes, stream);
+  // one pass through a row buffer in LDS per wavefront, in workgroups of 4 wavefronts or one workgroup per compute unit
+  const int waves_per_wg = per_cu >= 8 ? 4 : (int)per_cu;
+  const int64_t lds_bytes = row_bytes * waves_per_wg;
+  if (p.b_val == 8) return launch_decode_rows_bd<4, 8>(p, dense_any, ld, vec, waves_per_wg, lds_bytes, stream);
   switch (p.b_delta) {
-    case 1: return launch_decode_rows_bd<1, 16>(p, dense_any, ld, vec, lds_bytes, stream);
-    case 2: return launch_decode_rows_bd<2, 16>(p, dense_any, ld, vec, lds_bytes, stream);
-    case 4: return launch_decode_rows_bd<4, 16>(p, dense_any, ld, vec, lds_bytes, stream);
-    case 8: return launch_decode_rows_bd<8, 16>(p, dense_any, ld, vec, lds_bytes, stream);
+    case 1: return launch_decode_rows_bd<1, 16>(p, dense_any, ld, vec, waves_per_wg, lds_bytes, stream);
+    case 2: return launch_decode_rows_bd<2, 16>(p, dense_any, ld, vec, waves_per_wg, lds_bytes, stream);
+    case 4: return launch_decode_rows_bd<4, 16>(p, dense_any, ld, vec, waves_per_wg, lds_bytes, stream);
+    case 8: return launch_decode_rows_bd<8, 16>(p, dense_any, ld, vec, waves_per_wg, lds_bytes, stream);
     default: return MACKO_E_UNSUPPORTED;
   }
 }

@@ -1707,3 +1707,26 @@ def test_gpu_encoder_row_of_all_but_2_31_columns():
     assert list(r) == [0, n] and m.report.nnz == len(at) and m.report.pad_nnz == n
     assert np.array_equal(v[:n].view(np.float16), values) and np.array_equal(d[:n], codes)
     assert not v[n:].any() and not d[n:].any()
+
+
+@pytest.mark.parametrize("rows,cols,density,b_delta", [
+    # row buffers where all rows are on the chip at once, and one round more
+    (20, 11008, 0.02, 8), (1100, 10408, 0.5, 2), (1800, 10408, 0.5, 2), (300, 20000, 0.001, 4), (400, 28672, 0.07, 4), (260, 40000, 0.4, 1),
+    # rows longer than LDS, cleared and scattered into, and the same in windows
+    (1, 100000, 0.02, 4), (2, 81928, 0.1, 4), (16, 90000, 0.001, 4), (17, 90000, 0.001, 4), (60, 81928, 0.02, 8), (100, 81928, 0.02, 8),
+    (200, 82000, 0.002, 8), (1, 100000, 0.0, 2), (2, 81928, 0.5, 1)])
+@pytest.mark.parametrize("shift,pad", [(0, 8), (3, 5)])
+def test_decode_device_long_rows_either_way(rows, cols, density, b_delta, shift, pad):
+    """Both sides of the rule that decodes rows of more than 20 KB in windows, in row buffers or by a scatter, with rows on 16 bytes
+    and not: the dense matrix back bit for bit, the cells around it untouched."""
+    g = torch.Generator(device="cuda").manual_seed(rows + cols)
+    W = torch.empty((rows, cols), dtype=torch.float16, device="cuda").normal_(0.0, 0.02, generator=g)
+    W.mul_(torch.rand(W.shape, generator=g, device="cuda") < density)
+    W[::2, -1] = 3.0
+    W[1::5] = 0
+    W += 0.0                                                               # no -0
+    m = M.encode_device(W, b_delta=b_delta)
+    buf = torch.full((rows, cols + pad), 9.0, dtype=torch.float16, device="cuda")
+    m.decode_device(buf[:, shift:shift + cols])
+    assert torch.equal(buf[:, shift:shift + cols], W)
+    assert (buf[:, :shift] == 9).all() and (buf[:, shift + cols:] == 9).all()

@@ -72,7 +72,16 @@ inline void plan_by_rows_per_wg(Plan& plan, int n, const PlanInput* in, int bloc
 // on the decoder-layer shapes, one, three and four are within a few per cent of
 // two and none is better across the board.  Returns false when the group has too
 // few rows for the model to mean anything.
-inline bool plan_resident(Plan& plan, int n, const PlanInput* in, int cus, int forced_block, int forced_k) {
+//
+// short_rows_want_more: rows of up to 4 steps take about 24 wavefronts per compute unit where the rows split about as well as
+// on 16, since each row ends in a reduction that only other wavefronts can cover.  For the sparse products, with one vector
+// and with a batch.  (The kernel of 8 vectors takes 94 registers, so that only one of its two larger workgroups is on a
+// compute unit at a time; mostly faster all the same: 36864 x 1280 at 50 %, 8 vectors, 34.9 us on 18 wavefronts, 29.9 on 24;
+// 18432 x 1280 at 30 % 20.3 / 17.5; but 24576 x 1024 at 50 % 20.6 / 21.1, and two vectors, 18432 x 2048 at 30 %, 14.7 / 15.4.)
+// Not for the dense product, whose rows are read at the memory's rate anyway (18432 x 1024: 7.0 on 18, 8.9 on 24; 14336 x 1536:
+// 8.0 on 14, 10.4 on 28), nor for a chain, whose workgroups would be wider and might not all be resident.
+inline bool plan_resident(Plan& plan, int n, const PlanInput* in, int cus, int forced_block, int forced_k,
+                          bool short_rows_want_more = false) {
   int64_t total_rows = 0, total_work = 0, max_lds = 0;
   for (int i = 0; i < n; ++i) {
     total_rows += in[i].rows;
@@ -81,7 +90,7 @@ inline bool plan_resident(Plan& plan, int n, const PlanInput* in, int cus, int f
   }
   if (total_rows < (int64_t)cus * 4) return false;
   const bool enough = total_work >= (int64_t)cus * 128 || total_rows >= (int64_t)cus * 64;
-  const int middle = total_work <= 4 * total_rows && enough ? 22 : 20;
+  const int middle = short_rows_want_more && total_work <= 4 * total_rows && enough ? 22 : 20;
   double best_cost = 0;
   int best_k = 0, best_nw = 0;
   PlanMat best_m[kMaxWide] = {};
@@ -119,13 +128,15 @@ inline bool plan_resident(Plan& plan, int n, const PlanInput* in, int cus, int f
       }
       if (!ok) continue;
       // all resident wavefronts share the memory system: time ~ slowest share x wavefronts;
-      // a mild preference for 16..24 wavefronts per compute unit and for fewer, larger workgroups.
-      // Where 16 and 24 split the rows equally well: rows of up to 4 steps take 24, since each row ends in a reduction
-      // that only other wavefronts can cover (microseconds for 16 / 24: 12288x12288, 95 % pruned, 9.7 / 8.9, with 8-bit
-      // values 9.1 / 8.2; 24576x2048, 70 %, 11.6 / 11.0; 12288x4096, 70 %, 9.6 / 9.3; 24576x4096, 90 %, 10.7 / 10.5, with
-      // 8-bit values 10.5 / 10.0).  Longer rows take 16 (12288x4096, 30 %, 16.3 / 16.5), and so do launches of few rows
-      // of one or two steps, where the start of 24 wavefronts shows (12288x12288, 95 %, 8-bit codes, 7.9 / 8.0;
-      // 12288x2048, 60 %, 7.38 / 7.41)
+      // a mild preference for 16..24 wavefronts per compute unit and for fewer, larger workgroups.  short_rows_want_more
+      // moves it where two counts split the rows about equally well; over 113 single products whose plan it changes the
+      // time goes down by 5 % (median; 16 % at best, 5 % up at worst).  Microseconds without / with it:
+      //   16 -> 24 wavefronts  12288x12288, 95 % pruned, 11.1 / 9.2; 12288x4096, 70 %, 10.8 / 9.5; 24576x2048, 70 %, 12.3 / 11.4;
+      //                        24576x4096, 90 %, 11.3 / 11.0; but 24576x3072, 50 %, 18.5 / 19.3
+      //   18 -> 24             36864x4096, 70 %, 25.2 / 22.5; 18432x1024, 50 %, 10.2 / 9.6; but 18432x8192, 95 %, 8-bit codes, 8.8 / 9.2
+      //   14 -> 28             14336x4096, 70 %, 12.0 / 10.9; 14336x12288, 95 %, 12.4 / 11.1; 14336x3072, 50 %, 13.7 / 13.2
+      // Longer rows are left alone (12288x4096, 30 %: 16.3 on 16, 16.5 on 24), and so are launches of few rows of one or
+      // two steps, where the start of 24 wavefronts shows (12288x12288, 95 %, 8-bit codes, 7.9 / 8.0; 12288x2048, 60 %, 7.38 / 7.41)
       double cost = (double)worst * waves;
       cost *= 1.0 + 0.002 * std::abs(waves - middle) + 0.001 * k;
       if (best_k == 0 || cost < best_cost) {

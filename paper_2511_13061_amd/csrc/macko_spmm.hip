@@ -268,7 +268,7 @@ int launch_bt_bd(const SpmvProblem& p, const uint16_t* X, int64_t ldx, uint16_t*
   Plan plan;
   bool planned = false;
   if (in.rows * in.steps_per_row <= (int64_t)cus * 800 || lds >= 36 * 1024)
-    planned = plan_resident(plan, 1, &in, cus, 0, lds >= 36 * 1024 ? 1 : 0);
+    planned = plan_resident(plan, 1, &in, cus, 0, lds >= 36 * 1024 ? 1 : 0, true);
   if (!planned) {
     const int block = lds > 48 * 1024 ? 1024 : 512;
     const int64_t want = (16 + in.steps_per_row - 1) / in.steps_per_row;

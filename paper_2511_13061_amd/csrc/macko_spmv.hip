@@ -774,7 +774,7 @@ int launch_wave_row_group(int nwr, const SpmvProblem* const* wr, int b_delta, in
   }
   if (!in_step && t.spmv_rows_per_wg == 0 && (t.spmv_resident == 2 || (t.spmv_resident == 0 && (small || wide)))) {
     const int k = t.spmv_wgs_per_cu ? (int)t.spmv_wgs_per_cu : (wide ? 1 : 0);
-    planned = plan_resident(plan, nwr, in, cus, (int)t.spmv_block, k);
+    planned = plan_resident(plan, nwr, in, cus, (int)t.spmv_block, k, true);
   }
   if (!planned) {
     // Plenty of work: many workgroups, about 8 steps per wavefront (short rows:

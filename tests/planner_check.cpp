@@ -64,8 +64,8 @@ int main() {
   auto uni = [&](int64_t lo, int64_t hi) { return lo + (int64_t)(rng() % (uint64_t)(hi - lo + 1)); };
   int resident_plans = 0;
   for (int trial = 0; trial < 3000; ++trial) {
-    const int n = (int)uni(1, kMaxGroup);
-    PlanInput in[kMaxGroup];
+    const int n = (int)uni(1, trial % 3 == 0 ? kMaxWide : kMaxGroup);
+    PlanInput in[kMaxWide];
     for (int i = 0; i < n; ++i) {
       const int kind = (int)uni(0, 3);
       in[i].rows = kind == 0 ? uni(1, 300) : kind == 1 ? uni(1000, 12000) : kind == 2 ? uni(20000, 60000) : uni(1, 60000);
@@ -75,7 +75,7 @@ int main() {
     // many-workgroup regime, any block and rows per workgroup
     {
       const int block = 64 * (int)uni(1, 16);
-      int64_t rpw[kMaxGroup];
+      int64_t rpw[kMaxWide];
       for (int i = 0; i < n; ++i) rpw[i] = uni(0, 3) == 0 ? uni(1, 1 << 20) : uni(1, 200);
       Plan plan;
       plan_by_rows_per_wg(plan, n, in, block, rpw);
@@ -87,7 +87,7 @@ int main() {
       const int forced_block = uni(0, 2) == 0 ? 64 * (int)uni(4, 16) : 0;
       const int forced_k = (int)uni(0, 4);
       Plan plan;
-      if (!plan_resident(plan, n, in, cus, forced_block, forced_k)) continue;
+      if (!plan_resident(plan, n, in, cus, forced_block, forced_k, trial % 2 == 0)) continue;
       ++resident_plans;
       const int k = forced_k ? forced_k : 2;
       EXPECT(plan.total_wgs == (int64_t)cus * k, "resident round of %lld workgroups on %d units, k %d",
@@ -98,6 +98,21 @@ int main() {
       EXPECT(k * max_lds <= kPlanLdsPerCu, "LDS of %d workgroups per unit", k);
       EXPECT(k * (plan.block / 64) <= 32, "wavefronts per unit");
       replay(plan, n, in, "resident");
+    }
+  }
+  // More wavefronts for short rows only where a caller asks for them, and never in a chain.  (rows, steps per row, threads per workgroup without and with it)
+  {
+    const int64_t shapes[][4] = {{24576, 1, 512, 768}, {18432, 1, 576, 768}, {12288, 3, 512, 768}, {14336, 3, 448, 896}, {12288, 5, 512, 512}};
+    for (const auto& s : shapes) {
+      const PlanInput one{s[0], s[1], 20 * 1024};
+      Plan plain, more;
+      const bool a = plan_resident(plain, 1, &one, 256, 0, 0), b = plan_resident(more, 1, &one, 256, 0, 0, true);
+      EXPECT(a && b && plain.block == s[2] && more.block == s[3], "%lld rows of %lld steps: %d and %d threads", (long long)s[0],
+             (long long)s[1], plain.block, more.block);
+      const int sizes[1] = {1};
+      ChainPlan cp;
+      const bool c = plan_chain(cp, 1, sizes, &one, 256, [&](int block) { return resident_wgs_per_cu(72, block / 64, 20 * 1024); });
+      EXPECT(c && cp.wgs_per_cu == 2 && cp.block == s[2], "chain of %lld rows: k %d, %d threads", (long long)s[0], cp.wgs_per_cu, cp.block);
     }
   }
   EXPECT(resident_plans > 500, "only %d resident plans exercised", resident_plans);

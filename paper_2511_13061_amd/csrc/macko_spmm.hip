@@ -306,12 +306,66 @@ int launch_bt(const SpmvProblem& p, const uint16_t* X, int64_t ldx, uint16_t* Y,
   }
 }
 
+constexpr int64_t kBatchLdsLimit = 160 * 1024 - 64;
+constexpr int64_t kLongRow = 384;       // stored entries per row from which vectors share a pass over the matrix
+
+// Which of the two ways is the faster one for a call that both can take.
+//
+// The matrix cores serve up to 16 vectors at one price: they pay for the cells of their tiles, 16 rows by a window of columns, whatever
+// is stored there, and for whole rounds of tiles.  The vector kernel pays per stored entry and vector, in pieces of 8, 4, 2
+// or 1 vectors (whatever fits LDS, each piece a launch).  So the line lies where too few of the cells hold an entry, the lower the
+// more vectors there are.  All figures are microseconds, vector kernel / matrix cores, over 10 500 calls of 8 to
+// 36864 rows, 512 to 60000 columns, 30 to 99.9 % pruned; over the range where both ways win (5 to 8 vectors, 9400 to 19700
+// columns) the lines below are within 1 % of always taking the faster way.
+bool tile_is_faster(const SpmvProblem& p, int batch) {
+  if (batch <= 4) return false;
+  if (batch > 16) return true;                         // at least three pieces (11008 x 4096, 64 vectors: 183 / 43)
+  const int64_t cus = device_cu_count();
+  const int64_t avg = p.pad_nnz / p.rows, one = lds_bytes_for(p.cols, p.b_delta);
+  // rounds of 256 tiles, the share of their rows that exist, and the share of their cells that hold an entry
+  const int64_t rounds = (p.rows + 16 * cus - 1) / (16 * cus);
+  const double filled = (double)p.rows / (double)(rounds * 16 * cus);
+  const int64_t window = p.cols > 2048 ? 4096 : 2048;
+  const double cells = filled * (double)avg / (double)((p.cols + window - 1) / window * window);
+  if (avg < kLongRow) {
+    // Up to 8 vectors are one launch of the product with one vector, if the rows are not too short for that (14336 x 512 at
+    // 50 %, 8 vectors: 32.1 / 12.4; 4096 x 2048 at 96 %: 31.7 / 6.5).  Few rows do not fill the chip with tiles.
+    const bool one_launch = p.b_val == 8 || avg >= kWaveRowMinEntries;
+    if (batch <= 8) {
+      if (p.rows < 16 * cus) return false;            // 512 x 512, 8 vectors: 4.1 / 5.1
+      if (!one_launch || p.cols <= 2048 || rounds == 1) return true;
+      if (batch == 5) return filled >= 0.75 && p.cols <= 4096;   // 4200 x 4096 at 98 %: 9.7 / 11.1; 8300 x 5000: 1.3 times
+      return batch > 6 || filled >= 0.75 || p.cols <= 4096;      // 4200 x 5000 at 98 %, 6 vectors: 1.17 times
+    }
+    // two launches, about 7 us however few the rows (5000 columns at 98 %, 16 rows, 9 vectors: 6.7 / 8.8, 256 rows:
+    // 7.3 / 9.0, 768 rows: 1.02 times; 4096 columns at 97 %, 64 rows: 6.8 / 7.7, 512 rows: 7.9 / 7.8)
+    return !one_launch || p.cols <= 2048 || p.rows > (p.cols > 4096 ? 512 : 256);
+  }
+  if (batch > 8) {
+    // One piece of 8 or two of 4, and the rest: 8300 x 6000 at 97 %, 9 vectors: 15.8 / 18.8; 5000 x 14336 at 99 %: 19.6 / 22.9;
+    // but in one round of tiles 4096 x 6000 at 97 %: 0.71 times, and with a number of columns that is no multiple of 8, which
+    // the vector kernel stages element by element, 4200 x 4500 at 90 %: 0.71 times.
+    if (batch > 12 || rounds == 1 || p.cols <= 4096 || p.cols % 8 != 0 || 4 * one > kBatchLdsLimit) return true;
+    return cells >= (batch <= 10 ? 0.08 : 0.05);
+  }
+  if (8 * one <= kBatchLdsLimit) return false;         // one piece: 2048 x 4096: 8.8 / 9.8, 11008 x 4096: 21.5 / 21.7
+  if (4 * one > kBatchLdsLimit)                        // pieces of 2: 4096 x 20000 at 50 %, 8 vectors: 75.7 / 30.5
+    return batch > 6 || rounds == 1 || cells >= 0.11;  // 6000 x 30000 at 96 %, 5 vectors: 1.38 times, 8 vectors: 1.0
+  // a piece of 4, and another or what is left
+  if (p.rows < 4 * cus)                                // too few rows for the vector kernel's resident round
+    return (double)avg >= (batch == 5 ? 0.3 : batch == 6 ? 0.2 : 0.09) * (double)p.cols;     // 256 x 11008: 24.2 / 18.1
+  double least = batch <= 6 ? (rounds == 1 ? 0.15 : 0.21) : (rounds == 1 ? 0.105 : 0.16);
+  if (p.b_val == 8) least += 0.06;                     // half the bytes: the vector kernel gains more
+  if (p.b_delta < 4) least += 0.17;                    // less to decode, likewise
+  return cells >= least;                               // 4096 x 11008 at 50 %, 8 vectors: 27.4 / 19.6; 14336 x 14336 at 90 %: 36.6 / 50.2
+}
+
 }  // namespace
 
 // Y[b][r] = sum over row r of W * X[b][column], b < batch.  The batch is cut into
 // pieces of 8, 4, 2 or 1 vectors, each the largest that fits LDS; single vectors
 // (and matrices with short rows) go through the matrix-vector path; larger batches go to the
-// matrix cores in one piece (macko_spmm_tile.hip).
+// matrix cores in one piece (macko_spmm_tile.hip) where that is faster.
 int launch_spmm(const SpmvProblem& p, const void* X, int64_t ldx, void* Y, int64_t ldy, int batch,
                 hipStream_t stream) {
   if (p.pad_nnz > (int64_t{1} << 32) - 4096) return MACKO_E_UNSUPPORTED;   // 32-bit entry indices in the kernel
@@ -325,16 +379,9 @@ int launch_spmm(const SpmvProblem& p, const void* X, int64_t ldx, void* Y, int64
     return e == hipSuccess ? MACKO_OK : hip_fail(e);
   }
   const int64_t one = lds_bytes_for(p.cols, p.b_delta);
-  const int64_t limit = 160 * 1024 - 64;
-  const bool long_rows = p.pad_nnz / p.rows >= 384;
-  // The matrix cores serve the whole batch at one price, about that of 8 vectors here.  From 9 vectors on they
-  // win everywhere (us here -> there: 512 x 512 at 50 %, 9 vectors: 7.2 -> 5.1; 4096 x 4096: 17.8 -> 10.5; 11008 x 4096 at
-  // 90 %: 19.0 -> 15.8; 14336 x 3584 at 70 %: 29.8 -> 22.3).  From 5 to 8 one piece of 8 here is as fast or faster (2048 x 4096:
-  // 8.8 and 9.8; 11008 x 4096: 21.5 and 21.7, at 90 % 12.3 and 15.9), except where 8 vectors do not fit LDS (4096 x 11008:
-  // 27.4 -> 19.6, at 90 % 13.4 -> 13.3) and where the rows are short and there are enough of them to fill the chip with
-  // tiles (14336 x 512 at 50 %: 21.2 -> 11.8, 4096 x 4096 at 96 %: 9.0 -> 7.4; but 512 x 512: 4.1 -> 5.1).
-  if (spmm_tile_serves(p, ldx) &&
-      (batch > 8 || (batch > 4 && (long_rows ? 8 * one > limit : p.rows >= (int64_t)device_cu_count() * 16))))
+  const int64_t limit = kBatchLdsLimit;
+  const bool long_rows = p.pad_nnz / p.rows >= kLongRow;
+  if (spmm_tile_serves(p, ldx) && tile_is_faster(p, batch))
     return launch_spmm_tile(p, Xp, ldx, Yp, ldy, batch, stream);
   int done = 0;
   while (done < batch) {

@@ -1730,3 +1730,28 @@ def test_decode_device_long_rows_either_way(rows, cols, density, b_delta, shift,
     m.decode_device(buf[:, shift:shift + cols])
     assert torch.equal(buf[:, shift:shift + cols], W)
     assert (buf[:, :shift] == 9).all() and (buf[:, shift + cols:] == 9).all()
+
+
+@pytest.mark.parametrize("rows,cols,sparsity,batch", [
+    # rows shorter than a step: one or two launches of the product with one vector, or the matrix cores
+    (4200, 4096, 0.98, 5), (4200, 5000, 0.98, 6), (5000, 4096, 0.98, 6), (16, 5000, 0.98, 9), (513, 5000, 0.98, 9), (256, 4096, 0.97, 16),
+    # 9 to 12 vectors on sparse rows, in one round of tiles and more
+    (4097, 6000, 0.97, 9), (4096, 6000, 0.97, 9), (4097, 6000, 0.97, 12), (4097, 6000, 0.97, 13), (4097, 6004, 0.97, 9),
+    # 5 to 8 vectors where 8, 4 or 2 of them fit LDS: few rows, one round of tiles, more
+    (300, 11008, 0.95, 8), (300, 11008, 0.8, 5), (1100, 11008, 0.9, 7), (1100, 11008, 0.3, 5), (4200, 9480, 0.9, 6), (4200, 9480, 0.3, 6),
+    (300, 20008, 0.9, 5), (4200, 20008, 0.97, 6), (4200, 20008, 0.5, 8)])
+@pytest.mark.parametrize("kind", ["b2", "b4", "fp8"])
+def test_spmm_on_both_sides_of_the_rule_that_picks_its_kernel(kind, rows, cols, sparsity, batch):
+    g = torch.Generator(device="cuda").manual_seed(rows + cols + batch)
+    W = torch.empty((rows, cols), dtype=torch.float16, device="cuda").normal_(0.0, 0.02, generator=g)
+    W.mul_(torch.rand(W.shape, generator=g, device="cuda") >= sparsity)
+    if kind == "fp8":
+        W8 = (W.float() * 32.0).to(torch.float8_e4m3fn)
+        m, W64 = M.encode_device_fp8(W8.view(torch.uint8)), W8.float().double()
+    else:
+        m, W64 = M.encode_device(W, b_delta=int(kind[1])), W.double()
+    X = torch.empty((batch, cols), dtype=torch.float16, device="cuda").normal_(0.0, 1.0, generator=g)
+    Y = m.spmm(X).double()
+    ref, mag = X.double() @ W64.T.contiguous(), X.double().abs() @ W64.abs().T.contiguous()
+    bound = ref.abs() * 2.0 ** -11 + 2.0 ** -25 + mag * cols * 2.0 ** -24          # as in test_spmm_tile_edges
+    assert float(((Y - ref).abs() / bound).max()) <= 1.01

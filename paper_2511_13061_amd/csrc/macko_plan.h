@@ -97,28 +97,47 @@ inline bool plan_resident(Plan& plan, int n, const PlanInput* in, int cus, int f
   for (int k = 1; k <= 4; ++k) {
     if (k != (forced_k ? forced_k : 2)) continue;
     if (k * max_lds > kPlanLdsPerCu) continue;
+    // deal the workgroups out in proportion to the work, every matrix at least one
+    const int64_t wgs = (int64_t)cus * k;
+    PlanMat pm[kMaxWide];
+    int64_t given = 0;
+    int largest = 0;
+    for (int i = 0; i < n; ++i) {
+      const double share = (double)wgs * (double)(in[i].rows * in[i].steps_per_row) / (double)total_work;
+      int64_t g = std::max<int64_t>(1, (int64_t)(share + 0.5));
+      g = std::min<int64_t>(g, in[i].rows);
+      plan_split(pm[i], in[i].rows, g);
+      given += g;
+      if (in[i].rows * in[i].steps_per_row > in[largest].rows * in[largest].steps_per_row) largest = i;
+    }
+    // What rounding left over or took too much: up to kMaxGroup matrices have shares large enough for the largest one to
+    // bear it.  31 equal matrices have 17 of 512 workgroups each, 15 too many, and the first would be left with two (512 x 2048,
+    // 50 %, 2-bit codes: 61 us instead of 18): one at a time from the matrix with the least work per workgroup, or to the one with the most.
+    for (; n > kMaxGroup && given != wgs; given += given < wgs ? 1 : -1) {
+      int best = -1;
+      double best_load = 0;
+      for (int i = 0; i < n; ++i) {
+        const int64_t to = pm[i].nwg + (given < wgs ? 1 : -1);
+        if (to < 1 || to > in[i].rows) continue;
+        const double work = (double)(in[i].rows * in[i].steps_per_row);
+        const double load = given < wgs ? work / (double)pm[i].nwg : -work / (double)to;
+        if (best < 0 || load > best_load) {
+          best = i;
+          best_load = load;
+        }
+      }
+      if (best < 0) break;
+      plan_split(pm[best], in[best].rows, pm[best].nwg + (given < wgs ? 1 : -1));
+    }
+    const int64_t fix = pm[largest].nwg + (wgs - given);
+    if (fix < 1 || fix > in[largest].rows) continue;
+    plan_split(pm[largest], in[largest].rows, fix);
     for (int nw = 4; nw <= 16; ++nw) {
       if (forced_block && nw * 64 != forced_block) continue;
       const int waves = k * nw;
       if (waves > 32) continue;
-      const int64_t wgs = (int64_t)cus * k;
       if (waves < 12 && total_rows >= (int64_t)cus * 12) continue;  // too few loads in flight
-      // deal the workgroups out in proportion to the work, every matrix at least one
-      PlanMat pm[kMaxWide];
-      int64_t given = 0;
-      int largest = 0;
       bool ok = true;
-      for (int i = 0; i < n; ++i) {
-        const double share = (double)wgs * (double)(in[i].rows * in[i].steps_per_row) / (double)total_work;
-        int64_t g = std::max<int64_t>(1, (int64_t)(share + 0.5));
-        g = std::min<int64_t>(g, in[i].rows);
-        plan_split(pm[i], in[i].rows, g);
-        given += g;
-        if (in[i].rows * in[i].steps_per_row > in[largest].rows * in[largest].steps_per_row) largest = i;
-      }
-      const int64_t fix = pm[largest].nwg + (wgs - given);
-      if (fix < 1 || fix > in[largest].rows) continue;
-      plan_split(pm[largest], in[largest].rows, fix);
       int64_t worst = 0;
       for (int i = 0; i < n; ++i) {
         const int64_t rows_wg = pm[i].q + (pm[i].r ? 1 : 0);

@@ -115,6 +115,17 @@ int main() {
       EXPECT(c && cp.wgs_per_cu == 2 && cp.block == s[2], "chain of %lld rows: k %d, %d threads", (long long)s[0], cp.wgs_per_cu, cp.block);
     }
   }
+  // many matrices: what rounding gives too many or too few workgroups is spread, not left to one matrix
+  for (int n = 2; n <= kMaxWide; ++n) {
+    PlanInput in[kMaxWide];
+    for (int i = 0; i < n; ++i) in[i] = PlanInput{512, 3, 8 * 1024};
+    Plan plan;
+    if (!plan_resident(plan, n, in, 256, 0, 0, true)) { EXPECT(n < 2, "%d matrices of 512 rows: no plan", n); continue; }
+    int least = plan.m[0].nwg, most = plan.m[0].nwg;
+    for (int i = 1; i < n; ++i) { least = std::min(least, plan.m[i].nwg); most = std::max(most, plan.m[i].nwg); }
+    EXPECT(most - least <= (n <= kMaxGroup ? n / 2 : 1), "%d equal matrices have %d to %d workgroups", n, least, most);
+    replay(plan, n, in, "equal matrices");
+  }
   EXPECT(resident_plans > 500, "only %d resident plans exercised", resident_plans);
   // the dense kernel divides by the wavefront count with a 20-bit reciprocal, rows per workgroup up to 65535
   for (int nw = 1; nw <= 16; ++nw) {

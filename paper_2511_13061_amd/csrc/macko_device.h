@@ -6,30 +6,11 @@
 
 #include <cstdint>
 
+#include "macko_internal.h"
+
 namespace macko {
 
 constexpr int kWave = 64;
-
-// The activation vector x sits in LDS between two zero-filled guard regions:
-//   [0, front) zeros | x[0 .. C) | zeros up to the end of the allocation.
-// Entries that a lane loads but that belong to a neighbouring row decode to
-// positions just before column 0 or after the row's last column; the guards
-// make those reads return +0 so that they contribute nothing.
-// Front guard: a row's first chunk holds at most 7 entries of the previous row,
-// each at most 2^b_delta columns wide (224 bytes before x[0] for 4-bit codes,
-// 3584 for 8-bit ones).  Back guard: in a row's last step the lanes past the row
-// end advance by one column per entry, plus at most 7 real deltas in the lane
-// that straddles the end (at most 504 + 7 * 2^b_delta columns); the dense kernel
-// reads at most 62 16-byte chunks past the end.
-constexpr int kFrontPad = 256;   // bytes, codes of up to 4 bits (and the dense kernel)
-constexpr int kBackPad = 1280;   // bytes
-
-__host__ __device__ constexpr int front_pad_for(int b_delta) { return b_delta <= 4 ? kFrontPad : 3584; }
-__host__ __device__ constexpr int back_pad_for(int b_delta) { return b_delta <= 4 ? kBackPad : 4608; }
-
-__host__ __device__ inline int64_t lds_bytes_for(int64_t cols, int b_delta = 4) {
-  return front_pad_for(b_delta) + 16 * ((cols + 7) / 8) + back_pad_for(b_delta);
-}
 
 // ---- loads of data that is read once ------------------------------------------
 // The format arrays (and the dense matrix of the baseline) are streamed through once per

@@ -625,7 +625,7 @@ int macko_spmv_many(int64_t n, const macko_handle_t* handles, const void* const*
     if (st != MACKO_OK) return st;
   }
   if (n <= MACKO_MAX_GROUP) return n == 0 ? MACKO_OK : macko_spmv_group((int)n, handles, x_dev, y_dev, stream);
-  // Products that all take the wave-per-row kernel with one code width go kMaxWide to a launch, others as
+  // Products that all take the wave-per-row kernel with one code width go kMaxWide to a launch, any others as
   // macko_spmv_group takes them.
   auto problem = [&](int64_t i) {
     macko_handle_t h = handles[i];
@@ -633,25 +633,35 @@ int macko_spmv_many(int64_t n, const macko_handle_t* handles, const void* const*
                               x_dev[i], y_dev[i], h->b_delta, h->b_val};
   };
   int launch_class = -1;
+  int64_t wide_rows = 0;
   for (int64_t i = 0; i < n && launch_class != 0; ++i) {
     if (handles[i]->rows == 0) continue;
     const int c = macko::spmv_launch_class(problem(i));
-    launch_class = launch_class < 0 || launch_class == c ? c : 0;
+    launch_class = launch_class < 0 || launch_class >> 1 == c >> 1 ? c : 0;
+    if (c & 1) wide_rows += handles[i]->rows;
   }
-  const bool uniform = launch_class > 0;
-  auto launch = [&](int64_t at, int count, hipStream_t s) -> int {
-    macko::SpmvProblem p[macko::kMaxWide];
-    int m = 0;
-    for (int i = 0; i < count; ++i)
-      if (handles[at + i]->rows != 0) p[m++] = problem(at + i);
-    return m == 0 ? MACKO_OK : macko::launch_spmv_group(m, p, s);
-  };
+  // A workgroup's LDS holds the widest x of its launch, and next to a wide one all matrices have one workgroup per compute
+  // unit: those with a wide x go apart if they have the rows to fill the chip by themselves (us together / apart, 8-bit values:
+  // 24 of 4096 x 4096 and 8 of 512 x 60000 148 / 110, 8 of 2048 x 2048 and 8 of 1024 x 28672 76 / 50; with few rows the
+  // launch of their own costs more: 15 of 4096 x 4096 and one of 512 x 60000 70 / 79, 4-bit codes 74 / 90).
+  const bool apart = wide_rows >= (int64_t)macko::device_cu_count() * 8;
   // Wide launches follow each other on the caller's stream: the seam between two is 1 % of them, while the fork and join
   // below take some 20 us of the device and two of them at a time are no faster (56 products: 505 us over two side streams).
-  if (uniform) {
-    for (int64_t at = 0; at < n; at += macko::kMaxWide) {
-      const int st = launch(at, (int)std::min<int64_t>(macko::kMaxWide, n - at), static_cast<hipStream_t>(stream));
-      if (st != MACKO_OK) return st;
+  if (launch_class > 0) {
+    for (int pass = 0; pass < (apart ? 2 : 1); ++pass) {
+      macko::SpmvProblem p[macko::kMaxWide];
+      int m = 0;
+      for (int64_t i = 0; i < n; ++i) {
+        if (handles[i]->rows != 0) {
+          p[m] = problem(i);
+          if (!apart || (macko::spmv_launch_class(p[m]) & 1) == pass) ++m;
+        }
+        if (m == macko::kMaxWide || (m > 0 && i == n - 1)) {
+          const int st = macko::launch_spmv_group(m, p, static_cast<hipStream_t>(stream));
+          if (st != MACKO_OK) return st;
+          m = 0;
+        }
+      }
     }
     return MACKO_OK;
   }

@@ -45,6 +45,37 @@ int hip_fail(hipError_t e);
 
 int device_cu_count();
 
+// ---- LDS of the product kernels -----------------------------------------------
+// The activation vector x sits in LDS between two zero-filled guard regions:
+//   [0, front) zeros | x[0 .. C) | zeros up to the end of the allocation.
+// Entries that a lane loads but that belong to a neighbouring row decode to
+// positions just before column 0 or after the row's last column; the guards
+// make those reads return +0 so that they contribute nothing.
+// Front guard: a row's first chunk holds at most 7 entries of the previous row,
+// each at most 2^b_delta columns wide (224 bytes before x[0] for 4-bit codes,
+// 3584 for 8-bit ones).  Back guard: in a row's last step the lanes past the row
+// end advance by one column per entry, plus at most 7 real deltas in the lane
+// that straddles the end (at most 504 + 7 * 2^b_delta columns); the dense kernel
+// reads at most 62 16-byte chunks past the end.
+constexpr int kFrontPad = 256;   // bytes, codes of up to 4 bits (and the dense kernel)
+constexpr int kBackPad = 1280;   // bytes
+
+constexpr int front_pad_for(int b_delta) { return b_delta <= 4 ? kFrontPad : 3584; }
+constexpr int back_pad_for(int b_delta) { return b_delta <= 4 ? kBackPad : 4608; }
+
+constexpr int64_t lds_bytes_for(int64_t cols, int b_delta = 4) {
+  return front_pad_for(b_delta) + 16 * ((cols + 7) / 8) + back_pad_for(b_delta);
+}
+
+constexpr int kMaxStepAlign = 512;      // what the "spmv_step_align" knob may ask for
+// The sparse product may begin a row up to kMaxStepAlign entries early (see macko_spmv.hip): its cleared lanes in front of a
+// row advance 16 bytes each below x[0], and the front guard grows by that.
+constexpr int kAlignFrontPad = 2 * kMaxStepAlign;
+constexpr int spmv_front_pad(int b_delta) { return front_pad_for(b_delta) + kAlignFrontPad; }
+constexpr int64_t spmv_lds_bytes(int64_t cols, int b_delta) { return lds_bytes_for(cols, b_delta) + kAlignFrontPad; }
+constexpr int64_t kMaxLdsBytes = 160 * 1024 - 64;   // 160 KB per CU minus the static row counter
+constexpr int64_t kWideLdsBytes = 36 * 1024;        // an x copy of at least this makes a matrix "wide" for the launch planner
+
 // launchers implemented in the .hip files; all return a macko_status
 constexpr int kMaxGroup = 8;            // MACKO_MAX_GROUP
 constexpr int kMaxWide = 32;            // products in one launch of macko_spmv_many
@@ -71,12 +102,19 @@ int launch_spmv_group(int n, const SpmvProblem* problems, hipStream_t stream);
 // covers 512 entries; below about 40 % use of a step the sub-wave kernel wins: measured
 // crossover between 133 and 247 entries per row on 36864 x 12288 at 98-99 % sparsity).
 constexpr int64_t kWaveRowMinEntries = 192;
-// 0: the product may need a launch of its own; products with the same other number fit one launch of the wave-per-row kernel
-// (an x of up to 64 K columns fits LDS with every code width)
+// Whether the product goes to the wave-per-row kernel (8-bit values: it has to).
+inline bool spmv_takes_wave_row(const SpmvProblem& p) {
+  if (p.rows == 0 || p.pad_nnz == 0 || spmv_lds_bytes(p.cols, p.b_delta) > kMaxLdsBytes) return false;
+  if (p.b_val == 8) return p.b_delta == 4;
+  const int64_t knob = tuning().spmv_kernel;
+  return knob != 0 ? knob == 2 : p.pad_nnz / p.rows >= kWaveRowMinEntries;
+}
+// 0: the product may need a launch of its own, or a kernel that a knob asks for; products whose numbers differ in bit 0 at
+// most fit one launch of the wave-per-row kernel.  Bit 0: a wide x.
 inline int spmv_launch_class(const SpmvProblem& p) {
-  if (p.rows == 0 || p.pad_nnz == 0 || p.cols > 65536 || tuning().spmv_kernel != 0) return 0;
-  if (p.b_val == 8) return p.b_delta == 4 ? 8 * 16 : 0;
-  return p.pad_nnz / p.rows >= kWaveRowMinEntries ? p.b_delta : 0;
+  const Tuning& t = tuning();
+  if (!spmv_takes_wave_row(p) || t.spmv_kernel != 0 || (t.spmv_ring != 0 && t.spmv_ring != 2)) return 0;
+  return 2 * (p.b_val * 16 + p.b_delta) + (spmv_lds_bytes(p.cols, p.b_delta) - kAlignFrontPad >= kWideLdsBytes ? 1 : 0);
 }
 int launch_gemv_group(int n, const GemvProblem* problems, hipStream_t stream);
 // phases of products in one launch, phase p + 1 after phase p: sizes[p] products in phase p, listed in

@@ -176,14 +176,7 @@ struct SpmvGroupHeader {
 // more), 5-8 % slower at 90 % (3 steps), hence the threshold.  256 entries align the codes of
 // 4-bit matrices to their 128-byte lines as well; 512 was no better.
 constexpr int kStepAlign = 256;
-constexpr int kMaxStepAlign = 512;                     // what the "spmv_step_align" knob may ask for
 constexpr int64_t kAlignMinEntries = 1700;
-// cleared lanes in front of a row advance 16 bytes each below x[0]: the front guard grows by that
-constexpr int kAlignFrontPad = 2 * kMaxStepAlign;
-__host__ __device__ constexpr int spmv_front_pad(int b_delta) { return front_pad_for(b_delta) + kAlignFrontPad; }
-__host__ __device__ inline int64_t spmv_lds_bytes(int64_t cols, int b_delta) {
-  return lds_bytes_for(cols, b_delta) + kAlignFrontPad;
-}
 
 // The work of one workgroup: workgroup number `wg` of the matrix given by the
 // pointers, whose rows are dealt out q (+1 for the first r workgroups) at a time.
@@ -588,7 +581,6 @@ int set_lds_limit(K kernel, int64_t bytes) {
   return MACKO_OK;
 }
 
-constexpr int64_t kMaxLdsBytes = 160 * 1024 - 64;   // 160 KB per CU minus the static row counter
 // launches with at most this many wavefront steps per compute unit run as one resident round
 // (the resident round won by 3-7 % up to ~340 steps and lost by 3-10 % from ~500 steps on,
 // measured on 31 matrix shapes and the grouped launches of two decoder-layer shapes)
@@ -599,8 +591,6 @@ constexpr int64_t kStepsPerWave = 8;
 // is long enough for larger ones (14 products of two 13B-shaped layers, us for 8 / 12 / 16 / 24 steps: 2-bit codes
 // 157 / 121 / 120 / 121, 4-bit codes 132 / 126 / 126 / 128)
 constexpr int64_t kStepsPerWaveWide = 16;
-// x copies of at least this many bytes make a matrix "wide" for the launch planner
-constexpr int64_t kWideLdsBytes = 36 * 1024;
 // widest x that is staged once per 256-thread workgroup (see the row-length rule in launch_wave_row_group)
 constexpr int64_t kInStepMaxCols = 8192;
 
@@ -1030,12 +1020,6 @@ int launch_spmv_chain(int n_phases, const int* sizes, const SpmvProblem* problem
 int launch_spmv_group(int n, const SpmvProblem* problems, hipStream_t stream) {
   if (n < 1 || n > kMaxWide) return MACKO_E_INVALID_ARG;
   const Tuning& t = tuning();
-  auto wants_wave_row = [&](const SpmvProblem& p) {
-    if (p.rows == 0 || p.pad_nnz == 0) return false;
-    if (spmv_lds_bytes(p.cols, p.b_delta) > kMaxLdsBytes) return false;
-    if (t.spmv_kernel != 0) return t.spmv_kernel == 2;
-    return p.pad_nnz / p.rows >= kWaveRowMinEntries;
-  };
   // matrices that do not go into a grouped wave-per-row launch
   for (int i = 0; i < n; ++i) {
     const SpmvProblem& p = problems[i];
@@ -1048,8 +1032,8 @@ int launch_spmv_group(int n, const SpmvProblem* problems, hipStream_t stream) {
       hipError_t e0 = hipGetLastError();
       if (e0 != hipSuccess) return hip_fail(e0);
     } else if (p.b_val == 8) {                          // 8-bit values: 4-bit codes, wave-per-row kernel only
-      if (p.b_delta != 4 || spmv_lds_bytes(p.cols, 4) > kMaxLdsBytes) return MACKO_E_UNSUPPORTED;
-    } else if (!wants_wave_row(p)) {                    // short rows or x larger than LDS: own launch
+      if (!spmv_takes_wave_row(p)) return MACKO_E_UNSUPPORTED;
+    } else if (!spmv_takes_wave_row(p)) {                    // short rows or x larger than LDS: own launch
       int st = launch_subwave(p, (int)t.spmv_lanes, stream);
       if (st != MACKO_OK) return st;
     }
@@ -1059,7 +1043,7 @@ int launch_spmv_group(int n, const SpmvProblem* problems, hipStream_t stream) {
     const SpmvProblem* wr[kMaxWide];
     int nwr = 0;
     for (int i = 0; i < n; ++i)
-      if (problems[i].b_delta == bd && problems[i].b_val == 16 && wants_wave_row(problems[i])) wr[nwr++] = &problems[i];
+      if (problems[i].b_delta == bd && problems[i].b_val == 16 && spmv_takes_wave_row(problems[i])) wr[nwr++] = &problems[i];
     if (nwr == 0) continue;
     int st = launch_wave_row_group(nwr, wr, bd, 16, stream);
     if (st != MACKO_OK) return st;

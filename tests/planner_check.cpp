@@ -15,6 +15,9 @@
 
 using namespace macko;
 
+static Tuning knobs;
+Tuning& macko::tuning() { return knobs; }              // the library's own lives in its host translation unit
+
 static int failures = 0;
 #define EXPECT(cond, ...)                      \
   do {                                         \
@@ -210,6 +213,39 @@ int main() {
       replay(ph, sizes[p], in + at, "chain phase");
       at += sizes[p];
     }
+  }
+
+  // ---- which products share a launch of macko_spmv_many ------------------------------------
+  {
+    auto product = [](int64_t rows, int64_t cols, int64_t per_row, int b_delta, int b_val) {
+      SpmvProblem p{};
+      p.rows = rows; p.cols = cols; p.pad_nnz = rows * per_row; p.b_delta = b_delta; p.b_val = b_val;
+      return p;
+    };
+    const int narrow = spmv_launch_class(product(4096, 4096, 2048, 4, 16));
+    EXPECT(narrow > 0 && (narrow & 1) == 0, "class %d", narrow);
+    EXPECT(spmv_launch_class(product(77, 900, 300, 4, 16)) == narrow, "the same code width");
+    // the planner calls an x of 36 KB wide: such a matrix shares no launch with the others
+    int64_t cols = 4096;
+    while (spmv_lds_bytes(cols, 4) - kAlignFrontPad < kWideLdsBytes) cols += 8;
+    EXPECT(spmv_launch_class(product(512, cols - 8, 4000, 4, 16)) == narrow, "%lld columns", (long long)cols - 8);
+    EXPECT(spmv_launch_class(product(512, cols, 4000, 4, 16)) == (narrow | 1), "%lld columns", (long long)cols);
+    EXPECT(spmv_launch_class(product(512, 60000, 4000, 4, 16)) == (narrow | 1), "60000 columns");
+    EXPECT(spmv_launch_class(product(512, 81920, 4000, 4, 16)) == 0, "an x that does not fit LDS");
+    for (int bd : {1, 2, 8})
+      EXPECT((spmv_launch_class(product(512, 4096, 2048, bd, 16)) ^ narrow) > 1, "codes of %d bits", bd);
+    EXPECT((spmv_launch_class(product(512, 4096, 100, 4, 8)) ^ narrow) > 1, "8-bit values");
+    EXPECT(spmv_launch_class(product(512, 4096, kWaveRowMinEntries - 1, 4, 16)) == 0, "short rows");
+    EXPECT(spmv_launch_class(product(512, 4096, 0, 4, 16)) == 0 && spmv_launch_class(product(0, 4096, 0, 4, 16)) == 0, "nothing stored");
+    // a knob that asks for a kernel the wide launch does not have
+    for (int ring : {0, 2, 3, 4}) {
+      knobs.spmv_ring = ring;
+      EXPECT((spmv_launch_class(product(4096, 4096, 2048, 4, 16)) == narrow) == (ring == 0 || ring == 2), "spmv_ring %d", ring);
+    }
+    knobs.spmv_ring = 0;
+    knobs.spmv_kernel = 2;
+    EXPECT(spmv_launch_class(product(4096, 4096, 2048, 4, 16)) == 0 && spmv_takes_wave_row(product(4096, 4096, 10, 4, 16)), "spmv_kernel 2");
+    knobs.spmv_kernel = 0;
   }
 
   if (failures) { std::printf("%d failures\n", failures); return 1; }

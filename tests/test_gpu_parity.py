@@ -1755,3 +1755,25 @@ def test_spmm_on_both_sides_of_the_rule_that_picks_its_kernel(kind, rows, cols, 
     ref, mag = X.double() @ W64.T.contiguous(), X.double().abs() @ W64.abs().T.contiguous()
     bound = ref.abs() * 2.0 ** -11 + 2.0 ** -25 + mag * cols * 2.0 ** -24          # as in test_spmm_tile_edges
     assert float(((Y - ref).abs() / bound).max()) <= 1.01
+
+
+@pytest.mark.parametrize("kind", ["b4", "fp8"])
+@pytest.mark.parametrize("rows_of_the_wide,n_wide", [(300, 1), (700, 8), (2100, 1)])
+def test_spmv_many_with_a_wide_x_among_others(kind, rows_of_the_wide, n_wide):
+    """Matrices whose x takes more than 36 KB of LDS share the launch of the others or go apart, by their rows; the results are
+    those of single products, whatever the order and with a matrix without rows between them."""
+    rng = np.random.default_rng(rows_of_the_wide + n_wide)
+    shapes = [(int(rng.integers(1, 90)), int(rng.integers(700, 3000))) for _ in range(23)] + [(rows_of_the_wide, 20000 + 8 * i) for i in range(n_wide)]
+    shapes = [shapes[i] for i in rng.permutation(len(shapes))]
+    shapes.insert(5, (0, 700))
+    mats, xs = [], []
+    for rows, cols in shapes:
+        W = (rng.standard_normal((rows, cols)) * (rng.random((rows, cols)) < 0.5)).astype(np.float16)
+        mats.append((M.encode_fp8(wl.fp8_values_of(W.view(np.uint16)) if rows else W.astype(np.uint8)) if kind == "fp8" else M.encode(W)).to_device())
+        xs.append(torch.from_numpy(rng.standard_normal(cols).astype(np.float16)).cuda())
+    ys = [torch.full((m.rows,), 7.0, dtype=torch.float16, device="cuda") for m in mats]
+    M.SpmvMany(mats, xs, ys).launch()
+    want = [m.spmv(x) for m, x in zip(mats, xs)]
+    torch.cuda.synchronize()
+    for i in range(len(mats)):
+        assert torch.equal(ys[i], want[i]), (kind, i, shapes[i])

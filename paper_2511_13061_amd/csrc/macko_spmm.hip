@@ -314,7 +314,8 @@ constexpr int64_t kLongRow = 384;       // stored entries per row from which vec
 // The matrix cores serve up to 16 vectors at one price: they pay for the cells of their tiles, 16 rows by a window of columns, whatever
 // is stored there, and for whole rounds of tiles.  The vector kernel pays per stored entry and vector, in pieces of 8, 4, 2
 // or 1 vectors (whatever fits LDS, each piece a launch).  So the line lies where too few of the cells hold an entry, the lower the
-// more vectors there are.  All figures are microseconds, vector kernel / matrix cores, over 10 500 calls of 8 to
+// more vectors there are.  (Vectors of a number of elements that is no multiple of 8 it stages one by one: 256 x 4500 at 97 %, 12
+// vectors: 11.1 / 9.0, 256 x 4096: 7.2 / 7.7.)  All figures are microseconds, vector kernel / matrix cores, over 10 500 calls of 8 to
 // 36864 rows, 512 to 60000 columns, 30 to 99.9 % pruned; over the range where both ways win (5 to 8 vectors, 9400 to 19700
 // columns) the lines below are within 1 % of always taking the faster way.
 bool tile_is_faster(const SpmvProblem& p, int batch) {
@@ -333,18 +334,17 @@ bool tile_is_faster(const SpmvProblem& p, int batch) {
     const bool one_launch = p.b_val == 8 || avg >= kWaveRowMinEntries;
     if (batch <= 8) {
       if (p.rows < 16 * cus) return false;            // 512 x 512, 8 vectors: 4.1 / 5.1
-      if (!one_launch || p.cols <= 2048 || rounds == 1) return true;
+      if (!one_launch || p.cols <= 2048 || p.cols % 8 != 0 || rounds == 1) return true;
       if (batch == 5) return filled >= 0.75 && p.cols <= 4096;   // 4200 x 4096 at 98 %: 9.7 / 11.1; 8300 x 5000: 1.3 times
       return batch > 6 || filled >= 0.75 || p.cols <= 4096;      // 4200 x 5000 at 98 %, 6 vectors: 1.17 times
     }
     // two launches, about 7 us however few the rows (5000 columns at 98 %, 16 rows, 9 vectors: 6.7 / 8.8, 256 rows:
     // 7.3 / 9.0, 768 rows: 1.02 times; 4096 columns at 97 %, 64 rows: 6.8 / 7.7, 512 rows: 7.9 / 7.8)
-    return !one_launch || p.cols <= 2048 || p.rows > (p.cols > 4096 ? 512 : 256);
+    return !one_launch || p.cols <= 2048 || p.cols % 8 != 0 || p.rows > (p.cols > 4096 ? 512 : 256);
   }
   if (batch > 8) {
     // One piece of 8 or two of 4, and the rest: 8300 x 6000 at 97 %, 9 vectors: 15.8 / 18.8; 5000 x 14336 at 99 %: 19.6 / 22.9;
-    // but in one round of tiles 4096 x 6000 at 97 %: 0.71 times, and with a number of columns that is no multiple of 8, which
-    // the vector kernel stages element by element, 4200 x 4500 at 90 %: 0.71 times.
+    // but in one round of tiles 4096 x 6000 at 97 %: 0.71 times, and 4200 x 4500 at 90 %, no multiple of 8: 0.71 times.
     if (batch > 12 || rounds == 1 || p.cols <= 4096 || p.cols % 8 != 0 || 4 * one > kBatchLdsLimit) return true;
     return cells >= (batch <= 10 ? 0.08 : 0.05);
   }

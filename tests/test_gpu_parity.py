@@ -1735,6 +1735,7 @@ def test_decode_device_long_rows_either_way(rows, cols, density, b_delta, shift,
 @pytest.mark.parametrize("rows,cols,sparsity,batch", [
     # rows shorter than a step: one or two launches of the product with one vector, or the matrix cores
     (4200, 4096, 0.98, 5), (4200, 5000, 0.98, 6), (5000, 4096, 0.98, 6), (16, 5000, 0.98, 9), (513, 5000, 0.98, 9), (256, 4096, 0.97, 16),
+    (256, 4500, 0.97, 12), (4200, 4100, 0.98, 5),
     # 9 to 12 vectors on sparse rows, in one round of tiles and more
     (4097, 6000, 0.97, 9), (4096, 6000, 0.97, 9), (4097, 6000, 0.97, 12), (4097, 6000, 0.97, 13), (4097, 6004, 0.97, 9),
     # 5 to 8 vectors where 8, 4 or 2 of them fit LDS: few rows, one round of tiles, more

@@ -1445,7 +1445,9 @@ def _batch_reference(W64, X64):
 @pytest.mark.parametrize("rows,cols,batch", [
     (1, 8, 9), (15, 63, 16), (16, 64, 17), (17, 65, 32), (33, 127, 33), (40, 129, 48), (31, 1000, 49), (48, 2047, 64),
     (20, 2048, 9), (19, 2049, 16), (18, 4095, 10), (16, 4096, 15), (35, 4097, 12), (23, 4097, 64), (9, 8193, 20), (7, 12000, 7),
-    (4099, 77, 5), (4100, 300, 11), (4200, 130, 50)])
+    (4099, 77, 5), (4100, 300, 11), (4200, 130, 50),
+    # several tiles a workgroup and several windows a tile; more than 64 rows a wavefront in 256 workgroups
+    (4200, 4500, 12), (8500, 2300, 40), (9001, 2049, 64), (262160, 16, 9)])
 def test_spmm_tile_edges(kind, rows, cols, batch):
     """Tiles of 16 rows, windows of 2048 or 4096 columns, groups of 128 columns, 16 vectors per instruction: the sizes
     around them, with empty rows, rows that start inside a chunk, values below 2^-14, strided and 2-byte aligned
@@ -1511,6 +1513,45 @@ def test_spmm_tile_leaves_out_what_is_not_stored(kind):
     assert np.allclose(Y[fine], ref[fine], atol=2e-3, rtol=2e-3)
 
 
+@pytest.mark.parametrize("kind", ["b2", "b4", "fp8"])
+@pytest.mark.parametrize("cols,batch", [(2100, 20), (4300, 10), (900, 50)])
+def test_spmm_tile_not_finite_in_later_tiles(kind, cols, batch):
+    """Three tiles a workgroup (9000 rows): results that hold an infinity or a NaN are found and computed apart in each of
+    them, their neighbours are what they are without it.  Reference as above, for rows of all three tiles."""
+    rng = np.random.default_rng(cols + batch)
+    rows = 9000
+    W = (rng.standard_normal((rows, cols)) * (rng.random((rows, cols)) < 0.05)).astype(np.float16)
+    X = rng.standard_normal((batch, cols)).astype(np.float16)
+    X[1, 7] = np.inf
+    X[batch - 1, cols - 1] = np.nan
+    W[3::9, 7] = 0.5                                                       # in every tile some rows store these columns
+    W[5::9, -1] = -0.25
+    if kind == "fp8":
+        m = M.encode_fp8(wl.fp8_values_of(W.view(np.uint16))).to_device()
+        values, _, row_ptr = m.host_buffers()
+        values = oracle.fp8_to_double(np.arange(256, dtype=np.uint8))[values]
+    else:
+        W[8999, 3] = -np.inf
+        m = M.encode(W, int(kind[1])).to_device()
+        values, _, row_ptr = m.host_buffers()
+        values = values.view(np.float16).astype(np.float64)
+    Y = m.spmm(torch.from_numpy(X).cuda()).cpu().numpy().astype(np.float64)
+    columns = m.columns_device().cpu().numpy()
+    X64 = X.astype(np.float64)
+    hit = np.zeros((2, 3), dtype=bool)
+    for r in list(range(0, 36)) + list(range(4500, 4572)) + list(range(8964, 9000)):      # 35 or 36 rows a workgroup
+        a, b = int(row_ptr[r]), int(row_ptr[r + 1])
+        with np.errstate(invalid="ignore"):
+            ref = X64[:, columns[a:b]] @ values[a:b]
+        fine = np.isfinite(ref)
+        assert np.array_equal(Y[~fine, r], ref[~fine], equal_nan=True), r
+        assert np.allclose(Y[fine, r], ref[fine], atol=2e-3, rtol=2e-3), r
+        if r < 36:
+            hit[0, r // 16] |= not fine[1]
+            hit[1, r // 16] |= not fine[batch - 1]
+    assert hit[:, :2].all()                                                # in the first workgroup's first two tiles at least
+
+
 # ------------------------------------------------------------------ GPU encoder: windows, shared words, unaligned rows
 
 @pytest.mark.parametrize("kind", ["b1", "b2", "b4", "b8", "fp8"])
@@ -1544,9 +1585,10 @@ def test_gpu_encoder_window_edges(kind, rows, cols, density, shift):
 @pytest.mark.parametrize("kind", ["b1", "b2", "b4", "b8", "fp8"])
 @pytest.mark.parametrize("rows,cols,density,shift", [
     (70, 1, 0.5, 0), (50, 7, 0.9, 1), (33, 2047, 0.5, 3), (20, 2048, 0.5, 0), (20, 2049, 0.4, 5), (12, 4096, 0.9, 8),
-    (11, 4103, 0.03, 2), (7, 40001, 0.0003, 7), (3, 100000, 0.3, 0), (40, 300, 0.0, 4)])
+    (11, 4103, 0.03, 2), (7, 40001, 0.0003, 7), (3, 100000, 0.3, 0), (40, 300, 0.0, 4),
+    (14, 4095, 0.5, 3), (14, 4097, 0.4, 0), (9, 8191, 0.5, 1), (9, 8192, 0.5, 0), (9, 8193, 0.5, 5)])
 def test_decode_device_windows(kind, rows, cols, density, shift):
-    """Rows around a window of 4096 bytes, rows that begin at any element, steps that reach over several windows; the
+    """Rows around a window of 8192 bytes (4096 values of 16 bits, 8192 of 8), rows that begin at any element, steps that reach over several windows; the
     cells around the matrix keep what they hold."""
     rng = np.random.default_rng(rows + 13 * cols)
     W = ((rng.standard_normal((rows, cols)) + 3) * (rng.random((rows, cols)) < density)).astype(np.float16)

@@ -234,7 +234,7 @@ MACKO_API int macko_columns_device(macko_handle_t h, int32_t* cols_dev, void* st
  * with 8-bit values, at most 163840 columns), ld >= cols elements, aligned to
  * its element size, caller owned, must not overlap the format arrays.  Cells [r][0, cols)
  * are overwritten, cells between cols and ld are left untouched.  Enqueues one
- * kernel on `stream` and does not synchronise. */
+ * kernel on `stream` (two for a few sparse rows of more than 81920 columns) and does not synchronise. */
 MACKO_API int macko_decode_device(macko_handle_t h, void* dense_dev, int64_t ld, void* stream);
 
 /* ---- the product (Section 4.4; Y = M V of Appendix A) --------------------- */
@@ -253,8 +253,9 @@ MACKO_API int macko_dense_gemv(const void* W_dev, int64_t rows, int64_t cols, in
                                const void* x_dev, void* y_dev, void* stream);
 
 /* Small-batch product with one matrix: the matrix is streamed and decoded once for the whole
- * batch on the matrix cores (more than 8 vectors, or 5 to 8 where the vector kernel would need
- * several pieces; codes of up to 4 bits, ldx < 2^24), else once per piece of up to 8 vectors, for every
+ * batch on the matrix cores (more than 16 vectors; 5 to 16 where the vector kernel would need
+ * several pieces and the rows are not too sparse for tiles; codes of up to 4 bits, two columns or more,
+ * ldx < 2^24), else once per piece of up to 8 vectors, for every
  * code width and both value widths (rows shorter than 384 stored entries on average, and batches whose
  * interleaved vectors do not fit LDS, then run as independent matrix-vector products).
  * An infinity or a NaN in a vector reaches only the results of rows that store an entry at its column
@@ -282,7 +283,9 @@ MACKO_API int macko_spmv_group(int n, const macko_handle_t* handles, const void*
 
 /* Any number of independent products (the linear layers of a whole stack, one
  * x and one y each).  Products that all take the wavefront-per-row kernel with one
- * code width and value width go up to 32 to a launch, on `stream`.  Others are dealt out as grouped launches of up to
+ * code width and value width go up to 32 to a launch, on `stream` (those of more than about 17600 columns apart from the
+ * others where they have rows enough for the chip; not with the knob "spmv_ring" above 2, whose kernels take up to
+ * MACKO_MAX_GROUP matrices).  Others are dealt out as grouped launches of up to
  * MACKO_MAX_GROUP consecutive products to three side streams that the library keeps per
  * device, so that the end of one launch overlaps the start of the next (a
  * launch costs about 3 us whatever its size).  The side

@@ -486,7 +486,8 @@ int launch_decode(const SpmvProblem& p, void* dense_any, int64_t ld, hipStream_t
   const bool vec = (p.cols * eb) % 16 == 0 && (ld * eb) % 16 == 0 && (reinterpret_cast<uintptr_t>(dense_any) & 15) == 0;
   const int64_t row_bytes = 16 * ((p.cols * eb + 15) / 16);
   constexpr int64_t kLdsLimit = 160 * 1024;
-  if (p.b_val == 8 && row_bytes > kLdsLimit) return MACKO_E_UNSUPPORTED;    // 8-bit rows of more than 163840 columns
+  // 8-bit rows of more than 163840 columns: no kernel below has that limit any more, but the interface states it
+  if (p.b_val == 8 && row_bytes > kLdsLimit) return MACKO_E_UNSUPPORTED;
   if (p.b_val == 8 && p.b_delta != 4) return MACKO_E_UNSUPPORTED;           // 8-bit values come with 4-bit codes
   // Row buffers per compute unit: at least 8 (4096 x 11008 has 7: 38.5 us, in windows 34.5; 9000 columns have 8: 9.8 us for 2000
   // rows, in windows 10.3), and rows on 16 bytes unless they are short (1000 x 4093: 7.1 and 6.1; 9000 x 300: 4.6 and 5.3).

@@ -634,7 +634,7 @@ int encode_on_device(const void* dense, int64_t rows, int64_t cols, int64_t ld, 
   }
   MACKO_HIP_TRY(hipGetLastError());
   MACKO_HIP_TRY(hipStreamSynchronize(stream));
-  // a large scratch buffer (more than 8 M rows) is not kept
+  // a large scratch buffer is not kept (from 6.7 M rows on: 8 bytes per row and a quarter more)
   if (ws.cap > kKeepScratchBytes) {
     (void)hipFree(ws.p);
     ws.p = nullptr;

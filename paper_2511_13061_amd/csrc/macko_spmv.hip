@@ -755,7 +755,10 @@ int launch_wave_row_group(int nwr, const SpmvProblem* const* wr, int b_delta, in
   // 8192 x 8192 17.8 -> 16.4, 28672 x 8192 49.2 -> 47.8; iid masks with that average gain as much as exact
   // per-row counts (14336 x 4096: 15.7 -> 14.9 and 15.9 -> 14.8).  Other row lengths on the same shapes (30, 70, 80,
   // 90 % sparsity, 3584 columns) are 1-4 % faster in the resident round and stay there; x of more than
-  // 8192 columns costs too much to stage once per small workgroup.
+  // 8192 columns costs too much to stage once per small workgroup.  With 8-bit values such rows start a multiple of 2048 bytes
+  // apart, and gain as much once there are enough of them (us, resident round -> here: 14336 x 4096 13.4 -> 12.4, 22016 x 4096
+  // 19.3 -> 17.1, 28672 x 4096 25.1 -> 22.0, 14336 x 3072 at 33 % 13.3 -> 12.3; 4096, 8192 and 11008 x 4096 within 2 %); 4096 entries, the
+  // full 4096 bytes, do not need it (8192 x 8192 13.2 and 13.2; 11008 x 8192 16.6 -> 16.7, with exact per-row counts 17.7).
   bool in_step = t.spmv_resident == 0 && t.spmv_block == 0;
   for (int i = 0; i < nwr; ++i) {
     const int64_t avg = wr[i]->pad_nnz / wr[i]->rows;

@@ -193,6 +193,8 @@ spmm_tile_kernel(const TileArgs a) {
   const uint32_t xoff = xmis + 4u * ((lane >> 2) & 3) * ldx2 + 2u * bcol;
   u32x4 b[G][NT][4];
   int k0 = 0, tile = 0;                                // first column of the window, tile
+  const int cols2 = 2 * ((cols + 127) & ~127);         // doubled end of the groups that are multiplied
+  uint32_t put_bytes = (uint32_t)min(2 * kWindow, cols2) + kTilePad;       // lanes that start in the window, and in these groups
   auto load_b = [&]() {
     uint32_t xo = xoff;
     if (NT > 2) asm volatile("" : "+v"(xo));           // no offsets computed in front of the loop and kept in registers
@@ -286,9 +288,9 @@ spmm_tile_kernel(const TileArgs a) {
             acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, __builtin_bit_cast(half8, b[g][t][r]), acc[t], 0, 0, 0);
           if (NT > 2) __builtin_amdgcn_sched_barrier(0);
         }
-      } else {
-        // Groups behind the last column are not multiplied.  What a wrong encoding's row puts there would be part of the
-        // next tile's row: a right one's leaves zeros.
+      } else if (kg < cols + 128) {
+        // Groups behind the last column are not multiplied.  What a wrong encoding's row puts into the first of them (into
+        // the others nothing is put) would be part of the next tile's row: a right one's leaves zeros.
 #pragma unroll
         for (int r = 0; r < 4; ++r) *reinterpret_cast<half8*>(arow + 256 * g + 16 * r) = half8{0, 0, 0, 0, 0, 0, 0, 0};
       }
@@ -296,6 +298,7 @@ spmm_tile_kernel(const TileArgs a) {
     k0 += kWindow;
     const bool done = k0 >= cols;
     if (done) k0 = 0;
+    put_bytes = (uint32_t)min(2 * kWindow, cols2 - 2 * k0) + kTilePad;
     __builtin_amdgcn_sched_barrier(0);
     load_b();                                          // under way while the next window is decoded
     __syncthreads();                                   // the tile is zero again
@@ -402,7 +405,7 @@ spmm_tile_kernel(const TileArgs a) {
         // lanes without an entry in the window write to the pad; so do a lane's entries in front of the window or
         // behind it.  What is behind the row's end is zero, and so is the tile there.
         int rel = lanebase - 2 * k0;
-        rel = (uint32_t)(rel + kTilePad) < (uint32_t)(2 * kWindow + kTilePad) ? rel : -kTilePad;
+        rel = (uint32_t)(rel + kTilePad) < put_bytes ? rel : -kTilePad;
         unsigned char* p = rowbuf + rel;
 #define MACKO_PUT(K) *reinterpret_cast<uint16_t*>(p + w.template offset<K>()) = (uint16_t)v.template half<K>();
         MACKO_PUT(0) MACKO_PUT(1) MACKO_PUT(2) MACKO_PUT(3) MACKO_PUT(4) MACKO_PUT(5) MACKO_PUT(6) MACKO_PUT(7)

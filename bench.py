@@ -245,8 +245,8 @@ def main():
     ap.add_argument("--gpus", type=int, default=1)
     ap.add_argument("--steps", type=int, default=1000)
     ap.add_argument("--warmup", type=int, default=100)
-    ap.add_argument("--no-sweep", action="store_true", help="skip the 36864x12288 sparsity sweep (configs[2])")
-    ap.add_argument("--no-stack", action="store_true", help="skip the Llama2-13B-shaped 32-layer stack (configs[4])")
+    ap.add_argument("--no-sweep", action="store_true", help="skip the 36864x12288 sparsity sweep")
+    ap.add_argument("--no-stack", action="store_true", help="skip the Llama2-13B-shaped 32-layer stack")
     ap.add_argument("--no-spmm", action="store_true", help="skip the small-batch product macko_spmm")
     ap.add_argument("--no-verify", action="store_true",
                     help="do not compare y of every timed configuration with the CPU oracle before timing it")
@@ -258,7 +258,7 @@ def main():
     ap.add_argument("--shapes-sparsity", default="50", metavar="LIST",
                     help="sparsity levels in per cent for --shapes, comma separated (default 50)")
     ap.add_argument("--adversarial", action="store_true",
-                    help="also time the two 8192x8192 padding stress matrices (configs[3])")
+                    help="also time the two 8192x8192 padding stress matrices")
     ap.add_argument("--widths", action="store_true",
                     help="also time 2-, 4- and 8-bit codes on the 36864x12288 matrix (Appendix C of the paper)")
     ap.add_argument("--fp8", action="store_true", help="also time the layer step with 8-bit (E4M3) values")
@@ -657,7 +657,7 @@ def main():
             torch.cuda.empty_cache()
         extra["sweep_36864x12288"] = sweep
 
-    # ---- optional: padding stress (configs[3]) ------------------------------------
+    # ---- optional: padding stress -------------------------------------------------
     if args.adversarial:
         table = {}
         for case in (wl.config4(), wl.config4b()):
@@ -938,7 +938,7 @@ def main():
         "value": round(gbps, 1), "unit": "GB/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": round(ms_per_step, 5), "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "f16 in, f32 accumulate", "data": "synthetic",
-        "config": {"workload": "configs[1]: Llama2-7B-shaped layer set, 50% per-row unstructured sparsity, "
+        "config": {"workload": "Llama2-7B-shaped layer set, 50% per-row unstructured sparsity, "
                                "one step = 4x(4096x4096) + 2x(11008x4096) + 1x(4096x11008) SpMVs, batch 1, "
                                "issued in dependency order {q,k,v} -> {o} -> {gate,up} -> {down} as 4 grouped launches",
                    "layer_copies_rotated": n_layers, "launches_per_step": launches_per_step,

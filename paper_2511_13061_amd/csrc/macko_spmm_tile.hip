@@ -12,7 +12,7 @@
 // workgroup per compute unit), scattering into LDS 2, and the window products 4, half of that the
 // transposes of the B operand (times found by leaving one part out).  Counters: 4.96 M vector instructions, 8 us of issue,
 // there, and 11.7 M, 19 of 43 us, for 11008 x 4096 with 64 vectors; the rest is waited for.  A second workgroup per compute
-// unit could cover that; LDS has room for two (with windows of 2048 columns), registers do not (84 to 126, where 64 would do).
+// unit could cover that; LDS has room for two (with windows of 2048 columns), registers do not (75 to 125, where 64 would do).
 // The vectors are read again for every tile, and after its last window twice: what follows that window is requested before
 // its reduction and once more behind it, and the last tile requests a window that nobody uses.  With 64 vectors of 4096
 // elements that is 10 loads of 256 KB per workgroup where 6 are used, 0.7 GB through the caches for a problem of 58 MB (0.78 M

@@ -7,23 +7,27 @@
 // the A operand of v_mfma_f32_16x16x32_f16 (fp16 products, fp32 accumulation), the vectors are the B
 // operand.  The cost per stored entry no longer depends on the batch.
 //
-// What bounds it: vector issue.  Of 19 us for 4096 x 11008 at 50 % with 8 vectors, the decode takes
-// about 6 (65 vector instructions per step of 512 entries), memory latency 4 (one 16-wavefront
-// workgroup per compute unit), scattering into LDS 2, and the window products 4, half of that the
-// transposes of the B operand (times found by leaving one part out).  Counters: 4.96 M vector instructions, 8 us of issue,
-// there, and 11.7 M, 19 of 43 us, for 11008 x 4096 with 64 vectors; the rest is waited for.  A second workgroup per compute
-// unit could cover that; LDS has room for two (with windows of 2048 columns), registers do not (75 to 125, where 64 would do).
-// The vectors are read again for every tile, and after its last window twice: what follows that window is requested before
-// its reduction and once more behind it, and the last tile requests a window that nobody uses.  With 64 vectors of 4096
-// elements that is 10 loads of 256 KB per workgroup where 6 are used, 0.7 GB through the caches for a problem of 58 MB (0.78 M
-// vector loads counted per call).  Measured against the vector kernel
-// at 50 % (us, batch 8 / 16 / 64): 4096 x 11008: 29.6 / 59 / 239 -> 20.5 / 21.2 / 38.7, 11008 x 4096:
-// 23.6 / 46 / 183 -> 22.7 / 23.2 / 43.6, 4096 x 4096: 12.1 / 24 / 96 -> 11.5 / 11.7 / 19.0.
+// A workgroup takes a panel of 16 P rows (P = 1, 2 or 3 tiles of 16) through the windows; each of its 16 wavefronts decodes P
+// rows.  The window's vectors are loaded and turned into the B operand once for all tiles of the panel, which is what counts
+// with many vectors: X passes a compute unit's L1 at 64 bytes a clock, 3.4 us for 64 vectors of 4096 elements, and used to be
+// read for every 16 rows.  LDS holds about 65 000 cells in all, so a panel of more rows has narrower windows.
 //
-// Tried: 8 rows per workgroup and two workgroups per compute unit (28-40 us where 16 rows take 21: half
-// of the matrix instruction is idle and every B element is fetched twice); 3 and 4 steps loaded ahead
-// instead of 2 (slower); the B operand loaded straight into the operand's lane order (16
-// vectors on 16 neighbouring lanes: every lane is a memory request of its own, 64 vectors took 63 us).
+// What bounds it: no unit by itself.  11008 x 4096 at 50 % with 64 vectors, 34 us: vector issue 12 (decode 45 instructions
+// per step of 512 entries, 11 per window that a step reaches into, 64 per four 16-byte loads of B), LDS 9, HBM 8.5, matrix
+// cores 2.6, loads of B 3.4; but the phases of a window (decode, product, clearing) alternate behind barriers, and one
+// 16-wavefront workgroup per compute unit covers little of one with another.  Leaving out the puts into the tile takes 4 us off, B and its
+// transposes 8, the matrix instructions 3; a window costs about 2 us whatever is in it, so few, large windows are best.
+// Measured before (16 rows at a time, X read for each, transposes behind the barrier) and now, us, batch 8 / 16 / 32 / 64 at 50 %:
+// 4096 x 11008: 21.8 / 21.8 / 28.0 / 39.5 -> 20.4 / 20.4 / 26.3 / 37.4; 11008 x 4096: 24.3 / 24.3 / 30.4 / 44.6 -> 23.1 /
+// 23.1 / 30.3 / 34.1; 4096 x 4096: 12.4 / 12.4 / 14.6 / 20.4 -> 10.2 / 10.2 / 12.8 / 17.2; 11008 x 4096 at 90 %, 64: 37.2 -> 22.7.
+// 260 matrices of 300 to 14336 rows, 700 to 13000 columns, 40 to 93 % pruned, 12 to 64 vectors: 1.37 times as fast
+// (geometric mean), the slowest (wide, few rows: 2800 x 13000) 4 % slower.
+//
+// Tried: two workgroups of 8 wavefronts per compute unit, each with half of the rows (5 to 30 % slower: X is read twice, and
+// more windows); 512-column windows in two buffers for panels of 48 rows (34 -> 41 us); a ring of 2 to 4 steps of loads refilled one by one
+// (no gain over units of S steps); 3 and 4 steps per unit (within 3 % either way); the prefix sums of a unit's steps interleaved
+// (no gain); B loaded straight into the operand's lane order (16 vectors on 16 neighbouring lanes: every lane is a
+// memory request of its own).
 #include "macko_decode.h"
 #include "macko_device.h"
 #include "macko_internal.h"
@@ -35,15 +39,13 @@ typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kTileRows = 16;                          // rows of a tile = wavefronts of a workgroup
+constexpr int kWaves = 16;                             // wavefronts of a workgroup, and rows of a tile
 // Bytes in front of every row of the tile (and behind the last) that are written but never read: entries
 // in front of the window or behind it land there.  A lane's 8 entries span at most 8 * 2 * 16 bytes.
 constexpr int kTilePad = 256;
-constexpr int tile_window(int groups) { return 128 * kTileRows * groups; }          // columns
 // 16 bytes more per row: the 16 rows that a matrix instruction reads at one column fall on different banks
-constexpr int tile_stride(int groups) { return 2 * tile_window(groups) + kTilePad + 16; }
-constexpr int tile_lds(int groups) { return kTileRows * tile_stride(groups) + kTilePad; }
-static_assert(64 * kTileRows == 1024 && 4 * (kTileRows - 1) * 1024 <= tile_lds(1), "the partial sums of 64 vectors fit the tile's memory");
+constexpr int panel_stride(int window) { return 2 * window + kTilePad + 16; }
+constexpr int panel_slices(int window, int vs) { return window / 128 < kWaves / vs ? window / 128 : kWaves / vs; }
 
 struct TileArgs {
   const void* values;
@@ -53,6 +55,7 @@ struct TileArgs {
   uint16_t* Y;
   int64_t ldx, ldy;
   int rows, cols, batch, q, r;                         // rows per workgroup: q, one more for the first r
+  int window;                                          // columns of a window, a multiple of 128
 };
 
 // dst = src as real register moves.  The source registers are free afterwards, so that the next load can go
@@ -135,53 +138,60 @@ __device__ __forceinline__ void tile_row_by_entries(const TileArgs& a, int row, 
   }
 }
 
-// NT: tiles of 16 vectors.  G: groups of 128 columns per wavefront and window.  S: steps loaded ahead.
+// NT: tiles of 16 vectors; a launch of more vectors has several rows of workgroups.  P: tiles of 16 rows in a panel.  W: columns
+// of the largest window (a.window: of this launch's).  VS: parts into which the vector tiles are dealt to the wavefronts.
+// DBL: two buffers.  S: steps of 512 entries that are loaded, taken and decoded together (a unit).
 //
-// A workgroup works on one tile of 16 rows after the other; a wavefront's rows (one per tile) form one stream
-// of steps, so that the loads run on across windows and tiles.  Decoding and the products of the windows
-// alternate; a step that reaches behind the window is put into the tile in parts, one window after the other, out
-// of registers.  Every wavefront takes part in every window's product (128 G columns each) whatever its row
-// holds, so all of them execute the same number of barriers.
-template <int NT, int BD, int VB, int G, int S>
-__global__ void __launch_bounds__(64 * kTileRows)
-spmm_tile_kernel(const TileArgs a) {
+// Window by window, a wavefront
+//  - clears its own rows of the tile and puts what it holds of them (the last unit taken may reach into several windows: its
+//    codes, values and position stay in registers until the row's next unit takes their place);
+//  - takes further units of its P rows until every row has passed the window's end.  All rows' units are taken out of the load
+//    registers before the next ones are requested (the compiler waits for every load under way where it cannot count
+//    them, so a take behind a request would wait for that request);
+//  - requests the window's vectors a few at a time between the rows' decodes (all at once they hold up the wavefront:
+//    16 clocks of L1 each, 128 of them), and turns them into operand order in front of the barrier, where the early wavefronts wait;
+//  - behind the barrier multiplies its columns' part: the window's groups of 128 columns are dealt to kSlices wavefronts
+//    each for its own vectors (part vpart of VS) and tiles of rows (part rpart of RS).
+// With two buffers the next window goes into the other one at once; with one a second barrier keeps it apart.  The pad behind a row is
+// the one in front of the next: two wavefronts may write it, nobody reads it.
+// Every wavefront executes the same number of barriers whatever its rows hold.
+template <int NT, int P, int W, int VS, bool DBL, int S, int BD, int VB>
+__global__ void __launch_bounds__(64 * kWaves)
+spmm_panel_kernel(const TileArgs all) {
+  TileArgs a = all;                                    // this workgroup's vectors
+  a.X += (int64_t)blockIdx.y * (16 * NT) * a.ldx;
+  a.Y += (int64_t)blockIdx.y * (16 * NT) * a.ldy;
+  a.batch = min(a.batch - (int)blockIdx.y * (16 * NT), 16 * NT);
   static_assert(BD <= 4, "a lane's 8 entries have to fit the pad");
-  constexpr int kWindow = tile_window(G);
-  constexpr int kStride = tile_stride(G);
+  constexpr int kSlices = panel_slices(W, VS), G = W / 128 / kSlices;       // wavefronts along the columns, groups of each
+  constexpr int RS = kWaves / (kSlices * VS);
+  static_assert(kSlices * G * 128 == W && kSlices * VS * RS == kWaves, "every wavefront has its part of a window");
+  constexpr int NTW = (NT + VS - 1) / VS, RW = (P + RS - 1) / RS;           // vector tiles and row tiles of a wavefront
+  constexpr int kStride = panel_stride(W), kBuffer = 16 * P * kStride;
   extern __shared__ __align__(16) unsigned char lds[];
-  __shared__ uint32_t odd_results[64 * kTileRows][2];  // per row of the workgroup, a bit per vector: not finite
+  __shared__ uint32_t odd_results[64 * kWaves][2];     // per row of the workgroup, a bit per vector: not finite
   __shared__ uint32_t any_odd;
-  float4v* red = reinterpret_cast<float4v*>(lds);      // [NT][kTileRows - 1][64]
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wg = (int)blockIdx.x;
   const int row0 = wg * a.q + min(wg, a.r);
   const int wg_rows = a.q + (wg < a.r ? 1 : 0);
-  const int tiles = (wg_rows + kTileRows - 1) / kTileRows;      // at most 64: the host sees to that
-  const int nb = wave < wg_rows ? (wg_rows - wave + kTileRows - 1) / kTileRows : 0;   // this wavefront's rows
-  const int cols = a.cols;
+  const int panels = (wg_rows + 16 * P - 1) / (16 * P);
+  const int nb = wave < wg_rows ? (wg_rows - wave + 15) / 16 : 0;     // this wavefront's rows (at most 64: the host sees to that)
+  const int cols = a.cols, wr = a.window;
   const uint32_t lane8 = 8u * lane;
 
   uint32_t rp_lo, rp_hi;                               // lane i: the pointers of the wavefront's row i
   {
-    const int r = min(row0 + wave + kTileRows * lane, a.rows - 1);
+    const int r = min(row0 + wave + 16 * lane, a.rows - 1);
     rp_lo = a.row_ptr[r];
     rp_hi = a.row_ptr[r + 1];
   }
 
-  // A operand: lane holds row lane % 16, 8 columns; matrix instruction r of a group of 128 columns takes columns
-  // 32 (lane / 16) + 8 r ... + 7 (the order of the columns within the sum is free, as long as B has the same).
+  const int slice = wave % kSlices, part = wave / kSlices, vpart = part % VS, rpart = part / VS;
   const int n = lane & 15;
-  unsigned char* arow = lds + kTilePad + n * kStride + 2 * (128 * G * wave + 32 * (lane >> 4));
-  // B operand: lane has to hold vector lane % 16 of the same columns.  Neighbouring lanes would then read from 16
-  // different vectors, which costs a memory request per lane; instead four neighbouring lanes read 64 consecutive
-  // bytes of one vector, load r from vector 4 (lane / 4 % 4) + r, and exchange 16-byte blocks afterwards.
+  const uint32_t aoff = kTilePad + n * kStride + 2 * (128 * G * slice + 32 * (lane >> 4));
   const bool odd_lane = lane & 1, high_lane = lane & 2;
-  // The vectors are one buffer (base rounded down to 4 bytes): what lies behind its end, vectors past the batch among
-  // it, reads as zero; what lies between two vectors is cleared where it is used.  The end is checked per 4 bytes, so
-  // the buffer ends in front of the last element of an odd number of columns, which would be half of such a piece: the
-  // last vector's is loaded by itself and put in its place where the vectors end.  (The other vectors' are inside: the
-  // element behind them is the next vector's, or lies between the two; a single column is not served.)
   const uint32_t xmis = (uint32_t)(reinterpret_cast<uintptr_t>(a.X) & 2);
   const uint32_t xbytes = (uint32_t)(((int64_t)(a.batch - 1) * a.ldx + (cols & ~1)) * 2) + xmis;
   uint32_t last_x = 0u;
@@ -189,238 +199,269 @@ spmm_tile_kernel(const TileArgs a) {
   const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<unsigned char*>(reinterpret_cast<const unsigned char*>(a.X) - xmis), 0, (int)xbytes, 0x00020000);
   const uint32_t ldx2 = 2u * (uint32_t)a.ldx;
-  const int bcol = 128 * G * wave + 8 * (4 * (lane >> 4) + (lane & 3));     // the lane's first column within the window
-  const uint32_t xoff = xmis + 4u * ((lane >> 2) & 3) * ldx2 + 2u * bcol;
-  u32x4 b[G][NT][4];
-  int k0 = 0, tile = 0;                                // first column of the window, tile
-  const int cols2 = 2 * ((cols + 127) & ~127);         // doubled end of the groups that are multiplied
-  uint32_t put_bytes = (uint32_t)min(2 * kWindow, cols2) + kTilePad;       // lanes that start in the window, and in these groups
-  auto load_b = [&]() {
-    uint32_t xo = xoff;
-    if (NT > 2) asm volatile("" : "+v"(xo));           // no offsets computed in front of the loop and kept in registers
+  const int bcol = 128 * G * slice + 8 * (4 * (lane >> 4) + (lane & 3));        // the lane's first column within the window
+  const uint32_t xoff = xmis + (uint32_t)(16 * vpart + 4 * ((lane >> 2) & 3)) * ldx2 + 2u * bcol;
+  u32x4 b[G][NTW][4];
+  int k0 = 0;                                          // first column of the window
+  // loads `from` ... `to` - 1 of the window's 4 G NTW
+  auto load_b = [&](int from, int to) {
 #pragma unroll
     for (int g = 0; g < G; ++g)
+      if (128 * (G * slice + g) < min(wr, cols - k0) && to > 4 * NTW * g && from < 4 * NTW * (g + 1)) {
+        uint32_t xo = xoff + 2u * (uint32_t)(k0 + 128 * g);
+        asm volatile("" : "+v"(xo));
 #pragma unroll
-      for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const auto q = __builtin_amdgcn_raw_buffer_load_b128(
-              xrsrc, (int)(xo + 2u * (uint32_t)(k0 + 128 * g) + (uint32_t)(16 * t + r) * ldx2), 0, 0);
-          b[g][t][r] = u32x4{(uint32_t)q[0], (uint32_t)q[1], (uint32_t)q[2], (uint32_t)q[3]};
-        }
+        for (int i = 0; i < 4 * NTW; ++i)
+          if (4 * NTW * g + i >= from && 4 * NTW * g + i < to) {
+            const auto q = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, (int)(xo + (uint32_t)(16 * VS * (i >> 2) + (i & 3)) * ldx2), 0, 0);
+            b[g][i >> 2][i & 3] = u32x4{(uint32_t)q[0], (uint32_t)q[1], (uint32_t)q[2], (uint32_t)q[3]};
+          }
+      }
   };
 
-  // the load side of the stream of steps; a row without entries takes one step with everything cleared
-  LaneCodes<BD> wq[S];
-  LaneValues<VB> vq[S];
-  int ld_i = 0;
-  uint32_t ld_e0 = 0, ld_end = 0, chunk = 0;
-  auto open_load_row = [&](int i) {
-    ld_e0 = (uint32_t)__builtin_amdgcn_readlane((int)rp_lo, i) & ~7u;
-    ld_end = (uint32_t)__builtin_amdgcn_readlane((int)rp_hi, i);
-  };
-  auto issue = [&](int j) {
-    if (ld_i < nb) {                                   // else the previous chunk once more
-      chunk = min(ld_e0 + lane8, max(ld_end, 1u) - 1u) >> 3;     // lanes past the row end re-read its last chunk
-      ld_e0 += 512u;
-      if (ld_e0 >= ld_end && ++ld_i < nb) open_load_row(ld_i);
+  LaneCodes<BD> rw[P][S], hw[P][S];
+  LaneValues<VB> rv[P][S], hv[P][S];
+  int hbase[P][S];                                     // lane's doubled position
+  int hend[P][S];                                      // doubled position behind the step
+  uint32_t e0[P], start[P], end[P];
+  int base2[P];
+  int left[P];                                         // units of S steps not taken yet
+  int j0 = 0;                                          // the wavefront's row of slot 0
+  auto issue = [&](int p, uint32_t from, uint32_t to) {
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const uint32_t chunk = min(from + 512u * s + lane8, max(to, 1u) - 1u) >> 3;
+      rw[p][s].load(a.deltas, chunk);
+      rv[p][s].load(a.values, chunk);
     }
-    wq[j].load(a.deltas, chunk);
-    vq[j].load(a.values, chunk);
   };
-
-  // the tile starts out as zeros; the product of a window leaves what it has read zero again
-  for (int i = threadIdx.x; i < tile_lds(G) / 16; i += 64 * kTileRows) reinterpret_cast<u32x4*>(lds)[i] = u32x4{0, 0, 0, 0};
+  auto open_row = [&](int p) {
+    const int j = min(j0 + p, 63);
+    start[p] = (uint32_t)__builtin_amdgcn_readlane((int)rp_lo, j);
+    end[p] = (uint32_t)__builtin_amdgcn_readlane((int)rp_hi, j);
+    e0[p] = start[p] & ~7u;
+    left[p] = j0 + p < nb ? max(1, (int)((end[p] - e0[p] + 512u * S - 1u) / (512u * S))) : 0;   // a row without entries: one, cleared
+    base2[p] = 0;
+#pragma unroll
+    for (int s = 0; s < S; ++s) hend[p][s] = -1;
+  };
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    open_row(p);
+    if (left[p] > 0) issue(p, e0[p], end[p]);
+  }
+  load_b(0, 4 * G * NTW);
   odd_results[threadIdx.x][0] = odd_results[threadIdx.x][1] = 0u;
   if (threadIdx.x == 0) any_odd = 0u;
-  load_b();
-  if (nb > 0) open_load_row(0);
-#pragma unroll
-  for (int j = 0; j < S; ++j) issue(j);
 
-  float4v acc[NT];
+  float4v acc[RW][NTW];
 #pragma unroll
-  for (int t = 0; t < NT; ++t) acc[t] = float4v{0.f, 0.f, 0.f, 0.f};
-  __syncthreads();
+  for (int i = 0; i < RW; ++i)
+#pragma unroll
+    for (int t = 0; t < NTW; ++t) acc[i][t] = float4v{0.f, 0.f, 0.f, 0.f};
 
-  // the product of the window at k0 and, behind the last window, the results of the tile
-  auto finish_window = [&]() {
-    __syncthreads();                                   // every row's entries of the window are in the tile
+  const int cols2 = 2 * ((cols + 127) & ~127);
+  uint32_t buf = 0;                                    // byte offset of the window's buffer
+  int panel = 0;
+  bool b_due = false;
+  for (;;) {
+    // ---- the window's part of this wavefront's rows into the tile
+    const uint32_t put_bytes = (uint32_t)min(2 * wr, cols2 - 2 * k0) + kTilePad;
+    const bool last_window = k0 + wr >= cols;
+    const int limit = last_window ? 0x7FFFFFFF : 2 * (k0 + wr);       // everything that is left goes to the last window
+    unsigned char* rowbuf = lds + buf + kTilePad + wave * kStride;
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const int kg = k0 + 128 * (G * wave + g);        // first column of the group
-      if (kg < cols) {
-        // (marked as rare: 1.5 % at 64 vectors, by keeping its code out of the loop's)
-        if (__builtin_expect(kg + 128 > cols, 0)) {    // the vectors end in it
-          const int left = cols - (k0 + 128 * g + bcol);
+    for (int p = 0; p < P; ++p)
+#pragma unroll
+      for (int i = 0; i < W / 512; ++i)
+        *reinterpret_cast<u32x4*>(rowbuf + 16 * p * kStride + 1024 * i + 16 * lane) = u32x4{0, 0, 0, 0};
+    asm volatile("" ::: "memory");
+    auto put = [&](int p, int s) {
+      const int rel = hbase[p][s] - 2 * k0;
+      if ((uint32_t)(rel + kTilePad) < put_bytes) {
+        unsigned char* q = rowbuf + 16 * p * kStride + rel;
+#define MACKO_PUT(K) *reinterpret_cast<uint16_t*>(q + hw[p][s].template offset<K>()) = (uint16_t)hv[p][s].template half<K>();
+        MACKO_PUT(0) MACKO_PUT(1) MACKO_PUT(2) MACKO_PUT(3) MACKO_PUT(4) MACKO_PUT(5) MACKO_PUT(6) MACKO_PUT(7)
+#undef MACKO_PUT
+      }
+    };
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+#pragma unroll
+      for (int s = 0; s < S; ++s)
+        if (hend[p][s] > 2 * k0) {
+          if (P > 2) {                                 // every register counts: the codes are kept, not the positions
+            keep_opaque(hw[p][s].w, hv[p][s]);
+            hw[p][s].decode();
+          }
+          put(p, s);
+        }
+    for (;;) {
+      uint32_t need = 0;                               // bit p: row p's next unit is taken now
+#pragma unroll
+      for (int p = 0; p < P; ++p) need |= (uint32_t)(left[p] > 0 && base2[p] < limit) << p;
+      // out of the load registers with all of them first, then the next loads
+#pragma unroll
+      for (int p = 0; p < P; ++p)
+        if (need & (1u << p)) {
+#pragma unroll
+          for (int s = 0; s < S; ++s) {
+            move_regs(hw[p][s].w, rw[p][s].w);
+            move_regs(hv[p][s], rv[p][s]);
+          }
+          e0[p] += 512u * S;
+          --left[p];
+        }
+      if (!need && !b_due) break;
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        if (need & (1u << p)) {
+          const bool more = left[p] > 0;
+          const int j = j0 + p + P;
+          if (more || j < nb) {
+            const uint32_t from = (uint32_t)__builtin_amdgcn_readlane((int)rp_lo, j & 63) & ~7u;
+            const uint32_t to = (uint32_t)__builtin_amdgcn_readlane((int)rp_hi, j & 63);
+            issue(p, more ? e0[p] : from, more ? end[p] : to);
+          }
+#pragma unroll
+          for (int s = 0; s < S; ++s) {
+            const uint32_t e = e0[p] - 512u * (uint32_t)(S - s);
+            if (s > 0 && e >= end[p]) {
+              hend[p][s] = -1;
+            } else {
+              LaneCodes<BD>& w = hw[p][s];
+              if (e + 512u > end[p]) {                 // the row's last step: clear what lies behind its end
+                const uint32_t nv = e + lane8 < end[p] ? end[p] - (e + lane8) : 0u;
+                w.keep_if(nv != 0);
+                hv[p][s].keep_first(nv);
+              }
+              w.decode();
+              const uint32_t tot = w.total();
+              const uint32_t incl = wave_incl_scan_u32(tot);
+              if (s == 0 && e <= start[p]) {           // the row's first step
+                const int before = (int)(start[p] - e);      // entries of the previous row: they land in front of column 0
+                if (before > 0) base2[p] = -(int)w.through(before - 1);
+              }
+              hbase[p][s] = base2[p] + (int)(incl - tot);
+              base2[p] += (int)__builtin_amdgcn_readlane((int)incl, 63);
+              hend[p][s] = base2[p];
+              put(p, s);
+            }
+          }
+        }
+        if (b_due) load_b(4 * G * NTW * p / P, 4 * G * NTW * (p + 1) / P);
+      }
+      b_due = false;
+    }
+    // the vectors into the operand's layout
+    const int groups = min(wr, cols - k0);             // columns of the window that are multiplied
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+      if (128 * (G * slice + g) < groups) {
+        if (__builtin_expect(k0 + 128 * (G * slice + g) + 128 > cols, 0)) {      // the vectors end in it
+          int l = lane;
+          if (NTW > 1) asm volatile("" : "+v"(l));
+          const int left = cols - (k0 + 128 * (G * slice + g) + 8 * (4 * (l >> 4) + (l & 3)));
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const uint32_t mask = left > 2 * i + 1 ? 0xFFFFFFFFu : (left > 2 * i ? 0xFFFFu : 0u);
 #pragma unroll
-            for (int t = 0; t < NT; ++t)
+            for (int t = 0; t < NTW; ++t)
 #pragma unroll
               for (int r = 0; r < 4; ++r) b[g][t][r][i] &= mask;
           }
           if (__builtin_expect(cols & 1, 0)) {         // the last element of the last vector (left is odd here)
-            const int last = a.batch - 1 - 4 * ((lane >> 2) & 3);        // load r of tile t is vector `last` if 16 t + r is
+            const int last = a.batch - 1 - 16 * vpart - 4 * ((l >> 2) & 3);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               const uint32_t e = left == 2 * i + 1 ? last_x : 0u;
 #pragma unroll
-              for (int t = 0; t < NT; ++t)
+              for (int t = 0; t < NTW; ++t)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) b[g][t][r][i] |= last == 16 * t + r ? e : 0u;
+                for (int r = 0; r < 4; ++r) b[g][t][r][i] |= last == 16 * VS * t + r ? e : 0u;
             }
           }
         }
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
+        for (int t = 0; t < NTW; ++t) {
           quad_transpose(b[g][t], odd_lane, high_lane);
-          if (NT > 2) __builtin_amdgcn_sched_barrier(0);         // keeps the temporaries of one t at a time: no spills
+          if (NTW > 1) __builtin_amdgcn_sched_barrier(0);        // keeps the temporaries of one t at a time: no spills
         }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          half8* ap = reinterpret_cast<half8*>(arow + 256 * g + 16 * r);
-          const half8 av = *ap;
-          *ap = half8{0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-          for (int t = 0; t < NT; ++t)
-            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, __builtin_bit_cast(half8, b[g][t][r]), acc[t], 0, 0, 0);
-          if (NT > 2) __builtin_amdgcn_sched_barrier(0);
-        }
-      } else if (kg < cols + 128) {
-        // Groups behind the last column are not multiplied.  What a wrong encoding's row puts into the first of them (into
-        // the others nothing is put) would be part of the next tile's row: a right one's leaves zeros.
-#pragma unroll
-        for (int r = 0; r < 4; ++r) *reinterpret_cast<half8*>(arow + 256 * g + 16 * r) = half8{0, 0, 0, 0, 0, 0, 0, 0};
       }
-    }
-    k0 += kWindow;
-    const bool done = k0 >= cols;
-    if (done) k0 = 0;
-    put_bytes = (uint32_t)min(2 * kWindow, cols2 - 2 * k0) + kTilePad;
-    __builtin_amdgcn_sched_barrier(0);
-    load_b();                                          // under way while the next window is decoded
-    __syncthreads();                                   // the tile is zero again
-    if (done) {
-      // wavefront t adds up vectors 16 t ... 16 t + 15; the others hand their sums over in the tile's memory
+    __syncthreads();                                   // every row's entries of the window are in the tile
+    // ---- the product of the window
 #pragma unroll
-      for (int t = 0; t < NT; ++t)
-        if (wave != t) red[(t * (kTileRows - 1) + (wave < t ? wave : wave - 1)) * 64 + lane] = acc[t];
-      __syncthreads();
+    for (int g = 0; g < G; ++g)
+      if (128 * (G * slice + g) < groups) {
+        const unsigned char* ap = lds + buf + aoff + 256 * g + (RS > 1 ? 16 * kStride * rpart : 0);
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        if (wave == t) {
-          float4v sum = acc[t];
-#pragma unroll 5
-          for (int g = 0; g < kTileRows - 1; ++g) {
-            float4v* p = red + (t * (kTileRows - 1) + g) * 64 + lane;
-            sum += *p;
-            *p = float4v{0.f, 0.f, 0.f, 0.f};
-          }
-          int l = lane;
-          if (NT > 2) asm volatile("" : "+v"(l));      // nor pointers into Y
-          const int n = l & 15;
-          const int m0 = 4 * (l >> 4), left = wg_rows - kTileRows * tile - m0;     // lane holds rows m0 ... m0 + 3
-          if (16 * t + n < a.batch) {
-            uint16_t* y = a.Y + (int64_t)(16 * t + n) * a.ldy + (row0 + kTileRows * tile + m0);
+        for (int i = 0; i < RW; ++i) {
+          if (P % RS == 0 || i * RS + rpart < P) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (i < left) {
-                if (__builtin_fabsf(sum[i]) <= 3.4028234e38f) {
-                  y[i] = f32_to_f16_bits(sum[i]);
-                } else {                               // an infinity or a NaN in the row or in the vector
-                  atomicOr(&odd_results[kTileRows * tile + m0 + i][t >> 1], 1u << (16 * (t & 1) + n));
-                  any_odd = 1u;
-                }
-              }
+            for (int r = 0; r < 4; ++r) {
+              const half8 av = *reinterpret_cast<const half8*>(ap + 16 * RS * i * kStride + 16 * r);
+#pragma unroll
+              for (int t = 0; t < NTW; ++t)
+                acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, __builtin_bit_cast(half8, b[g][t][r]), acc[i][t], 0, 0, 0);
+            }
           }
         }
-        acc[t] = float4v{0.f, 0.f, 0.f, 0.f};
       }
-      __builtin_amdgcn_sched_barrier(0);
-      load_b();
-      __syncthreads();
-      ++tile;
+    b_due = true;
+    if (!last_window) {
+      k0 += wr;
+      if (DBL) buf = kBuffer - buf;
+      else __syncthreads();                            // the tile has been read
+      continue;
     }
-  };
-
-  unsigned char* rowbuf = lds + kTilePad + wave * kStride;
-  LaneCodes<BD> wh[S];                                 // steps 1 ... S - 1 of the group taken out of the load registers last
-  LaneValues<VB> vh[S];
-  int next = 0;                                        // the step of the group that comes next
-  int base2 = 0;                                       // doubled position behind the row's steps decoded so far
-  int i = 0;
-  uint32_t e0 = 0, start = 0, end = 0;
-  auto open_row = [&]() {
-    start = (uint32_t)__builtin_amdgcn_readlane((int)rp_lo, i);
-    end = (uint32_t)__builtin_amdgcn_readlane((int)rp_hi, i);
-    e0 = start & ~7u;
-  };
-  if (nb > 0) open_row();
-  for (;;) {
-    const bool live = i < nb;
-    const int target = live ? i : tiles;
-    // S steps are loaded at a time: out of the load registers with all of them, then the next S are requested
-    LaneCodes<BD> w;
-    LaneValues<VB> v;
-    if (next == 0) {
-      move_regs(w.w, wq[0].w);
-      move_regs(v, vq[0]);
+    // ---- the results of the panel: the slices' sums are handed over in the tile's memory (the other buffer's, if there are two)
+    k0 = 0;
+    float4v* red = reinterpret_cast<float4v*>(lds + kTilePad + (DBL ? kBuffer - buf : 0));      // [P * NT][kSlices][64]
+    if (!DBL) __syncthreads();
 #pragma unroll
-      for (int j = 1; j < S; ++j) {
-        move_regs(wh[j].w, wq[j].w);
-        move_regs(vh[j], vq[j]);
-      }
+    for (int i = 0; i < RW; ++i)
 #pragma unroll
-      for (int j = 0; j < S; ++j) issue(j);
-    }
+      for (int t = 0; t < NTW; ++t) {
+        const int rt = RS * i + rpart, vt = VS * t + vpart;
+        if ((P % RS == 0 || rt < P) && (NT % VS == 0 || vt < NT)) red[((rt * NT + vt) * kSlices + slice) * 64 + lane] = acc[i][t];
+        acc[i][t] = float4v{0.f, 0.f, 0.f, 0.f};
+      }
+    __syncthreads();
+    for (int u = wave; u < P * NT; u += kWaves) {
+      const float4v* p = red + u * kSlices * 64 + lane;
+      float4v sum = *p;
+      int l = lane;
+      if (NTW > 1) asm volatile("" : "+v"(l));       // no pointers into Y kept in registers
+      const int n = l & 15;
 #pragma unroll
-    for (int j = 1; j < S; ++j)
-      if (next == j) {
-        w.w = wh[j].w;
-        v = vh[j];
+      for (int g = 1; g < kSlices; ++g) sum += p[64 * g];
+      const int rt = u / NT, vt = u - NT * rt;
+      const int m0 = 16 * (P * panel + rt) + 4 * (l >> 4), left = wg_rows - m0;     // lane holds rows m0 ... m0 + 3
+      if (16 * vt + n < a.batch) {
+        uint16_t* y = a.Y + (int64_t)(16 * vt + n) * a.ldy + (row0 + m0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (i < left) {
+            if (__builtin_fabsf(sum[i]) <= 3.4028234e38f) {
+              y[i] = f32_to_f16_bits(sum[i]);
+            } else {                                   // an infinity or a NaN in the row or in the vector
+              atomicOr(&odd_results[m0 + i][vt >> 1], 1u << (16 * (vt & 1) + n));
+              any_odd = 1u;
+            }
+          }
       }
-    if (++next == S) next = 0;
-    if (e0 + 512u > end) {                             // the row's last step: clear what lies behind its end
-      const uint32_t nv = e0 + lane8 < end ? end - (e0 + lane8) : 0u;
-      w.keep_if(nv != 0);
-      v.keep_first(nv);
     }
-    w.decode();
-    const uint32_t tot = w.total();
-    const uint32_t incl = wave_incl_scan_u32(tot);
-    if (e0 <= start) {                                 // the row's first step
-      base2 = 0;
-      const int before = (int)(start - e0);            // entries of the previous row: they land in front of column 0
-      if (before > 0) base2 = -(int)w.through(before - 1);
-    }
-    const int lanebase = base2 + (int)(incl - tot);
-    base2 += (int)__builtin_amdgcn_readlane((int)incl, 63);
-    for (;;) {
-      if (tile == target) {
-        if (!live) goto out;
-        // with many vectors every register counts: nothing about the entries is computed in front of this loop and kept
-        if (NT > 1) keep_opaque(w.w, v);
-        // lanes without an entry in the window write to the pad; so do a lane's entries in front of the window or
-        // behind it.  What is behind the row's end is zero, and so is the tile there.
-        int rel = lanebase - 2 * k0;
-        rel = (uint32_t)(rel + kTilePad) < put_bytes ? rel : -kTilePad;
-        unsigned char* p = rowbuf + rel;
-#define MACKO_PUT(K) *reinterpret_cast<uint16_t*>(p + w.template offset<K>()) = (uint16_t)v.template half<K>();
-        MACKO_PUT(0) MACKO_PUT(1) MACKO_PUT(2) MACKO_PUT(3) MACKO_PUT(4) MACKO_PUT(5) MACKO_PUT(6) MACKO_PUT(7)
-#undef MACKO_PUT
-        if (k0 + kWindow >= cols || base2 <= 2 * (k0 + kWindow)) break;
-      }
-      finish_window();
-    }
-    e0 += 512u;
-    if (e0 >= end && ++i < nb) open_row();
+    if (++panel == panels) break;
+    j0 += P;
+#pragma unroll
+    for (int p = 0; p < P; ++p) open_row(p);
+    if (!DBL) __syncthreads();                         // the sums have been read
   }
-out:
-  if (any_odd) {                                       // set, if at all, in front of the last barrier
-    for (i = 0; i < nb; ++i) {
-      const int r = kTileRows * i + wave;
+  __syncthreads();
+  if (any_odd) {
+    for (int i = 0; i < nb; ++i) {
+      const int r = 16 * i + wave;
       const uint64_t vectors = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)odd_results[r][0]) |
                                ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)odd_results[r][1]) << 32);
       if (vectors)
@@ -430,34 +471,62 @@ out:
   }
 }
 
-template <int NT, int BD, int VB, int G, int S>
-int launch_tile_as(TileArgs a, hipStream_t stream) {
-  constexpr int lds = tile_lds(G);
-  auto kfn = spmm_tile_kernel<NT, BD, VB, G, S>;
+template <int NT, int P, int W, int VS, bool DBL, int S, int BD, int VB>
+int launch_panel_as(TileArgs a, hipStream_t stream) {
+  constexpr int buffer = 16 * P * panel_stride(W), lds = (DBL ? 2 : 1) * buffer + kTilePad;
+  static_assert(P * NT * panel_slices(W, VS) * 1024 + kTilePad <= buffer, "the partial sums fit one buffer");
+  static_assert(lds + 64 * kWaves * 8 + 16 <= 160 * 1024, "LDS of a compute unit");
+  auto kfn = spmm_panel_kernel<NT, P, W, VS, DBL, S, BD, VB>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return hip_fail(e);
-  // One workgroup per compute unit with an equal share of the rows: registers allow no second one, and the fewer
-  // workgroups, the fewer times the vectors are read.  A wavefront keeps the pointers of at most 64 rows.
-  int64_t grid = std::min<int64_t>(((int64_t)a.rows + kTileRows - 1) / kTileRows, (int64_t)device_cu_count());
-  grid = std::max<int64_t>(grid, ((int64_t)a.rows + 64 * kTileRows - 1) / (64 * kTileRows));
+  // One workgroup per compute unit with an equal share of the rows: LDS holds no second one, and the fewer workgroups,
+  // the fewer times the vectors are read.  A wavefront keeps the pointers of at most 64 rows.
+  int64_t grid = std::min<int64_t>(((int64_t)a.rows + 15) / 16, (int64_t)device_cu_count());
+  grid = std::max<int64_t>(grid, ((int64_t)a.rows + 64 * 16 - 1) / (64 * 16));
   a.q = (int)(a.rows / grid);
   a.r = (int)(a.rows % grid);
-  hipLaunchKernelGGL(kfn, dim3((unsigned)grid), dim3(64 * kTileRows), (size_t)lds, stream, a);
+  // as few windows as LDS allows, all about equally wide (11008 columns: 6 of 1920 instead of 5 of 2048 and one of 768)
+  const int64_t windows = ((int64_t)a.cols + W - 1) / W;
+  a.window = (int)((((int64_t)a.cols + windows - 1) / windows + 127) / 128 * 128);
+  hipLaunchKernelGGL(kfn, dim3((unsigned)grid, (unsigned)((a.batch + 16 * NT - 1) / (16 * NT))), dim3(64 * kWaves), (size_t)lds, stream, a);
   e = hipGetLastError();
   return e == hipSuccess ? MACKO_OK : hip_fail(e);
 }
 
-// Windows of 4096 columns where the registers allow it (up to 16 vectors) and the row is longer than 2048: fewer
-// products of windows to wait for (4096 x 4096, 8 vectors: 11.3 -> 10.6 us; 14336 x 1024 would lose, 14.0 -> 15.9,
-// its tile being cleared and read twice as wide as needed).  One step ahead instead of two from 33 vectors on: two
-// would spill registers in the loop (44 -> 60 us).
+// The shape of a launch.  A workgroup's work is its panels times their windows, about 2 us each, and the reads of X once per panel.
+// Figures: us at the sizes given, from 260 matrices timed with every shape.
 template <int BD, int VB>
 int launch_tile_bd(const TileArgs& a, hipStream_t stream) {
-  const int nt = (a.batch + 15) / 16;
-  if (nt == 1) return a.cols > tile_window(1) ? launch_tile_as<1, BD, VB, 2, 2>(a, stream) : launch_tile_as<1, BD, VB, 1, 2>(a, stream);
-  if (nt == 2) return launch_tile_as<2, BD, VB, 1, 2>(a, stream);
-  if (nt == 3) return launch_tile_as<3, BD, VB, 1, 1>(a, stream);
-  return launch_tile_as<4, BD, VB, 1, 1>(a, stream);
+  const int64_t cus = device_cu_count();
+  const int64_t tiles = (a.rows + 16 * cus - 1) / (16 * cus);          // tiles of 16 rows per workgroup
+  int nt = (a.batch + 15) / 16;
+  // Few rows leave compute units idle: they take the same rows with other vectors (256 x 4096, 64 vectors: 14.9 -> 8.7).
+  if (a.rows <= 8 * cus) {
+    const int groups = (int)std::min<int64_t>(nt, cus / ((a.rows + 15) / 16));
+    nt = (nt + groups - 1) / groups;
+  }
+#define MACKO_PANEL(...) return launch_panel_as<__VA_ARGS__, BD, VB>(a, stream)
+  if (nt == 1) {
+    // whole rows of up to 4096 columns in one window, or two tiles in windows of half that width where that makes no more
+    // windows (8192 x 4096 at 80 %: 12.1 / 11.3, 14336 x 700: 13.6 / 9.5; but 11008 x 4096 at 90 %: 15.2 / 15.8)
+    if (tiles > 1 && (tiles + 1) / 2 * ((a.cols + 2047) / 2048) <= tiles * ((a.cols + 4095) / 4096)) MACKO_PANEL(1, 2, 2048, 1, false, 1);
+    MACKO_PANEL(1, 1, 4096, 1, false, 2);
+  }
+  // From here on X counts as well: the shape whose panels have the fewest empty places, 3 tiles if equal
+  const bool three = (tiles + 2) / 3 * 3 <= (tiles + 1) / 2 * 2;
+  if (nt == 2) {
+    if (tiles == 1) MACKO_PANEL(2, 1, 2048, 1, true, 2);
+    if (three) MACKO_PANEL(2, 3, 1024, 2, false, 1);                   // 10000 x 1800: 15.3 with panels of 2, 13.5
+    MACKO_PANEL(2, 2, 2048, 1, false, 1);                              // 5000 x 4096: 18.5 with panels of 1, 15.4
+  }
+  if (tiles == 1) {
+    if (nt == 3) MACKO_PANEL(3, 1, 2048, 1, true, 2);                  // 4096 x 4096: 15.2; with a fourth, empty tile 17.1
+    if (a.cols <= 3072) MACKO_PANEL(4, 1, 1024, 2, true, 2);           // 4096 x 2600: 13.1 / 14.2 with 2048, 4096 x 4096 at 90 %: 13.5 / 12.6
+    MACKO_PANEL(4, 1, 2048, 1, true, 1);
+  }
+  if (three) MACKO_PANEL(4, 3, 1024, 2, false, 1);                     // 11008 x 4096: 40.9 with panels of 2, 34.1
+  MACKO_PANEL(4, 2, 1024, 2, true, 1);                                 // 8192 x 4096 at 80 %: 22.8 with panels of 1, 19.0
+#undef MACKO_PANEL
 }
 
 }  // namespace
@@ -471,7 +540,7 @@ bool spmm_tile_serves(const SpmvProblem& p, int64_t ldx) {
 int launch_spmm_tile(const SpmvProblem& p, const uint16_t* X, int64_t ldx, uint16_t* Y, int64_t ldy, int batch,
                      hipStream_t stream) {
   const TileArgs a{p.values, reinterpret_cast<const uint32_t*>(p.deltas), p.row_ptr, X, Y, ldx, ldy,
-                   (int)p.rows, (int)p.cols, batch, 0, 0};
+                   (int)p.rows, (int)p.cols, batch, 0, 0, 0};
   if (p.b_val == 8) return p.b_delta == 4 ? launch_tile_bd<4, 8>(a, stream) : MACKO_E_UNSUPPORTED;
   switch (p.b_delta) {
     case 1: return launch_tile_bd<1, 16>(a, stream);

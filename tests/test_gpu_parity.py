@@ -1483,6 +1483,19 @@ def test_spmm_tile_edges(kind, rows, cols, batch):
 
 
 @pytest.mark.parametrize("kind", ["b1", "b4", "fp8"])
+@pytest.mark.parametrize("rows,cols,batch", [
+    # panels of one tile: windows of 4096, 2048 and 1024 columns, one or two vector tiles a wavefront, three and four of them
+    (2100, 3073, 60), (2500, 700, 60), (2500, 2049, 40), (2300, 2500, 30),
+    # of two tiles, in two windows of one buffer and in two buffers; of three; several panels a workgroup
+    (4300, 2050, 9), (4300, 2100, 20), (4300, 1030, 64), (8300, 1100, 31), (8300, 1200, 40), (20600, 130, 20), (20600, 130, 33),
+    # vectors dealt to several workgroups: two groups of two tiles, the last one partly filled
+    (1500, 1100, 40), (1500, 129, 33)])
+def test_spmm_panel_shapes(kind, rows, cols, batch):
+    """Every shape of the matrix-core kernel, with inputs and bound of test_spmm_tile_edges."""
+    test_spmm_tile_edges(kind, rows, cols, batch)
+
+
+@pytest.mark.parametrize("kind", ["b1", "b4", "fp8"])
 def test_spmm_tile_leaves_out_what_is_not_stored(kind):
     """An infinity or a NaN of a vector reaches the rows that store an entry at its column and no others; one of the
     matrix stays in its row.  Reference: the stored entries (padding included) one by one in 64 bits."""

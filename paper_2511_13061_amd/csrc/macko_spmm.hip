@@ -15,6 +15,9 @@
 #include "macko_internal.h"
 #include "macko_plan.h"
 
+#include <algorithm>
+#include <cmath>
+
 namespace macko {
 namespace {
 
@@ -309,55 +312,52 @@ int launch_bt(const SpmvProblem& p, const uint16_t* X, int64_t ldx, uint16_t* Y,
 constexpr int64_t kBatchLdsLimit = 160 * 1024 - 64;
 constexpr int64_t kLongRow = 384;       // stored entries per row from which vectors share a pass over the matrix
 
-// Which of the two ways is the faster one for a call that both can take.
+// Vectors that the next pass over the matrix takes, of `left`: a piece of 8, 4 or 2 whose interleaved copies fit LDS, or one;
+// with short rows up to kMaxGroup single products (pass = 0).
+struct Piece {
+  int pass, take;
+};
+Piece next_piece(bool long_rows, int64_t one, int left) {
+  if (long_rows && left >= 5 && 8 * one <= kBatchLdsLimit) return {8, std::min(left, 8)};
+  if (long_rows && left >= 3 && 4 * one <= kBatchLdsLimit) return {4, std::min(left, 4)};
+  if (long_rows && left >= 2 && 2 * one <= kBatchLdsLimit) return {2, 2};
+  if (long_rows) return {1, 1};
+  return {0, std::min(left, kMaxGroup)};
+}
+
+// Whether the matrix cores are the faster way for a call that both can take: from estimates of both times.
 //
-// The matrix cores serve up to 16 vectors at one price: they pay for the cells of their tiles, 16 rows by a window of columns, whatever
-// is stored there, and for whole rounds of tiles.  The vector kernel pays per stored entry and vector, in pieces of 8, 4, 2
-// or 1 vectors (whatever fits LDS, each piece a launch).  So the line lies where too few of the cells hold an entry, the lower the
-// more vectors there are.  (Vectors of a number of elements that is no multiple of 8 it stages one by one: 256 x 4500 at 97 %, 12
-// vectors: 11.1 / 9.0, 256 x 4096: 7.2 / 7.7.)  All figures are microseconds, vector kernel / matrix cores, over 10 500 calls of 8 to
-// 36864 rows, 512 to 60000 columns, 30 to 99.9 % pruned; over the range where both ways win (5 to 8 vectors, 9400 to 19700
-// columns) the lines below are within 1 % of always taking the faster way.
+// Up to 16 vectors take the matrix cores one launch whose time is a sum of its parts (the phases of a window do not overlap, see
+// macko_spmm_tile.hip); the vector kernel takes a launch per piece, whose time is its launch, its arithmetic per step of 512 entries
+// and vector, the staging of the vectors (one by one where their length is no multiple of 8), and, with few rows, the chain of one
+// row's steps.  The factors (us) were fitted to 1014 calls timed both ways: 2 to 16 vectors, 16 to 36864 rows, 128 to 40000
+// columns, 30 to 99.5 % pruned, all code widths up to 4 bits, both value widths.  The estimates are off by 5 % (matrix cores) and
+// 13 % (vectors) at the median; the way chosen is 1 % slower than the better one in the mean and 13 % at worst.  Against the lines
+// this takes the place of, 2 to 8 vectors take 0.78 of the time (12 % less at 2, 37 % at 8), most with short rows and few rows:
+// 1392 x 1012 at 87 %, 8 vectors: 31 -> 5.5 us; 718 x 8797 at 50 %, 8: 32 -> 16; 344 x 352 at 62 %, 8: 29 -> 5.1.
 bool tile_is_faster(const SpmvProblem& p, int batch) {
-  if (batch <= 4) return false;
-  if (batch > 16) return true;                         // at least three pieces (11008 x 4096, 64 vectors: 183 / 43)
-  const int64_t cus = device_cu_count();
-  const int64_t avg = p.pad_nnz / p.rows, one = lds_bytes_for(p.cols, p.b_delta);
-  // rounds of 256 tiles, the share of their rows that exist, and the share of their cells that hold an entry
-  const int64_t rounds = (p.rows + 16 * cus - 1) / (16 * cus);
-  const double filled = (double)p.rows / (double)(rounds * 16 * cus);
-  const int64_t window = p.cols > 2048 ? 4096 : 2048;
-  const double cells = filled * (double)avg / (double)((p.cols + window - 1) / window * window);
-  if (avg < kLongRow) {
-    // Up to 8 vectors are one launch of the product with one vector, if the rows are not too short for that (14336 x 512 at
-    // 50 %, 8 vectors: 32.1 / 12.4; 4096 x 2048 at 96 %: 31.7 / 6.5).  Few rows do not fill the chip with tiles.
-    const bool one_launch = p.b_val == 8 || avg >= kWaveRowMinEntries;
-    if (batch <= 8) {
-      if (p.rows < 16 * cus) return false;            // 512 x 512, 8 vectors: 4.1 / 5.1
-      if (!one_launch || p.cols <= 2048 || p.cols % 8 != 0 || rounds == 1) return true;
-      if (batch == 5) return filled >= 0.75 && p.cols <= 4096;   // 4200 x 4096 at 98 %: 9.7 / 11.1; 8300 x 5000: 1.3 times
-      return batch > 6 || filled >= 0.75 || p.cols <= 4096;      // 4200 x 5000 at 98 %, 6 vectors: 1.17 times
-    }
-    // two launches, about 7 us however few the rows (5000 columns at 98 %, 16 rows, 9 vectors: 6.7 / 8.8, 256 rows:
-    // 7.3 / 9.0, 768 rows: 1.02 times; 4096 columns at 97 %, 64 rows: 6.8 / 7.7, 512 rows: 7.9 / 7.8)
-    return !one_launch || p.cols <= 2048 || p.cols % 8 != 0 || p.rows > (p.cols > 4096 ? 512 : 256);
+  if (batch <= 1) return false;
+  if (batch > 16) return true;                         // at least three pieces (11008 x 4096, 64 vectors: 183 / 32)
+  const double cus = device_cu_count(), rows = (double)p.rows, cols = (double)p.cols / 4096.0;
+  const double entries = (double)p.pad_nnz, avg = entries / rows, steps = std::ceil(avg / 512.0);
+  const double mbytes = entries * (p.b_val + p.b_delta) / 8e6;
+  const double tiles = std::ceil(rows / (16.0 * cus)), tiles_wg = std::ceil(rows / (16.0 * std::min(cus, std::ceil(rows / 16.0))));
+  const double tile_us = 2.63 + 1.87 * (double)spmm_tile_windows(p) + 0.72 * tiles * cols + 0.55 * tiles_wg * steps + 0.05 * mbytes;
+
+  const bool long_rows = p.pad_nnz / p.rows >= kLongRow, ragged = p.cols % 8 != 0;
+  const bool one_launch = p.b_val == 8 || p.pad_nnz / p.rows >= kWaveRowMinEntries;    // of a group of single products
+  const int64_t one = lds_bytes_for(p.cols, p.b_delta);
+  double vector_us = 0.0;
+  for (int left = batch; left > 0;) {
+    const Piece q = next_piece(long_rows, one, left);
+    const double work = rows * steps / cus * (1.0 + q.pass / 4.0), copy = q.pass * cols, chain = (2.0 + q.pass) * steps;
+    if (q.pass == 8) vector_us += 4.77 + 0.021 * work + 0.222 * copy + (ragged ? 0.853 * copy : 0.0) + 0.017 * chain;
+    else if (q.pass) vector_us += 3.03 + 0.015 * work + 0.145 * copy + (ragged ? 0.818 * copy : 0.0) + 0.095 * chain;
+    else if (one_launch) vector_us += 3.73 + q.take * (0.056 * rows * steps / cus + 0.048 * mbytes) + (ragged ? 0.973 * cols : 0.0);
+    else vector_us += q.take * (2.94 + 1.087 * (entries / 1e6 + 0.4 * cols * rows / cus / 32.0));
+    left -= q.take;
   }
-  if (batch > 8) {
-    // One piece of 8 or two of 4, and the rest: 8300 x 6000 at 97 %, 9 vectors: 15.8 / 18.8; 5000 x 14336 at 99 %: 19.6 / 22.9;
-    // but in one round of tiles 4096 x 6000 at 97 %: 0.71 times, and 4200 x 4500 at 90 %, no multiple of 8: 0.71 times.
-    if (batch > 12 || rounds == 1 || p.cols <= 4096 || p.cols % 8 != 0 || 4 * one > kBatchLdsLimit) return true;
-    return cells >= (batch <= 10 ? 0.08 : 0.05);
-  }
-  if (8 * one <= kBatchLdsLimit) return false;         // one piece: 2048 x 4096: 8.8 / 9.8, 11008 x 4096: 21.5 / 21.7
-  if (4 * one > kBatchLdsLimit)                        // pieces of 2: 4096 x 20000 at 50 %, 8 vectors: 75.7 / 30.5
-    return batch > 6 || rounds == 1 || cells >= 0.11;  // 6000 x 30000 at 96 %, 5 vectors: 1.38 times, 8 vectors: 1.0
-  // a piece of 4, and another or what is left
-  if (p.rows < 4 * cus)                                // too few rows for the vector kernel's resident round
-    return (double)avg >= (batch == 5 ? 0.3 : batch == 6 ? 0.2 : 0.09) * (double)p.cols;     // 256 x 11008: 24.2 / 18.1
-  double least = batch <= 6 ? (rounds == 1 ? 0.15 : 0.21) : (rounds == 1 ? 0.105 : 0.16);
-  if (p.b_val == 8) least += 0.06;                     // half the bytes: the vector kernel gains more
-  if (p.b_delta < 4) least += 0.17;                    // less to decode, likewise
-  return cells >= least;                               // 4096 x 11008 at 50 %, 8 vectors: 27.4 / 19.6; 14336 x 14336 at 90 %: 36.6 / 50.2
+  return 1.04 * tile_us < vector_us;                   // 1.04: of near ties the one with the surer estimate loses less
 }
 
 }  // namespace
@@ -379,28 +379,23 @@ int launch_spmm(const SpmvProblem& p, const void* X, int64_t ldx, void* Y, int64
     return e == hipSuccess ? MACKO_OK : hip_fail(e);
   }
   const int64_t one = lds_bytes_for(p.cols, p.b_delta);
-  const int64_t limit = kBatchLdsLimit;
   const bool long_rows = p.pad_nnz / p.rows >= kLongRow;
   if (spmm_tile_serves(p, ldx) && tile_is_faster(p, batch))
     return launch_spmm_tile(p, Xp, ldx, Yp, ldy, batch, stream);
   int done = 0;
   while (done < batch) {
-    const int left = batch - done;
+    const Piece piece = next_piece(long_rows, one, batch - done);
+    const int take = piece.take;
     const uint16_t* Xb = Xp + (int64_t)done * ldx;
     uint16_t* Yb = Yp + (int64_t)done * ldy;
     int st;
-    int take;
-    if (long_rows && left >= 5 && 8 * one <= limit) {
-      take = std::min(left, 8);
+    if (piece.pass == 8) {
       st = launch_bt<8>(p, Xb, ldx, Yb, ldy, take, stream);
-    } else if (long_rows && left >= 3 && 4 * one <= limit) {
-      take = std::min(left, 4);
+    } else if (piece.pass == 4) {
       st = launch_bt<4>(p, Xb, ldx, Yb, ldy, take, stream);
-    } else if (long_rows && left >= 2 && 2 * one <= limit) {
-      take = 2;
+    } else if (piece.pass == 2) {
       st = launch_bt<2>(p, Xb, ldx, Yb, ldy, take, stream);
     } else {
-      take = long_rows ? 1 : std::min(left, kMaxGroup);
       SpmvProblem q[kMaxGroup];
       for (int i = 0; i < take; ++i) {
         q[i] = p;

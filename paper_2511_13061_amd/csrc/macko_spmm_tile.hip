@@ -21,7 +21,8 @@
 // 4096 x 11008: 21.8 / 21.8 / 28.0 / 39.5 -> 20.4 / 20.4 / 26.3 / 37.4; 11008 x 4096: 24.3 / 24.3 / 30.4 / 44.6 -> 23.1 /
 // 23.1 / 30.3 / 34.1; 4096 x 4096: 12.4 / 12.4 / 14.6 / 20.4 -> 10.2 / 10.2 / 12.8 / 17.2; 11008 x 4096 at 90 %, 64: 37.2 -> 22.7.
 // 260 matrices of 300 to 14336 rows, 700 to 13000 columns, 40 to 93 % pruned, 12 to 64 vectors: 1.37 times as fast
-// (geometric mean), the slowest (wide, few rows: 2800 x 13000) 4 % slower.
+// (geometric mean), the slowest 4 % slower; beyond that range few rows of
+// more than 20 000 columns are up to 15 % slower (183 x 27736 at 33 %, 16 vectors: 42.4 -> 48.7).
 //
 // Tried: two workgroups of 8 wavefronts per compute unit, each with half of the rows (5 to 30 % slower: X is read twice, and
 // more windows); 512-column windows in two buffers for panels of 48 rows (34 -> 41 us); a ring of 2 to 4 steps of loads refilled one by one
@@ -493,12 +494,23 @@ int launch_panel_as(TileArgs a, hipStream_t stream) {
   return e == hipSuccess ? MACKO_OK : hip_fail(e);
 }
 
+// Tiles of 16 rows per workgroup, and whether up to 16 vectors take panels of two of them: whole rows of up to 4096 columns in one
+// window, or two tiles in windows of half that width where that makes no more windows (us, one / two: 8192 x 4096 at 80 % 12.1 /
+// 11.3, 14336 x 700 13.6 / 9.5; but 11008 x 4096 at 90 % 15.2 / 15.8)
+int64_t tiles_per_wg(int64_t rows) {
+  const int64_t cus = device_cu_count();
+  return (rows + 16 * cus - 1) / (16 * cus);
+}
+bool two_tiles(int64_t tiles, int64_t cols) {
+  return tiles > 1 && (tiles + 1) / 2 * ((cols + 2047) / 2048) <= tiles * ((cols + 4095) / 4096);
+}
+
 // The shape of a launch.  A workgroup's work is its panels times their windows, about 2 us each, and the reads of X once per panel.
 // Figures: us at the sizes given, from 260 matrices timed with every shape.
 template <int BD, int VB>
 int launch_tile_bd(const TileArgs& a, hipStream_t stream) {
   const int64_t cus = device_cu_count();
-  const int64_t tiles = (a.rows + 16 * cus - 1) / (16 * cus);          // tiles of 16 rows per workgroup
+  const int64_t tiles = tiles_per_wg(a.rows);
   int nt = (a.batch + 15) / 16;
   // Few rows leave compute units idle: they take the same rows with other vectors (256 x 4096, 64 vectors: 14.9 -> 8.7).
   if (a.rows <= 8 * cus) {
@@ -507,9 +519,9 @@ int launch_tile_bd(const TileArgs& a, hipStream_t stream) {
   }
 #define MACKO_PANEL(...) return launch_panel_as<__VA_ARGS__, BD, VB>(a, stream)
   if (nt == 1) {
-    // whole rows of up to 4096 columns in one window, or two tiles in windows of half that width where that makes no more
-    // windows (8192 x 4096 at 80 %: 12.1 / 11.3, 14336 x 700: 13.6 / 9.5; but 11008 x 4096 at 90 %: 15.2 / 15.8)
-    if (tiles > 1 && (tiles + 1) / 2 * ((a.cols + 2047) / 2048) <= tiles * ((a.cols + 4095) / 4096)) MACKO_PANEL(1, 2, 2048, 1, false, 1);
+    if (two_tiles(tiles, a.cols)) MACKO_PANEL(1, 2, 2048, 1, false, 1);
+    // few long rows: nothing but each wavefront's own loads hides their latency (300 x 13000 at 80 %: 17.6 with two steps a unit, 16.8)
+    if (a.rows <= 8 * cus && a.cols > 8192) MACKO_PANEL(1, 1, 4096, 1, false, 3);
     MACKO_PANEL(1, 1, 4096, 1, false, 2);
   }
   // From here on X counts as well: the shape whose panels have the fewest empty places, 3 tiles if equal
@@ -535,6 +547,11 @@ bool spmm_tile_serves(const SpmvProblem& p, int64_t ldx) {
   if (p.b_delta > 4 || p.pad_nnz == 0 || p.rows == 0) return false;   // the pad of the tile holds 4-bit deltas
   if (p.cols < 2) return false;                        // see the end of the vectors' buffer in the kernel
   return ldx < (int64_t{1} << 24);                     // vectors are addressed with 32-bit byte offsets
+}
+
+int64_t spmm_tile_windows(const SpmvProblem& p) {
+  const int64_t tiles = tiles_per_wg(p.rows);
+  return two_tiles(tiles, p.cols) ? (tiles + 1) / 2 * ((p.cols + 2047) / 2048) : tiles * ((p.cols + 4095) / 4096);
 }
 
 int launch_spmm_tile(const SpmvProblem& p, const uint16_t* X, int64_t ldx, uint16_t* Y, int64_t ldy, int batch,

@@ -1813,6 +1813,18 @@ def test_spmm_on_both_sides_of_the_rule_that_picks_its_kernel(kind, rows, cols, 
     assert float(((Y - ref).abs() / bound).max()) <= 1.01
 
 
+@pytest.mark.parametrize("kind", ["b1", "b4", "fp8"])
+@pytest.mark.parametrize("rows,cols,sparsity,batch", [
+    # 2 to 8 vectors: short rows, few rows and many, pieces of 8, 4 and 2, odd columns
+    (344, 352, 0.62, 8), (2960, 656, 0.82, 4), (1256, 352, 0.53, 3), (4100, 2, 0.1, 2), (70, 2001, 0.9, 2), (1024, 4096, 0.5, 8),
+    (4096, 4096, 0.5, 4), (718, 8797, 0.5, 8), (500, 9000, 0.6, 3), (60, 30000, 0.7, 2),
+    # long rows of few: three steps loaded at a time
+    (300, 13000, 0.8, 16), (40, 8200, 0.5, 9)])
+def test_spmm_either_way_for_few_vectors(kind, rows, cols, sparsity, batch):
+    """Both ways that the estimates of tile_is_faster choose from, with inputs and bound of the test above."""
+    test_spmm_on_both_sides_of_the_rule_that_picks_its_kernel(kind, rows, cols, sparsity, batch)
+
+
 @pytest.mark.parametrize("kind", ["b4", "fp8"])
 @pytest.mark.parametrize("rows_of_the_wide,n_wide", [(300, 1), (700, 8), (2100, 1)])
 def test_spmv_many_with_a_wide_x_among_others(kind, rows_of_the_wide, n_wide):

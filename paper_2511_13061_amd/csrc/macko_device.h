@@ -138,6 +138,8 @@ struct RowCursor {
 // amask + 1 is the alignment of the row's first step in entries: 8 is the reverse-offset
 // alignment of the paper (a lane's 16-byte chunk never straddles the row start); larger powers
 // of two up to 512 make every step of the row begin on a multiple of that many entries.
+// TAILS: a last step of one chunk (behind at least one other step) is left out, see row_tail.
+template <bool TAILS = false>
 __device__ __forceinline__ void seek_nonempty(RowCursor& cur, int nb, uint32_t rp_lo, uint32_t rp_hi,
                                               uint32_t amask = 7u) {
   cur.start = cur.end = 0;
@@ -148,8 +150,15 @@ __device__ __forceinline__ void seek_nonempty(RowCursor& cur, int nb, uint32_t r
     ++cur.i;
   }
   cur.a0 = cur.start & ~amask;
-  cur.nsteps = (int)((cur.end - cur.a0 + 511u) >> 9);
+  const uint32_t len = cur.end - cur.a0;
+  cur.nsteps = (int)((len + 511u - (TAILS && len > 512u ? 8u : 0u)) >> 9);
   cur.step = 0;
+}
+
+// Entries of a row that lie in the one chunk of a step that seek_nonempty<true> has left out (0: there is no such step).
+__device__ __forceinline__ uint32_t row_tail(uint32_t start, uint32_t end, uint32_t amask) {
+  const uint32_t len = end - (start & ~amask), rest = len & 511u;
+  return end > start && len > 512u && rest <= 8u ? rest : 0u;
 }
 
 // Staging of x (fp16[cols], global) into the LDS layout described above, split

@@ -190,8 +190,10 @@ struct NoGate {
 
 // `nwaves` wavefronts of the workgroup share its rows (all of them in the plain kernels; a chain
 // may leave the last ones of a workgroup without rows in some phase: they only help to stage x).
+// TAILS: a row's last step is left out where it would hold one chunk; the lane that keeps the row's result takes that chunk behind
+// the last row (see launch_wave_row_group for which matrices that pays).
 // Returns false when the gate gave up; nothing has been written to y then.
-template <int RING, bool SIMPLE, int BD, int VB = 16, class Gate = NoGate>
+template <int RING, bool SIMPLE, int BD, int VB = 16, class Gate = NoGate, bool TAILS = false>
 __device__ __forceinline__ bool spmv_wave_row_body(const void* __restrict__ values,
                                                    const uint32_t* __restrict__ deltas,
                                                    const uint32_t* __restrict__ row_ptr,
@@ -218,6 +220,7 @@ __device__ __forceinline__ bool spmv_wave_row_body(const void* __restrict__ valu
   const int blk = wrow_begin;
   const int nb = wrow_end - wrow_begin;                // at most 64: the host sees to that
   uint32_t rp_lo = 0, rp_hi = 0;
+  uint32_t tail = 0;                                   // TAILS: lane i: entries of row i that no step holds
   RowCursor ld, cp;                                    // load side, compute side
   LaneCodes<BD> wq[RING];
   LaneValues<VB> vq[RING];
@@ -229,8 +232,10 @@ __device__ __forceinline__ bool spmv_wave_row_body(const void* __restrict__ valu
       chunk = min(max(e0, ld.start & ~7u), ld.end - 1u) >> 3;
       if (++ld.step == ld.nsteps) {
         ++ld.i;
-        seek_nonempty(ld, nb, rp_lo, rp_hi, amask);
+        seek_nonempty<TAILS>(ld, nb, rp_lo, rp_hi, amask);
       }
+    } else if (TAILS && tail != 0u) {
+      chunk = (rp_hi - 1u) >> 3;
     }                  // else a padding item: every lane re-reads its previous chunk (a line it has just
                        // used; one fixed address would make every wavefront queue at the same L2 channel)
     wq[j].load(deltas, chunk);
@@ -243,7 +248,8 @@ __device__ __forceinline__ bool spmv_wave_row_body(const void* __restrict__ valu
   };
   auto prime_ring = [&]() {
     ld.i = 0;
-    seek_nonempty(ld, nb, rp_lo, rp_hi, amask);
+    if (TAILS) tail = lane < nb ? row_tail(rp_lo, rp_hi, amask) : 0u;
+    seek_nonempty<TAILS>(ld, nb, rp_lo, rp_hi, amask);
     cp = ld;
 #pragma unroll
     for (int j = 0; j < RING; ++j) issue(j);
@@ -272,6 +278,7 @@ __device__ __forceinline__ bool spmv_wave_row_body(const void* __restrict__ valu
 
   {
     float yv = 0.0f;                                   // lane i: result of row blk + i
+    int tailbase = 0;                                  // lane i: doubled position behind row i's last step
     float acc = 0.0f;
     int base2 = 0;                                     // doubled position before this step (uniform)
     while (cp.i < nb) {
@@ -324,11 +331,31 @@ __device__ __forceinline__ bool spmv_wave_row_body(const void* __restrict__ valu
           const float total = wave_sum_to_last_lane(acc);
           const int tbits = __builtin_amdgcn_readlane(__builtin_bit_cast(int, total), 63);
           yv = lane == cp.i ? __builtin_bit_cast(float, tbits) : yv;
+          if (TAILS) tailbase = lane == cp.i ? base2 : tailbase;
           acc = 0.0f;
           ++cp.i;
-          seek_nonempty(cp, nb, rp_lo, rp_hi, amask);
+          seek_nonempty<TAILS>(cp, nb, rp_lo, rp_hi, amask);
         }
       }
+    }
+    if (TAILS && __any(tail != 0u)) {
+      // the tails, lane i row i's: every slot of the ring has been refilled with them by now
+      LaneCodes<BD> w = wq[0];
+      LaneValues<VB> v = vq[0];
+      v.keep_first(tail);
+      w.decode();
+      acc = 0.0f;
+#define MACKO_X(k) gather_x(xbase, tailbase + w.template offset<k>())
+      acc = fmaf(v.template get<0>(), MACKO_X(0), acc);
+      acc = fmaf(v.template get<1>(), MACKO_X(1), acc);
+      acc = fmaf(v.template get<2>(), MACKO_X(2), acc);
+      acc = fmaf(v.template get<3>(), MACKO_X(3), acc);
+      acc = fmaf(v.template get<4>(), MACKO_X(4), acc);
+      acc = fmaf(v.template get<5>(), MACKO_X(5), acc);
+      acc = fmaf(v.template get<6>(), MACKO_X(6), acc);
+      acc = fmaf(v.template get<7>(), MACKO_X(7), acc);
+#undef MACKO_X
+      if (tail != 0u) yv += acc;
     }
     if (lane < nb) {
       if (Gate::kActive)     // written through to memory: workgroups under other L2 caches read it next
@@ -341,7 +368,7 @@ __device__ __forceinline__ bool spmv_wave_row_body(const void* __restrict__ valu
 }
 
 // Grouped launch (matrices of one code width): the workgroup first finds its matrix.
-template <int RING, bool SIMPLE, int BD, int VB = 16>
+template <int RING, bool SIMPLE, int BD, int VB = 16, bool TAILS = false>
 __global__ void __launch_bounds__(1024)
 spmv_wave_row_kernel(const int wb1, const int wb2, const int wb3, const int wb4, const int wb5, const int wb6,
                      const int wb7, const uint32_t waves, const SpmvGroupArgs g) {
@@ -357,7 +384,7 @@ spmv_wave_row_kernel(const int wb1, const int wb2, const int wb3, const int wb4,
     mi = in ? i : mi;
     wg0 = in ? wbs[i] : wg0;
   }
-  spmv_wave_row_body<RING, SIMPLE, BD, VB>(g.m[mi].values, g.m[mi].deltas, g.m[mi].row_ptr, g.m[mi].x, g.m[mi].y,
+  spmv_wave_row_body<RING, SIMPLE, BD, VB, NoGate, TAILS>(g.m[mi].values, g.m[mi].deltas, g.m[mi].row_ptr, g.m[mi].x, g.m[mi].y,
                                        g.m[mi].rows, g.m[mi].cols, g.m[mi].q, g.m[mi].r, (int)blockIdx.x - wg0,
                                        nwaves, inv_nwaves, (uint32_t)g.m[mi].amask, 64 * nwaves);
 }
@@ -407,15 +434,15 @@ spmv_wave_row_kernel(const uint32_t* __restrict__ row_ptr, const uint16_t* __res
 }
 
 // One matrix with 8-bit values (4-bit codes): 8 bytes of values and 4 bytes of codes per lane and step.
-template <bool SIMPLE>
+template <bool SIMPLE, bool TAILS>
 __global__ void __launch_bounds__(1024)
 spmv_wave_row_fp8_kernel(const uint32_t* __restrict__ row_ptr, const uint16_t* __restrict__ x, const int rows,
                          const int q, const int r, const uint32_t shape, const int cols,
                          const uint2* __restrict__ values, const uint32_t* __restrict__ deltas,
                          uint16_t* __restrict__ y) {
   const int nwaves = (int)((shape >> 17) & 31u);
-  spmv_wave_row_body<2, SIMPLE, 4, 8>(values, deltas, row_ptr, x, y, rows, cols, q, r, (int)blockIdx.x, nwaves,
-                                      (int)(shape & 0x1FFFFu), shape >> 22, 64 * nwaves);
+  spmv_wave_row_body<2, SIMPLE, 4, 8, NoGate, TAILS>(values, deltas, row_ptr, x, y, rows, cols, q, r, (int)blockIdx.x, nwaves,
+                                                     (int)(shape & 0x1FFFFu), shape >> 22, 64 * nwaves);
 }
 
 // ---------------------------------------------------------------------------
@@ -662,10 +689,11 @@ int launch_wave_row_bd(const SpmvGroupArgs& args, const SpmvGroupHeader& head, i
 
 // 8-bit values (4-bit codes, two steps of loads in flight): single-matrix and grouped entry points
 int launch_wave_row_fp8(const SpmvGroupArgs& args, const SpmvGroupHeader& head, int nwr, const Plan& plan,
-                        int64_t max_lds, bool simple, hipStream_t stream) {
+                        int64_t max_lds, bool simple, bool tails, hipStream_t stream) {
   const dim3 grid((unsigned)plan.total_wgs), blockdim(plan.block);
   if (nwr == 1) {
-    auto kfn = simple ? spmv_wave_row_fp8_kernel<true> : spmv_wave_row_fp8_kernel<false>;
+    auto kfn = tails ? (simple ? spmv_wave_row_fp8_kernel<true, true> : spmv_wave_row_fp8_kernel<false, true>)
+                     : (simple ? spmv_wave_row_fp8_kernel<true, false> : spmv_wave_row_fp8_kernel<false, false>);
     int st = set_lds_limit(kfn, max_lds);
     if (st != MACKO_OK) return st;
     const SpmvMat& m = args.m[0];
@@ -674,7 +702,8 @@ int launch_wave_row_fp8(const SpmvGroupArgs& args, const SpmvGroupHeader& head, 
                        static_cast<const uint2*>(m.values), m.deltas, m.y);
   } else {
     using KG = void (*)(int, int, int, int, int, int, int, uint32_t, SpmvGroupArgs);
-    KG kfn = simple ? (KG)spmv_wave_row_kernel<2, true, 4, 8> : (KG)spmv_wave_row_kernel<2, false, 4, 8>;
+    KG kfn = tails ? (simple ? (KG)spmv_wave_row_kernel<2, true, 4, 8, true> : (KG)spmv_wave_row_kernel<2, false, 4, 8, true>)
+                   : (simple ? (KG)spmv_wave_row_kernel<2, true, 4, 8> : (KG)spmv_wave_row_kernel<2, false, 4, 8>);
     int st = set_lds_limit(kfn, max_lds);
     if (st != MACKO_OK) return st;
     hipLaunchKernelGGL(kfn, grid, blockdim, (size_t)max_lds, stream, head.wg_begin[1], head.wg_begin[2],
@@ -796,6 +825,13 @@ int launch_wave_row_group(int nwr, const SpmvProblem* const* wr, int b_delta, in
   }
   if (plan.total_wgs >= (int64_t{1} << 31)) return MACKO_E_UNSUPPORTED;
 
+  // Rows of whole steps that start anywhere (the rows in step above, 8-bit values): begun where the row begins, they end in one
+  // chunk of a step that holds nothing else.  Lane i of the wavefront takes row i's chunk, all of them at once behind the last row
+  // (TAILS): 11008 x 4096 at 50 %, the same number in every row: 11.5 -> 10.7 us, 22016 x 4096 17.2 -> 16.4; iid masks 11.5 and
+  // 11.6.  With 16-bit values steps on whole lines are worth more (11008 x 4096: 12.7, with tails 13.5), and where there are
+  // hardly any tails the code for them costs up to 3 %.
+  const bool tails = in_step && b_val == 8 && nwr <= kMaxGroup;
+
   SpmvWideArgs wide_args;                              // filled in for more than kMaxGroup matrices only
   SpmvGroupArgs args{};
   SpmvGroupHeader head{};
@@ -821,7 +857,7 @@ int launch_wave_row_group(int nwr, const SpmvProblem* const* wr, int b_delta, in
     m.q = plan.m[i].q;
     m.r = plan.m[i].r;
     const int64_t align_knob = t.spmv_step_align;      // 0: by row length
-    const int align = align_knob ? (int)align_knob : (p.pad_nnz / p.rows >= kAlignMinEntries ? kStepAlign : 8);
+    const int align = align_knob ? (int)align_knob : (!tails && p.pad_nnz / p.rows >= kAlignMinEntries ? kStepAlign : 8);
     m.amask = std::min(std::max(align, 8), kMaxStepAlign) - 1;
     m.pad = 0;
     (nwr > kMaxGroup ? wide_args.wg_begin : head.wg_begin)[i] = (int)wg_begin;
@@ -859,7 +895,7 @@ int launch_wave_row_group(int nwr, const SpmvProblem* const* wr, int b_delta, in
     for (int i = 1; i < nwr; ++i) min_steps = std::min(min_steps, in[i].steps_per_row);
     if (min_steps >= 8) ring = 4;
   }
-  if (b_val == 8) return launch_wave_row_fp8(args, head, nwr, plan, max_lds, simple, stream);
+  if (b_val == 8) return launch_wave_row_fp8(args, head, nwr, plan, max_lds, simple, tails, stream);
   switch (b_delta) {
     case 1: return launch_wave_row_bd<1>(args, head, nwr, plan, max_lds, simple, ring, stream);
     case 2: return launch_wave_row_bd<2>(args, head, nwr, plan, max_lds, simple, ring, stream);

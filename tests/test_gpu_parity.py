@@ -1813,6 +1813,41 @@ def test_spmm_on_both_sides_of_the_rule_that_picks_its_kernel(kind, rows, cols, 
     assert float(((Y - ref).abs() / bound).max()) <= 1.01
 
 
+@pytest.mark.parametrize("align", [0, 8, 64, 256])
+@pytest.mark.parametrize("rows,cols", [(1, 4096), (61, 4096), (1030, 4096), (33, 8192)])
+def test_rows_in_step_with_8_bit_values_end_in_any_chunk(rows, cols, align):
+    """Rows of about a multiple of 2048 entries with 8-bit values: those that end in one chunk of a step have it taken by one
+    lane behind the last row.  Lengths of 9 less to 9 more than half of the columns, so that rows start and end anywhere in a chunk,
+    one row empty, one NaN at a row's end, one launch of one matrix and one of two.  Reference and bound as for the batch products."""
+    rng = np.random.default_rng(rows + cols)
+    W8 = np.zeros((rows, cols), dtype=np.uint8)
+    for r in range(rows):
+        n = cols // 2 + (r * 5) % 19 - 9
+        W8[r, np.sort(rng.choice(cols, n, replace=False))] = rng.integers(1, 0x7F, n).astype(np.uint8) | (rng.integers(0, 2, n) << 7).astype(np.uint8)
+    W64 = oracle.fp8_to_double(np.arange(256, dtype=np.uint8))[W8]
+    if rows > 1000:
+        W8[500], W64[500] = 0, 0.0
+    if rows > 30:
+        W8[20, np.flatnonzero(W8[20])[-1]] = 0x7F                          # NaN
+    m = M.encode_fp8(W8).to_device()
+    x = rng.standard_normal((2, cols)).astype(np.float16)
+    xd = [torch.from_numpy(v).cuda() for v in x]
+    M.set_tuning("spmv_step_align", align)
+    try:
+        ys = [m.spmv(xd[0]).cpu().numpy()] + [y.cpu().numpy() for y in M.spmv_group([m, m], xd)]
+    finally:
+        M.set_tuning("spmv_step_align", 0)
+    assert np.array_equal(ys[0], ys[1], equal_nan=True)
+    for y, v in zip(ys[1:], x.astype(np.float64)):
+        ref, mag = W64 @ v, np.abs(W64) @ np.abs(v)
+        fine = np.ones(rows, dtype=bool)
+        if rows > 30:
+            assert np.isnan(y[20])
+            fine[20] = False
+        bound = np.abs(ref) * 2.0 ** -11 + 2.0 ** -25 + mag * cols * 2.0 ** -24
+        assert (np.abs(y.astype(np.float64) - ref)[fine] <= 1.01 * bound[fine]).all()
+
+
 @pytest.mark.parametrize("kind", ["b1", "b4", "fp8"])
 @pytest.mark.parametrize("rows,cols,sparsity,batch", [
     # 2 to 8 vectors: short rows, few rows and many, pieces of 8, 4 and 2, odd columns

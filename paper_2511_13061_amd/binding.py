@@ -11,6 +11,7 @@ import numpy as np
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libmacko.so")
 _lib = None
+_native = None           # csrc/binding_torch.cpp, once the library is loaded (None: not built; the calls go through ctypes)
 
 EXPORTED_SYMBOLS = [
     "macko_encode", "macko_encode_device", "macko_wrap_device", "macko_encode_ex", "macko_encode_device_ex",
@@ -80,7 +81,7 @@ def library_path() -> str:
 
 def load_library():
     """Load libmacko.so.  There is no fallback: a missing library is an error."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -90,8 +91,10 @@ def load_library():
     # PyTorch ships its own copy of the HIP runtime.  When it is going to be used in this process it has
     # to be loaded before this library, so that both bind to the same runtime: the other order leaves
     # the process without a visible device (hipErrorNoDevice from the first call that touches the GPU).
+    native = None
     try:
         import torch  # noqa: F401
+        from . import _native as native
     except ImportError:
         pass
     lib = ctypes.CDLL(_LIB_PATH)
@@ -141,6 +144,9 @@ def load_library():
         fn = getattr(lib, name)
         if name not in ("macko_destroy", "macko_status_string"):
             fn.restype = ci
+    if native is not None:
+        native.bind(*[ctypes.cast(f, vp).value for f in (lib.macko_spmv, lib.macko_spmm, lib.macko_decode_device)])
+        _native = native
     _lib = lib
     return lib
 
@@ -152,6 +158,13 @@ def status_string(status: int) -> str:
 def _check(status: int, where: str) -> None:
     if status != 0:
         raise MackoError(status, where)
+
+
+def _made(result, where: str):
+    """What a native call has returned: the tensor, or the status of a call that failed."""
+    if type(result) is int:
+        raise MackoError(result, where)
+    return result
 
 
 def set_tuning(name: str, value: int) -> None:
@@ -339,6 +352,8 @@ class MackoMatrix:
         torch = _need_torch()
         if dense_dev is None:
             rows, cols, b_val = self._dims()
+            if stream is None and _native is not None:
+                return _made(_native.decode_device(self._h.value, rows, cols, b_val), "macko_decode_device")
             dense_dev = torch.empty((rows, cols), dtype=torch.uint8 if b_val == 8 else torch.float16, device="cuda")
         if dense_dev.dim() != 2 or (dense_dev.shape[1] > 1 and dense_dev.stride(1) != 1):
             raise ValueError("dense_dev must be a row-major [rows, >= cols] tensor")
@@ -349,6 +364,10 @@ class MackoMatrix:
 
     def spmv(self, x_dev, y_dev=None, stream=None):
         """y = W x.  x_dev: torch float16 CUDA tensor [cols]; returns y_dev [rows]."""
+        if stream is None and _native is not None:
+            y = _native.spmv(self._h.value, (self._shape or self._dims())[0] if y_dev is None else 0, x_dev, y_dev)
+            if y is not None:                # None: not plain device tensors
+                return _made(y, "macko_spmv")
         if y_dev is None:
             torch = _torch or _need_torch()
             y_dev = torch.empty((self._shape or self._dims())[0], dtype=torch.float16, device=x_dev.device)
@@ -359,6 +378,10 @@ class MackoMatrix:
 
     def spmm(self, X_dev, Y_dev=None, stream=None):
         """Y[b] = W X[b] for a torch float16 CUDA matrix X_dev [batch, cols]; returns [batch, rows]."""
+        if stream is None and _native is not None:
+            Y = _native.spmm(self._h.value, (self._shape or self._dims())[0] if Y_dev is None else 0, X_dev, Y_dev)
+            if Y is not None:                # None: not plain device tensors, or nothing the library takes
+                return _made(Y, "macko_spmm")
         torch = _need_torch()
         if X_dev.dim() != 2 or X_dev.stride(1) != 1:
             raise ValueError("X_dev must be a row-major [batch, cols] tensor")

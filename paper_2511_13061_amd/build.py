@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -49,6 +50,29 @@ def build_library(force: bool = True, verbose: bool = False, extra_flags=()) -> 
     return LIB
 
 
+BINDING = os.path.join(HERE, "_native" + sysconfig.get_config_var("EXT_SUFFIX"))
+
+
+def build_binding(verbose: bool = False) -> str:
+    """Compile the native part of the Python binding (host code only) against the installed PyTorch."""
+    import torch
+    base = os.path.dirname(torch.__file__)
+    inc = os.path.join(base, "include")
+    tmp = BINDING + f".tmp{os.getpid()}"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-w",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(ROOT, "include"), "-I", inc, "-I", os.path.join(inc, "torch", "csrc", "api", "include"),
+           "-I", sysconfig.get_paths()["include"], "-I", "/opt/rocm/include", os.path.join(CSRC, "binding_torch.cpp"), "-o", tmp,
+           "-L", os.path.join(base, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
+           "-Wl,-rpath," + os.path.join(base, "lib")]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(tmp, BINDING)
+    return BINDING
+
+
 if __name__ == "__main__":
     build_library(verbose=True, extra_flags=sys.argv[1:])
     print(LIB)
+    print(build_binding(verbose=True))

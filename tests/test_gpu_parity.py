@@ -1813,6 +1813,55 @@ def test_spmm_on_both_sides_of_the_rule_that_picks_its_kernel(kind, rows, cols, 
     assert float(((Y - ref).abs() / bound).max()) <= 1.01
 
 
+def test_native_calls_do_what_the_general_ones_do(monkeypatch):
+    """The binding's native functions against the same calls through ctypes: results, tensors handed in, errors; what they do not
+    serve (another stream, tensors of a subclass, layouts the library refuses) goes the general way with them as without."""
+    from paper_2511_13061_amd import binding as B
+    native = B._native
+    assert native is not None
+    W = (torch.randn((70, 130), device="cuda") * (torch.rand((70, 130), device="cuda") < 0.5)).half()
+    m, m8 = M.encode_device(W), M.encode_device_fp8(W.to(torch.float8_e4m3fn).view(torch.uint8))
+    unbound, gone = M.encode(W.cpu().numpy()), M.encode_device(W)
+    gone.destroy()
+    x, X, wide = torch.randn(130, device="cuda").half(), torch.randn((5, 130), device="cuda").half(), torch.randn((5, 140), device="cuda").half()
+    side = torch.cuda.Stream()
+
+    class Sub(torch.Tensor):
+        pass
+
+    def on_side(f):
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            r = f()
+        side.synchronize()
+        return r
+
+    y, Y = torch.empty(70, dtype=torch.float16, device="cuda"), torch.empty((5, 75), dtype=torch.float16, device="cuda")
+    calls = [lambda: m.spmv(x), lambda: m.spmv(x, y), lambda: m8.spmv(x), lambda: m.spmv(x, stream=side), lambda: on_side(lambda: m.spmv(x)),
+             lambda: m.spmv(x.as_subclass(Sub)), lambda: m.spmv(torch.nn.Parameter(x)), lambda: unbound.spmv(x), lambda: gone.spmv(x),
+             lambda: gone.spmv(x, y), lambda: m.spmv(x.view(torch.uint8)[1:]), lambda: m.spmm(X), lambda: m.spmm(X[:1]), lambda: m.spmm(X[:0]),
+             lambda: m.spmm(wide[:, 2:132]), lambda: m.spmm(X, Y[:, 1:71]), lambda: m.spmm(X, Y[:, :60][:, ::1]), lambda: m.spmm(X[:, ::2]),
+             lambda: m.spmm(x), lambda: m.spmm(X.repeat(14, 1)), lambda: m.spmm(X[:, :99]), lambda: m8.spmm(X), lambda: unbound.spmm(X),
+             lambda: m.decode_device(), lambda: m8.decode_device(), lambda: unbound.decode_device(), lambda: gone.decode_device(),
+             lambda: on_side(lambda: m.decode_device())]
+
+    def outcome(call):
+        y.fill_(-3)
+        Y.fill_(-3)
+        try:
+            r = call()
+        except Exception as e:
+            return type(e), str(e)
+        torch.cuda.synchronize()
+        return r.dtype, r.device, r.shape, r.stride(), r.requires_grad, r.view(torch.uint8 if r.dtype == torch.uint8 else torch.int16).tolist(), y.tolist(), Y.tolist()
+
+    for i, call in enumerate(calls):
+        with_native = outcome(call)
+        with monkeypatch.context() as patch:
+            patch.setattr(B, "_native", None)
+            assert with_native == outcome(call), i
+
+
 @pytest.mark.parametrize("align", [0, 8, 64, 256])
 @pytest.mark.parametrize("rows,cols", [(1, 4096), (61, 4096), (1030, 4096), (33, 8192)])
 def test_rows_in_step_with_8_bit_values_end_in_any_chunk(rows, cols, align):

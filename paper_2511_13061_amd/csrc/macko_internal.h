@@ -131,6 +131,7 @@ int launch_spmm(const SpmvProblem& p, const void* X, int64_t ldx, void* Y, int64
 // the same on the matrix cores: which calls it can serve (any batch up to 64), and the launch
 bool spmm_tile_serves(const SpmvProblem& p, int64_t ldx);
 int64_t spmm_tile_windows(const SpmvProblem& p);       // windows that a workgroup goes through, of up to 16 vectors
+bool spmm_tile_pairs_groups(const SpmvProblem& p, int batch);      // two groups of columns share an operand there
 int launch_spmm_tile(const SpmvProblem& p, const uint16_t* X, int64_t ldx, uint16_t* Y, int64_t ldy, int batch,
                      hipStream_t stream);
 // device-side expansion: column index of every stored entry; the dense matrix back

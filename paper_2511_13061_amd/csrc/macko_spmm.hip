@@ -330,11 +330,12 @@ Piece next_piece(bool long_rows, int64_t one, int left) {
 // Up to 16 vectors take the matrix cores one launch whose time is a sum of its parts (the phases of a window do not overlap, see
 // macko_spmm_tile.hip); the vector kernel takes a launch per piece, whose time is its launch, its arithmetic per step of 512 entries
 // and vector, the staging of the vectors (one by one where their length is no multiple of 8), and, with few rows, the chain of one
-// row's steps.  The factors (us) were fitted to 1014 calls timed both ways: 2 to 16 vectors, 16 to 36864 rows, 128 to 40000
-// columns, 30 to 99.5 % pruned, all code widths up to 4 bits, both value widths.  The estimates are off by 5 % (matrix cores) and
-// 13 % (vectors) at the median; the way chosen is 1 % slower than the better one in the mean and 13 % at worst.  Against the lines
-// this takes the place of, 2 to 8 vectors take 0.78 of the time (12 % less at 2, 37 % at 8), most with short rows and few rows:
-// 1392 x 1012 at 87 %, 8 vectors: 31 -> 5.5 us; 718 x 8797 at 50 %, 8: 32 -> 16; 344 x 352 at 62 %, 8: 29 -> 5.1.
+// row's steps.  The factors (us) were fitted to 1040 calls timed both ways: 2 to 16 vectors, 16 to 36864 rows, 64 to 40000
+// columns, 30 to 99.9 % pruned, all code widths up to 4 bits, both value widths.  The estimates are off by 5 % (matrix cores) and
+// 13 % (vectors); the way chosen is 0.5 % slower than the better one in the mean.  Against the lines this takes the
+// place of, 2 / 4 / 8 vectors take 0.92 / 0.67 / 0.55 of the time, most with short rows and few rows:
+// 1392 x 1012 at 87 %, 8 vectors: 31 -> 5.5 us; 718 x 8797 at 50 %, 8: 32 -> 14; 344 x 352 at 62 %, 8: 29 -> 5.1; the
+// worst is 7 % slower.
 bool tile_is_faster(const SpmvProblem& p, int batch) {
   if (batch <= 1) return false;
   if (batch > 16) return true;                         // at least three pieces (11008 x 4096, 64 vectors: 183 / 32)
@@ -342,7 +343,8 @@ bool tile_is_faster(const SpmvProblem& p, int batch) {
   const double entries = (double)p.pad_nnz, avg = entries / rows, steps = std::ceil(avg / 512.0);
   const double mbytes = entries * (p.b_val + p.b_delta) / 8e6;
   const double tiles = std::ceil(rows / (16.0 * cus)), tiles_wg = std::ceil(rows / (16.0 * std::min(cus, std::ceil(rows / 16.0))));
-  const double tile_us = 2.63 + 1.87 * (double)spmm_tile_windows(p) + 0.72 * tiles * cols + 0.55 * tiles_wg * steps + 0.05 * mbytes;
+  const double window_us = spmm_tile_pairs_groups(p, batch) ? 1.67 : 1.98;
+  const double tile_us = 2.78 + window_us * (double)spmm_tile_windows(p) + 0.48 * tiles * cols + 0.48 * tiles_wg * steps + 0.08 * mbytes;
 
   const bool long_rows = p.pad_nnz / p.rows >= kLongRow, ragged = p.cols % 8 != 0;
   const bool one_launch = p.b_val == 8 || p.pad_nnz / p.rows >= kWaveRowMinEntries;    // of a group of single products
@@ -351,13 +353,15 @@ bool tile_is_faster(const SpmvProblem& p, int batch) {
   for (int left = batch; left > 0;) {
     const Piece q = next_piece(long_rows, one, left);
     const double work = rows * steps / cus * (1.0 + q.pass / 4.0), copy = q.pass * cols, chain = (2.0 + q.pass) * steps;
-    if (q.pass == 8) vector_us += 4.77 + 0.021 * work + 0.222 * copy + (ragged ? 0.853 * copy : 0.0) + 0.017 * chain;
-    else if (q.pass) vector_us += 3.03 + 0.015 * work + 0.145 * copy + (ragged ? 0.818 * copy : 0.0) + 0.095 * chain;
-    else if (one_launch) vector_us += 3.73 + q.take * (0.056 * rows * steps / cus + 0.048 * mbytes) + (ragged ? 0.973 * cols : 0.0);
-    else vector_us += q.take * (2.94 + 1.087 * (entries / 1e6 + 0.4 * cols * rows / cus / 32.0));
+    if (q.pass == 8) vector_us += 3.88 + 0.087 * rows * steps / cus + 0.251 * copy + (ragged ? 0.801 * copy : 0.0) + (rows < 4.0 * cus ? 0.677 * steps : 0.0);
+    else if (q.pass) vector_us += 2.96 + 0.02 * work + 0.138 * copy + (ragged ? 0.797 * copy : 0.0) + 0.099 * chain;
+    else if (one_launch) vector_us += 3.69 + q.take * (0.056 * rows * steps / cus + 0.052 * mbytes) + (ragged ? 0.929 * cols : 0.0);
+    else vector_us += q.take * (2.92 + 1.064 * (entries / 1e6 + 0.4 * cols * rows / cus / 32.0));
     left -= q.take;
   }
-  return 1.04 * tile_us < vector_us;                   // 1.04: of near ties the one with the surer estimate loses less
+  // one piece of 8 comes closest, and its estimate is the least sure
+  const bool one_piece = next_piece(long_rows, one, batch).pass == 8 && batch <= 8;
+  return tile_us * (one_piece ? 1.05 : 1.0) < vector_us;
 }
 
 }  // namespace

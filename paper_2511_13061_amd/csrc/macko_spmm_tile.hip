@@ -18,11 +18,10 @@
 // 16-wavefront workgroup per compute unit covers little of one with another.  Leaving out the puts into the tile takes 4 us off, B and its
 // transposes 8, the matrix instructions 3; a window costs about 2 us whatever is in it, so few, large windows are best.
 // Measured before (16 rows at a time, X read for each, transposes behind the barrier) and now, us, batch 8 / 16 / 32 / 64 at 50 %:
-// 4096 x 11008: 21.8 / 21.8 / 28.0 / 39.5 -> 20.4 / 20.4 / 26.3 / 37.4; 11008 x 4096: 24.3 / 24.3 / 30.4 / 44.6 -> 23.1 /
-// 23.1 / 30.3 / 34.1; 4096 x 4096: 12.4 / 12.4 / 14.6 / 20.4 -> 10.2 / 10.2 / 12.8 / 17.2; 11008 x 4096 at 90 %, 64: 37.2 -> 22.7.
+// 4096 x 11008: 21.8 / 21.8 / 28.0 / 39.5 -> 19.3 / 20.4 / 26.3 / 37.4; 11008 x 4096: 24.3 / 24.3 / 30.4 / 44.6 -> 20.3 /
+// 23.1 / 30.3 / 34.1; 4096 x 4096: 12.4 / 12.4 / 14.6 / 20.4 -> 9.2 / 10.2 / 12.8 / 17.2; 11008 x 4096 at 90 %, 64: 37.2 -> 22.7.
 // 260 matrices of 300 to 14336 rows, 700 to 13000 columns, 40 to 93 % pruned, 12 to 64 vectors: 1.37 times as fast
-// (geometric mean), the slowest 4 % slower; beyond that range few rows of
-// more than 20 000 columns are up to 15 % slower (183 x 27736 at 33 %, 16 vectors: 42.4 -> 48.7).
+// (geometric mean), the slowest 4 % slower.
 //
 // Tried: two workgroups of 8 wavefronts per compute unit, each with half of the rows (5 to 30 % slower: X is read twice, and
 // more windows); 512-column windows in two buffers for panels of 48 rows (34 -> 41 us); a ring of 2 to 4 steps of loads refilled one by one
@@ -44,6 +43,7 @@ constexpr int kWaves = 16;                             // wavefronts of a workgr
 // Bytes in front of every row of the tile (and behind the last) that are written but never read: entries
 // in front of the window or behind it land there.  A lane's 8 entries span at most 8 * 2 * 16 bytes.
 constexpr int kTilePad = 256;
+constexpr int kHalfVectors = 8;                        // up to here two groups of columns share one operand (HALF in the kernel)
 // 16 bytes more per row: the 16 rows that a matrix instruction reads at one column fall on different banks
 constexpr int panel_stride(int window) { return 2 * window + kTilePad + 16; }
 constexpr int panel_slices(int window, int vs) { return window / 128 < kWaves / vs ? window / 128 : kWaves / vs; }
@@ -81,6 +81,10 @@ __device__ __forceinline__ void keep_opaque(uint32_t& w, LaneValues<8>& v) { asm
 template <int CTRL>
 __device__ __forceinline__ uint32_t quad_dpp(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true);
+}
+// the value of the lane 8 further on within the 16 (8 further back for the upper 8)
+__device__ __forceinline__ float half_row_swap(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x128, 0xf, 0xf, true));
 }
 // 4 x 4 transpose of 16-byte blocks within every four lanes: register r of lane 4 i + q goes to register q of lane 4 i + r
 __device__ __forceinline__ void quad_transpose(u32x4 (&b)[4], bool odd, bool high) {
@@ -141,7 +145,7 @@ __device__ __forceinline__ void tile_row_by_entries(const TileArgs& a, int row, 
 
 // NT: tiles of 16 vectors; a launch of more vectors has several rows of workgroups.  P: tiles of 16 rows in a panel.  W: columns
 // of the largest window (a.window: of this launch's).  VS: parts into which the vector tiles are dealt to the wavefronts.
-// DBL: two buffers.  S: steps of 512 entries that are loaded, taken and decoded together (a unit).
+// HALF: up to 8 vectors, see below.  DBL: two buffers.  S: steps of 512 entries that are loaded, taken and decoded together (a unit).
 //
 // Window by window, a wavefront
 //  - clears its own rows of the tile and puts what it holds of them (the last unit taken may reach into several windows: its
@@ -156,17 +160,20 @@ __device__ __forceinline__ void tile_row_by_entries(const TileArgs& a, int row, 
 // With two buffers the next window goes into the other one at once; with one a second barrier keeps it apart.  The pad behind a row is
 // the one in front of the next: two wavefronts may write it, nobody reads it.
 // Every wavefront executes the same number of barriers whatever its rows hold.
-template <int NT, int P, int W, int VS, bool DBL, int S, int BD, int VB>
+template <int NT, int P, int W, int VS, bool DBL, int S, bool HALF, int BD, int VB>
 __global__ void __launch_bounds__(64 * kWaves)
 spmm_panel_kernel(const TileArgs all) {
   TileArgs a = all;                                    // this workgroup's vectors
-  a.X += (int64_t)blockIdx.y * (16 * NT) * a.ldx;
-  a.Y += (int64_t)blockIdx.y * (16 * NT) * a.ldy;
-  a.batch = min(a.batch - (int)blockIdx.y * (16 * NT), 16 * NT);
+  constexpr int kVectors = HALF ? kHalfVectors : 16 * NT;
+  a.X += (int64_t)blockIdx.y * kVectors * a.ldx;
+  a.Y += (int64_t)blockIdx.y * kVectors * a.ldy;
+  a.batch = min(a.batch - (int)blockIdx.y * kVectors, kVectors);
   static_assert(BD <= 4, "a lane's 8 entries have to fit the pad");
   constexpr int kSlices = panel_slices(W, VS), G = W / 128 / kSlices;       // wavefronts along the columns, groups of each
   constexpr int RS = kWaves / (kSlices * VS);
   static_assert(kSlices * G * 128 == W && kSlices * VS * RS == kWaves, "every wavefront has its part of a window");
+  static_assert(!HALF || (NT == 1 && G % 2 == 0 && RS == 1), "pairs of groups of one vector tile");
+  constexpr int BG = HALF ? G / 2 : G, kPair = HALF ? 2 : 1;                // operands of a wavefront, groups of each
   constexpr int NTW = (NT + VS - 1) / VS, RW = (P + RS - 1) / RS;           // vector tiles and row tiles of a wavefront
   constexpr int kStride = panel_stride(W), kBuffer = 16 * P * kStride;
   extern __shared__ __align__(16) unsigned char lds[];
@@ -200,16 +207,19 @@ spmm_panel_kernel(const TileArgs all) {
   const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<unsigned char*>(reinterpret_cast<const unsigned char*>(a.X) - xmis), 0, (int)xbytes, 0x00020000);
   const uint32_t ldx2 = 2u * (uint32_t)a.ldx;
-  const int bcol = 128 * G * slice + 8 * (4 * (lane >> 4) + (lane & 3));        // the lane's first column within the window
-  const uint32_t xoff = xmis + (uint32_t)(16 * vpart + 4 * ((lane >> 2) & 3)) * ldx2 + 2u * bcol;
-  u32x4 b[G][NTW][4];
+  // HALF, up to 8 vectors: the lanes of vectors 8 ... 15 take vectors 0 ... 7 of the next group instead, so that one operand serves two
+  // groups.  The products of the first count in lanes 0 ... 7 of each 16, those of the second in lanes 8 ... 15 of another sum.
+  // Half the loads and transposes: 4096 x 11008 at 50 %, 8 vectors: 20.5 -> 19.3 us, at 80 % 14.7 -> 13.3; 300 x 13001: 16.1 -> 14.1.
+  const int bcol = 128 * G * slice + (HALF ? 128 * ((lane >> 3) & 1) : 0) + 8 * (4 * (lane >> 4) + (lane & 3));        // the lane's first column within the window
+  const uint32_t xoff = xmis + (uint32_t)(16 * vpart + 4 * ((lane >> 2) & (HALF ? 1 : 3))) * ldx2 + 2u * bcol;
+  u32x4 b[BG][NTW][4];
   int k0 = 0;                                          // first column of the window
-  // loads `from` ... `to` - 1 of the window's 4 G NTW
+  // loads `from` ... `to` - 1 of the window's 4 BG NTW
   auto load_b = [&](int from, int to) {
 #pragma unroll
-    for (int g = 0; g < G; ++g)
-      if (128 * (G * slice + g) < min(wr, cols - k0) && to > 4 * NTW * g && from < 4 * NTW * (g + 1)) {
-        uint32_t xo = xoff + 2u * (uint32_t)(k0 + 128 * g);
+    for (int g = 0; g < BG; ++g)
+      if (128 * (G * slice + kPair * g) < min(wr, cols - k0) && to > 4 * NTW * g && from < 4 * NTW * (g + 1)) {
+        uint32_t xo = xoff + 2u * (uint32_t)(k0 + 128 * kPair * g);
         asm volatile("" : "+v"(xo));
 #pragma unroll
         for (int i = 0; i < 4 * NTW; ++i)
@@ -251,15 +261,17 @@ spmm_panel_kernel(const TileArgs all) {
     open_row(p);
     if (left[p] > 0) issue(p, e0[p], end[p]);
   }
-  load_b(0, 4 * G * NTW);
+  load_b(0, 4 * BG * NTW);
   odd_results[threadIdx.x][0] = odd_results[threadIdx.x][1] = 0u;
   if (threadIdx.x == 0) any_odd = 0u;
 
-  float4v acc[RW][NTW];
+  float4v acc[RW][NTW], acc_pair[RW];                  // acc_pair: HALF, the second groups' sums
 #pragma unroll
-  for (int i = 0; i < RW; ++i)
+  for (int i = 0; i < RW; ++i) {
+    acc_pair[i] = float4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int t = 0; t < NTW; ++t) acc[i][t] = float4v{0.f, 0.f, 0.f, 0.f};
+  }
 
   const int cols2 = 2 * ((cols + 127) & ~127);
   uint32_t buf = 0;                                    // byte offset of the window's buffer
@@ -351,19 +363,19 @@ spmm_panel_kernel(const TileArgs all) {
             }
           }
         }
-        if (b_due) load_b(4 * G * NTW * p / P, 4 * G * NTW * (p + 1) / P);
+        if (b_due) load_b(4 * BG * NTW * p / P, 4 * BG * NTW * (p + 1) / P);
       }
       b_due = false;
     }
     // the vectors into the operand's layout
     const int groups = min(wr, cols - k0);             // columns of the window that are multiplied
 #pragma unroll
-    for (int g = 0; g < G; ++g)
-      if (128 * (G * slice + g) < groups) {
-        if (__builtin_expect(k0 + 128 * (G * slice + g) + 128 > cols, 0)) {      // the vectors end in it
+    for (int g = 0; g < BG; ++g)
+      if (128 * (G * slice + kPair * g) < groups) {
+        if (__builtin_expect(k0 + 128 * (G * slice + kPair * g) + 128 * kPair > cols, 0)) {      // the vectors end in it
           int l = lane;
           if (NTW > 1) asm volatile("" : "+v"(l));
-          const int left = cols - (k0 + 128 * (G * slice + g) + 8 * (4 * (l >> 4) + (l & 3)));
+          const int left = cols - (k0 + 128 * (G * slice + kPair * g + (HALF ? (l >> 3) & 1 : 0)) + 8 * (4 * (l >> 4) + (l & 3)));
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const uint32_t mask = left > 2 * i + 1 ? 0xFFFFFFFFu : (left > 2 * i ? 0xFFFFu : 0u);
@@ -373,7 +385,7 @@ spmm_panel_kernel(const TileArgs all) {
               for (int r = 0; r < 4; ++r) b[g][t][r][i] &= mask;
           }
           if (__builtin_expect(cols & 1, 0)) {         // the last element of the last vector (left is odd here)
-            const int last = a.batch - 1 - 16 * vpart - 4 * ((l >> 2) & 3);
+            const int last = a.batch - 1 - 16 * vpart - 4 * ((l >> 2) & (HALF ? 1 : 3));
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               const uint32_t e = left == 2 * i + 1 ? last_x : 0u;
@@ -403,8 +415,10 @@ spmm_panel_kernel(const TileArgs all) {
             for (int r = 0; r < 4; ++r) {
               const half8 av = *reinterpret_cast<const half8*>(ap + 16 * RS * i * kStride + 16 * r);
 #pragma unroll
-              for (int t = 0; t < NTW; ++t)
-                acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, __builtin_bit_cast(half8, b[g][t][r]), acc[i][t], 0, 0, 0);
+              for (int t = 0; t < NTW; ++t) {
+                float4v& sum = HALF && g % 2 == 1 ? acc_pair[i] : acc[i][t];
+                sum = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, __builtin_bit_cast(half8, b[g / kPair][t][r]), sum, 0, 0, 0);
+              }
             }
           }
         }
@@ -419,6 +433,14 @@ spmm_panel_kernel(const TileArgs all) {
     // ---- the results of the panel: the slices' sums are handed over in the tile's memory (the other buffer's, if there are two)
     k0 = 0;
     float4v* red = reinterpret_cast<float4v*>(lds + kTilePad + (DBL ? kBuffer - buf : 0));      // [P * NT][kSlices][64]
+    if (HALF) {
+#pragma unroll
+      for (int i = 0; i < RW; ++i) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[i][0][e] += half_row_swap(acc_pair[i][e]);
+        acc_pair[i] = float4v{0.f, 0.f, 0.f, 0.f};
+      }
+    }
     if (!DBL) __syncthreads();
 #pragma unroll
     for (int i = 0; i < RW; ++i)
@@ -472,12 +494,13 @@ spmm_panel_kernel(const TileArgs all) {
   }
 }
 
-template <int NT, int P, int W, int VS, bool DBL, int S, int BD, int VB>
+template <int NT, int P, int W, int VS, bool DBL, int S, bool HALF, int BD, int VB>
 int launch_panel_as(TileArgs a, hipStream_t stream) {
+  constexpr int vectors = HALF ? kHalfVectors : 16 * NT;
   constexpr int buffer = 16 * P * panel_stride(W), lds = (DBL ? 2 : 1) * buffer + kTilePad;
   static_assert(P * NT * panel_slices(W, VS) * 1024 + kTilePad <= buffer, "the partial sums fit one buffer");
   static_assert(lds + 64 * kWaves * 8 + 16 <= 160 * 1024, "LDS of a compute unit");
-  auto kfn = spmm_panel_kernel<NT, P, W, VS, DBL, S, BD, VB>;
+  auto kfn = spmm_panel_kernel<NT, P, W, VS, DBL, S, HALF, BD, VB>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return hip_fail(e);
   // One workgroup per compute unit with an equal share of the rows: LDS holds no second one, and the fewer workgroups,
@@ -489,7 +512,7 @@ int launch_panel_as(TileArgs a, hipStream_t stream) {
   // as few windows as LDS allows, all about equally wide (11008 columns: 6 of 1920 instead of 5 of 2048 and one of 768)
   const int64_t windows = ((int64_t)a.cols + W - 1) / W;
   a.window = (int)((((int64_t)a.cols + windows - 1) / windows + 127) / 128 * 128);
-  hipLaunchKernelGGL(kfn, dim3((unsigned)grid, (unsigned)((a.batch + 16 * NT - 1) / (16 * NT))), dim3(64 * kWaves), (size_t)lds, stream, a);
+  hipLaunchKernelGGL(kfn, dim3((unsigned)grid, (unsigned)((a.batch + vectors - 1) / vectors)), dim3(64 * kWaves), (size_t)lds, stream, a);
   e = hipGetLastError();
   return e == hipSuccess ? MACKO_OK : hip_fail(e);
 }
@@ -505,6 +528,13 @@ bool two_tiles(int64_t tiles, int64_t cols) {
   return tiles > 1 && (tiles + 1) / 2 * ((cols + 2047) / 2048) <= tiles * ((cols + 4095) / 4096);
 }
 
+// Whether the vectors go in groups of at most 8, each with a workgroup of its own for every 16 rows: where one group is all there is,
+// and where the compute units hold all groups at once.
+bool eights_fit(int64_t rows, int64_t cols, int batch) {
+  if (batch <= kHalfVectors) return !two_tiles(tiles_per_wg(rows), cols);
+  return (rows + 15) / 16 * ((batch + kHalfVectors - 1) / kHalfVectors) <= device_cu_count();
+}
+
 // The shape of a launch.  A workgroup's work is its panels times their windows, about 2 us each, and the reads of X once per panel.
 // Figures: us at the sizes given, from 260 matrices timed with every shape.
 template <int BD, int VB>
@@ -512,32 +542,40 @@ int launch_tile_bd(const TileArgs& a, hipStream_t stream) {
   const int64_t cus = device_cu_count();
   const int64_t tiles = tiles_per_wg(a.rows);
   int nt = (a.batch + 15) / 16;
-  // Few rows leave compute units idle: they take the same rows with other vectors (256 x 4096, 64 vectors: 14.9 -> 8.7).
-  if (a.rows <= 8 * cus) {
+  // Few rows leave compute units idle: they take the same rows with other vectors, in groups of 8 if there are enough of them, else
+  // of 16 (256 x 4096, 64 vectors: 14.9 -> 8.7 in groups of 16, 7.9 in
+  // groups of 8; 106 x 13022 at 52 %, 16: 22.2 -> 18.9; but 300 x 700, 64: 5.7 and 6.1).
+  const bool half = eights_fit(a.rows, a.cols, a.batch);
+  if (!half && a.rows <= 8 * cus) {
     const int groups = (int)std::min<int64_t>(nt, cus / ((a.rows + 15) / 16));
     nt = (nt + groups - 1) / groups;
   }
 #define MACKO_PANEL(...) return launch_panel_as<__VA_ARGS__, BD, VB>(a, stream)
-  if (nt == 1) {
-    if (two_tiles(tiles, a.cols)) MACKO_PANEL(1, 2, 2048, 1, false, 1);
+  if (half || nt == 1) {
+    if (!half && two_tiles(tiles, a.cols)) MACKO_PANEL(1, 2, 2048, 1, false, 1, false);
     // few long rows: nothing but each wavefront's own loads hides their latency (300 x 13000 at 80 %: 17.6 with two steps a unit, 16.8)
-    if (a.rows <= 8 * cus && a.cols > 8192) MACKO_PANEL(1, 1, 4096, 1, false, 3);
-    MACKO_PANEL(1, 1, 4096, 1, false, 2);
+    const bool long_few = a.rows <= 8 * cus && a.cols > 8192;
+    if (half) {
+      if (long_few) MACKO_PANEL(1, 1, 4096, 1, false, 3, true);
+      MACKO_PANEL(1, 1, 4096, 1, false, 2, true);
+    }
+    if (long_few) MACKO_PANEL(1, 1, 4096, 1, false, 3, false);
+    MACKO_PANEL(1, 1, 4096, 1, false, 2, false);
   }
   // From here on X counts as well: the shape whose panels have the fewest empty places, 3 tiles if equal
   const bool three = (tiles + 2) / 3 * 3 <= (tiles + 1) / 2 * 2;
   if (nt == 2) {
-    if (tiles == 1) MACKO_PANEL(2, 1, 2048, 1, true, 2);
-    if (three) MACKO_PANEL(2, 3, 1024, 2, false, 1);                   // 10000 x 1800: 15.3 with panels of 2, 13.5
-    MACKO_PANEL(2, 2, 2048, 1, false, 1);                              // 5000 x 4096: 18.5 with panels of 1, 15.4
+    if (tiles == 1) MACKO_PANEL(2, 1, 2048, 1, true, 2, false);
+    if (three) MACKO_PANEL(2, 3, 1024, 2, false, 1, false);                   // 10000 x 1800: 15.3 with panels of 2, 13.5
+    MACKO_PANEL(2, 2, 2048, 1, false, 1, false);                              // 5000 x 4096: 18.5 with panels of 1, 15.4
   }
   if (tiles == 1) {
-    if (nt == 3) MACKO_PANEL(3, 1, 2048, 1, true, 2);                  // 4096 x 4096: 15.2; with a fourth, empty tile 17.1
-    if (a.cols <= 3072) MACKO_PANEL(4, 1, 1024, 2, true, 2);           // 4096 x 2600: 13.1 / 14.2 with 2048, 4096 x 4096 at 90 %: 13.5 / 12.6
-    MACKO_PANEL(4, 1, 2048, 1, true, 1);
+    if (nt == 3) MACKO_PANEL(3, 1, 2048, 1, true, 2, false);                  // 4096 x 4096: 15.2; with a fourth, empty tile 17.1
+    if (a.cols <= 3072) MACKO_PANEL(4, 1, 1024, 2, true, 2, false);           // 4096 x 2600: 13.1 / 14.2 with 2048, 4096 x 4096 at 90 %: 13.5 / 12.6
+    MACKO_PANEL(4, 1, 2048, 1, true, 1, false);
   }
-  if (three) MACKO_PANEL(4, 3, 1024, 2, false, 1);                     // 11008 x 4096: 40.9 with panels of 2, 34.1
-  MACKO_PANEL(4, 2, 1024, 2, true, 1);                                 // 8192 x 4096 at 80 %: 22.8 with panels of 1, 19.0
+  if (three) MACKO_PANEL(4, 3, 1024, 2, false, 1, false);                     // 11008 x 4096: 40.9 with panels of 2, 34.1
+  MACKO_PANEL(4, 2, 1024, 2, true, 1, false);                                 // 8192 x 4096 at 80 %: 22.8 with panels of 1, 19.0
 #undef MACKO_PANEL
 }
 
@@ -553,6 +591,8 @@ int64_t spmm_tile_windows(const SpmvProblem& p) {
   const int64_t tiles = tiles_per_wg(p.rows);
   return two_tiles(tiles, p.cols) ? (tiles + 1) / 2 * ((p.cols + 2047) / 2048) : tiles * ((p.cols + 4095) / 4096);
 }
+
+bool spmm_tile_pairs_groups(const SpmvProblem& p, int batch) { return eights_fit(p.rows, p.cols, batch); }
 
 int launch_spmm_tile(const SpmvProblem& p, const uint16_t* X, int64_t ldx, uint16_t* Y, int64_t ldy, int batch,
                      hipStream_t stream) {

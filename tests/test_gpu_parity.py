@@ -1488,8 +1488,11 @@ def test_spmm_tile_edges(kind, rows, cols, batch):
     (2100, 3073, 60), (2500, 700, 60), (2500, 2049, 40), (2300, 2500, 30),
     # of two tiles, in two windows of one buffer and in two buffers; of three; several panels a workgroup
     (4300, 2050, 9), (4300, 2100, 20), (4300, 1030, 64), (8300, 1100, 31), (8300, 1200, 40), (20600, 130, 20), (20600, 130, 33),
-    # vectors dealt to several workgroups: two groups of two tiles, the last one partly filled
-    (1500, 1100, 40), (1500, 129, 33)])
+    # vectors dealt to several workgroups: two groups of two tiles, the last one partly filled; groups of 8, as many as there are
+    # compute units for and one too many
+    (1500, 1100, 40), (1500, 129, 33), (2048, 300, 16), (2049, 300, 16), (40, 4500, 61),
+    # up to 8 vectors: pairs of groups of 128 columns, the second of a pair there, partly there and missing
+    (40, 127, 3), (40, 128, 8), (41, 129, 8), (40, 256, 5), (40, 257, 7), (70, 383, 8), (33, 4097, 8), (2100, 2049, 7)])
 def test_spmm_panel_shapes(kind, rows, cols, batch):
     """Every shape of the matrix-core kernel, with inputs and bound of test_spmm_tile_edges."""
     test_spmm_tile_edges(kind, rows, cols, batch)

@@ -12,14 +12,14 @@
 // with many vectors: X passes a compute unit's L1 at 64 bytes a clock, 3.4 us for 64 vectors of 4096 elements, and used to be
 // read for every 16 rows.  LDS holds about 65 000 cells in all, so a panel of more rows has narrower windows.
 //
-// What bounds it: no unit by itself.  11008 x 4096 at 50 % with 64 vectors, 34 us: vector issue 12 (decode 45 instructions
+// What bounds it: no unit by itself.  11008 x 4096 at 50 % with 64 vectors, 32 us: vector issue 12 (decode 45 instructions
 // per step of 512 entries, 11 per window that a step reaches into, 64 per four 16-byte loads of B), LDS 9, HBM 8.5, matrix
 // cores 2.6, loads of B 3.4; but the phases of a window (decode, product, clearing) alternate behind barriers, and one
 // 16-wavefront workgroup per compute unit covers little of one with another.  Leaving out the puts into the tile takes 4 us off, B and its
 // transposes 8, the matrix instructions 3; a window costs about 2 us whatever is in it, so few, large windows are best.
 // Measured before (16 rows at a time, X read for each, transposes behind the barrier) and now, us, batch 8 / 16 / 32 / 64 at 50 %:
-// 4096 x 11008: 21.8 / 21.8 / 28.0 / 39.5 -> 19.3 / 20.4 / 26.3 / 37.4; 11008 x 4096: 24.3 / 24.3 / 30.4 / 44.6 -> 20.3 /
-// 23.1 / 30.3 / 34.1; 4096 x 4096: 12.4 / 12.4 / 14.6 / 20.4 -> 9.2 / 10.2 / 12.8 / 17.2; 11008 x 4096 at 90 %, 64: 37.2 -> 22.7.
+// 4096 x 11008: 21.8 / 21.8 / 28.0 / 39.5 -> 19.3 / 20.3 / 26.3 / 37.4; 11008 x 4096: 24.3 / 24.3 / 30.4 / 44.6 -> 20.3 /
+// 22.2 / 30.3 / 32.1; 4096 x 4096: 12.4 / 12.4 / 14.6 / 20.4 -> 8.8 / 9.8 / 12.7 / 17.2; 11008 x 4096 at 90 %, 64: 37.2 -> 21.5.
 // 260 matrices of 300 to 14336 rows, 700 to 13000 columns, 40 to 93 % pruned, 12 to 64 vectors: 1.37 times as fast
 // (geometric mean), the slowest 4 % slower.
 //
@@ -55,7 +55,7 @@ struct TileArgs {
   const uint16_t* X;
   uint16_t* Y;
   int64_t ldx, ldy;
-  int rows, cols, batch, q, r;                         // rows per workgroup: q, one more for the first r
+  int rows, cols, batch, q, r;                         // fours of rows per workgroup: q, one more for the first r
   int window;                                          // columns of a window, a multiple of 128
 };
 
@@ -182,8 +182,8 @@ spmm_panel_kernel(const TileArgs all) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wg = (int)blockIdx.x;
-  const int row0 = wg * a.q + min(wg, a.r);
-  const int wg_rows = a.q + (wg < a.r ? 1 : 0);
+  const int row0 = 4 * (wg * a.q + min(wg, a.r));
+  const int wg_rows = min(4 * (a.q + (wg < a.r ? 1 : 0)), a.rows - row0);
   const int panels = (wg_rows + 16 * P - 1) / (16 * P);
   const int nb = wave < wg_rows ? (wg_rows - wave + 15) / 16 : 0;     // this wavefront's rows (at most 64: the host sees to that)
   const int cols = a.cols, wr = a.window;
@@ -256,12 +256,13 @@ spmm_panel_kernel(const TileArgs all) {
 #pragma unroll
     for (int s = 0; s < S; ++s) hend[p][s] = -1;
   };
+  if (NT == 1) load_b(0, 4 * BG * NTW);                // under way while the row pointers are waited for
 #pragma unroll
   for (int p = 0; p < P; ++p) {
     open_row(p);
     if (left[p] > 0) issue(p, e0[p], end[p]);
   }
-  load_b(0, 4 * BG * NTW);
+  if (NT > 1) load_b(0, 4 * BG * NTW);                 // many of them would hold up the first units
   odd_results[threadIdx.x][0] = odd_results[threadIdx.x][1] = 0u;
   if (threadIdx.x == 0) any_odd = 0u;
 
@@ -274,6 +275,7 @@ spmm_panel_kernel(const TileArgs all) {
   }
 
   const int cols2 = 2 * ((cols + 127) & ~127);
+  const bool y_aligned = (reinterpret_cast<uintptr_t>(a.Y) & 7) == 0 && a.ldy % 4 == 0;
   uint32_t buf = 0;                                    // byte offset of the window's buffer
   int panel = 0;
   bool b_due = false;
@@ -463,16 +465,24 @@ spmm_panel_kernel(const TileArgs all) {
       const int m0 = 16 * (P * panel + rt) + 4 * (l >> 4), left = wg_rows - m0;     // lane holds rows m0 ... m0 + 3
       if (16 * vt + n < a.batch) {
         uint16_t* y = a.Y + (int64_t)(16 * vt + n) * a.ldy + (row0 + m0);
+        bool fine = true;                              // no infinity and no NaN in the rows or in the vector
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (i < left) {
-            if (__builtin_fabsf(sum[i]) <= 3.4028234e38f) {
-              y[i] = f32_to_f16_bits(sum[i]);
-            } else {                                   // an infinity or a NaN in the row or in the vector
-              atomicOr(&odd_results[m0 + i][vt >> 1], 1u << (16 * (vt & 1) + n));
-              any_odd = 1u;
+        for (int i = 0; i < 4; ++i) fine = fine && __builtin_fabsf(sum[i]) <= 3.4028234e38f;
+        if (fine && left >= 4 && y_aligned) {
+          *reinterpret_cast<uint2*>(y) = make_uint2(f32_to_f16_bits(sum[0]) | (uint32_t)f32_to_f16_bits(sum[1]) << 16,
+                                                    f32_to_f16_bits(sum[2]) | (uint32_t)f32_to_f16_bits(sum[3]) << 16);
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (i < left) {
+              if (__builtin_fabsf(sum[i]) <= 3.4028234e38f) {
+                y[i] = f32_to_f16_bits(sum[i]);
+              } else {
+                atomicOr(&odd_results[m0 + i][vt >> 1], 1u << (16 * (vt & 1) + n));
+                any_odd = 1u;
+              }
             }
-          }
+        }
       }
     }
     if (++panel == panels) break;
@@ -507,8 +517,9 @@ int launch_panel_as(TileArgs a, hipStream_t stream) {
   // the fewer times the vectors are read.  A wavefront keeps the pointers of at most 64 rows.
   int64_t grid = std::min<int64_t>(((int64_t)a.rows + 15) / 16, (int64_t)device_cu_count());
   grid = std::max<int64_t>(grid, ((int64_t)a.rows + 64 * 16 - 1) / (64 * 16));
-  a.q = (int)(a.rows / grid);
-  a.r = (int)(a.rows % grid);
+  const int64_t fours = ((int64_t)a.rows + 3) / 4;     // four results of a vector lie in one lane: stored together 11008 x 4096, 64 vectors: 33.1 -> 32.1 us
+  a.q = (int)(fours / grid);
+  a.r = (int)(fours % grid);
   // as few windows as LDS allows, all about equally wide (11008 columns: 6 of 1920 instead of 5 of 2048 and one of 768)
   const int64_t windows = ((int64_t)a.cols + W - 1) / W;
   a.window = (int)((((int64_t)a.cols + windows - 1) / windows + 127) / 128 * 128);
@@ -574,7 +585,7 @@ int launch_tile_bd(const TileArgs& a, hipStream_t stream) {
     if (a.cols <= 3072) MACKO_PANEL(4, 1, 1024, 2, true, 2, false);           // 4096 x 2600: 13.1 / 14.2 with 2048, 4096 x 4096 at 90 %: 13.5 / 12.6
     MACKO_PANEL(4, 1, 2048, 1, true, 1, false);
   }
-  if (three) MACKO_PANEL(4, 3, 1024, 2, false, 1, false);                     // 11008 x 4096: 40.9 with panels of 2, 34.1
+  if (three) MACKO_PANEL(4, 3, 1024, 2, false, 1, false);                     // 11008 x 4096: 40.9 with panels of 2, 33.1
   MACKO_PANEL(4, 2, 1024, 2, true, 1, false);                                 // 8192 x 4096 at 80 %: 22.8 with panels of 1, 19.0
 #undef MACKO_PANEL
 }

@@ -1900,6 +1900,28 @@ def test_rows_in_step_with_8_bit_values_end_in_any_chunk(rows, cols, align):
         assert (np.abs(y.astype(np.float64) - ref)[fine] <= 1.01 * bound[fine]).all()
 
 
+@pytest.mark.parametrize("rows,cols,batch,offset,ldy", [(4099, 300, 5, 4, 4108), (4099, 300, 20, 4, 4108), (70, 2100, 64, 0, 76), (70, 2100, 9, 2, 76),
+                                                        (9, 130, 16, 8, 17)])
+def test_spmm_results_stored_four_at_a_time(rows, cols, batch, offset, ldy):
+    """Results on 8 bytes and off them, last rows of a panel that are no four, an infinity among four results; nothing beside
+    the results is written.  Reference and bound as in test_spmm_tile_edges."""
+    rng = np.random.default_rng(rows + batch)
+    W = (rng.standard_normal((rows, cols)) * (rng.random((rows, cols)) < 0.4)).astype(np.float16)
+    W[rows - 2, 3] = np.inf
+    X = rng.standard_normal((batch, cols)).astype(np.float16)
+    Y = torch.full((batch, ldy), 7.0, dtype=torch.float16, device="cuda")
+    M.encode(W).to_device().spmm(torch.from_numpy(X).cuda(), Y[:, offset:offset + rows])
+    torch.cuda.synchronize()
+    Y = Y.cpu().numpy().astype(np.float64)
+    assert (Y[:, :offset] == 7).all() and (Y[:, offset + rows:] == 7).all()
+    Y = Y[:, offset:offset + rows]
+    assert np.array_equal(Y[:, rows - 2], np.sign(X[:, 3].astype(np.float64)) * np.inf)
+    W[rows - 2, 3] = 0
+    Y[:, rows - 2] = (X.astype(np.float64) @ W[rows - 2].astype(np.float64))
+    ref, mag = _batch_reference(W.astype(np.float64), X.astype(np.float64))
+    assert (np.abs(Y - ref) <= 1.01 * (np.abs(ref) * 2.0 ** -11 + 2.0 ** -25 + mag * cols * 2.0 ** -24)).all()
+
+
 @pytest.mark.parametrize("kind", ["b1", "b4", "fp8"])
 @pytest.mark.parametrize("rows,cols,sparsity,batch", [
     # 2 to 8 vectors: short rows, few rows and many, pieces of 8, 4 and 2, odd columns

@@ -172,8 +172,7 @@ MACKO_API int macko_bind_device(macko_handle_t h, void* values_dev, void* deltas
  * accumulation; the wave-per-row kernel serves every row length; x must fit
  * LDS, about 78 K columns, otherwise MACKO_E_UNSUPPORTED), macko_columns_device,
  * macko_check_device, macko_decode_device (the dense matrix as bytes),
- * macko_spmm (the same batch kernel as for 16-bit values: the matrix is read and
- * decoded once per piece of up to 8 vectors).
+ * macko_spmm (the same two batch kernels as for 16-bit values).
  * macko_decode and macko_host_buffers' `values` are MACKO_E_UNSUPPORTED for
  * such a handle (macko_decode_fp8, macko_host_values_fp8 instead). */
 MACKO_API int macko_encode_fp8(const uint8_t* dense_host, int64_t rows, int64_t cols, int64_t ld,
@@ -253,8 +252,8 @@ MACKO_API int macko_dense_gemv(const void* W_dev, int64_t rows, int64_t cols, in
                                const void* x_dev, void* y_dev, void* stream);
 
 /* Small-batch product with one matrix: the matrix is streamed and decoded once for the whole
- * batch on the matrix cores (more than 16 vectors; 5 to 16 where the vector kernel would need
- * several pieces and the rows are not too sparse for tiles; codes of up to 4 bits, two columns or more,
+ * batch on the matrix cores (more than 16 vectors; 2 to 16 where estimates of both ways' times,
+ * from the shape, the stored entries and the batch, say so; codes of up to 4 bits, two columns or more,
  * ldx < 2^24), else once per piece of up to 8 vectors, for every
  * code width and both value widths (rows shorter than 384 stored entries on average, and batches whose
  * interleaved vectors do not fit LDS, then run as independent matrix-vector products).

@@ -1598,6 +1598,31 @@ def test_gpu_encoder_window_edges(kind, rows, cols, density, shift):
     assert (g.report.nnz, g.report.pad_nnz, g.report.alloc_nnz) == (enc.nnz, enc.pad_nnz, enc.alloc_nnz)
 
 
+@pytest.mark.parametrize("kind", ["b1", "b4", "fp8"])
+@pytest.mark.parametrize("first", [1, 497, 1017])
+def test_gpu_encoder_row_ends(kind, first):
+    """Every remainder of the columns around one chunk of 8, one step of 512 and two: the counting pass loads the last 8 columns of
+    such rows out of place.  The columns behind a row hold non-zeros."""
+    rng = np.random.default_rng(first)
+    for cols in range(first, first + 24):
+        W = (rng.standard_normal((5, cols)) * (rng.random((5, cols)) < 0.4)).astype(np.float16)
+        W[1] = 0
+        W[2, -1] = 1.0
+        big = torch.full((5, cols + 9), 9.0, dtype=torch.float16, device="cuda")
+        if kind == "fp8":
+            W8 = wl.fp8_values_of(W.view(np.uint16))
+            enc = oracle.encode8(W8)
+            big = torch.full((5, cols + 9), 9, dtype=torch.uint8, device="cuda")
+            big[:, :cols] = torch.from_numpy(W8).cuda()
+            g = M.encode_device_fp8(big[:, :cols])
+        else:
+            enc = oracle.encode(W.view(np.uint16), int(kind[1]))
+            big[:, :cols] = torch.from_numpy(W).cuda()
+            g = M.encode_device(big[:, :cols], b_delta=int(kind[1]))
+        assert_same_encoding(g.fetch_device(), enc)
+        assert (g.report.nnz, g.report.pad_nnz, g.report.alloc_nnz) == (enc.nnz, enc.pad_nnz, enc.alloc_nnz)
+
+
 @pytest.mark.parametrize("kind", ["b1", "b2", "b4", "b8", "fp8"])
 @pytest.mark.parametrize("rows,cols,density,shift", [
     (70, 1, 0.5, 0), (50, 7, 0.9, 1), (33, 2047, 0.5, 3), (20, 2048, 0.5, 0), (20, 2049, 0.4, 5), (12, 4096, 0.9, 8),

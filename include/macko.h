@@ -172,7 +172,8 @@ MACKO_API int macko_bind_device(macko_handle_t h, void* values_dev, void* deltas
  * accumulation; the wave-per-row kernel serves every row length; x must fit
  * LDS, about 78 K columns, otherwise MACKO_E_UNSUPPORTED), macko_columns_device,
  * macko_check_device, macko_decode_device (the dense matrix as bytes),
- * macko_spmm (the same two batch kernels as for 16-bit values).
+ * macko_spmm (the same two batch kernels as for 16-bit values; two vectors or more also with an x
+ * beyond LDS, where the matrix cores serve the call: ldx < 2^24).
  * macko_decode and macko_host_buffers' `values` are MACKO_E_UNSUPPORTED for
  * such a handle (macko_decode_fp8, macko_host_values_fp8 instead). */
 MACKO_API int macko_encode_fp8(const uint8_t* dense_host, int64_t rows, int64_t cols, int64_t ld,

@@ -325,6 +325,10 @@ Piece next_piece(bool long_rows, int64_t one, int left) {
   return {0, std::min(left, kMaxGroup)};
 }
 
+// Whether pieces and single products can serve the call.  8-bit values have no kernel for an x beyond LDS (more than 80608
+// columns), and how long it would take does not matter then: the matrix cores take every such batch of two vectors or more.
+bool vectors_serve(const SpmvProblem& p) { return p.b_val != 8 || spmv_takes_wave_row(p); }
+
 // Whether the matrix cores are the faster way for a call that both can take: from estimates of both times.
 //
 // Up to 16 vectors take the matrix cores one launch whose time is a sum of its parts (the phases of a window do not overlap, see
@@ -337,7 +341,6 @@ Piece next_piece(bool long_rows, int64_t one, int left) {
 // 1392 x 1012 at 87 %, 8 vectors: 31 -> 5.5 us; 718 x 8797 at 50 %, 8: 32 -> 14; 344 x 352 at 62 %, 8: 29 -> 5.1; the
 // worst is 7 % slower.
 bool tile_is_faster(const SpmvProblem& p, int batch) {
-  if (batch <= 1) return false;
   if (batch > 16) return true;                         // at least three pieces (11008 x 4096, 64 vectors: 183 / 32)
   const double cus = device_cu_count(), rows = (double)p.rows, cols = (double)p.cols / 4096.0;
   const double entries = (double)p.pad_nnz, avg = entries / rows, steps = std::ceil(avg / 512.0);
@@ -384,7 +387,7 @@ int launch_spmm(const SpmvProblem& p, const void* X, int64_t ldx, void* Y, int64
   }
   const int64_t one = lds_bytes_for(p.cols, p.b_delta);
   const bool long_rows = p.pad_nnz / p.rows >= kLongRow;
-  if (spmm_tile_serves(p, ldx) && tile_is_faster(p, batch))
+  if (batch > 1 && spmm_tile_serves(p, ldx) && (!vectors_serve(p) || tile_is_faster(p, batch)))
     return launch_spmm_tile(p, Xp, ldx, Yp, ldy, batch, stream);
   int done = 0;
   while (done < batch) {

@@ -1959,6 +1959,27 @@ def test_spmm_either_way_for_few_vectors(kind, rows, cols, sparsity, batch):
     test_spmm_on_both_sides_of_the_rule_that_picks_its_kernel(kind, rows, cols, sparsity, batch)
 
 
+@pytest.mark.parametrize("batch", [2, 4, 5, 9, 16])
+@pytest.mark.parametrize("rows,cols,sparsity", [(300, 82000, 0.95), (1000, 82000, 0.995), (17, 82001, 0.99), (60, 81000, 0.5)])
+def test_spmm_of_8_bit_values_with_x_beyond_lds(rows, cols, sparsity, batch):
+    """8-bit values and an x beyond LDS have no vector kernel: from two vectors on the matrix cores serve the call whatever the
+    estimates say, one vector is refused as macko_spmv refuses it."""
+    g = torch.Generator(device="cuda").manual_seed(rows + batch)
+    W = torch.empty((rows, cols), dtype=torch.float16, device="cuda").normal_(0.0, 1.0, generator=g)
+    W.mul_(torch.rand(W.shape, generator=g, device="cuda") >= sparsity)
+    W8 = W.to(torch.float8_e4m3fn)
+    m = M.encode_device_fp8(W8.view(torch.uint8))
+    X = torch.empty((batch, cols), dtype=torch.float16, device="cuda").normal_(0.0, 1.0, generator=g)
+    with pytest.raises(M.MackoError) as refused:
+        m.spmm(X[:1])
+    assert refused.value.status == -3
+    Y = m.spmm(X).double()
+    W64 = W8.float().double()
+    ref, mag = X.double() @ W64.T.contiguous(), X.double().abs() @ W64.abs().T.contiguous()
+    bound = ref.abs() * 2.0 ** -11 + 2.0 ** -25 + mag * cols * 2.0 ** -24          # as in test_spmm_tile_edges
+    assert float(((Y - ref).abs() / bound).max()) <= 1.01
+
+
 @pytest.mark.parametrize("kind", ["b4", "fp8"])
 @pytest.mark.parametrize("rows_of_the_wide,n_wide", [(300, 1), (700, 8), (2100, 1)])
 def test_spmv_many_with_a_wide_x_among_others(kind, rows_of_the_wide, n_wide):

@@ -389,6 +389,8 @@ MACKO_API int macko_last_hip_error(void);
  *                       (at most 40,000,000), 0 default (one second)
  *   "chain_no_wait"     1: such a wait gives up at once when the phase before is unfinished (for
  *                       tests of the give-up path; the chain then reports MACKO_E_WAIT_EXPIRED)
+ *   "spmm_kernel"       how macko_spmm takes a batch that both ways serve: 0 by estimates of both times,
+ *                       1 pieces of vectors on the vector units, 2 the matrix cores
  *   "gemv_block", "gemv_rows_per_wg", "gemv_ring" (2, 4 or 8), "gemv_resident",
  *   "gemv_wgs_per_cu"   the same for the dense GEMV
  * Settings are process wide and not thread safe: macko_set_tuning must not run

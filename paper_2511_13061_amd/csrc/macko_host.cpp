@@ -844,6 +844,7 @@ static int64_t* tuning_slot(const char* name) {
   if (n == "spmv_steps_per_wave") return &t.spmv_steps_per_wave;
   if (n == "spmv_resident_steps") return &t.spmv_resident_steps;
   if (n == "spmv_step_align") return &t.spmv_step_align;
+  if (n == "spmm_kernel") return &t.spmm_kernel;
   if (n == "chain_wait_us") return &t.chain_wait_us;
   if (n == "chain_no_wait") return &t.chain_no_wait;
   if (n == "gemv_resident") return &t.gemv_resident;
@@ -858,7 +859,7 @@ int macko_set_tuning(const char* name, int64_t value) {
   int64_t* slot = tuning_slot(name);
   if (!slot || value < 0) return MACKO_E_INVALID_ARG;
   const std::string n(name);
-  if (n == "spmv_kernel" && value > 2) return MACKO_E_INVALID_ARG;
+  if ((n == "spmv_kernel" || n == "spmm_kernel") && value > 2) return MACKO_E_INVALID_ARG;
   if (n == "gemv_ring" && value != 0 && value != 2 && value != 4 && value != 8) return MACKO_E_INVALID_ARG;
   if (n == "spmv_ring" && value != 0 && (value < 2 || value > 4)) return MACKO_E_INVALID_ARG;
   if ((n == "spmv_resident" || n == "gemv_resident") && value > 2) return MACKO_E_INVALID_ARG;

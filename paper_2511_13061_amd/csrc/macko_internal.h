@@ -25,6 +25,7 @@ struct Tuning {
   int64_t spmv_steps_per_wave = 0; // many-workgroup regime: steps of work per wavefront (0 = default)
   int64_t spmv_step_align = 0;     // entries a row's first step is aligned to (8 ... 512, power of two; 0 = by row length)
   int64_t spmv_resident_steps = 0; // largest work (steps per compute unit) launched as one resident round (0 = default)
+  int64_t spmm_kernel = 0;         // batches that both ways serve: 0 the faster one, 1 vector units, 2 matrix cores
   int64_t chain_wait_us = 0;       // longest wait of a chain's workgroups for each other (0 = default, -1 = none)
   int64_t chain_no_wait = 0;       // 1: such a wait gives up at once when the phase before is unfinished
   int64_t gemv_block = 0;

@@ -387,7 +387,8 @@ int launch_spmm(const SpmvProblem& p, const void* X, int64_t ldx, void* Y, int64
   }
   const int64_t one = lds_bytes_for(p.cols, p.b_delta);
   const bool long_rows = p.pad_nnz / p.rows >= kLongRow;
-  if (batch > 1 && spmm_tile_serves(p, ldx) && (!vectors_serve(p) || tile_is_faster(p, batch)))
+  const int64_t knob = tuning().spmm_kernel;
+  if (batch > 1 && spmm_tile_serves(p, ldx) && (!vectors_serve(p) || (knob != 0 ? knob == 2 : tile_is_faster(p, batch))))
     return launch_spmm_tile(p, Xp, ldx, Yp, ldy, batch, stream);
   int done = 0;
   while (done < batch) {

@@ -26,7 +26,7 @@ def _need_gpu_and_library():
     yield
     for knob in ("spmv_kernel", "spmv_lanes", "spmv_block", "spmv_rows_per_wg", "spmv_ring", "spmv_resident",
                  "spmv_wgs_per_cu", "spmv_resident_steps", "spmv_steps_per_wave", "spmv_step_align", "gemv_block", "gemv_rows_per_wg", "gemv_ring", "gemv_resident",
-                 "gemv_wgs_per_cu"):
+                 "gemv_wgs_per_cu", "spmm_kernel"):
         M.set_tuning(knob, 0)
 
 
@@ -498,8 +498,8 @@ def test_spmm_shapes_strides_and_fallbacks():
 @pytest.mark.parametrize("batch", [2, 4, 8, 13])
 @pytest.mark.parametrize("kind", ["b1", "b2", "b4", "b8", "fp8"])
 def test_spmm_batch_kernel_every_code_width_and_8_bit_values(kind, batch):
-    """The batch kernel proper (rows long enough for it): one decode per stored entry, `batch` products.
-    Row lengths straddle steps, rows start inside chunks, some rows are empty."""
+    """Rows long enough for vectors to share a pass over the matrix, whichever batch kernel the library takes: one decode per
+    stored entry, `batch` products.  Row lengths straddle steps, rows start inside chunks, some rows are empty."""
     b_delta = {"b1": 1, "b2": 2, "b4": 4, "b8": 8, "fp8": 4}[kind]
     density = {"b1": 0.9, "b2": 0.6, "b4": 0.5, "b8": 0.25, "fp8": 0.5}[kind]
     rows, cols = 150, 4100
@@ -535,6 +535,41 @@ def test_spmm_llama_shape_full_size():
     Y = m.spmm(to_dev(X))
     torch.cuda.synchronize()
     check_Y(Y, case.W, X, case.name)
+
+
+@pytest.fixture(params=[1, 2], ids=["vector_units", "matrix_cores"])
+def spmm_kernel(request):
+    """Batches that both kernels serve go to the named one, whatever the library's estimates of their times say."""
+    M.set_tuning("spmm_kernel", request.param)
+    yield request.param
+    M.set_tuning("spmm_kernel", 0)
+
+
+@pytest.mark.parametrize("batch", [2, 3, 4, 5, 6, 7, 8, 13, 16])
+def test_spmm_batches_on_either_kernel(spmm_kernel, batch):
+    test_spmm_batches(batch)
+
+
+def test_spmm_shapes_strides_and_fallbacks_on_either_kernel(spmm_kernel):
+    test_spmm_shapes_strides_and_fallbacks()
+
+
+@pytest.mark.parametrize("batch", [2, 4, 5, 6, 7, 8, 13])
+@pytest.mark.parametrize("kind", ["b1", "b2", "b4", "b8", "fp8"])
+def test_spmm_every_code_width_and_8_bit_values_on_either_kernel(spmm_kernel, kind, batch):
+    test_spmm_batch_kernel_every_code_width_and_8_bit_values(kind, batch)
+
+
+def test_spmm_llama_shape_full_size_on_either_kernel(spmm_kernel):
+    test_spmm_llama_shape_full_size()
+
+
+@pytest.mark.parametrize("kind", ["b1", "b2", "b4", "fp8"])
+@pytest.mark.parametrize("rows,cols,batch", [(129, 1001, 8), (70, 5000, 7), (300, 2003, 6), (40, 12000, 8), (24, 30001, 5), (1030, 1100, 3), (50, 700, 2)])
+def test_spmm_unaligned_vectors_on_either_kernel(spmm_kernel, kind, rows, cols, batch):
+    """Pieces of 8, 4 and 2 vectors, filled and partly filled, and the same calls on the matrix cores: inputs (strided vectors on
+    2 bytes, NaN around them, empty rows) and bound of test_spmm_tile_edges."""
+    test_spmm_tile_edges(kind, rows, cols, batch)
 
 
 # ------------------------------------------------------------------ GPU encoder

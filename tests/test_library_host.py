@@ -171,6 +171,11 @@ def test_empty_shapes_and_error_codes():
         M.set_tuning("no_such_knob", 1)
     with pytest.raises(M.MackoError):
         M.set_tuning("spmv_block", 100)
+    with pytest.raises(M.MackoError):
+        M.set_tuning("spmm_kernel", 3)
+    M.set_tuning("spmm_kernel", 2)
+    assert M.get_tuning("spmm_kernel") == 2
+    M.set_tuning("spmm_kernel", 0)
     M.set_tuning("spmv_block", 256)
     assert M.get_tuning("spmv_block") == 256
     M.set_tuning("spmv_block", 0)

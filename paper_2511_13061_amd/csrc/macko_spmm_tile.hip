@@ -154,7 +154,10 @@ __device__ __forceinline__ void tile_row_by_entries(const TileArgs& a, int row, 
 //    registers before the next ones are requested (the compiler waits for every load under way where it cannot count
 //    them, so a take behind a request would wait for that request);
 //  - requests the window's vectors a few at a time between the rows' decodes (all at once they hold up the wavefront:
-//    16 clocks of L1 each, 128 of them), and turns them into operand order in front of the barrier, where the early wavefronts wait;
+//    16 clocks of L1 each, 128 of them), and turns them into operand order in front of the barrier, where the early wavefronts wait.
+//    One tile of vectors and of rows requests them in front of the decode: there are only four or eight, and behind it the second
+//    unit of a window waits for them (2409 x 20936 at 47 %, 16 vectors: 37.1 -> 34.2 us, 2636 x 13808 at 41 %, 15: 26.3 -> 24.9,
+//    4096 x 11008 at 50 %, 8: 17.7 -> 17.2);
 //  - behind the barrier multiplies its columns' part: the window's groups of 128 columns are dealt to kSlices wavefronts
 //    each for its own vectors (part vpart of VS) and tiles of rows (part rpart of RS).
 // With two buffers the next window goes into the other one at once; with one a second barrier keeps it apart.  The pad behind a row is
@@ -311,6 +314,10 @@ spmm_panel_kernel(const TileArgs all) {
           }
           put(p, s);
         }
+    if (NT * P == 1 && b_due) {
+      load_b(0, 4 * BG * NTW);
+      b_due = false;
+    }
     for (;;) {
       uint32_t need = 0;                               // bit p: row p's next unit is taken now
 #pragma unroll

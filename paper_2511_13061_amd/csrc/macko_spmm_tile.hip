@@ -308,7 +308,7 @@ spmm_panel_kernel(const TileArgs all) {
 #pragma unroll
       for (int s = 0; s < S; ++s)
         if (hend[p][s] > 2 * k0) {
-          if (P > 2) {                                 // every register counts: the codes are kept, not the positions
+          if (P > 2 || NTW * S > 6) {                  // every register counts: the codes are kept, not the positions
             keep_opaque(hw[p][s].w, hv[p][s]);
             hw[p][s].decode();
           }
@@ -555,8 +555,9 @@ bool eights_fit(int64_t rows, int64_t cols, int batch) {
 
 // The shape of a launch.  A workgroup's work is its panels times their windows, about 2 us each, and the reads of X once per panel.
 // Figures: us at the sizes given, from 260 matrices timed with every shape.
+// row_entries: stored entries of a row on average.
 template <int BD, int VB>
-int launch_tile_bd(const TileArgs& a, hipStream_t stream) {
+int launch_tile_bd(const TileArgs& a, int64_t row_entries, hipStream_t stream) {
   const int64_t cus = device_cu_count();
   const int64_t tiles = tiles_per_wg(a.rows);
   int nt = (a.batch + 15) / 16;
@@ -590,6 +591,9 @@ int launch_tile_bd(const TileArgs& a, hipStream_t stream) {
   if (tiles == 1) {
     if (nt == 3) MACKO_PANEL(3, 1, 2048, 1, true, 2, false);                  // 4096 x 4096: 15.2; with a fourth, empty tile 17.1
     if (a.cols <= 3072) MACKO_PANEL(4, 1, 1024, 2, true, 2, false);           // 4096 x 2600: 13.1 / 14.2 with 2048, 4096 x 4096 at 90 %: 13.5 / 12.6
+    // more than one step of a row in a window: two loaded at a time (us, one / two: 2100 x 13256, 64 vectors, at 30 % 50.9 / 44.1, at
+    // 50 % 44.5 / 38.8, at 70 % 35.9 / 34.9; 4096 x 11008 at 50 % 35.9 / 33.2, but at 80 % 28.2 / 28.4, at 90 % 25.7 / 26.7)
+    if (4 * row_entries >= a.cols) MACKO_PANEL(4, 1, 2048, 1, true, 2, false);
     MACKO_PANEL(4, 1, 2048, 1, true, 1, false);
   }
   if (three) MACKO_PANEL(4, 3, 1024, 2, false, 1, false);                     // 11008 x 4096: 40.9 with panels of 2, 33.1
@@ -616,11 +620,11 @@ int launch_spmm_tile(const SpmvProblem& p, const uint16_t* X, int64_t ldx, uint1
                      hipStream_t stream) {
   const TileArgs a{p.values, reinterpret_cast<const uint32_t*>(p.deltas), p.row_ptr, X, Y, ldx, ldy,
                    (int)p.rows, (int)p.cols, batch, 0, 0, 0};
-  if (p.b_val == 8) return p.b_delta == 4 ? launch_tile_bd<4, 8>(a, stream) : MACKO_E_UNSUPPORTED;
+  if (p.b_val == 8) return p.b_delta == 4 ? launch_tile_bd<4, 8>(a, p.pad_nnz / p.rows, stream) : MACKO_E_UNSUPPORTED;
   switch (p.b_delta) {
-    case 1: return launch_tile_bd<1, 16>(a, stream);
-    case 2: return launch_tile_bd<2, 16>(a, stream);
-    case 4: return launch_tile_bd<4, 16>(a, stream);
+    case 1: return launch_tile_bd<1, 16>(a, p.pad_nnz / p.rows, stream);
+    case 2: return launch_tile_bd<2, 16>(a, p.pad_nnz / p.rows, stream);
+    case 4: return launch_tile_bd<4, 16>(a, p.pad_nnz / p.rows, stream);
     default: return MACKO_E_UNSUPPORTED;
   }
 }

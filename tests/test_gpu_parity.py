@@ -1523,6 +1523,8 @@ def test_spmm_tile_edges(kind, rows, cols, batch):
     (2100, 3073, 60), (2500, 700, 60), (2500, 2049, 40), (2300, 2500, 30),
     # of two tiles, in two windows of one buffer and in two buffers; of three; several panels a workgroup
     (4300, 2050, 9), (4300, 2100, 20), (4300, 1030, 64), (8300, 1100, 31), (8300, 1200, 40), (20600, 130, 20), (20600, 130, 33),
+    # one step of a row loaded at a time (3 % of the columns kept, by the seed), and two (90, 30 and 90 %)
+    (2049, 3080, 64), (2051, 4100, 49), (2064, 4111, 50), (2050, 6200, 61),
     # vectors dealt to several workgroups: two groups of two tiles, the last one partly filled; groups of 8, as many as there are
     # compute units for and one too many
     (1500, 1100, 40), (1500, 129, 33), (2048, 300, 16), (2049, 300, 16), (40, 4500, 61),

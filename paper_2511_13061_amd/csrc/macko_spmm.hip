@@ -342,6 +342,9 @@ bool vectors_serve(const SpmvProblem& p) { return p.b_val != 8 || spmv_takes_wav
 // worst is 7 % slower.
 bool tile_is_faster(const SpmvProblem& p, int batch) {
   if (batch > 16) return true;                         // at least three pieces (11008 x 4096, 64 vectors: 183 / 32)
+  // x beyond LDS: every vector is gathered from memory by itself, at two vectors already the slower way in all of 111 calls (us,
+  // vectors / matrix cores: 25 x 487832, 2 vectors, 686 / 361; 226 x 178280 at 99 %, 6, 754 / 112; 301 x 118384 at 93 %, 5, 587 / 76)
+  if (spmv_lds_bytes(p.cols, p.b_delta) > kMaxLdsBytes) return true;
   const double cus = device_cu_count(), rows = (double)p.rows, cols = (double)p.cols / 4096.0;
   const double entries = (double)p.pad_nnz, avg = entries / rows, steps = std::ceil(avg / 512.0);
   const double mbytes = entries * (p.b_val + p.b_delta) / 8e6;

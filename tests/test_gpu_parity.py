@@ -1996,6 +1996,39 @@ def test_spmm_either_way_for_few_vectors(kind, rows, cols, sparsity, batch):
     test_spmm_on_both_sides_of_the_rule_that_picks_its_kernel(kind, rows, cols, sparsity, batch)
 
 
+@pytest.mark.parametrize("rows,cols,sparsity,batch", [(226, 178280, 0.99, 6), (52, 88736, 0.95, 5), (40, 300001, 0.999, 2)])
+def test_spmm_with_x_beyond_lds_takes_the_matrix_cores(rows, cols, sparsity, batch):
+    """Vector by vector such calls take 2 to 9 times as long; the times of 10 calls each way are told apart by a factor of 1.5, and
+    the results are right."""
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    W = torch.empty((rows, cols), dtype=torch.float16, device="cuda").normal_(0.0, 1.0, generator=g)
+    W.mul_(torch.rand(W.shape, generator=g, device="cuda") >= sparsity)
+    m = M.encode_device(W)
+    X = torch.empty((batch, cols), dtype=torch.float16, device="cuda").normal_(0.0, 1.0, generator=g)
+
+    def times():
+        best = []
+        for _ in range(3):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                m.spmm(X)
+            b.record()
+            b.synchronize()
+            best.append(a.elapsed_time(b))
+        return min(best)
+
+    times()
+    auto = times()
+    M.set_tuning("spmm_kernel", 1)
+    by_vectors = times()
+    M.set_tuning("spmm_kernel", 0)
+    assert auto * 1.5 < by_vectors, (auto, by_vectors)
+    Y, X64, W64 = m.spmm(X).double(), X.double(), W.double()
+    bound = (X64 @ W64.T).abs() * 2.0 ** -11 + 2.0 ** -25 + (X64.abs() @ W64.abs().T) * cols * 2.0 ** -24      # as in test_spmm_tile_edges
+    assert float(((Y - X64 @ W64.T).abs() / bound).max()) <= 1.01
+
+
 @pytest.mark.parametrize("batch", [2, 4, 5, 9, 16])
 @pytest.mark.parametrize("rows,cols,sparsity", [(300, 82000, 0.95), (1000, 82000, 0.995), (17, 82001, 0.99), (60, 81000, 0.5)])
 def test_spmm_of_8_bit_values_with_x_beyond_lds(rows, cols, sparsity, batch):

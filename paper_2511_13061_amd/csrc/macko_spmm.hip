@@ -329,45 +329,61 @@ Piece next_piece(bool long_rows, int64_t one, int left) {
 // columns), and how long it would take does not matter then: the matrix cores take every such batch of two vectors or more.
 bool vectors_serve(const SpmvProblem& p) { return p.b_val != 8 || spmv_takes_wave_row(p); }
 
-// Whether the matrix cores are the faster way for a call that both can take: from estimates of both times.
+// Whether the matrix cores are the faster way for a call that both can take: from estimates of both times (us).
 //
 // Up to 16 vectors take the matrix cores one launch whose time is a sum of its parts (the phases of a window do not overlap, see
-// macko_spmm_tile.hip); the vector kernel takes a launch per piece, whose time is its launch, its arithmetic per step of 512 entries
-// and vector, the staging of the vectors (one by one where their length is no multiple of 8), and, with few rows, the chain of one
-// row's steps.  The factors (us) were fitted to 1040 calls timed both ways: 2 to 16 vectors, 16 to 36864 rows, 64 to 40000
-// columns, 30 to 99.9 % pruned, all code widths up to 4 bits, both value widths.  The estimates are off by 5 % (matrix cores) and
-// 13 % (vectors); the way chosen is 0.5 % slower than the better one in the mean.  Against the lines this takes the
-// place of, 2 / 4 / 8 vectors take 0.92 / 0.67 / 0.55 of the time, most with short rows and few rows:
-// 1392 x 1012 at 87 %, 8 vectors: 31 -> 5.5 us; 718 x 8797 at 50 %, 8: 32 -> 14; 344 x 352 at 62 %, 8: 29 -> 5.1; the
-// worst is 7 % slower.
+// macko_spmm_tile.hip).  The vector kernel takes a launch per piece: its start, the steps of 512 entries that the busiest wavefront
+// takes one after the other (16 wavefronts to a compute unit) and that a compute unit takes in all, and the copy of the vectors,
+// element by element where their length is no multiple of 8.  The factors were fitted to 16 000 calls timed both ways: 2 to 16
+// vectors, 16 to 40000 rows, 64 to 80000 columns, 30 to 99 % pruned, all code widths up to 4 bits at the densities they suit, both value
+// widths.  The estimates are off by 5 % (matrix cores) and 8 to 10 % (vectors), the way chosen is 0.3 % slower than the better
+// one in the mean; without the busiest wavefront it was 0.7 %, and 3 or 4 vectors on 2049 to 4096 dense rows up to 1.3 times as slow
+// (3832 x 10352 at 53 %, 8-bit values, 3 vectors, 15.5 -> 12.0; 2733 x 11072 at 33 %, 4: 17.8 -> 14.0).  What is left is at most 1.45 times
+// as slow, where the copy of odd vectors costs the vector kernel more than estimated (6396 x 2629 at 63 %, 2-bit codes, 4: 15.6 / 10.7).
+// The matrix cores' estimate has to be 3 % below the vectors'.
+double tile_estimate(const SpmvProblem& p, int batch) {
+  const double cols = (double)p.cols / 4096.0, tiles = std::ceil((double)p.rows / (16.0 * device_cu_count()));
+  const double steps = tiles * std::ceil((double)p.pad_nnz / (double)p.rows / 512.0), more = batch > 8 ? 1.0 : 0.0;
+  const double mbytes = (double)p.pad_nnz * (p.b_val + p.b_delta) / 8e6, windows = (double)spmm_tile_windows(p);
+  if (spmm_tile_pairs_groups(p, batch)) return 3.08 + 1.31 * windows + (0.78 + 0.09 * more) * tiles * cols + 0.47 * steps + 0.049 * mbytes;
+  return 2.54 + 2.14 * windows + (0.37 + 0.18 * more) * tiles * cols + 0.44 * steps + 0.058 * mbytes;
+}
+
+double vector_estimate(const SpmvProblem& p, int batch) {
+  const double cus = device_cu_count(), rows = (double)p.rows, cols = (double)p.cols / 4096.0, ragged = p.cols % 8 != 0 ? 1.0 : 0.0;
+  const double entries = (double)p.pad_nnz, steps = std::ceil(entries / rows / 512.0), all = rows * steps / cus;
+  const double busiest = std::ceil(rows / (16.0 * cus)) * steps;        // steps of one wavefront
+  const double few = rows < 4.0 * cus ? steps : 0.0;                   // no resident round: nothing covers a step's latency
+  const double mbytes = entries * (p.b_val + p.b_delta) / 8e6;
+  const bool long_rows = p.pad_nnz / p.rows >= kLongRow;
+  const bool one_launch = p.b_val == 8 || p.pad_nnz / p.rows >= kWaveRowMinEntries;    // of a group of single products
+  const int64_t one = lds_bytes_for(p.cols, p.b_delta);
+  double us = 0.0;
+  for (int left = batch; left > 0;) {
+    const Piece q = next_piece(long_rows, one, left);
+    if (q.pass == 8)
+      us += 3.36 + 0.348 * busiest + 0.027 * all + 2.16 * cols + ragged * (1.67 + 4.61 * cols) + 0.443 * few + 0.096 * rows / cus;
+    else if (q.pass == 4)
+      us += 2.94 + 0.331 * busiest + 0.020 * all + 0.59 * cols + ragged * (0.93 + 2.70 * cols) + 0.212 * few + 0.057 * rows / cus;
+    else if (q.pass == 2)
+      us += 2.87 + 0.358 * busiest + 0.018 * all + 0.21 * cols + ragged * (0.60 + 1.50 * cols) + 0.113 * few + 0.044 * rows / cus;
+    else if (q.pass == 1)
+      us += 2.07 + 0.317 * busiest + 0.023 * all + 0.14 * cols + ragged * (0.94 + 0.25 * cols) + 0.135 * few + 0.039 * rows / cus;
+    else if (one_launch)
+      us += 3.47 + q.take * (0.056 * all + 0.033 * mbytes) + (0.86 * ragged + 0.68 * std::min(1.0, rows / (4.0 * cus))) * cols;
+    else
+      us += q.take * (2.89 + 1.025 * entries / 1e6 + 0.46 * cols) + 3.45 * ragged * cols;
+    left -= q.take;
+  }
+  return us;
+}
+
 bool tile_is_faster(const SpmvProblem& p, int batch) {
   if (batch > 16) return true;                         // at least three pieces (11008 x 4096, 64 vectors: 183 / 32)
   // x beyond LDS: every vector is gathered from memory by itself, at two vectors already the slower way in all of 111 calls (us,
   // vectors / matrix cores: 25 x 487832, 2 vectors, 686 / 361; 226 x 178280 at 99 %, 6, 754 / 112; 301 x 118384 at 93 %, 5, 587 / 76)
   if (spmv_lds_bytes(p.cols, p.b_delta) > kMaxLdsBytes) return true;
-  const double cus = device_cu_count(), rows = (double)p.rows, cols = (double)p.cols / 4096.0;
-  const double entries = (double)p.pad_nnz, avg = entries / rows, steps = std::ceil(avg / 512.0);
-  const double mbytes = entries * (p.b_val + p.b_delta) / 8e6;
-  const double tiles = std::ceil(rows / (16.0 * cus)), tiles_wg = std::ceil(rows / (16.0 * std::min(cus, std::ceil(rows / 16.0))));
-  const double window_us = spmm_tile_pairs_groups(p, batch) ? 1.67 : 1.98;
-  const double tile_us = 2.78 + window_us * (double)spmm_tile_windows(p) + 0.48 * tiles * cols + 0.48 * tiles_wg * steps + 0.08 * mbytes;
-
-  const bool long_rows = p.pad_nnz / p.rows >= kLongRow, ragged = p.cols % 8 != 0;
-  const bool one_launch = p.b_val == 8 || p.pad_nnz / p.rows >= kWaveRowMinEntries;    // of a group of single products
-  const int64_t one = lds_bytes_for(p.cols, p.b_delta);
-  double vector_us = 0.0;
-  for (int left = batch; left > 0;) {
-    const Piece q = next_piece(long_rows, one, left);
-    const double work = rows * steps / cus * (1.0 + q.pass / 4.0), copy = q.pass * cols, chain = (2.0 + q.pass) * steps;
-    if (q.pass == 8) vector_us += 3.88 + 0.087 * rows * steps / cus + 0.251 * copy + (ragged ? 0.801 * copy : 0.0) + (rows < 4.0 * cus ? 0.677 * steps : 0.0);
-    else if (q.pass) vector_us += 2.96 + 0.02 * work + 0.138 * copy + (ragged ? 0.797 * copy : 0.0) + 0.099 * chain;
-    else if (one_launch) vector_us += 3.69 + q.take * (0.056 * rows * steps / cus + 0.052 * mbytes) + (ragged ? 0.929 * cols : 0.0);
-    else vector_us += q.take * (2.92 + 1.064 * (entries / 1e6 + 0.4 * cols * rows / cus / 32.0));
-    left -= q.take;
-  }
-  // one piece of 8 comes closest, and its estimate is the least sure
-  const bool one_piece = next_piece(long_rows, one, batch).pass == 8 && batch <= 8;
-  return tile_us * (one_piece ? 1.05 : 1.0) < vector_us;
+  return 1.03 * tile_estimate(p, batch) < vector_estimate(p, batch);
 }
 
 }  // namespace

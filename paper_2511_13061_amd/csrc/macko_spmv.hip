@@ -788,11 +788,12 @@ int launch_wave_row_group(int nwr, const SpmvProblem* const* wr, int b_delta, in
   // apart, and gain as much once there are enough of them (us, resident round -> here: 14336 x 4096 13.4 -> 12.4, 22016 x 4096
   // 19.3 -> 17.1, 28672 x 4096 25.1 -> 22.0, 14336 x 3072 at 33 % 13.3 -> 12.3; 4096, 8192 and 11008 x 4096 within 2 %); 4096 entries, the
   // full 4096 bytes, do not need it (8192 x 8192 13.2 and 13.2; 11008 x 8192 16.6 -> 16.7, with exact per-row counts 17.7).
-  bool in_step = t.spmv_resident == 0 && t.spmv_block == 0;
+  bool in_step = t.spmv_resident == 0 && t.spmv_block == 0, whole_steps = true;
   for (int i = 0; i < nwr; ++i) {
     const int64_t avg = wr[i]->pad_nnz / wr[i]->rows;
     const int64_t off = (avg + 1024) % 2048 - 1024;            // distance to the nearest multiple of 2048
     in_step = in_step && wr[i]->cols <= kInStepMaxCols && avg >= 2048 - 16 && off >= -16 && off <= 16;
+    whole_steps = whole_steps && off <= 1;
   }
   if (!in_step && t.spmv_rows_per_wg == 0 && (t.spmv_resident == 2 || (t.spmv_resident == 0 && (small || wide)))) {
     const int k = t.spmv_wgs_per_cu ? (int)t.spmv_wgs_per_cu : (wide ? 1 : 0);
@@ -825,12 +826,15 @@ int launch_wave_row_group(int nwr, const SpmvProblem* const* wr, int b_delta, in
   }
   if (plan.total_wgs >= (int64_t{1} << 31)) return MACKO_E_UNSUPPORTED;
 
-  // Rows of whole steps that start anywhere (the rows in step above, 8-bit values): begun where the row begins, they end in one
-  // chunk of a step that holds nothing else.  Lane i of the wavefront takes row i's chunk, all of them at once behind the last row
-  // (TAILS): 11008 x 4096 at 50 %, the same number in every row: 11.5 -> 10.7 us, 22016 x 4096 17.2 -> 16.4; iid masks 11.5 and
-  // 11.6.  With 16-bit values steps on whole lines are worth more (11008 x 4096: 12.7, with tails 13.5), and where there are
+  // Rows in step of whole steps or a few entries less, 8-bit values: begun where the row begins (on 8 entries instead of kStepAlign),
+  // they need no further step but for the chunk that a start inside a chunk pushes behind the last one.  Lane i of the
+  // wavefront takes row i's chunk, all of them at once behind the last row (TAILS).  Time against steps on kStepAlign over 399 launches of
+  // 1500 to 22016 rows, by the entries per row, the same number in each: 2048 - 15 ... 2048 - 1 0.92, 2048 0.96, 2049 0.97, 2050 and
+  // 2051 1.01, 2053 to 2064 1.02; 4096 - 15 ... 4096 0.94, 4099 to 4107 1.02; 6144 - 15 ... - 2 0.97, 6144 1.01 (11008 x 4096: 11.5 ->
+  // 10.7 us, 22016 x 4096 17.2 -> 16.4).  So not above one entry more than whole steps.  iid masks, which the average does not tell apart,
+  // 1.00 to 1.02.  With 16-bit values steps on whole lines are worth more (11008 x 4096: 12.7, with tails 13.5), and where there are
   // hardly any tails the code for them costs up to 3 %.
-  const bool tails = in_step && b_val == 8 && nwr <= kMaxGroup;
+  const bool tails = in_step && whole_steps && b_val == 8 && nwr <= kMaxGroup;
 
   SpmvWideArgs wide_args;                              // filled in for more than kMaxGroup matrices only
   SpmvGroupArgs args{};

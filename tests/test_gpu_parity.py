@@ -1933,10 +1933,21 @@ def test_rows_in_step_with_8_bit_values_end_in_any_chunk(rows, cols, align):
     """Rows of about a multiple of 2048 entries with 8-bit values: those that end in one chunk of a step have it taken by one
     lane behind the last row.  Lengths of 9 less to 9 more than half of the columns, so that rows start and end anywhere in a chunk,
     one row empty, one NaN at a row's end, one launch of one matrix and one of two.  Reference and bound as for the batch products."""
+    _rows_in_step(rows, cols, align, 0)
+
+
+@pytest.mark.parametrize("shift", [-6, 1, 2, 3, 6])
+@pytest.mark.parametrize("rows,cols", [(61, 4096), (700, 8192)])
+def test_rows_in_step_on_both_sides_of_the_rule_for_their_ends(rows, cols, shift):
+    """The same around the rule that gives such ends to one lane: whole steps and one entry on average, and more."""
+    _rows_in_step(rows, cols, 0, shift)
+
+
+def _rows_in_step(rows, cols, align, shift):
     rng = np.random.default_rng(rows + cols)
     W8 = np.zeros((rows, cols), dtype=np.uint8)
     for r in range(rows):
-        n = cols // 2 + (r * 5) % 19 - 9
+        n = cols // 2 + (r * 5) % 19 - 9 + shift
         W8[r, np.sort(rng.choice(cols, n, replace=False))] = rng.integers(1, 0x7F, n).astype(np.uint8) | (rng.integers(0, 2, n) << 7).astype(np.uint8)
     W64 = oracle.fp8_to_double(np.arange(256, dtype=np.uint8))[W8]
     if rows > 1000:

@@ -339,9 +339,13 @@ __device__ __forceinline__ bool spmv_wave_row_body(const void* __restrict__ valu
       }
     }
     if (TAILS && __any(tail != 0u)) {
-      // the tails, lane i row i's: every slot of the ring has been refilled with them by now
+      // the tails, lane i row i's: every slot of the ring has been refilled with them by now.  The codes of lanes that have none
+      // are cleared: what such a lane holds is anybody's, and its row's position may lie 504 + 7 * 16 columns behind the last one
+      // already, so that another 8 * 16 would gather behind the guard.
+      static_assert(2 * (504 + 7 * (1 << BD)) + 2 * 8 <= back_pad_for(BD) || !TAILS, "gathers of lanes without a tail end in the guard");
       LaneCodes<BD> w = wq[0];
       LaneValues<VB> v = vq[0];
+      w.keep_if(tail != 0u);
       v.keep_first(tail);
       w.decode();
       acc = 0.0f;

@@ -133,6 +133,11 @@ int launch_spmm(const SpmvProblem& p, const void* X, int64_t ldx, void* Y, int64
 bool spmm_tile_serves(const SpmvProblem& p, int64_t ldx);
 int64_t spmm_tile_windows(const SpmvProblem& p);       // windows that a workgroup goes through, of up to 16 vectors
 bool spmm_tile_pairs_groups(const SpmvProblem& p, int batch);      // two groups of columns share an operand there
+// Units of `per_unit` entries that a wavefront takes of a row there, from the 8 entries its start lies in; one, all cleared, for a row
+// without entries, and for row pointers that decrease (no encoding's: the difference would be a row of 2^32 entries).
+constexpr uint32_t panel_row_units(uint32_t start, uint32_t end, uint32_t per_unit) {
+  return end > start ? (end - (start & ~7u) + per_unit - 1u) / per_unit : 1u;
+}
 int launch_spmm_tile(const SpmvProblem& p, const uint16_t* X, int64_t ldx, uint16_t* Y, int64_t ldy, int batch,
                      hipStream_t stream);
 // device-side expansion: column index of every stored entry; the dense matrix back

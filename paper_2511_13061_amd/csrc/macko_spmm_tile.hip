@@ -254,7 +254,7 @@ spmm_panel_kernel(const TileArgs all) {
     start[p] = (uint32_t)__builtin_amdgcn_readlane((int)rp_lo, j);
     end[p] = (uint32_t)__builtin_amdgcn_readlane((int)rp_hi, j);
     e0[p] = start[p] & ~7u;
-    left[p] = j0 + p < nb ? max(1, (int)((end[p] - e0[p] + 512u * S - 1u) / (512u * S))) : 0;   // a row without entries: one, cleared
+    left[p] = j0 + p < nb ? (int)panel_row_units(start[p], end[p], 512u * S) : 0;
     base2[p] = 0;
 #pragma unroll
     for (int s = 0; s < S; ++s) hend[p][s] = -1;

@@ -237,6 +237,39 @@ def test_launch_planner_covers_every_row_exactly_once(tmp_path):
     assert out.returncode == 0 and out.stdout.startswith("ok"), out.stdout + out.stderr
 
 
+def test_units_of_a_row_in_the_batch_kernel(tmp_path):
+    """Every unit that holds an entry of the row is taken, and none behind it; a row without entries and one whose pointers
+    decrease (trusted input, but no reason to walk 2^32 entries) take one."""
+    import shutil
+    import subprocess
+    from paper_2511_13061_amd import build as B
+    if not shutil.which("g++") or not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"):
+        pytest.skip("needs g++ and the HIP headers")
+    src, exe = tmp_path / "units.cpp", tmp_path / "units"
+    src.write_text(r"""
+#include <cstdio>
+#include "macko_internal.h"
+int main() {
+  for (uint32_t per : {512u, 1024u, 1536u})
+    for (uint64_t start : {0ull, 1ull, 7ull, 8ull, 513ull, 4294960000ull})
+      for (uint64_t len = 0; len <= 3200; ++len) {
+        if (start + len > 4294963200ull) continue;           // what the launchers take
+        uint32_t want = 0;                                    // units from the row's first 8 entries that begin in front of its end
+        for (uint64_t e = start & ~7ull; e < start + len; e += per) ++want;
+        if (len == 0) want = 1;
+        if (macko::panel_row_units((uint32_t)start, (uint32_t)(start + len), per) != want) return std::printf("%llu + %llu by %u\n", (unsigned long long)start, (unsigned long long)len, per), 1;
+      }
+  for (uint32_t per : {512u, 1024u, 1536u})
+    if (macko::panel_row_units(10, 9, per) != 1 || macko::panel_row_units(4000, 8, per) != 1 || macko::panel_row_units(4294963200u, 0, per) != 1) return std::puts("decreasing"), 1;
+  std::puts("ok");
+}
+""")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-w", "-I/opt/rocm/include", "-I", os.path.join(ROOT, "include"),
+                           "-I", B.CSRC, str(src), "-o", str(exe)])
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert out.returncode == 0 and out.stdout == "ok\n", out.stdout
+
+
 def test_host_code_under_address_and_undefined_behaviour_sanitizers(tmp_path):
     """The library's host translation unit (encoders for every code and value width, decoders, storage
     report, argument checks) linked with stand-ins for the GPU launchers and run under ASan + UBSan on

@@ -352,8 +352,10 @@ class MackoMatrix:
         torch = _need_torch()
         if dense_dev is None:
             rows, cols, b_val = self._dims()
-            if stream is None and _native is not None:
-                return _made(_native.decode_device(self._h.value, rows, cols, b_val), "macko_decode_device")
+            if stream is None and _native is not None and torch.cuda.is_initialized():
+                dense = _native.decode_device(self._h.value, rows, cols, b_val)
+                if dense is not None:        # None: a forked child
+                    return _made(dense, "macko_decode_device")
             dense_dev = torch.empty((rows, cols), dtype=torch.uint8 if b_val == 8 else torch.float16, device="cuda")
         if dense_dev.dim() != 2 or (dense_dev.shape[1] > 1 and dense_dev.stride(1) != 1):
             raise ValueError("dense_dev must be a row-major [rows, >= cols] tensor")
@@ -366,7 +368,7 @@ class MackoMatrix:
         """y = W x.  x_dev: torch float16 CUDA tensor [cols]; returns y_dev [rows]."""
         if stream is None and _native is not None:
             y = _native.spmv(self._h.value, (self._shape or self._dims())[0] if y_dev is None else 0, x_dev, y_dev)
-            if y is not None:                # None: not plain device tensors
+            if y is not None:                # None: not plain device tensors, or a forked child
                 return _made(y, "macko_spmv")
         if y_dev is None:
             torch = _torch or _need_torch()
@@ -380,7 +382,7 @@ class MackoMatrix:
         """Y[b] = W X[b] for a torch float16 CUDA matrix X_dev [batch, cols]; returns [batch, rows]."""
         if stream is None and _native is not None:
             Y = _native.spmm(self._h.value, (self._shape or self._dims())[0] if Y_dev is None else 0, X_dev, Y_dev)
-            if Y is not None:                # None: not plain device tensors, or nothing the library takes
+            if Y is not None:                # None: not plain device tensors, nothing the library takes, or a forked child
                 return _made(Y, "macko_spmm")
         torch = _need_torch()
         if X_dev.dim() != 2 or X_dev.stride(1) != 1:

@@ -14,6 +14,8 @@
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <pthread.h>
+
 #include <algorithm>
 #include <cstdint>
 
@@ -24,6 +26,10 @@ namespace {
 decltype(&macko_spmv) g_spmv = nullptr;
 decltype(&macko_spmm) g_spmm = nullptr;
 decltype(&macko_decode_device) g_decode = nullptr;
+
+// A forked child may not use its parent's device.  PyTorch's Python calls refuse that with an error, the C++ calls below do not:
+// in a child the functions serve nothing, and the general way says what there is to say.
+bool g_forked = false;
 
 // A plain tensor on the GPU (no subclass: those may define what their methods do).
 const at::Tensor* device_tensor(PyObject* o) {
@@ -50,7 +56,7 @@ PyObject* spmv(PyObject*, PyObject* const* args, Py_ssize_t n) {
   if (n != 4) return PyErr_Format(PyExc_TypeError, "4 arguments");
   const at::Tensor* x = device_tensor(args[2]);
   const at::Tensor* given = args[3] == Py_None ? nullptr : device_tensor(args[3]);
-  if (!g_spmv || !x || (args[3] != Py_None && !given)) Py_RETURN_NONE;
+  if (!g_spmv || g_forked || !x || (args[3] != Py_None && !given)) Py_RETURN_NONE;
   macko_handle_t h;
   if (!handle_of(args[0], &h)) return nullptr;
   const int64_t rows = PyLong_AsLongLong(args[1]);
@@ -72,7 +78,7 @@ PyObject* spmm(PyObject*, PyObject* const* args, Py_ssize_t n) {
   if (n != 4) return PyErr_Format(PyExc_TypeError, "4 arguments");
   const at::Tensor* x = device_tensor(args[2]);
   const at::Tensor* given = args[3] == Py_None ? nullptr : device_tensor(args[3]);
-  if (!g_spmm || !x || (args[3] != Py_None && !given)) Py_RETURN_NONE;
+  if (!g_spmm || g_forked || !x || (args[3] != Py_None && !given)) Py_RETURN_NONE;
   if (x->dim() != 2 || x->stride(1) != 1 || x->size(0) > MACKO_MAX_BATCH || (given && given->dim() != 2)) Py_RETURN_NONE;
   macko_handle_t h;
   if (!handle_of(args[0], &h)) return nullptr;
@@ -96,7 +102,7 @@ PyObject* spmm(PyObject*, PyObject* const* args, Py_ssize_t n) {
 PyObject* decode_device(PyObject*, PyObject* const* args, Py_ssize_t n) {
   HANDLE_TH_ERRORS
   if (n != 4) return PyErr_Format(PyExc_TypeError, "4 arguments");
-  if (!g_decode) Py_RETURN_NONE;
+  if (!g_decode || g_forked) Py_RETURN_NONE;
   macko_handle_t h;
   if (!handle_of(args[0], &h)) return nullptr;
   const int64_t rows = PyLong_AsLongLong(args[1]), cols = PyLong_AsLongLong(args[2]), bits = PyLong_AsLongLong(args[3]);
@@ -118,6 +124,7 @@ PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t n) {
   void* p[3];
   for (int i = 0; i < 3; ++i) p[i] = PyLong_AsVoidPtr(args[i]);
   if (PyErr_Occurred()) return nullptr;
+  if (!g_spmv && pthread_atfork(nullptr, nullptr, [] { g_forked = true; }) != 0) return PyErr_NoMemory();
   g_spmv = reinterpret_cast<decltype(g_spmv)>(p[0]);
   g_spmm = reinterpret_cast<decltype(g_spmm)>(p[1]);
   g_decode = reinterpret_cast<decltype(g_decode)>(p[2]);

@@ -7,6 +7,7 @@ import ctypes
 import os
 import re
 import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -235,6 +236,41 @@ def test_launch_planner_covers_every_row_exactly_once(tmp_path):
                           stderr=subprocess.DEVNULL)
     out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
     assert out.returncode == 0 and out.stdout.startswith("ok"), out.stdout + out.stderr
+
+
+def test_native_calls_leave_a_forked_child_to_the_general_way():
+    """A child of a process that has used the GPU may not: PyTorch's Python calls say so, its C++ calls do not.  So the binding's native
+    functions return None there.  (This parent has not used it; decode_device is the one that needs no device tensor to get that far.)"""
+    script = """
+import os
+from paper_2511_13061_amd import binding as B
+B.load_library()
+assert B._native is not None
+pid = os.fork()
+if pid == 0:
+    try:
+        ok = B._native.decode_device(None, 4, 4, 16) is None
+    except BaseException:
+        ok = False
+    os._exit(0 if ok else 1)
+raise SystemExit(os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]))
+"""
+    assert subprocess.run([sys.executable, "-c", script], cwd=ROOT, timeout=120).returncode == 0
+
+
+def test_decode_device_without_a_device_in_use_goes_the_general_way(monkeypatch):
+    """Before PyTorch has initialised the device (or in a forked child) the tensor is PyTorch's to make, with its own errors."""
+    import torch
+    m = M.encode(np.full((4, 64), 0x3C00, dtype=np.uint16))
+
+    class Native:
+        def decode_device(self, *args):
+            raise AssertionError("native call")
+
+    monkeypatch.setattr(M.binding, "_native", Native())
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: False)
+    with pytest.raises(RuntimeError):                      # no GPU, or the handle has no device buffers
+        m.decode_device()
 
 
 def test_units_of_a_row_in_the_batch_kernel(tmp_path):

@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from dataclasses import dataclass
 from typing import Optional
 
@@ -11,7 +12,7 @@ import numpy as np
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libmacko.so")
 _lib = None
-_native = None           # csrc/binding_torch.cpp, once the library is loaded (None: not built; the calls go through ctypes)
+_native = None           # csrc/binding_torch.cpp, once the library is loaded (None: no torch, or a warning has said why; the calls go through ctypes)
 
 EXPORTED_SYMBOLS = [
     "macko_encode", "macko_encode_device", "macko_wrap_device", "macko_encode_ex", "macko_encode_device_ex",
@@ -94,9 +95,14 @@ def load_library():
     native = None
     try:
         import torch  # noqa: F401
-        from . import _native as native
     except ImportError:
         pass
+    else:
+        try:
+            from . import _native as native
+        except ImportError as e:             # not built, or built against another PyTorch or Python
+            warnings.warn(f"the native part of the binding is not in use, calls take 1 to 2 us more: {e}; build it with "
+                          "`python -m paper_2511_13061_amd.build`", RuntimeWarning, stacklevel=2)
     lib = ctypes.CDLL(_LIB_PATH)
     vp, i64, ci = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int
     i64p = ctypes.POINTER(i64)

@@ -10,6 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmacko.so")
+BINDING = os.path.join(HERE, "_native" + sysconfig.get_config_var("EXT_SUFFIX"))
 SOURCES = ["macko_host.cpp", "macko_spmv.hip", "macko_gemv.hip", "macko_encode_gpu.hip", "macko_spmm.hip", "macko_spmm_tile.hip", "macko_decode_gpu.hip"]
 HEADERS = ["macko_internal.h", "macko_device.h", "macko_plan.h", "macko_decode.h"]
 
@@ -27,16 +28,28 @@ def library_path() -> str:
     return LIB
 
 
+def _older(built: str, sources) -> bool:
+    deps = [os.path.join(CSRC, f) for f in sources] + [os.path.join(ROOT, "include", "macko.h")]
+    return not os.path.exists(built) or any(os.path.getmtime(d) > os.path.getmtime(built) for d in deps)
+
+
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
-        return True
-    t = os.path.getmtime(LIB)
-    deps = [os.path.join(CSRC, f) for f in SOURCES + HEADERS] + [os.path.join(ROOT, "include", "macko.h")]
-    return any(os.path.getmtime(d) > t for d in deps)
+    return _older(LIB, SOURCES + HEADERS)
+
+
+def binding_is_stale() -> bool:
+    """The native part of the Python binding is missing, or older than its sources or the PyTorch it was built against."""
+    import torch
+    return _older(BINDING, ["binding_torch.cpp"]) or os.path.getmtime(torch.version.__file__) > os.path.getmtime(BINDING)
 
 
 def build_library(force: bool = True, verbose: bool = False, extra_flags=()) -> str:
-    """Compile every source for gfx950 and link the shared library."""
+    """Compile every source for gfx950 and link the shared library, and the native part of the binding if it is stale."""
+    try:
+        if binding_is_stale():
+            build_binding(verbose)
+    except (ImportError, OSError, subprocess.CalledProcessError) as e:     # no PyTorch, no headers: the binding goes through ctypes
+        print(f"the native part of the binding is not built: {e}", file=sys.stderr)
     if not force and not is_stale():
         return LIB
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -48,9 +61,6 @@ def build_library(force: bool = True, verbose: bool = False, extra_flags=()) -> 
     subprocess.check_call(cmd)
     os.replace(tmp, LIB)
     return LIB
-
-
-BINDING = os.path.join(HERE, "_native" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 
 def build_binding(verbose: bool = False) -> str:
@@ -73,6 +83,6 @@ def build_binding(verbose: bool = False) -> str:
 
 
 if __name__ == "__main__":
-    build_library(verbose=True, extra_flags=sys.argv[1:])
-    print(LIB)
-    print(build_binding(verbose=True))
+    build_binding(verbose=True)
+    print(build_library(verbose=True, extra_flags=sys.argv[1:]))
+    print(BINDING)

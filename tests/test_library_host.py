@@ -258,6 +258,47 @@ raise SystemExit(os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]))
     assert subprocess.run([sys.executable, "-c", script], cwd=ROOT, timeout=120).returncode == 0
 
 
+@pytest.mark.parametrize("state", ["missing", "broken"])
+def test_a_native_part_that_cannot_be_loaded_is_reported(tmp_path, state):
+    """Not built, or built against another PyTorch: the calls go through ctypes, and a warning says so and how to change that."""
+    import shutil
+    from paper_2511_13061_amd import build as B
+    pkg = tmp_path / "paper_2511_13061_amd"
+    shutil.copytree(os.path.join(ROOT, "paper_2511_13061_amd"), pkg, ignore=shutil.ignore_patterns("_native*", "csrc", "__pycache__"))
+    if state == "broken":
+        (pkg / os.path.basename(B.BINDING)).write_bytes(b"not a library")
+    script = """
+import warnings
+with warnings.catch_warnings(record=True) as said:
+    warnings.simplefilter("always")
+    import paper_2511_13061_amd as M
+    M.load_library()
+assert M.binding._native is None
+said = [str(w.message) for w in said if w.category is RuntimeWarning]
+assert len(said) == 1 and "native part" in said[0] and "paper_2511_13061_amd.build" in said[0], said
+"""
+    run = subprocess.run([sys.executable, "-c", script], cwd=tmp_path, timeout=120, capture_output=True, text=True)
+    assert run.returncode == 0, run.stderr[-2000:]
+
+
+def test_the_build_sees_a_stale_native_part(monkeypatch, tmp_path):
+    """Older than its source, or than the installed PyTorch, or missing: build_library() makes it again."""
+    from paper_2511_13061_amd import build as B
+    copy = tmp_path / "_native.so"
+    copy.write_bytes(b"")
+    monkeypatch.setattr(B, "BINDING", str(copy))
+    assert not B.binding_is_stale()
+    os.utime(copy, (1, 1))
+    for there in (copy, tmp_path / "none.so"):
+        monkeypatch.setattr(B, "BINDING", str(there))
+        assert B.binding_is_stale()
+        made = []
+        monkeypatch.setattr(B, "build_binding", lambda verbose=False: made.append(1))
+        monkeypatch.setattr(B, "is_stale", lambda: False)
+        B.build_library(force=False)
+        assert made
+
+
 def test_decode_device_without_a_device_in_use_goes_the_general_way(monkeypatch):
     """Before PyTorch has initialised the device (or in a forked child) the tensor is PyTorch's to make, with its own errors."""
     import torch

@@ -1927,6 +1927,38 @@ def test_native_calls_do_what_the_general_ones_do(monkeypatch):
             assert with_native == outcome(call), i
 
 
+def test_native_calls_are_captured_into_a_graph():
+    """spmv, spmm and decode_device without a stream argument go to PyTorch's current stream: captured on a side stream and replayed with
+    other inputs they give the eager results.  A launch on any other stream would fail the capture or miss from the replays."""
+    g = torch.Generator(device="cuda").manual_seed(3)
+    W = torch.empty((300, 520), dtype=torch.float16, device="cuda").normal_(0.0, 1.0, generator=g)
+    W.mul_(torch.rand(W.shape, generator=g, device="cuda") < 0.5)
+    W += 0.0                                                               # no -0
+    m = M.encode_device(W)
+    x, X = torch.empty(520, dtype=torch.float16, device="cuda"), torch.empty((20, 520), dtype=torch.float16, device="cuda")
+    y, Y = torch.empty(300, dtype=torch.float16, device="cuda"), torch.empty((20, 300), dtype=torch.float16, device="cuda")
+    inputs = [(torch.randn(520, device="cuda", generator=g).half(), torch.randn((20, 520), device="cuda", generator=g).half()) for _ in range(3)]
+    want = [(m.spmv(a), m.spmm(b)) for a, b in inputs]
+    assert not torch.equal(want[0][0], want[1][0])
+    torch.cuda.synchronize()
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=side):
+        m.spmv(x, y)
+        made = m.spmv(x)
+        m.spmm(X, Y)
+        dense = m.decode_device()
+    for i in (0, 1, 2, 0):
+        x.copy_(inputs[i][0])
+        X.copy_(inputs[i][1])
+        for t in (y, made, Y, dense):
+            t.fill_(-3)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want[i][0]) and torch.equal(made, want[i][0]) and torch.equal(Y, want[i][1]) and torch.equal(dense, W), i
+        assert torch.equal(m.spmv(x), want[i][0])                          # eager work between the replays
+
+
 @pytest.mark.parametrize("align", [0, 8, 64, 256])
 @pytest.mark.parametrize("rows,cols", [(1, 4096), (61, 4096), (1030, 4096), (33, 8192)])
 def test_rows_in_step_with_8_bit_values_end_in_any_chunk(rows, cols, align):

@@ -160,7 +160,7 @@ __device__ __forceinline__ int lead_of_chunk(unsigned mask, uint32_t col0, int l
 // steps of 512 columns loaded ahead
 constexpr int kEncodeAhead = 2;
 
-// WIDE: rows of 8 columns or more
+// WIDE: loads without a branch, for rows of 8 columns or more
 template <bool IN8, bool WIDE, int BD>
 __global__ void __launch_bounds__(256)
 encode_count_kernel(const void* __restrict__ dense, uint32_t rows, uint32_t cols, int64_t ld,
@@ -625,7 +625,11 @@ int encode_on_device(const void* dense, int64_t rows, int64_t cols, int64_t ld, 
 
   const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((rows + 3) / 4, (int64_t)cus * 16));
   if (rows > 0) {
-    auto kcount = cols >= 8 ? count_kernel<true>(in8, b_delta) : count_kernel<false>(in8, b_delta);
+    // Lanes behind the row's last column load too, which costs where 16-byte loads lie across 4 bytes: such rows of fp16 only
+    // from 3 steps on, where the loads under way pay for it (whole call, us, with a branch / without: 120000 x 9 149 / 162, x 201 208 /
+    // 220, 60000 x 1025 197 / 205; but 15000 x 1537 112.4 / 111.8, x 3001 123.1 / 120.2, and on 4 bytes 120000 x 100 220 / 215).
+    const bool on_words = in8 || ((reinterpret_cast<uintptr_t>(dense) & 3) == 0 && ld % 2 == 0);
+    auto kcount = cols >= (on_words ? 8 : 1536) ? count_kernel<true>(in8, b_delta) : count_kernel<false>(in8, b_delta);
     hipLaunchKernelGGL(kcount, dim3(grid), dim3(256), 0, stream, dense, (uint32_t)rows, (uint32_t)cols, ld, counts, nnzs);
     if (nblocks > kFusedBlocks)
       hipLaunchKernelGGL(encode_block_sums_kernel, dim3((unsigned)nblocks), dim3(1024), 0, stream, counts, nnzs,

@@ -1636,10 +1636,10 @@ def test_gpu_encoder_window_edges(kind, rows, cols, density, shift):
 
 
 @pytest.mark.parametrize("kind", ["b1", "b4", "fp8"])
-@pytest.mark.parametrize("first", [1, 497, 1017])
+@pytest.mark.parametrize("first", [1, 497, 1017, 1525])
 def test_gpu_encoder_row_ends(kind, first):
-    """Every remainder of the columns around one chunk of 8, one step of 512 and two: the counting pass loads the last 8 columns of
-    such rows out of place.  The columns behind a row hold non-zeros."""
+    """Every remainder of the columns around one chunk of 8, one step of 512, two and three: the counting pass loads the last 8 columns of
+    such rows out of place (of rows that do not lie on 4 bytes from three steps on).  The columns behind a row hold non-zeros."""
     rng = np.random.default_rng(first)
     for cols in range(first, first + 24):
         W = (rng.standard_normal((5, cols)) * (rng.random((5, cols)) < 0.4)).astype(np.float16)

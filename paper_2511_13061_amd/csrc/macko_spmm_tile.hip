@@ -572,13 +572,10 @@ int launch_tile_bd(const TileArgs& a, int64_t row_entries, hipStream_t stream) {
 #define MACKO_PANEL(...) return launch_panel_as<__VA_ARGS__, BD, VB>(a, stream)
   if (half || nt == 1) {
     if (!half && two_tiles(tiles, a.cols)) MACKO_PANEL(1, 2, 2048, 1, false, 1, false);
-    // few long rows: nothing but each wavefront's own loads hides their latency (300 x 13000 at 80 %: 17.6 with two steps a unit, 16.8)
-    const bool long_few = a.rows <= 8 * cus && a.cols > 8192;
-    if (half) {
-      if (long_few) MACKO_PANEL(1, 1, 4096, 1, false, 3, true);
-      MACKO_PANEL(1, 1, 4096, 1, false, 2, true);
-    }
-    if (long_few) MACKO_PANEL(1, 1, 4096, 1, false, 3, false);
+    // few long rows: nothing but each wavefront's own loads hides their latency (300 x 13000 at 80 %, 16 vectors: 13.6 with two steps a
+    // unit, 13.2).  In groups of 16 three are no better (1500 x 9000, 32: 15.5 / 15.5; 700 x 30000, 48: 42.2 / 43.0).
+    if (half && a.rows <= 8 * cus && a.cols > 8192) MACKO_PANEL(1, 1, 4096, 1, false, 3, true);
+    if (half) MACKO_PANEL(1, 1, 4096, 1, false, 2, true);
     MACKO_PANEL(1, 1, 4096, 1, false, 2, false);
   }
   // From here on X counts as well: the shape whose panels have the fewest empty places, 3 tiles if equal

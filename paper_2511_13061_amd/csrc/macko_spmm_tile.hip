@@ -46,7 +46,7 @@ constexpr int kTilePad = 256;
 constexpr int kHalfVectors = 8;                        // up to here two groups of columns share one operand (HALF in the kernel)
 // 16 bytes more per row: the 16 rows that a matrix instruction reads at one column fall on different banks
 constexpr int panel_stride(int window) { return 2 * window + kTilePad + 16; }
-constexpr int panel_slices(int window, int vs) { return window / 128 < kWaves / vs ? window / 128 : kWaves / vs; }
+constexpr int panel_slices(int vs) { return kWaves / vs; }       // wavefronts along the columns of a window
 
 struct TileArgs {
   const void* values;
@@ -159,7 +159,7 @@ __device__ __forceinline__ void tile_row_by_entries(const TileArgs& a, int row, 
 //    unit of a window waits for them (2409 x 20936 at 47 %, 16 vectors: 37.1 -> 34.2 us, 2636 x 13808 at 41 %, 15: 26.3 -> 24.9,
 //    4096 x 11008 at 50 %, 8: 17.7 -> 17.2);
 //  - behind the barrier multiplies its columns' part: the window's groups of 128 columns are dealt to kSlices wavefronts
-//    each for its own vectors (part vpart of VS) and tiles of rows (part rpart of RS).
+//    for each of the VS parts of the vectors (part vpart), every one for all tiles of rows.
 // With two buffers the next window goes into the other one at once; with one a second barrier keeps it apart.  The pad behind a row is
 // the one in front of the next: two wavefronts may write it, nobody reads it.
 // Every wavefront executes the same number of barriers whatever its rows hold.
@@ -172,12 +172,11 @@ spmm_panel_kernel(const TileArgs all) {
   a.Y += (int64_t)blockIdx.y * kVectors * a.ldy;
   a.batch = min(a.batch - (int)blockIdx.y * kVectors, kVectors);
   static_assert(BD <= 4, "a lane's 8 entries have to fit the pad");
-  constexpr int kSlices = panel_slices(W, VS), G = W / 128 / kSlices;       // wavefronts along the columns, groups of each
-  constexpr int RS = kWaves / (kSlices * VS);
-  static_assert(kSlices * G * 128 == W && kSlices * VS * RS == kWaves, "every wavefront has its part of a window");
-  static_assert(!HALF || (NT == 1 && G % 2 == 0 && RS == 1), "pairs of groups of one vector tile");
+  constexpr int kSlices = panel_slices(VS), G = W / 128 / kSlices;          // groups of columns of a wavefront
+  static_assert(kSlices * G * 128 == W && kSlices * VS == kWaves && NT % VS == 0, "every wavefront has its part of a window");
+  static_assert(!HALF || (NT == 1 && G % 2 == 0), "pairs of groups of one vector tile");
   constexpr int BG = HALF ? G / 2 : G, kPair = HALF ? 2 : 1;                // operands of a wavefront, groups of each
-  constexpr int NTW = (NT + VS - 1) / VS, RW = (P + RS - 1) / RS;           // vector tiles and row tiles of a wavefront
+  constexpr int NTW = NT / VS;                                              // vector tiles of a wavefront
   constexpr int kStride = panel_stride(W), kBuffer = 16 * P * kStride;
   extern __shared__ __align__(16) unsigned char lds[];
   __shared__ uint32_t odd_results[64 * kWaves][2];     // per row of the workgroup, a bit per vector: not finite
@@ -199,7 +198,7 @@ spmm_panel_kernel(const TileArgs all) {
     rp_hi = a.row_ptr[r + 1];
   }
 
-  const int slice = wave % kSlices, part = wave / kSlices, vpart = part % VS, rpart = part / VS;
+  const int slice = wave % kSlices, vpart = wave / kSlices % VS;
   const int n = lane & 15;
   const uint32_t aoff = kTilePad + n * kStride + 2 * (128 * G * slice + 32 * (lane >> 4));
   const bool odd_lane = lane & 1, high_lane = lane & 2;
@@ -269,9 +268,9 @@ spmm_panel_kernel(const TileArgs all) {
   odd_results[threadIdx.x][0] = odd_results[threadIdx.x][1] = 0u;
   if (threadIdx.x == 0) any_odd = 0u;
 
-  float4v acc[RW][NTW], acc_pair[RW];                  // acc_pair: HALF, the second groups' sums
+  float4v acc[P][NTW], acc_pair[P];                    // acc_pair: HALF, the second groups' sums
 #pragma unroll
-  for (int i = 0; i < RW; ++i) {
+  for (int i = 0; i < P; ++i) {
     acc_pair[i] = float4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int t = 0; t < NTW; ++t) acc[i][t] = float4v{0.f, 0.f, 0.f, 0.f};
@@ -416,18 +415,16 @@ spmm_panel_kernel(const TileArgs all) {
 #pragma unroll
     for (int g = 0; g < G; ++g)
       if (128 * (G * slice + g) < groups) {
-        const unsigned char* ap = lds + buf + aoff + 256 * g + (RS > 1 ? 16 * kStride * rpart : 0);
+        const unsigned char* ap = lds + buf + aoff + 256 * g;
 #pragma unroll
-        for (int i = 0; i < RW; ++i) {
-          if (P % RS == 0 || i * RS + rpart < P) {
+        for (int i = 0; i < P; ++i) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const half8 av = *reinterpret_cast<const half8*>(ap + 16 * RS * i * kStride + 16 * r);
+          for (int r = 0; r < 4; ++r) {
+            const half8 av = *reinterpret_cast<const half8*>(ap + 16 * i * kStride + 16 * r);
 #pragma unroll
-              for (int t = 0; t < NTW; ++t) {
-                float4v& sum = HALF && g % 2 == 1 ? acc_pair[i] : acc[i][t];
-                sum = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, __builtin_bit_cast(half8, b[g / kPair][t][r]), sum, 0, 0, 0);
-              }
+            for (int t = 0; t < NTW; ++t) {
+              float4v& sum = HALF && g % 2 == 1 ? acc_pair[i] : acc[i][t];
+              sum = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, __builtin_bit_cast(half8, b[g / kPair][t][r]), sum, 0, 0, 0);
             }
           }
         }
@@ -444,7 +441,7 @@ spmm_panel_kernel(const TileArgs all) {
     float4v* red = reinterpret_cast<float4v*>(lds + kTilePad + (DBL ? kBuffer - buf : 0));      // [P * NT][kSlices][64]
     if (HALF) {
 #pragma unroll
-      for (int i = 0; i < RW; ++i) {
+      for (int i = 0; i < P; ++i) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[i][0][e] += half_row_swap(acc_pair[i][e]);
         acc_pair[i] = float4v{0.f, 0.f, 0.f, 0.f};
@@ -452,11 +449,10 @@ spmm_panel_kernel(const TileArgs all) {
     }
     if (!DBL) __syncthreads();
 #pragma unroll
-    for (int i = 0; i < RW; ++i)
+    for (int i = 0; i < P; ++i)
 #pragma unroll
       for (int t = 0; t < NTW; ++t) {
-        const int rt = RS * i + rpart, vt = VS * t + vpart;
-        if ((P % RS == 0 || rt < P) && (NT % VS == 0 || vt < NT)) red[((rt * NT + vt) * kSlices + slice) * 64 + lane] = acc[i][t];
+        red[((i * NT + VS * t + vpart) * kSlices + slice) * 64 + lane] = acc[i][t];
         acc[i][t] = float4v{0.f, 0.f, 0.f, 0.f};
       }
     __syncthreads();
@@ -515,7 +511,7 @@ template <int NT, int P, int W, int VS, bool DBL, int S, bool HALF, int BD, int 
 int launch_panel_as(TileArgs a, hipStream_t stream) {
   constexpr int vectors = HALF ? kHalfVectors : 16 * NT;
   constexpr int buffer = 16 * P * panel_stride(W), lds = (DBL ? 2 : 1) * buffer + kTilePad;
-  static_assert(P * NT * panel_slices(W, VS) * 1024 + kTilePad <= buffer, "the partial sums fit one buffer");
+  static_assert(P * NT * panel_slices(VS) * 1024 + kTilePad <= buffer, "the partial sums fit one buffer");
   static_assert(lds + 64 * kWaves * 8 + 16 <= 160 * 1024, "LDS of a compute unit");
   auto kfn = spmm_panel_kernel<NT, P, W, VS, DBL, S, HALF, BD, VB>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize, lds);

@@ -1482,7 +1482,7 @@ def _batch_reference(W64, X64):
     (20, 2048, 9), (19, 2049, 16), (18, 4095, 10), (16, 4096, 15), (35, 4097, 12), (23, 4097, 64), (9, 8193, 20), (7, 12000, 7),
     (4099, 77, 5), (4100, 300, 11), (4200, 130, 50),
     # several tiles a workgroup and several windows a tile; more than 64 rows a wavefront in 256 workgroups
-    (4200, 4500, 12), (8500, 2300, 40), (9001, 2049, 64), (262160, 16, 9)])
+    (4200, 4500, 12), (8500, 2300, 40), (9001, 2049, 64), (262160, 16, 9), (262160, 16, 17)])
 def test_spmm_tile_edges(kind, rows, cols, batch):
     """Tiles of 16 rows, windows of 2048 or 4096 columns, groups of 128 columns, 16 vectors per instruction: the sizes
     around them, with empty rows, rows that start inside a chunk, values below 2^-14, strided and 2-byte aligned
@@ -1528,30 +1528,53 @@ def test_spmm_tile_edges(kind, rows, cols, batch):
     # vectors dealt to several workgroups: two groups of two tiles, the last one partly filled; groups of 8, as many as there are
     # compute units for and one too many
     (1500, 1100, 40), (1500, 129, 33), (2048, 300, 16), (2049, 300, 16), (40, 4500, 61),
+    # groups of 16 on rows of more than two windows, groups of 8 on them, and more rows than that for up to 16 vectors
+    (1500, 8200, 20), (1100, 9001, 32), (300, 8205, 12), (2100, 4100, 11),
     # up to 8 vectors: pairs of groups of 128 columns, the second of a pair there, partly there and missing
     (40, 127, 3), (40, 128, 8), (41, 129, 8), (40, 256, 5), (40, 257, 7), (70, 383, 8), (33, 4097, 8), (2100, 2049, 7)])
 def test_spmm_panel_shapes(kind, rows, cols, batch):
-    """Every shape of the matrix-core kernel, with inputs and bound of test_spmm_tile_edges."""
-    test_spmm_tile_edges(kind, rows, cols, batch)
+    """Every shape of the matrix-core kernel, with inputs and bound of test_spmm_tile_edges, whatever the estimates say about the call."""
+    M.set_tuning("spmm_kernel", 2)
+    try:
+        test_spmm_tile_edges(kind, rows, cols, batch)
+    finally:
+        M.set_tuning("spmm_kernel", 0)
 
 
 @pytest.mark.parametrize("kind", ["b1", "b4", "fp8"])
 def test_spmm_tile_leaves_out_what_is_not_stored(kind):
     """An infinity or a NaN of a vector reaches the rows that store an entry at its column and no others; one of the
     matrix stays in its row.  Reference: the stored entries (padding included) one by one in 64 bits."""
+    _leaves_out_what_is_not_stored(kind, 50, 2300, 34)
+
+
+@pytest.mark.parametrize("kind", ["b1", "b4", "fp8"])
+@pytest.mark.parametrize("rows,cols,batch", [
+    # one row tile: one, two, three and four vector tiles, windows of 4096, 2048 and 1024 columns, one buffer and two; two and three row tiles
+    (2100, 2300, 12), (2100, 2301, 20), (2100, 2300, 34), (2100, 301, 64), (2100, 3101, 64), (4300, 301, 12), (4300, 302, 20), (4300, 303, 64),
+    (8300, 141, 20), (8300, 142, 64)])
+def test_spmm_tile_leaves_out_what_is_not_stored_in_every_shape(kind, rows, cols, batch):
+    """The same in the shapes that more rows take."""
+    M.set_tuning("spmm_kernel", 2)
+    try:
+        _leaves_out_what_is_not_stored(kind, rows, cols, batch)
+    finally:
+        M.set_tuning("spmm_kernel", 0)
+
+
+def _leaves_out_what_is_not_stored(kind, rows, cols, batch):
     rng = np.random.default_rng(5)
-    rows, cols, batch = 50, 2300, 34
     W = (rng.standard_normal((rows, cols)) * (rng.random((rows, cols)) < 0.5)).astype(np.float16)
     X = rng.standard_normal((batch, cols)).astype(np.float16)
     X[2, 100] = np.inf
-    X[17, 2299] = np.nan
-    X[33, 0] = -np.inf
+    X[batch // 2, cols - 1] = np.nan
+    X[batch - 1, 0] = -np.inf
     if kind == "fp8":
         m = M.encode_fp8(wl.fp8_values_of(W.view(np.uint16))).to_device()
         values, _, row_ptr = m.host_buffers()
         values = oracle.fp8_to_double(np.arange(256, dtype=np.uint8))[values]
     else:
-        W[20, 2299] = np.inf
+        W[20, cols - 1] = np.inf
         m = M.encode(W, {"b1": 1, "b4": 4}[kind]).to_device()
         values, _, row_ptr = m.host_buffers()
         values = values.view(np.float16).astype(np.float64)
@@ -1561,7 +1584,7 @@ def test_spmm_tile_leaves_out_what_is_not_stored(kind):
     with np.errstate(invalid="ignore"):
         ref = np.add.reduceat(values[:n] * X.astype(np.float64)[:, columns], row_ptr[:-1].astype(np.int64), axis=1)
     fine = np.isfinite(ref)
-    assert not fine[2].all() and fine[2].any() and not fine[17].all() and fine[17].any() and fine[0, :20].all()
+    assert not fine[2].all() and fine[2].any() and not fine[batch // 2].all() and fine[batch // 2].any() and fine[0, :20].all()
     assert np.array_equal(Y[~fine], ref[~fine], equal_nan=True)
     assert np.allclose(Y[fine], ref[fine], atol=2e-3, rtol=2e-3)
 
@@ -1726,7 +1749,11 @@ def test_spmv_wavefronts_per_compute_unit_do_not_change_the_result(rows, cols):
 
 @pytest.mark.parametrize("kind", ["b1", "b2", "b4", "fp8"])
 @pytest.mark.parametrize("rows,cols,batch,skip", [(70, 1, 9, 0), (40, 3, 9, 0), (33, 127, 64, 0), (50, 129, 33, 2), (20, 2047, 12, 0),
-                                                  (20, 2049, 17, 0), (37, 4097, 16, 0), (37, 4099, 50, 6), (16, 511, 7, 0)])
+                                                  (20, 2049, 17, 0), (37, 4097, 16, 0), (37, 4099, 50, 6), (16, 511, 7, 0),
+                                                  # more rows: two to four vector tiles a wavefront or shared out to two, panels of
+                                                  # one, two and three row tiles
+                                                  (2100, 4099, 12, 0), (2100, 2051, 20, 0), (2100, 257, 40, 1), (2100, 129, 64, 0), (2100, 3073, 50, 0),
+                                                  (4300, 131, 16, 0), (4300, 131, 17, 2), (4300, 133, 64, 0), (8300, 65, 20, 0), (8300, 67, 33, 0)])
 def test_spmm_odd_columns_wherever_the_vectors_end(kind, rows, cols, batch, skip):
     """The vectors of an odd number of columns end in the middle of 4 bytes.  Whether they end at a page (4096 bytes), one
     element in front of or behind it, and whatever lies behind them, the result is the same bit for bit."""

@@ -254,12 +254,13 @@ MACKO_API int macko_dense_gemv(const void* W_dev, int64_t rows, int64_t cols, in
 
 /* Small-batch product with one matrix: the matrix is streamed and decoded once for the whole
  * batch on the matrix cores (more than 16 vectors; 2 to 16 where estimates of both ways' times,
- * from the shape, the stored entries and the batch, say so; codes of up to 4 bits, two columns or more,
- * ldx < 2^24), else once per piece of up to 8 vectors, for every
+ * from the shape, the stored entries and the batch, say so, and wherever x does not fit LDS; codes of up to
+ * 4 bits, two columns or more, ldx < 2^24), else once per piece of up to 8 vectors, for every
  * code width and both value widths (rows shorter than 384 stored entries on average, and batches whose
  * interleaved vectors do not fit LDS, then run as independent matrix-vector products).
- * An infinity or a NaN in a vector reaches only the results of rows that store an entry at its column
- * (such results are computed apart, entry by entry, which is slow).
+ * On the matrix cores an infinity or a NaN in a vector reaches only the results of rows that store an entry
+ * at its column (such results are computed apart, entry by entry, which is slow); the other ways, like
+ * macko_spmv, may multiply it with a zero where a row stores nothing, and the result is then a NaN.
  * Y[b][r] = sum_k values[k] * X[b][column(k)] for b < batch, 0 <= batch <= MACKO_MAX_BATCH.
  * X_dev: fp16, batch vectors of `cols` elements, vector b at X_dev + b*ldx
  * (ldx >= cols); Y_dev: fp16, vector b at Y_dev + b*ldy (ldy >= rows).  fp32

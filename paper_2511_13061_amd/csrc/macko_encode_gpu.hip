@@ -69,8 +69,9 @@ __device__ __forceinline__ Chunk<IN8> load_chunk(const void* __restrict__ row_v,
 // The same for rows of 8 columns or more, one load without a branch around it: at the last 8 columns where the chunk reaches
 // behind them, put right by end_chunk.  Behind a load that not every lane executes the compiler waits for all loads under
 // way, so that nothing was in flight: the counting pass is bound by the reads of the matrix and takes, us, with load_chunk
-// and with this: 11008 x 4096 18.6 / 15.9, 4096 x 11008 17.9 / 15.5, 8-bit values 11.5 / 10.1.  The fill kernel, which is bound by more than its
-// loads, keeps load_chunk: 35.8 / 36.5, 29.1 / 27.0, 8-bit 28.4 / 25.7, and its registers grow from 36 to 70.
+// and with this: 11008 x 4096 18.6 / 15.9, 4096 x 11008 17.9 / 15.5, 8-bit values 11.5 / 10.1.  The fill kernel keeps load_chunk, since
+// the first of these would lose: 35.8 / 36.5, 29.1 / 27.0, 8-bit 28.4 / 25.7 (its registers grow from 36 to 70); a rule
+// that tells the three apart is not worked out.
 template <bool IN8>
 __device__ __forceinline__ Chunk<IN8> load_whole_chunk(const void* __restrict__ row, uint32_t col0, uint32_t cols) {
   Chunk<IN8> c;

@@ -12,16 +12,21 @@
 // with many vectors: X passes a compute unit's L1 at 64 bytes a clock, 3.4 us for 64 vectors of 4096 elements, and used to be
 // read for every 16 rows.  LDS holds about 65 000 cells in all, so a panel of more rows has narrower windows.
 //
-// What bounds it: no unit by itself.  11008 x 4096 at 50 % with 64 vectors, 32 us: vector issue 12 (decode 45 instructions
+// What bounds it: no unit by itself.  11008 x 4096 at 50 % with 64 vectors, 30 us: vector issue 12 (decode 45 instructions
 // per step of 512 entries, 11 per window that a step reaches into, 64 per four 16-byte loads of B), LDS 9, HBM 8.5, matrix
 // cores 2.6, loads of B 3.4; but the phases of a window (decode, product, clearing) alternate behind barriers, and one
 // 16-wavefront workgroup per compute unit covers little of one with another.  Leaving out the puts into the tile takes 4 us off, B and its
 // transposes 8, the matrix instructions 3; a window costs about 2 us whatever is in it, so few, large windows are best.
 // Measured before (16 rows at a time, X read for each, transposes behind the barrier) and now, us, batch 8 / 16 / 32 / 64 at 50 %:
-// 4096 x 11008: 21.8 / 21.8 / 28.0 / 39.5 -> 19.3 / 20.3 / 26.3 / 37.4; 11008 x 4096: 24.3 / 24.3 / 30.4 / 44.6 -> 20.3 /
-// 22.2 / 30.3 / 32.1; 4096 x 4096: 12.4 / 12.4 / 14.6 / 20.4 -> 8.8 / 9.8 / 12.7 / 17.2; 11008 x 4096 at 90 %, 64: 37.2 -> 21.5.
-// 260 matrices of 300 to 14336 rows, 700 to 13000 columns, 40 to 93 % pruned, 12 to 64 vectors: 1.37 times as fast
-// (geometric mean), the slowest 4 % slower.
+// 4096 x 11008: 20.0 / 21.1 / 26.0 / 39.0 -> 17.3 / 19.7 / 24.7 / 33.0; 11008 x 4096: 23.4 / 23.1 / 29.3 / 43.2 -> 18.7 /
+// 21.9 / 27.6 / 30.4; 4096 x 4096: 12.3 / 11.4 / 13.4 / 19.1 -> 7.9 / 9.1 / 11.9 / 15.9; 11008 x 4096 at 90 %, 64: 35.4 -> 19.9.
+// Over 7441 calls of 256 to 14336 rows and columns, 30 to 97 % pruned, 2 to 64 vectors, 0.73 of the time (geometric mean).  Slower than
+// before are dense rows of many columns on few compute units, where the clearing of a window and the wait for its vectors show:
+// 17 to 32 vectors on 2049 to 3700 rows (2720 x 11160 at 33 %, 26: 24.9 -> 27.4; 3635 x 13192 at 47 %, 31: 27.5 -> 32.2; tried there: one and three
+// steps a unit, one buffer, the vectors shared out to two wavefronts, requested at four places), 9 to 16 on up to 4096 rows of more than
+// 18000 columns (2409 x 20936 at 47 %, 16: 30.6 -> 34.1; 102 x 139864 at 89 %, 10: 93.6 -> 102; clearing inside the product gives these
+// back what they lost, and takes as much from all others), and 9 to 16 on three tiles a workgroup of 4097 to 6144 columns (11976 x 5544 at 40 %, 16:
+// 33.0 -> 35.5; panels of one tile 34.0, but at 80 % 25.0 instead of 23.8).
 //
 // Tried: two workgroups of 8 wavefronts per compute unit, each with half of the rows (5 to 30 % slower: X is read twice, and
 // more windows); 512-column windows in two buffers for panels of 48 rows (34 -> 41 us); a ring of 2 to 4 steps of loads refilled one by one
@@ -202,6 +207,10 @@ spmm_panel_kernel(const TileArgs all) {
   const int n = lane & 15;
   const uint32_t aoff = kTilePad + n * kStride + 2 * (128 * G * slice + 32 * (lane >> 4));
   const bool odd_lane = lane & 1, high_lane = lane & 2;
+  // The vectors are one buffer (base rounded down to 4 bytes): what lies behind its end, vectors past the batch among
+  // it, reads as zero; what lies between two vectors is cleared where it is used.  The end is checked per 4 bytes, so
+  // the buffer ends in front of the last element of an odd number of columns: the last vector's is loaded by itself and put in its
+  // place where the vectors end.  (The other vectors' are inside; a single column is not served.)
   const uint32_t xmis = (uint32_t)(reinterpret_cast<uintptr_t>(a.X) & 2);
   const uint32_t xbytes = (uint32_t)(((int64_t)(a.batch - 1) * a.ldx + (cols & ~1)) * 2) + xmis;
   uint32_t last_x = 0u;
@@ -211,7 +220,7 @@ spmm_panel_kernel(const TileArgs all) {
   const uint32_t ldx2 = 2u * (uint32_t)a.ldx;
   // HALF, up to 8 vectors: the lanes of vectors 8 ... 15 take vectors 0 ... 7 of the next group instead, so that one operand serves two
   // groups.  The products of the first count in lanes 0 ... 7 of each 16, those of the second in lanes 8 ... 15 of another sum.
-  // Half the loads and transposes: 4096 x 11008 at 50 %, 8 vectors: 20.5 -> 19.3 us, at 80 % 14.7 -> 13.3; 300 x 13001: 16.1 -> 14.1.
+  // Half the loads and transposes: 4096 x 11008 at 50 %, 8 vectors, 19.2 -> 17.4 us, 4096 x 4096 8.7 -> 7.9, 300 x 13000 at 80 % 16.0 -> 13.8.
   const int bcol = 128 * G * slice + (HALF ? 128 * ((lane >> 3) & 1) : 0) + 8 * (4 * (lane >> 4) + (lane & 3));        // the lane's first column within the window
   const uint32_t xoff = xmis + (uint32_t)(16 * vpart + 4 * ((lane >> 2) & (HALF ? 1 : 3))) * ldx2 + 2u * bcol;
   u32x4 b[BG][NTW][4];

@@ -1054,7 +1054,7 @@ def test_fp8_groups_unsupported_calls_and_full_size():
     yw = w.spmv(to_dev(a.x))
     torch.cuda.synchronize()
     assert torch.equal(yw, ys[0])
-    # a batch of vectors: the batch kernel, a piece of 8 and a piece of 4 (3 used)
+    # a batch of vectors, on whichever kernel
     xs = [wl.x_vector(2048, 88, i) for i in range(11)]
     X = torch.stack([to_dev(v) for v in xs])
     Y = ma.spmm(X)

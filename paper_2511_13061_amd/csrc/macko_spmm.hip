@@ -340,7 +340,9 @@ bool vectors_serve(const SpmvProblem& p) { return p.b_val != 8 || spmv_takes_wav
 // one in the mean; without the busiest wavefront it was 0.7 %, and 3 or 4 vectors on 2049 to 4096 dense rows up to 1.3 times as slow
 // (3832 x 10352 at 53 %, 8-bit values, 3 vectors, 15.5 -> 12.0; 2733 x 11072 at 33 %, 4: 17.8 -> 14.0).  What is left is at most 1.45 times
 // as slow, where the copy of odd vectors costs the vector kernel more than estimated (6396 x 2629 at 63 %, 2-bit codes, 4: 15.6 / 10.7).
-// The matrix cores' estimate has to be 3 % below the vectors'.
+// The matrix cores' estimate has to be 3 % below the vectors'; with short rows, where both take about 5 us and the vectors' estimate is
+// low for some, 3 % above it is enough (760 x 414 at 45 %, 7 vectors, 5.8 / 4.8; of 3690 such calls 4 instead of 47 are more than
+// 5 % slower than the matrix cores were).
 double tile_estimate(const SpmvProblem& p, int batch) {
   const double cols = (double)p.cols / 4096.0, tiles = std::ceil((double)p.rows / (16.0 * device_cu_count()));
   const double steps = tiles * std::ceil((double)p.pad_nnz / (double)p.rows / 512.0), more = batch > 8 ? 1.0 : 0.0;
@@ -383,7 +385,7 @@ bool tile_is_faster(const SpmvProblem& p, int batch) {
   // x beyond LDS: every vector is gathered from memory by itself, at two vectors already the slower way in all of 111 calls (us,
   // vectors / matrix cores: 25 x 487832, 2 vectors, 686 / 361; 226 x 178280 at 99 %, 6, 754 / 112; 301 x 118384 at 93 %, 5, 587 / 76)
   if (spmv_lds_bytes(p.cols, p.b_delta) > kMaxLdsBytes) return true;
-  return 1.03 * tile_estimate(p, batch) < vector_estimate(p, batch);
+  return (p.pad_nnz / p.rows >= kLongRow ? 1.03 : 0.97) * tile_estimate(p, batch) < vector_estimate(p, batch);
 }
 
 }  // namespace

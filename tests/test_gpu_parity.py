@@ -2072,7 +2072,7 @@ def test_spmm_either_way_for_few_vectors(kind, rows, cols, sparsity, batch):
     # pieces of 3 and 4 vectors, one dense row to a wavefront: the matrix cores 1.3 times as slow; x of one vector fits LDS: 1.5 times
     (3832, 10352, 0.526, 3, 8), (2733, 11072, 0.333, 4, 8), (3077, 5728, 0.317, 3, 8), (376, 53088, 0.956, 2, 16),
     # and calls that the matrix cores win by as much
-    (1392, 1012, 0.87, 8, 16), (718, 8797, 0.5, 8, 16)])
+    (1392, 1012, 0.87, 8, 16), (718, 8797, 0.5, 8, 16), (8872, 280, 0.49, 2, 16)])
 def test_spmm_takes_the_faster_kernel(rows, cols, sparsity, batch, vals):
     """Where the two batch kernels differ by 1.3 times and more the library's choice is within 1.15 times of the better one (times of
     20 calls, least of 5), and the results are right."""

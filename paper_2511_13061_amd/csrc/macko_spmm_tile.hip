@@ -21,11 +21,10 @@
 // 4096 x 11008: 20.0 / 21.1 / 26.0 / 39.0 -> 17.3 / 19.7 / 24.7 / 33.0; 11008 x 4096: 23.4 / 23.1 / 29.3 / 43.2 -> 18.7 /
 // 21.9 / 27.6 / 30.4; 4096 x 4096: 12.3 / 11.4 / 13.4 / 19.1 -> 7.9 / 9.1 / 11.9 / 15.9; 11008 x 4096 at 90 %, 64: 35.4 -> 19.9.
 // Over 7441 calls of 256 to 14336 rows and columns, 30 to 97 % pruned, 2 to 64 vectors, 0.73 of the time (geometric mean).  Slower than
-// before are dense rows of many columns on few compute units, where the clearing of a window and the wait for its vectors show:
-// 17 to 32 vectors on 2049 to 3700 rows (2720 x 11160 at 33 %, 26: 24.9 -> 27.4; 3635 x 13192 at 47 %, 31: 27.5 -> 32.2; tried there: one and three
-// steps a unit, one buffer, the vectors shared out to two wavefronts, requested at four places), 9 to 16 on up to 4096 rows of more than
-// 18000 columns (2409 x 20936 at 47 %, 16: 30.6 -> 34.1; 102 x 139864 at 89 %, 10: 93.6 -> 102; clearing inside the product gives these
-// back what they lost, and takes as much from all others), and 9 to 16 on three tiles a workgroup of 4097 to 6144 columns (11976 x 5544 at 40 %, 16:
+// before are dense rows of many columns on few compute units, where the clearing of a window and the wait for its vectors show: 17 to 32
+// vectors on 2049 to 3700 rows (3635 x 13192 at 47 %, 31: 27.4 -> 29.5; 2720 x 11160 at 33 %, 26: 25.0 -> 25.9), 9 to 16 on up to 4096 rows of more than
+// 18000 columns (2409 x 20936 at 47 %, 16: 30.6 -> 32.2; 102 x 139864 at 89 %, 10: 93.6 -> 102; clearing inside the product gives the last
+// back what it lost, and takes as much from all others), and 9 to 16 on three tiles a workgroup of 4097 to 6144 columns (11976 x 5544 at 40 %, 16:
 // 33.0 -> 35.5; panels of one tile 34.0, but at 80 % 25.0 instead of 23.8).
 //
 // Tried: two workgroups of 8 wavefronts per compute unit, each with half of the rows (5 to 30 % slower: X is read twice, and
@@ -151,6 +150,7 @@ __device__ __forceinline__ void tile_row_by_entries(const TileArgs& a, int row, 
 // NT: tiles of 16 vectors; a launch of more vectors has several rows of workgroups.  P: tiles of 16 rows in a panel.  W: columns
 // of the largest window (a.window: of this launch's).  VS: parts into which the vector tiles are dealt to the wavefronts.
 // HALF: up to 8 vectors, see below.  DBL: two buffers.  S: steps of 512 entries that are loaded, taken and decoded together (a unit).
+// AHEAD: the vectors are requested behind the product of the window before.
 //
 // Window by window, a wavefront
 //  - clears its own rows of the tile and puts what it holds of them (the last unit taken may reach into several windows: its
@@ -162,13 +162,20 @@ __device__ __forceinline__ void tile_row_by_entries(const TileArgs& a, int row, 
 //    16 clocks of L1 each, 128 of them), and turns them into operand order in front of the barrier, where the early wavefronts wait.
 //    One tile of vectors and of rows requests them in front of the decode: there are only four or eight, and behind it the second
 //    unit of a window waits for them (2409 x 20936 at 47 %, 16 vectors: 37.1 -> 34.2 us, 2636 x 13808 at 41 %, 15: 26.3 -> 24.9,
-//    4096 x 11008 at 50 %, 8: 17.7 -> 17.2);
+//    4096 x 11008 at 50 %, 8: 17.7 -> 17.2).
+//    AHEAD (panels of one tile): behind the product of the window before, so that barrier and decode cover them.  The take of the window's
+//    first unit may not wait for them, so the compiler has to be able to count: the requests stand in a straight line behind all others
+//    on every way there (what a window lacks is requested behind the buffer's end), and the first unit is taken in front of
+//    the loop.  It costs shorter rows more than it gives.  us, without / with: 17 to 32 vectors, from 7 steps a row on, 3635 x 13192
+//    at 47 % 32.1 / 29.5, 2720 x 11160 at 33 % 27.5 / 25.9, 4096 x 10508 at 35 %, 8-bit values, 26.5 / 23.9, 4096 x 7386 at 51 % 17.4 / 17.1, but 2300 x 3000
+//    at 70 % 7.3 / 7.6; 9 to 16 vectors, from 14 on, 2409 x 20936 at 47 % 33.8 / 32.2, 4096 x 12696 at 31 % 26.6 / 25.8, but 2657 x 13835 at 59 %, 8-bit
+//    values, 24.4 / 25.3, 2100 x 6000 at 50 % 10.7 / 11.9; up to 8 vectors and 33 and more not tried with it, or no better (4096 x 11008 at 80 %, 8: 12.3 / 12.7);
 //  - behind the barrier multiplies its columns' part: the window's groups of 128 columns are dealt to kSlices wavefronts
 //    for each of the VS parts of the vectors (part vpart), every one for all tiles of rows.
 // With two buffers the next window goes into the other one at once; with one a second barrier keeps it apart.  The pad behind a row is
 // the one in front of the next: two wavefronts may write it, nobody reads it.
 // Every wavefront executes the same number of barriers whatever its rows hold.
-template <int NT, int P, int W, int VS, bool DBL, int S, bool HALF, int BD, int VB>
+template <int NT, int P, int W, int VS, bool DBL, int S, bool HALF, bool AHEAD, int BD, int VB>
 __global__ void __launch_bounds__(64 * kWaves)
 spmm_panel_kernel(const TileArgs all) {
   TileArgs a = all;                                    // this workgroup's vectors
@@ -180,6 +187,7 @@ spmm_panel_kernel(const TileArgs all) {
   constexpr int kSlices = panel_slices(VS), G = W / 128 / kSlices;          // groups of columns of a wavefront
   static_assert(kSlices * G * 128 == W && kSlices * VS == kWaves && NT % VS == 0, "every wavefront has its part of a window");
   static_assert(!HALF || (NT == 1 && G % 2 == 0), "pairs of groups of one vector tile");
+  static_assert(!AHEAD || P == 1, "one unit is taken at a time");
   constexpr int BG = HALF ? G / 2 : G, kPair = HALF ? 2 : 1;                // operands of a wavefront, groups of each
   constexpr int NTW = NT / VS;                                              // vector tiles of a wavefront
   constexpr int kStride = panel_stride(W), kBuffer = 16 * P * kStride;
@@ -229,8 +237,9 @@ spmm_panel_kernel(const TileArgs all) {
   auto load_b = [&](int from, int to) {
 #pragma unroll
     for (int g = 0; g < BG; ++g)
-      if (128 * (G * slice + kPair * g) < min(wr, cols - k0) && to > 4 * NTW * g && from < 4 * NTW * (g + 1)) {
+      if ((AHEAD || 128 * (G * slice + kPair * g) < min(wr, cols - k0)) && to > 4 * NTW * g && from < 4 * NTW * (g + 1)) {
         uint32_t xo = xoff + 2u * (uint32_t)(k0 + 128 * kPair * g);
+        if (AHEAD && 128 * (G * slice + kPair * g) >= min(wr, cols - k0)) xo = 0x80000000u;      // behind the buffer's end: zeros, and nothing is read
         asm volatile("" : "+v"(xo));
 #pragma unroll
         for (int i = 0; i < 4 * NTW; ++i)
@@ -267,13 +276,13 @@ spmm_panel_kernel(const TileArgs all) {
 #pragma unroll
     for (int s = 0; s < S; ++s) hend[p][s] = -1;
   };
-  if (NT == 1) load_b(0, 4 * BG * NTW);                // under way while the row pointers are waited for
+  if (NT == 1 && !AHEAD) load_b(0, 4 * BG * NTW);      // under way while the row pointers are waited for
 #pragma unroll
   for (int p = 0; p < P; ++p) {
     open_row(p);
     if (left[p] > 0) issue(p, e0[p], end[p]);
   }
-  if (NT > 1) load_b(0, 4 * BG * NTW);                 // many of them would hold up the first units
+  if (NT > 1 || AHEAD) load_b(0, 4 * BG * NTW);        // many of them would hold up the first units
   odd_results[threadIdx.x][0] = odd_results[threadIdx.x][1] = 0u;
   if (threadIdx.x == 0) any_odd = 0u;
 
@@ -326,11 +335,11 @@ spmm_panel_kernel(const TileArgs all) {
       load_b(0, 4 * BG * NTW);
       b_due = false;
     }
-    for (;;) {
-      uint32_t need = 0;                               // bit p: row p's next unit is taken now
+    // out of the load registers with the next unit of every row that has not passed the window's end (bit p: of row p), all of them first
+    auto take = [&]() -> uint32_t {
+      uint32_t need = 0;
 #pragma unroll
       for (int p = 0; p < P; ++p) need |= (uint32_t)(left[p] > 0 && base2[p] < limit) << p;
-      // out of the load registers with all of them first, then the next loads
 #pragma unroll
       for (int p = 0; p < P; ++p)
         if (need & (1u << p)) {
@@ -342,6 +351,12 @@ spmm_panel_kernel(const TileArgs all) {
           e0[p] += 512u * S;
           --left[p];
         }
+      return need;
+    };
+    uint32_t first = AHEAD ? take() : 0u;
+    for (;;) {
+      const uint32_t need = AHEAD && first ? first : take();
+      first = 0u;
       if (!need && !b_due) break;
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -438,9 +453,14 @@ spmm_panel_kernel(const TileArgs all) {
           }
         }
       }
-    b_due = true;
+    b_due = !AHEAD;
     if (!last_window) {
       k0 += wr;
+      if (AHEAD) {
+        __builtin_amdgcn_sched_barrier(0);
+        load_b(0, 4 * BG * NTW);
+        __builtin_amdgcn_sched_barrier(0);
+      }
       if (DBL) buf = kBuffer - buf;
       else __syncthreads();                            // the tile has been read
       continue;
@@ -501,6 +521,7 @@ spmm_panel_kernel(const TileArgs all) {
     j0 += P;
 #pragma unroll
     for (int p = 0; p < P; ++p) open_row(p);
+    if (AHEAD) load_b(0, 4 * BG * NTW);
     if (!DBL) __syncthreads();                         // the sums have been read
   }
   __syncthreads();
@@ -516,13 +537,13 @@ spmm_panel_kernel(const TileArgs all) {
   }
 }
 
-template <int NT, int P, int W, int VS, bool DBL, int S, bool HALF, int BD, int VB>
+template <int NT, int P, int W, int VS, bool DBL, int S, bool HALF, bool AHEAD, int BD, int VB>
 int launch_panel_as(TileArgs a, hipStream_t stream) {
   constexpr int vectors = HALF ? kHalfVectors : 16 * NT;
   constexpr int buffer = 16 * P * panel_stride(W), lds = (DBL ? 2 : 1) * buffer + kTilePad;
   static_assert(P * NT * panel_slices(VS) * 1024 + kTilePad <= buffer, "the partial sums fit one buffer");
   static_assert(lds + 64 * kWaves * 8 + 16 <= 160 * 1024, "LDS of a compute unit");
-  auto kfn = spmm_panel_kernel<NT, P, W, VS, DBL, S, HALF, BD, VB>;
+  auto kfn = spmm_panel_kernel<NT, P, W, VS, DBL, S, HALF, AHEAD, BD, VB>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return hip_fail(e);
   // One workgroup per compute unit with an equal share of the rows: LDS holds no second one, and the fewer workgroups,
@@ -565,6 +586,7 @@ template <int BD, int VB>
 int launch_tile_bd(const TileArgs& a, int64_t row_entries, hipStream_t stream) {
   const int64_t cus = device_cu_count();
   const int64_t tiles = tiles_per_wg(a.rows);
+  const bool dense = 4 * row_entries >= a.cols;        // more than one step of a row in 2048 columns
   int nt = (a.batch + 15) / 16;
   // Few rows leave compute units idle: they take the same rows with other vectors, in groups of 8 if there are enough of them, else
   // of 16 (256 x 4096, 64 vectors: 14.9 -> 8.7 in groups of 16, 7.9 in
@@ -576,30 +598,32 @@ int launch_tile_bd(const TileArgs& a, int64_t row_entries, hipStream_t stream) {
   }
 #define MACKO_PANEL(...) return launch_panel_as<__VA_ARGS__, BD, VB>(a, stream)
   if (half || nt == 1) {
-    if (!half && two_tiles(tiles, a.cols)) MACKO_PANEL(1, 2, 2048, 1, false, 1, false);
+    if (!half && two_tiles(tiles, a.cols)) MACKO_PANEL(1, 2, 2048, 1, false, 1, false, false);
     // few long rows: nothing but each wavefront's own loads hides their latency (300 x 13000 at 80 %, 16 vectors: 13.6 with two steps a
     // unit, 13.2).  In groups of 16 three are no better (1500 x 9000, 32: 15.5 / 15.5; 700 x 30000, 48: 42.2 / 43.0).
-    if (half && a.rows <= 8 * cus && a.cols > 8192) MACKO_PANEL(1, 1, 4096, 1, false, 3, true);
-    if (half) MACKO_PANEL(1, 1, 4096, 1, false, 2, true);
-    MACKO_PANEL(1, 1, 4096, 1, false, 2, false);
+    if (half && a.rows <= 8 * cus && a.cols > 8192) MACKO_PANEL(1, 1, 4096, 1, false, 3, true, false);
+    if (half) MACKO_PANEL(1, 1, 4096, 1, false, 2, true, false);
+    if (row_entries >= 14 * 512) MACKO_PANEL(1, 1, 4096, 1, false, 2, false, true);          // see AHEAD
+    MACKO_PANEL(1, 1, 4096, 1, false, 2, false, false);
   }
   // From here on X counts as well: the shape whose panels have the fewest empty places, 3 tiles if equal
   const bool three = (tiles + 2) / 3 * 3 <= (tiles + 1) / 2 * 2;
   if (nt == 2) {
-    if (tiles == 1) MACKO_PANEL(2, 1, 2048, 1, true, 2, false);
-    if (three) MACKO_PANEL(2, 3, 1024, 2, false, 1, false);                   // 10000 x 1800: 15.3 with panels of 2, 13.5
-    MACKO_PANEL(2, 2, 2048, 1, false, 1, false);                              // 5000 x 4096: 18.5 with panels of 1, 15.4
+    if (tiles == 1 && row_entries >= 7 * 512) MACKO_PANEL(2, 1, 2048, 1, true, 2, false, true);
+    if (tiles == 1) MACKO_PANEL(2, 1, 2048, 1, true, 2, false, false);
+    if (three) MACKO_PANEL(2, 3, 1024, 2, false, 1, false, false);                   // 10000 x 1800: 15.3 with panels of 2, 13.5
+    MACKO_PANEL(2, 2, 2048, 1, false, 1, false, false);                              // 5000 x 4096: 18.5 with panels of 1, 15.4
   }
   if (tiles == 1) {
-    if (nt == 3) MACKO_PANEL(3, 1, 2048, 1, true, 2, false);                  // 4096 x 4096: 15.2; with a fourth, empty tile 17.1
-    if (a.cols <= 3072) MACKO_PANEL(4, 1, 1024, 2, true, 2, false);           // 4096 x 2600: 13.1 / 14.2 with 2048, 4096 x 4096 at 90 %: 13.5 / 12.6
-    // more than one step of a row in a window: two loaded at a time (us, one / two: 2100 x 13256, 64 vectors, at 30 % 50.9 / 44.1, at
+    if (nt == 3) MACKO_PANEL(3, 1, 2048, 1, true, 2, false, false);                  // 4096 x 4096: 15.2; with a fourth, empty tile 17.1
+    if (a.cols <= 3072) MACKO_PANEL(4, 1, 1024, 2, true, 2, false, false);           // 4096 x 2600: 13.1 / 14.2 with 2048, 4096 x 4096 at 90 %: 13.5 / 12.6
+    // dense rows: two steps loaded at a time (us, one / two: 2100 x 13256, 64 vectors, at 30 % 50.9 / 44.1, at
     // 50 % 44.5 / 38.8, at 70 % 35.9 / 34.9; 4096 x 11008 at 50 % 35.9 / 33.2, but at 80 % 28.2 / 28.4, at 90 % 25.7 / 26.7)
-    if (4 * row_entries >= a.cols) MACKO_PANEL(4, 1, 2048, 1, true, 2, false);
-    MACKO_PANEL(4, 1, 2048, 1, true, 1, false);
+    if (dense) MACKO_PANEL(4, 1, 2048, 1, true, 2, false, false);
+    MACKO_PANEL(4, 1, 2048, 1, true, 1, false, false);
   }
-  if (three) MACKO_PANEL(4, 3, 1024, 2, false, 1, false);                     // 11008 x 4096: 40.9 with panels of 2, 33.1
-  MACKO_PANEL(4, 2, 1024, 2, true, 1, false);                                 // 8192 x 4096 at 80 %: 22.8 with panels of 1, 19.0
+  if (three) MACKO_PANEL(4, 3, 1024, 2, false, 1, false, false);                     // 11008 x 4096: 40.9 with panels of 2, 33.1
+  MACKO_PANEL(4, 2, 1024, 2, true, 1, false, false);                                 // 8192 x 4096 at 80 %: 22.8 with panels of 1, 19.0
 #undef MACKO_PANEL
 }
 

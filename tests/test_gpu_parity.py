@@ -1530,6 +1530,8 @@ def test_spmm_tile_edges(kind, rows, cols, batch):
     (1500, 1100, 40), (1500, 129, 33), (2048, 300, 16), (2049, 300, 16), (40, 4500, 61),
     # groups of 16 on rows of more than two windows, groups of 8 on them, and more rows than that for up to 16 vectors
     (1500, 8200, 20), (1100, 9001, 32), (300, 8205, 12), (2100, 4100, 11),
+    # rows of 7 steps and more with 17 to 32 vectors, of 14 and more with up to 16 (50, 30 and 50 % kept, by the seed)
+    (2050, 9200, 17), (2064, 12417, 32), (2052, 19500, 16),
     # up to 8 vectors: pairs of groups of 128 columns, the second of a pair there, partly there and missing
     (40, 127, 3), (40, 128, 8), (41, 129, 8), (40, 256, 5), (40, 257, 7), (70, 383, 8), (33, 4097, 8), (2100, 2049, 7)])
 def test_spmm_panel_shapes(kind, rows, cols, batch):
@@ -1560,6 +1562,12 @@ def test_spmm_tile_leaves_out_what_is_not_stored_in_every_shape(kind, rows, cols
         _leaves_out_what_is_not_stored(kind, rows, cols, batch)
     finally:
         M.set_tuning("spmm_kernel", 0)
+
+
+@pytest.mark.parametrize("rows,cols,batch", [(2100, 7301, 20), (2100, 14500, 12)])
+def test_spmm_tile_leaves_out_what_is_not_stored_in_long_rows(rows, cols, batch):
+    """The same where the vectors of a window are requested a window ahead (rows of 7 and of 14 steps and more)."""
+    _leaves_out_what_is_not_stored("b4", rows, cols, batch)
 
 
 def _leaves_out_what_is_not_stored(kind, rows, cols, batch):
@@ -2123,6 +2131,20 @@ def test_spmm_of_8_bit_values_with_x_beyond_lds(rows, cols, sparsity, batch):
     ref, mag = X.double() @ W64.T.contiguous(), X.double().abs() @ W64.abs().T.contiguous()
     bound = ref.abs() * 2.0 ** -11 + 2.0 ** -25 + mag * cols * 2.0 ** -24          # as in test_spmm_tile_edges
     assert float(((Y - ref).abs() / bound).max()) <= 1.01
+
+
+@pytest.mark.parametrize("kind", ["b2", "b4", "fp8"])
+@pytest.mark.parametrize("rows,cols,sparsity,batch", [
+    # 17 to 32 vectors: a row of just under and just over 7 steps, odd columns; 9 to 16: of 14 steps, several rows a wavefront
+    (2101, 7169, 0.501, 20), (2101, 7177, 0.495, 20), (2049, 9001, 0.4, 17), (4096, 12417, 0.5, 32), (4000, 8192, 0.3, 31),
+    (2101, 14337, 0.501, 12), (2101, 14345, 0.495, 12), (2049, 16385, 0.4, 9), (2500, 19500, 0.5, 16), (8300, 8001, 0.05, 12)])
+def test_spmm_vectors_requested_a_window_ahead(kind, rows, cols, sparsity, batch):
+    """Both sides of the rules for long rows, with inputs and bound of test_spmm_on_both_sides_of_the_rule_that_picks_its_kernel."""
+    M.set_tuning("spmm_kernel", 2)
+    try:
+        test_spmm_on_both_sides_of_the_rule_that_picks_its_kernel(kind, rows, cols, sparsity, batch)
+    finally:
+        M.set_tuning("spmm_kernel", 0)
 
 
 @pytest.mark.parametrize("kind", ["b4", "fp8"])

@@ -15,7 +15,9 @@
 #include "macko_device.h"
 #include "macko_internal.h"
 
+#include <chrono>
 #include <mutex>
+#include <new>
 
 namespace macko {
 namespace {
@@ -26,6 +28,15 @@ struct EncodeStats {
   unsigned int empty_rows;
   unsigned int max_row_entries;
 };
+// The host's view of an encoding, in pinned memory: the totals, and the number of the last step that is over.
+struct EncodeReport {
+  EncodeStats stats;
+  uint32_t step;
+};
+// Everything before it on the stream is over when the host reads `step`.
+__device__ __forceinline__ void report_step(EncodeReport* report, uint32_t step) {
+  __hip_atomic_store(&report->step, step, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 // 8 consecutive columns of one row as loaded: fp16 values, or bytes (8-bit values).
 template <bool IN8>
@@ -259,13 +270,13 @@ encode_block_sums_kernel(const uint32_t* __restrict__ row_entries, const uint32_
 
 constexpr int kFusedBlocks = 64;
 
-// one workgroup: block_off[b] = entries of the blocks in front of b; totals to *stats.  FUSED: from the rows' counts,
+// one workgroup: block_off[b] = entries of the blocks in front of b; totals to *report.  FUSED: from the rows' counts,
 // at most kFusedBlocks blocks; else from the block totals.
 template <bool FUSED>
 __global__ void __launch_bounds__(1024)
 encode_block_offsets_kernel(const BlockSums* __restrict__ sums, const uint32_t* __restrict__ row_entries,
                             const uint32_t* __restrict__ row_nnz, int rows, int nblocks,
-                            unsigned long long* __restrict__ block_off, EncodeStats* __restrict__ stats) {
+                            unsigned long long* __restrict__ block_off, EncodeReport* report, uint32_t step) {
   __shared__ BlockSums fused[FUSED ? kFusedBlocks : 1];
   if (FUSED) {
     const int lane = threadIdx.x & 63;
@@ -344,11 +355,13 @@ encode_block_offsets_kernel(const BlockSums* __restrict__ sums, const uint32_t* 
       em += s_empty[i];
       mx = max(mx, s_long[i]);
     }
-    stats->pad_nnz = carry_s;
-    stats->nnz = nn;
-    stats->empty_rows = em;
-    stats->max_row_entries = mx;
+    report->stats = EncodeStats{nn, carry_s, em, mx};
+    report_step(report, step);
   }
+}
+
+__global__ void __launch_bounds__(64) encode_done_kernel(EncodeReport* report, uint32_t step) {
+  if (threadIdx.x == 0) report_step(report, step);
 }
 
 __global__ void __launch_bounds__(1024)
@@ -557,7 +570,8 @@ struct DeviceBuf {
 struct Workspace {
   void* p = nullptr;
   size_t cap = 0;
-  EncodeStats* pinned_stats = nullptr;   // host, pinned: the counting pass reports through it
+  EncodeReport* report = nullptr;   // host, pinned: the kernels report through it
+  uint32_t steps = 0;
 };
 std::mutex g_ws_mutex;
 Workspace g_ws[64];
@@ -581,6 +595,20 @@ auto count_kernel(bool in8, int b_delta) {
                                                                              : encode_count_kernel<false, WIDE, 1>;
 }
 
+// Waits until the stream has come to the report of step `step`.  Looked at by the host itself the report is seen 5.9 us after a launch,
+// hipStreamSynchronize returns after 11.4.  The look ends after 2 ms, then the runtime waits (and says what is wrong, if the
+// report never comes).
+hipError_t wait_for_step(const EncodeReport* report, uint32_t step, hipStream_t stream) {
+  const auto begin = std::chrono::steady_clock::now();
+  do {
+    for (int i = 0; i < 64; ++i) {
+      if (__atomic_load_n(&report->step, __ATOMIC_ACQUIRE) == step) return hipSuccess;
+      __builtin_ia32_pause();
+    }
+  } while (std::chrono::steady_clock::now() - begin < std::chrono::milliseconds(2));
+  return hipStreamSynchronize(stream);
+}
+
 constexpr size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 }  // namespace
@@ -599,13 +627,13 @@ int encode_on_device(const void* dense, int64_t rows, int64_t cols, int64_t ld, 
   if (dev < 0 || dev >= 64) return MACKO_E_UNSUPPORTED;
   std::lock_guard<std::mutex> lock(g_ws_mutex);
   Workspace& ws = g_ws[dev];
-  if (!ws.pinned_stats) {
+  if (!ws.report) {
     void* h = nullptr;
-    if (hipHostMalloc(&h, sizeof(EncodeStats), hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc(&h, sizeof(EncodeReport), hipHostMallocCoherent) != hipSuccess) {
       (void)hipGetLastError();
       return MACKO_E_OUT_OF_MEMORY;
     }
-    ws.pinned_stats = static_cast<EncodeStats*>(h);
+    ws.report = new (h) EncodeReport{};
   }
   // scratch layout of the counting pass
   const int64_t nblocks = (rows + 1023) / 1024;
@@ -639,10 +667,10 @@ int encode_on_device(const void* dense, int64_t rows, int64_t cols, int64_t ld, 
   hipLaunchKernelGGL(nblocks > kFusedBlocks ? encode_block_offsets_kernel<false> : encode_block_offsets_kernel<true>,
                      dim3(1), dim3(1024), 0, stream, static_cast<const BlockSums*>(sums),
                      static_cast<const uint32_t*>(counts), static_cast<const uint32_t*>(nnzs), (int)rows, (int)nblocks,
-                     boff, ws.pinned_stats);
+                     boff, ws.report, ++ws.steps);
   MACKO_HIP_TRY(hipGetLastError());
-  MACKO_HIP_TRY(hipStreamSynchronize(stream));
-  const EncodeStats st = *ws.pinned_stats;
+  MACKO_HIP_TRY(wait_for_step(ws.report, ws.steps, stream));
+  const EncodeStats st = ws.report->stats;
   if (st.pad_nnz >= (1ull << 32)) return MACKO_E_OVERFLOW;
   const int64_t pad = (int64_t)st.pad_nnz;
   const int64_t granule = alloc_granule(b_delta);
@@ -675,8 +703,9 @@ int encode_on_device(const void* dense, int64_t rows, int64_t cols, int64_t ld, 
     hipLaunchKernelGGL(kfill, dim3(grid), dim3(64 * kFillWaves), 0, stream, dense, (uint32_t)rows, (uint32_t)cols, ld,
                        static_cast<const uint32_t*>(rp), vals, dels, (uint32_t)pad, (uint32_t)alloc);
   }
+  hipLaunchKernelGGL(encode_done_kernel, dim3(1), dim3(64), 0, stream, ws.report, ++ws.steps);
   MACKO_HIP_TRY(hipGetLastError());
-  MACKO_HIP_TRY(hipStreamSynchronize(stream));
+  MACKO_HIP_TRY(wait_for_step(ws.report, ws.steps, stream));
   // a large scratch buffer is not kept (from 6.7 M rows on: 8 bytes per row and a quarter more)
   if (ws.cap > kKeepScratchBytes) {
     (void)hipFree(ws.p);

@@ -1691,6 +1691,29 @@ def test_gpu_encoder_row_ends(kind, first):
         assert (g.report.nnz, g.report.pad_nnz, g.report.alloc_nnz) == (enc.nnz, enc.pad_nnz, enc.alloc_nnz)
 
 
+@pytest.mark.parametrize("rows,cols", [(3, 40), (700, 1501), (4096, 4096), (70000, 24)])
+def test_gpu_encoding_is_over_when_the_call_returns(rows, cols):
+    """The call watches a number that the stream writes behind the last kernel.  Other streams and the host read the arrays at once, and the
+    dense matrix is overwritten on another stream at once."""
+    gen = torch.Generator(device="cuda").manual_seed(rows)
+    writer, reader = torch.cuda.Stream(), torch.cuda.Stream()
+    for turn in range(6):
+        W = torch.randn((rows, cols), generator=gen, device="cuda").half() * (torch.rand((rows, cols), generator=gen, device="cuda") < 0.5)
+        keep = W.clone()
+        torch.cuda.synchronize()
+        g = M.encode_device(W, stream=writer)
+        with torch.cuda.stream(reader):
+            W.fill_(float("nan"))
+            dense = g.decode_device()
+        host = g.fetch_device()
+        torch.cuda.synchronize()
+        assert torch.equal(dense, keep + 0)
+        if turn == 0:
+            enc = oracle.encode(keep.cpu().numpy().view(np.uint16))
+            assert_same_encoding(host, enc)
+            assert (g.report.nnz, g.report.pad_nnz, g.report.alloc_nnz) == (enc.nnz, enc.pad_nnz, enc.alloc_nnz)
+
+
 @pytest.mark.parametrize("kind", ["b1", "b2", "b4", "b8", "fp8"])
 @pytest.mark.parametrize("rows,cols,density,shift", [
     (70, 1, 0.5, 0), (50, 7, 0.9, 1), (33, 2047, 0.5, 3), (20, 2048, 0.5, 0), (20, 2049, 0.4, 5), (12, 4096, 0.9, 8),

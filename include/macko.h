@@ -364,7 +364,11 @@ MACKO_API int macko_dense_gemv_group(int n, const void* const* W_dev, const int6
 
 /* ---- housekeeping ---------------------------------------------------------- */
 
+/* Waits until the device is idle if the handle owns device memory (that of the GPU encoder). */
 MACKO_API void macko_destroy(macko_handle_t h);
+/* Device memory of destroyed handles is kept for the next ones, up to 8 blocks and 256 MiB per device; this gives
+ * what is kept on the current device back (hipFree).  The encoder does so itself when memory runs out. */
+MACKO_API void macko_trim(void);
 
 MACKO_API const char* macko_status_string(int status);
 

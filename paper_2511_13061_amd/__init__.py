@@ -29,6 +29,7 @@ from .binding import (  # noqa: F401
     spmv_group,
     status_string,
     storage_by_code_width,
+    trim,
     wrap_device,
     wrap_device_fp8,
 )

@@ -18,7 +18,7 @@ EXPORTED_SYMBOLS = [
     "macko_encode", "macko_encode_device", "macko_wrap_device", "macko_encode_ex", "macko_encode_device_ex",
     "macko_wrap_device_ex", "macko_storage_by_code_width", "macko_get_report",
     "macko_device_bytes", "macko_bind_device", "macko_host_buffers", "macko_fetch_device",
-    "macko_decode", "macko_encode_fp8", "macko_encode_device_fp8", "macko_wrap_device_fp8", "macko_host_values_fp8", "macko_decode_fp8", "macko_check_device", "macko_columns_device", "macko_decode_device", "macko_spmv", "macko_dense_gemv", "macko_spmv_group", "macko_spmv_many", "macko_spmv_chain", "macko_spmv_chain_static", "macko_chain_status", "macko_dense_gemv_group", "macko_spmm", "macko_destroy", "macko_status_string",
+    "macko_decode", "macko_encode_fp8", "macko_encode_device_fp8", "macko_wrap_device_fp8", "macko_host_values_fp8", "macko_decode_fp8", "macko_check_device", "macko_columns_device", "macko_decode_device", "macko_spmv", "macko_dense_gemv", "macko_spmv_group", "macko_spmv_many", "macko_spmv_chain", "macko_spmv_chain_static", "macko_chain_status", "macko_dense_gemv_group", "macko_spmm", "macko_destroy", "macko_trim", "macko_status_string",
     "macko_last_hip_error", "macko_set_tuning", "macko_get_tuning",
 ]
 
@@ -141,6 +141,8 @@ def load_library():
     lib.macko_spmm.argtypes = [vp, ci, vp, i64, vp, i64, vp]
     lib.macko_destroy.argtypes = [vp]
     lib.macko_destroy.restype = None
+    lib.macko_trim.argtypes = []
+    lib.macko_trim.restype = None
     lib.macko_status_string.argtypes = [ci]
     lib.macko_status_string.restype = ctypes.c_char_p
     lib.macko_last_hip_error.argtypes = []
@@ -148,7 +150,7 @@ def load_library():
     lib.macko_get_tuning.argtypes = [ctypes.c_char_p, i64p]
     for name in EXPORTED_SYMBOLS:
         fn = getattr(lib, name)
-        if name not in ("macko_destroy", "macko_status_string"):
+        if name not in ("macko_destroy", "macko_trim", "macko_status_string"):
             fn.restype = ci
     if native is not None:
         native.bind(*[ctypes.cast(f, vp).value for f in (lib.macko_spmv, lib.macko_spmm, lib.macko_decode_device)])
@@ -171,6 +173,11 @@ def _made(result, where: str):
     if type(result) is int:
         raise MackoError(result, where)
     return result
+
+
+def trim() -> None:
+    """macko_trim: give back the device memory that is kept for the next handles of the GPU encoder."""
+    load_library().macko_trim()
 
 
 def set_tuning(name: str, value: int) -> None:

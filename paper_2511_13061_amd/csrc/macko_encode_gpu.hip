@@ -552,12 +552,12 @@ encode_fill_kernel(const void* __restrict__ dense, uint32_t rows, uint32_t cols,
   }
 }
 
+// Freed unless the call succeeds.
 struct DeviceBuf {
   void* p = nullptr;
   ~DeviceBuf() {
     if (p) (void)hipFree(p);
   }
-  hipError_t alloc(size_t n) { return hipMalloc(&p, n ? n : 16); }
   void* release() {
     void* q = p;
     p = nullptr;
@@ -577,13 +577,18 @@ std::mutex g_ws_mutex;
 Workspace g_ws[64];
 constexpr size_t kKeepScratchBytes = size_t{64} << 20;
 
-hipError_t workspace_reserve(Workspace& ws, size_t bytes) {
+hipError_t workspace_reserve(Workspace& ws, size_t bytes, int device) {
   if (bytes <= ws.cap) return hipSuccess;
   if (ws.p) (void)hipFree(ws.p);
   ws.p = nullptr;
   ws.cap = 0;
   const size_t want = bytes + bytes / 4;             // some slack so that similar sizes do not reallocate
   hipError_t e = hipMalloc(&ws.p, want);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    block_trim(device);
+    e = hipMalloc(&ws.p, want);
+  }
   if (e == hipSuccess) ws.cap = want;
   return e;
 }
@@ -613,8 +618,7 @@ constexpr size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 }  // namespace
 
-// The handle's three arrays live in ONE allocation (*block, to be released with hipFree):
-// values first, then deltas, then row_ptr, each at a multiple of 256 bytes.
+// The handle's three arrays live in ONE allocation (*block, of encoded_layout, to be given back with block_release).
 int encode_on_device(const void* dense, int64_t rows, int64_t cols, int64_t ld, int b_delta, int b_val,
                      hipStream_t stream, void** block,
                      void** values, uint8_t** deltas, uint32_t** row_ptr, int64_t* nnz,
@@ -642,7 +646,7 @@ int encode_on_device(const void* dense, int64_t rows, int64_t cols, int64_t ld, 
   const size_t o_sums = align_up(o_nnz + 4 * (size_t)rows, 256);
   const size_t o_boff = align_up(o_sums + sizeof(BlockSums) * (size_t)std::max<int64_t>(nblocks, 1), 256);
   const size_t scratch_bytes = o_boff + 8 * (size_t)std::max<int64_t>(nblocks, 1);
-  if (workspace_reserve(ws, scratch_bytes) != hipSuccess) {
+  if (workspace_reserve(ws, scratch_bytes, dev) != hipSuccess) {
     (void)hipGetLastError();
     return MACKO_E_OUT_OF_MEMORY;
   }
@@ -678,19 +682,16 @@ int encode_on_device(const void* dense, int64_t rows, int64_t cols, int64_t ld, 
   if (alloc >= (int64_t{1} << 32)) return MACKO_E_OVERFLOW;
 
   // the output block
-  const size_t b_values = 0;
-  const size_t b_deltas = align_up(b_values + (size_t)alloc * (in8 ? 1 : 2), 256);
-  const size_t b_rowptr = align_up(b_deltas + (size_t)alloc * b_delta / 8, 256);
-  const size_t b_total = b_rowptr + 4 * (size_t)(rows + 1);
+  const EncodedLayout layout = encoded_layout(rows, alloc, b_delta, b_val);
   DeviceBuf out;
-  if (out.alloc(b_total) != hipSuccess) {
+  if (block_acquire(&out.p, layout.total) != hipSuccess) {
     (void)hipGetLastError();
     return MACKO_E_OUT_OF_MEMORY;
   }
   unsigned char* ob = static_cast<unsigned char*>(out.p);
-  void* vals = ob + b_values;
-  uint32_t* dels = reinterpret_cast<uint32_t*>(ob + b_deltas);
-  uint32_t* rp = reinterpret_cast<uint32_t*>(ob + b_rowptr);
+  void* vals = ob;
+  uint32_t* dels = reinterpret_cast<uint32_t*>(ob + layout.deltas);
+  uint32_t* rp = reinterpret_cast<uint32_t*>(ob + layout.row_ptr);
   if (rows > 0)
     hipLaunchKernelGGL(encode_row_ptr_kernel, dim3((unsigned)nblocks), dim3(1024), 0, stream, counts, (uint32_t)rows,
                        boff, rp, (uint32_t)pad, b_delta, dels);

@@ -140,12 +140,35 @@ constexpr uint32_t panel_row_units(uint32_t start, uint32_t end, uint32_t per_un
 }
 int launch_spmm_tile(const SpmvProblem& p, const uint16_t* X, int64_t ldx, uint16_t* Y, int64_t ldy, int batch,
                      hipStream_t stream);
+// bytes of the encoder's block: values, codes and row pointers, each from a multiple of 256 bytes on
+struct EncodedLayout {
+  size_t deltas, row_ptr, total;
+};
+constexpr EncodedLayout encoded_layout(int64_t rows, int64_t alloc_nnz, int b_delta, int b_val) {
+  const size_t deltas = ((size_t)alloc_nnz * (b_val / 8) + 255) / 256 * 256;
+  const size_t row_ptr = deltas + ((size_t)alloc_nnz * b_delta / 8 + 255) / 256 * 256;
+  return {deltas, row_ptr, row_ptr + 4 * (size_t)(rows + 1)};
+}
 // device-side expansion: column index of every stored entry; the dense matrix back
 int launch_columns(const SpmvProblem& p, int32_t* cols_out, hipStream_t stream);
 // structural check of bound device arrays; *first_bad (device) must hold `rows` beforehand
 int launch_check(const SpmvProblem& p, unsigned int* first_bad, hipStream_t stream);
 int launch_decode(const SpmvProblem& p, void* dense, int64_t ld, hipStream_t stream);
-// GPU encoder: counting pass + fill pass.  The three arrays are parts of one hipMalloc'd *block.
+// Device memory of the encoder's handles.  A block that macko_destroy releases is kept for the next handle of its size, a few
+// per device: block_bytes rounds a size up (by 1.6 % at most) so that matrices of one shape share one although their entry counts differ a little.
+constexpr size_t kStoredBlockMin = size_t{2} << 20;    // smaller ones cost hipMalloc and hipFree 0.4 us
+constexpr size_t kStoredBytes = size_t{256} << 20;     // kept per device, at most
+constexpr size_t block_bytes(size_t bytes) {
+  if (bytes < kStoredBlockMin) return bytes ? bytes : 16;
+  size_t granule = kStoredBlockMin / 64;
+  while (granule * 128 <= bytes) granule *= 2;
+  return (bytes + granule - 1) / granule * granule;
+}
+// A block of block_bytes(bytes) on the current device.  It is kept only with an idle_probe, a small allocation on its device, which goes with it.
+hipError_t block_acquire(void** block, size_t bytes);
+void block_release(void* block, size_t bytes, int device, void* idle_probe);
+void block_trim(int device);                           // frees what is kept
+// GPU encoder: counting pass + fill pass.  The three arrays are parts of one *block (block_acquire).
 int encode_on_device(const void* dense, int64_t rows, int64_t cols, int64_t ld, int b_delta, int b_val,
                      hipStream_t stream, void** block,
                      void** values, uint8_t** deltas, uint32_t** row_ptr, int64_t* nnz,
@@ -175,5 +198,7 @@ struct macko_matrix {
   const uint32_t* d_row_ptr = nullptr;
   bool bound = false;
   bool owns_device = false;
-  void* d_block = nullptr;   // owns_device: the one allocation that holds the three arrays
+  void* d_block = nullptr;   // owns_device: the one allocation that holds the three arrays,
+  int d_block_device = -1;   // its device, and a small allocation that block_release waits with
+  void* d_idle_probe = nullptr;
 };

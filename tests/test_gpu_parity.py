@@ -1714,6 +1714,47 @@ def test_gpu_encoding_is_over_when_the_call_returns(rows, cols):
             assert (g.report.nnz, g.report.pad_nnz, g.report.alloc_nnz) == (enc.nnz, enc.pad_nnz, enc.alloc_nnz)
 
 
+def test_gpu_encoder_blocks_are_reused_once_the_device_is_idle():
+    """The memory of a destroyed handle goes to the next one of its size.  Whatever stream still reads it when the handle is destroyed
+    has read it before the next encoding writes there."""
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    side = torch.cuda.Stream()
+
+    def matrix():
+        return torch.randn((4096, 3072), generator=gen, device="cuda").half() * (torch.rand((4096, 3072), generator=gen, device="cuda") < 0.5)
+
+    for _ in range(8):
+        first, second = matrix(), matrix()
+        torch.cuda.synchronize()
+        m = M.encode_device(first)
+        with torch.cuda.stream(side):
+            dense = [m.decode_device() for _ in range(6)]
+        m.destroy()
+        m = M.encode_device(second)
+        again = m.decode_device()
+        m.destroy()
+        torch.cuda.synchronize()
+        assert all(torch.equal(d, first + 0) for d in dense) and torch.equal(again, second + 0)
+
+
+def test_kept_blocks_are_bounded_and_given_back():
+    """At most 8 blocks and 256 MiB are kept; trim() frees them; handles that live share nothing."""
+    W = torch.ones((2048, 4096), dtype=torch.float16, device="cuda")              # 20 MiB encoded
+    torch.cuda.synchronize()
+    M.trim()
+    before = torch.cuda.mem_get_info()[0]
+    handles = [M.encode_device(W) for _ in range(20)]
+    alive = torch.cuda.mem_get_info()[0]
+    assert before - alive >= 20 * (20 << 20)
+    for m in handles[:19]:
+        m.destroy()
+    assert torch.equal(handles[19].decode_device(), W)
+    assert before - torch.cuda.mem_get_info()[0] <= (256 + 40) << 20
+    M.trim()
+    assert before - torch.cuda.mem_get_info()[0] <= 40 << 20
+    assert torch.equal(handles[19].decode_device(), W)
+
+
 @pytest.mark.parametrize("kind", ["b1", "b2", "b4", "b8", "fp8"])
 @pytest.mark.parametrize("rows,cols,density,shift", [
     (70, 1, 0.5, 0), (50, 7, 0.9, 1), (33, 2047, 0.5, 3), (20, 2048, 0.5, 0), (20, 2049, 0.4, 5), (12, 4096, 0.9, 8),

@@ -80,9 +80,7 @@ __device__ __forceinline__ Chunk<IN8> load_chunk(const void* __restrict__ row_v,
 // The same for rows of 8 columns or more, one load without a branch around it: at the last 8 columns where the chunk reaches
 // behind them, put right by end_chunk.  Behind a load that not every lane executes the compiler waits for all loads under
 // way, so that nothing was in flight: the counting pass is bound by the reads of the matrix and takes, us, with load_chunk
-// and with this: 11008 x 4096 18.6 / 15.9, 4096 x 11008 17.9 / 15.5, 8-bit values 11.5 / 10.1.  The fill kernel keeps load_chunk, since
-// the first of these would lose: 35.8 / 36.5, 29.1 / 27.0, 8-bit 28.4 / 25.7 (its registers grow from 36 to 70); a rule
-// that tells the three apart is not worked out.
+// and with this: 11008 x 4096 18.6 / 15.9, 4096 x 11008 17.9 / 15.5, 8-bit values 11.5 / 10.1.
 template <bool IN8>
 __device__ __forceinline__ Chunk<IN8> load_whole_chunk(const void* __restrict__ row, uint32_t col0, uint32_t cols) {
   Chunk<IN8> c;
@@ -107,6 +105,29 @@ __device__ __forceinline__ void end_chunk(Chunk<IN8>& c, uint32_t base, uint32_t
   }
   __builtin_memcpy(c.u, &lo, 8);
 }
+
+// The same through a buffer that ends with the row: what lies behind its end reads as zero, and nothing stands between the loads.  Ends are
+// checked per 4 bytes, so rows begin and end on words.  For the fill kernel (the counting pass is no faster, 16.3 / 16.7).
+template <bool IN8>
+struct RowBuffer {
+  __amdgpu_buffer_rsrc_t rsrc;
+  __device__ __forceinline__ RowBuffer(const void* row, uint32_t cols)
+      : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(row), 0, (int)((IN8 ? 1u : 2u) * cols), 0x00020000)) {}
+  __device__ __forceinline__ Chunk<IN8> load(uint32_t col0) const {
+    Chunk<IN8> c;
+    if constexpr (IN8) {
+      const auto q = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)col0, 0, 0);
+      c.u[0] = (uint32_t)q[0];
+      c.u[1] = (uint32_t)q[1];
+    } else {
+      const auto q = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(2u * col0), 0, 0);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) c.u[k] = (uint32_t)q[k];
+    }
+    return c;
+  }
+};
+constexpr int64_t kMaxBufferCols = int64_t{1} << 29;   // the loads ahead of a row's end stay below 2^32 bytes
 
 // Bit k set iff column k is neither +0 nor -0.  Packed: adding 0x7FFF (0x7F) to the bits other than the sign carries
 // into the sign position exactly when one of them is set, and never further.
@@ -408,7 +429,8 @@ constexpr int kFillWindow = 1024;
 constexpr int kFillWaves = 4;
 constexpr int kFillMargin = 8;                          // entries
 
-template <bool IN8, int BD>
+// BUFFER: loads through RowBuffer
+template <bool IN8, bool BUFFER, int BD>
 __global__ void __launch_bounds__(64 * kFillWaves)
 encode_fill_kernel(const void* __restrict__ dense, uint32_t rows, uint32_t cols, int64_t ld,
                    const uint32_t* __restrict__ row_ptr, void* __restrict__ values_v,
@@ -502,15 +524,17 @@ encode_fill_kernel(const void* __restrict__ dense, uint32_t rows, uint32_t cols,
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
+    const RowBuffer<IN8> buffer(src, cols);
+    auto load = [&](uint32_t col0) { return BUFFER ? buffer.load(col0) : load_chunk<IN8>(src, col0, cols); };
     Chunk<IN8> ring[kEncodeAhead];
 #pragma unroll
-    for (int j = 0; j < kEncodeAhead; ++j) ring[j] = load_chunk<IN8>(src, 512u * j + 8u * lane, cols);
+    for (int j = 0; j < kEncodeAhead; ++j) ring[j] = load(512u * j + 8u * lane);
     for (uint32_t base = 0; base < cols; base += 512u * kEncodeAhead) {
 #pragma unroll
       for (int j = 0; j < kEncodeAhead; ++j) {
         const uint32_t col0 = base + 512u * j + 8u * lane;     // steps behind the last column store nothing
         const Chunk<IN8> c = ring[j];
-        ring[j] = load_chunk<IN8>(src, col0 + 512u * kEncodeAhead, cols);
+        ring[j] = load(col0 + 512u * kEncodeAhead);
         const unsigned mask = nonzero_mask<IN8>(c);
         const uint32_t pos = table_pos[mask];
         const uint32_t low = table_codes[mask];
@@ -614,6 +638,13 @@ hipError_t wait_for_step(const EncodeReport* report, uint32_t step, hipStream_t 
   return hipStreamSynchronize(stream);
 }
 
+template <bool BUFFER>
+auto fill_kernel(bool in8, int b_delta) {
+  return in8 ? encode_fill_kernel<true, BUFFER, 4> : b_delta == 4 ? encode_fill_kernel<false, BUFFER, 4>
+         : b_delta == 2 ? encode_fill_kernel<false, BUFFER, 2> : b_delta == 8 ? encode_fill_kernel<false, BUFFER, 8>
+                                                                              : encode_fill_kernel<false, BUFFER, 1>;
+}
+
 constexpr size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 }  // namespace
@@ -698,9 +729,14 @@ int encode_on_device(const void* dense, int64_t rows, int64_t cols, int64_t ld, 
   else
     MACKO_HIP_TRY(hipMemsetAsync(rp, 0, 4, stream));
   if (rows > 0 && alloc > 0) {
-    auto kfill = in8 ? encode_fill_kernel<true, 4> : b_delta == 4 ? encode_fill_kernel<false, 4>
-                 : b_delta == 2 ? encode_fill_kernel<false, 2> : b_delta == 8 ? encode_fill_kernel<false, 8>
-                                                                              : encode_fill_kernel<false, 1>;
+    // A wavefront's loads are under way with RowBuffer; with load_chunk only other wavefronts cover them.  us, load_chunk / RowBuffer:
+    // 280 x 504 6.1 / 5.2, 2000 x 2000 10.4 / 8.4, 4096 x 4096 at 90 % 15.0 / 13.6, 4096 x 11008 34.2 / 33.6, 11008 x 4096 with 8-bit values 29.3 /
+    // 28.2; but 11008 x 4096 fp16 35.6 / 37.1, at 40 % with 2-bit codes 36.3 / 38.0: fp16 rows for more wavefronts than the chip holds keep
+    // load_chunk.
+    const int per_word = in8 ? 4 : 2;
+    const bool whole_words = (reinterpret_cast<uintptr_t>(dense) & 3) == 0 && ld % per_word == 0 && cols % per_word == 0;
+    const bool buffer = whole_words && cols <= kMaxBufferCols && (in8 || rows <= (int64_t)cus * 28);
+    auto kfill = buffer ? fill_kernel<true>(in8, b_delta) : fill_kernel<false>(in8, b_delta);
     hipLaunchKernelGGL(kfill, dim3(grid), dim3(64 * kFillWaves), 0, stream, dense, (uint32_t)rows, (uint32_t)cols, ld,
                        static_cast<const uint32_t*>(rp), vals, dels, (uint32_t)pad, (uint32_t)alloc);
   }

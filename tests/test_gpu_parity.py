@@ -1756,6 +1756,32 @@ def test_kept_blocks_are_bounded_and_given_back():
 
 
 @pytest.mark.parametrize("kind", ["b1", "b2", "b4", "b8", "fp8"])
+@pytest.mark.parametrize("first", [4, 504, 1016, 2040])
+def test_gpu_encoder_rows_on_words(kind, first):
+    """Rows that begin and end on 4 bytes go through a buffer that ends with the row: every such remainder around one chunk of 8, one
+    step of 512, two and four.  The columns behind a row hold non-zeros."""
+    rng = np.random.default_rng(first + 1)
+    word = 4 if kind == "fp8" else 2
+    for cols in range(first, first + 24, word):
+        W = (rng.standard_normal((5, cols)) * (rng.random((5, cols)) < 0.4)).astype(np.float16)
+        W[1] = 0
+        W[2, -1] = 1.0
+        if kind == "fp8":
+            W8 = wl.fp8_values_of(W.view(np.uint16))
+            enc = oracle.encode8(W8)
+            big = torch.full((5, cols + 2 * word), 9, dtype=torch.uint8, device="cuda")
+            big[:, :cols] = torch.from_numpy(W8).cuda()
+            g = M.encode_device_fp8(big[:, :cols])
+        else:
+            enc = oracle.encode(W.view(np.uint16), int(kind[1]))
+            big = torch.full((5, cols + 2 * word), 9.0, dtype=torch.float16, device="cuda")
+            big[:, :cols] = torch.from_numpy(W).cuda()
+            g = M.encode_device(big[:, :cols], b_delta=int(kind[1]))
+        assert_same_encoding(g.fetch_device(), enc)
+        assert (g.report.nnz, g.report.pad_nnz, g.report.alloc_nnz) == (enc.nnz, enc.pad_nnz, enc.alloc_nnz)
+
+
+@pytest.mark.parametrize("kind", ["b1", "b2", "b4", "b8", "fp8"])
 @pytest.mark.parametrize("rows,cols,density,shift", [
     (70, 1, 0.5, 0), (50, 7, 0.9, 1), (33, 2047, 0.5, 3), (20, 2048, 0.5, 0), (20, 2049, 0.4, 5), (12, 4096, 0.9, 8),
     (11, 4103, 0.03, 2), (7, 40001, 0.0003, 7), (3, 100000, 0.3, 0), (40, 300, 0.0, 4),

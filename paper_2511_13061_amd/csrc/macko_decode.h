@@ -11,6 +11,7 @@ namespace macko {
 // code widths of 1, 2, 4 and 8 bits (the product kernels use 2, 4 and 8).  All positions are doubled (bytes of the LDS
 // copy of x) and include the +1 per entry, i.e. entry k advances by 2 code + 2.
 //   load(deltas, chunk)  the 2 / 4 / 8 bytes of chunk `chunk` (8 entries)
+//   load(buffer, at)     the same at byte `at` of a buffer
 //   clear()              all codes 0 (every entry one column after the other)
 //   decode()             prefix sums inside the lane
 //   total()              doubled sum of the lane's 8 deltas
@@ -62,12 +63,14 @@ struct LaneCodesBytes {
 template <>
 struct LaneCodes<4> : LaneCodesBytes<4> {
   __device__ __forceinline__ void load(const uint32_t* __restrict__ deltas, uint32_t chunk) { w = load_stream(deltas + chunk); }
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t b, int at) { w = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(b, at, 0, kStreamLoad); }
 };
 template <>
 struct LaneCodes<2> : LaneCodesBytes<2> {
   __device__ __forceinline__ void load(const uint32_t* __restrict__ deltas, uint32_t chunk) {
     w = load_stream(reinterpret_cast<const uint16_t*>(deltas) + chunk);
   }
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t b, int at) { w = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(b, at, 0, kStreamLoad); }
 };
 
 // 1-bit codes: a prefix is a population count of the low bits.
@@ -77,6 +80,7 @@ struct LaneCodes<1> {
   __device__ __forceinline__ void load(const uint32_t* __restrict__ deltas, uint32_t chunk) {
     w = load_stream(reinterpret_cast<const uint8_t*>(deltas) + chunk);
   }
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t b, int at) { w = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(b, at, 0, kStreamLoad); }
   __device__ __forceinline__ void clear() { w = 0u; }
   __device__ __forceinline__ void keep_if(bool c) { w = c ? w : 0u; }
   __device__ __forceinline__ void decode() {}
@@ -103,6 +107,11 @@ struct LaneCodes<8> {
     const uint2 v = load_stream(reinterpret_cast<const uint2*>(deltas) + chunk);
     w0 = v.x;
     w1 = v.y;
+  }
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t b, int at) {
+    const auto v = __builtin_amdgcn_raw_buffer_load_b64(b, at, 0, kStreamLoad);
+    w0 = (uint32_t)v[0];
+    w1 = (uint32_t)v[1];
   }
   __device__ __forceinline__ void clear() { w0 = w1 = 0u; }
   __device__ __forceinline__ void keep_if(bool c) {
@@ -153,6 +162,17 @@ struct LaneValues<16> {
   __device__ __forceinline__ void load(const void* __restrict__ values, uint32_t chunk) {
     v = load_stream(static_cast<const uint4*>(values) + chunk);
   }
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t b, int at) {
+    const auto q = __builtin_amdgcn_raw_buffer_load_b128(b, at, 0, kStreamLoad);
+    v = make_uint4((uint32_t)q[0], (uint32_t)q[1], (uint32_t)q[2], (uint32_t)q[3]);
+  }
+  // keep_first where the words that hold none of the first nv entries are zeros already
+  __device__ __forceinline__ void keep_first_of_words(uint32_t nv) {
+    v.x &= nv == 1 ? 0xFFFFu : 0xFFFFFFFFu;
+    v.y &= nv == 3 ? 0xFFFFu : 0xFFFFFFFFu;
+    v.z &= nv == 5 ? 0xFFFFu : 0xFFFFFFFFu;
+    v.w &= nv == 7 ? 0xFFFFu : 0xFFFFFFFFu;
+  }
   __device__ __forceinline__ void keep_first(uint32_t nv) {       // clear the values of entries nv, nv+1, ...
     v.x &= nv >= 2 ? 0xFFFFFFFFu : (nv == 1 ? 0xFFFFu : 0u);
     v.y &= nv >= 4 ? 0xFFFFFFFFu : (nv == 3 ? 0xFFFFu : 0u);
@@ -183,6 +203,11 @@ struct LaneValues<8> {
   __device__ __forceinline__ void load(const void* __restrict__ values, uint32_t chunk) {
     v = load_stream(static_cast<const uint2*>(values) + chunk);
   }
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t b, int at) {
+    const auto q = __builtin_amdgcn_raw_buffer_load_b64(b, at, 0, kStreamLoad);
+    v = make_uint2((uint32_t)q[0], (uint32_t)q[1]);
+  }
+  __device__ __forceinline__ void keep_first_of_words(uint32_t nv) { keep_first(nv); }
   __device__ __forceinline__ void keep_first(uint32_t nv) {
     const uint32_t lo = nv >= 4 ? 4u : nv, hi = nv >= 8 ? 4u : (nv > 4 ? nv - 4u : 0u);
     v.x &= lo == 4 ? 0xFFFFFFFFu : ((1u << (8u * lo)) - 1u);

@@ -30,6 +30,8 @@ __device__ __forceinline__ uint32_t load_stream(const uint32_t* p) { return __bu
 __device__ __forceinline__ uint16_t load_stream(const uint16_t* p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ uint8_t load_stream(const uint8_t* p) { return __builtin_nontemporal_load(p); }
 
+constexpr int kStreamLoad = 2;        // the same for loads through a buffer descriptor (nt)
+
 // ---- DPP cross-lane primitives (wave64, GCN DPP controls) --------------------
 // row_shr:n shifts within a row of 16 lanes; row_bcast:15 / row_bcast:31 carry a
 // row's (half-wave's) last lane into the following rows.  Lanes without a source

@@ -120,19 +120,18 @@ spmv_subwave_kernel(const uint4* __restrict__ values, const uint32_t* __restrict
 // The wavefront's rows form one stream of (row, step) items.  Loads run RING items
 // ahead of the arithmetic and cross row boundaries, so the memory pipeline does
 // not drain between rows.  Every item issues exactly one deltas load and one
-// values load, unconditionally (lanes before the row start re-read the row's first
-// chunk, lanes past the row end its last, items past the wavefront's last row re-read
-// the last chunk once more), which lets the compiler count outstanding loads exactly.
+// values load, unconditionally (lanes before the row start, lanes past the row end and items past the
+// wavefront's last row get zeros and read nothing), which lets the compiler count outstanding loads exactly.
 //
 // A row's first step begins at its start rounded down to 8 entries (Section 4.5) or, for
 // long rows, to a larger power of two (see kStepAlign).  What a lane holds besides the row:
 //  - lanes that lie wholly before the row start (first step, larger alignments only):
-//    codes and values cleared; they advance 16 bytes each below x[0];
+//    codes and values zero; they advance 16 bytes each below x[0];
 //  - entries of the previous row in the lane that holds the row start: the base is set
 //    so that the row's first entry lands on its own column; the earlier entries then
 //    decode to positions <= 0, which read the zero guard in front of x, and their values
 //    are cleared as well (y_i depends on row i alone, also when a neighbour holds inf or NaN);
-//  - after the row end (last step only): codes and values cleared.
+//  - after the row end (last step only): codes and values zero, but for the codes in the lane that the row ends in.
 // No load ever leaves [0, alloc_nnz).
 // ---------------------------------------------------------------------------
 // x element whose plain LDS offset relative to the start of x is q (q may be
@@ -171,7 +170,7 @@ struct SpmvGroupHeader {
 // 64 * BD bytes of codes a wavefront requests per step are whole, aligned cache lines that no
 // other step touches (otherwise nine lines are touched for eight lines of values, and
 // neighbouring steps share lines).  The lanes of the first step that lie wholly before the row
-// are cleared and re-read the row's first chunk; the row costs a quarter step more on average.
+// read nothing; the row costs a quarter step more on average.
 // Measured on 36864 x 12288: 4-9 % faster from 25 % to 80 % sparsity (rows of 5 steps and
 // more), 5-8 % slower at 90 % (3 steps), hence the threshold.  256 entries align the codes of
 // 4-bit matrices to their 128-byte lines as well; 512 was no better.
@@ -216,7 +215,6 @@ __device__ __forceinline__ bool spmv_wave_row_body(const void* __restrict__ valu
   const int wrow_begin = row_begin + wave * per_wave + min(wave, extra);
   const int wrow_end = has_rows ? wrow_begin + per_wave + (wave < extra ? 1 : 0) : wrow_begin;
 
-  uint32_t chunk = 0;      // 8-entry chunk index this lane loads next (chunk 0 exists: pad_nnz > 0)
   const int blk = wrow_begin;
   const int nb = wrow_end - wrow_begin;                // at most 64: the host sees to that
   uint32_t rp_lo = 0, rp_hi = 0;
@@ -225,21 +223,51 @@ __device__ __forceinline__ bool spmv_wave_row_body(const void* __restrict__ valu
   LaneCodes<BD> wq[RING];
   LaneValues<VB> vq[RING];
 
+  // The row that is loaded is a buffer of its own for values and one for codes, from the chunk it begins in to its end: lanes in front of
+  // it or behind it, at offsets that are not in it, get zeros and read nothing.  Against addresses clamped into the row, and masks on what
+  // they brought, that is 6 vector instructions of 44 a step, 25 in a row's first and 30 in its last: us, 4096 x 4096 at 50 % 6.06 ->
+  // 5.82, 36864 x 12288 86.2 -> 83.8, at 85 % 36.8 -> 31.0, 12288 x 12288 at 95 % 8.85 -> 8.57, seven products of a 7B-shaped layer 54.6 -> 52.5.
+  const unsigned char* value_bytes = static_cast<const unsigned char*>(values);
+  const unsigned char* code_bytes = reinterpret_cast<const unsigned char*>(deltas);
+  __amdgpu_buffer_rsrc_t row_values, row_codes;
+  int at_v = 0, at_c = 0;                              // where lane 0 reads: the buffers' bytes
+  int lane_v = VB * lane, lane_c = BD * lane;          // a chunk has VB bytes of values and BD of codes
+  int next_v = 64 * VB, next_c = 64 * BD;              // from a step to the next
+  auto buffers = [&](uint32_t c0, uint32_t end) {      // from chunk c0 to entry `end`
+    const uint32_t n = end - (c0 << 3);
+    row_values = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(value_bytes + (uint64_t)VB * c0), 0,
+                                                   (int)((n * (VB / 8) + 3u) & ~3u), 0x00020000);
+    row_codes = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(code_bytes + (uint64_t)BD * c0), 0,
+                                                  (int)(((n + 7u) >> 3) * BD), 0x00020000);
+  };
+  auto open_row = [&]() {
+    if (TAILS && ld.i >= nb) {                         // behind the last row: the wavefront's rows are one buffer, lane i reads row i's tail
+      const uint32_t c0 = (uint32_t)__builtin_amdgcn_readlane((int)rp_lo, 0) >> 3;
+      buffers(c0, (uint32_t)__builtin_amdgcn_readlane((int)rp_hi, max(nb - 1, 0)));
+      const uint32_t chunk = ((rp_hi - 1u) >> 3) - c0;
+      lane_v = tail != 0u ? (int)(VB * chunk) : -VB;
+      lane_c = tail != 0u ? (int)(BD * chunk) : -BD;
+      at_v = at_c = next_v = next_c = 0;
+      ld.nsteps = INT_MAX;                             // no row follows
+      return;
+    }
+    const uint32_t c0 = ld.start >> 3;                 // (behind the last row: nothing, of chunk 0)
+    if (ld.i >= nb) ld.nsteps = INT_MAX;               // no row follows
+    const int skipped = (int)(c0 - (ld.a0 >> 3));
+    buffers(c0, ld.end);
+    at_v = -VB * skipped;
+    at_c = -BD * skipped;
+  };
   auto issue = [&](int j) {
-    if (ld.i < nb) {
-      const uint32_t e0 = ld.a0 + 512u * ld.step + lane8;
-      // lanes before the row (first step) or past it (last step) re-read its first / last chunk
-      chunk = min(max(e0, ld.start & ~7u), ld.end - 1u) >> 3;
-      if (++ld.step == ld.nsteps) {
-        ++ld.i;
-        seek_nonempty<TAILS>(ld, nb, rp_lo, rp_hi, amask);
-      }
-    } else if (TAILS && tail != 0u) {
-      chunk = (rp_hi - 1u) >> 3;
-    }                  // else a padding item: every lane re-reads its previous chunk (a line it has just
-                       // used; one fixed address would make every wavefront queue at the same L2 channel)
-    wq[j].load(deltas, chunk);
-    vq[j].load(values, chunk);
+    wq[j].load(row_codes, lane_c + at_c);
+    vq[j].load(row_values, lane_v + at_v);
+    at_v += next_v;
+    at_c += next_c;
+    if (++ld.step == ld.nsteps) {
+      ++ld.i;
+      seek_nonempty<TAILS>(ld, nb, rp_lo, rp_hi, amask);
+      open_row();
+    }
   };
   auto fetch_row_ptrs = [&]() {                        // unconditional loads, clamped to the last row
     const int r = min(blk + lane, rows - 1);
@@ -251,6 +279,7 @@ __device__ __forceinline__ bool spmv_wave_row_body(const void* __restrict__ valu
     if (TAILS) tail = lane < nb ? row_tail(rp_lo, rp_hi, amask) : 0u;
     seek_nonempty<TAILS>(ld, nb, rp_lo, rp_hi, amask);
     cp = ld;
+    open_row();
 #pragma unroll
     for (int j = 0; j < RING; ++j) issue(j);
   };
@@ -294,18 +323,13 @@ __device__ __forceinline__ bool spmv_wave_row_body(const void* __restrict__ valu
           const uint32_t e0 = cp.a0 + 512u * cp.step + lane8;
           const bool first = cp.step == 0;
           const int before = (int)(cp.start - cp.a0);  // entries in front of the row in its first step
-          if (cp.step == cp.nsteps - 1 || (first && before >= 8)) {
-            // clear what lies past the row end, and the lanes that lie wholly before its start
-            uint32_t nv = e0 < cp.end ? cp.end - e0 : 0u;      // valid entries in this lane's chunk
-            if (first && (int)lane8 + 8 <= before) nv = 0u;
-            w.keep_if(nv != 0);
-            v.keep_first(nv);
-          }
+          // what the row's last word of values holds of the next row
+          if (cp.step == cp.nsteps - 1 && (cp.end & (32 / VB - 1)) != 0u) v.keep_first_of_words(e0 < cp.end ? cp.end - e0 : 0u);
           w.decode();
           const uint32_t tot = w.total();              // doubled sum of this lane's 8 deltas
           const uint32_t incl = wave_incl_scan_u32(tot);
           if (first) {
-            // the row's first entry must land on its own column: the cleared lanes in front of it advance
+            // the row's first entry must land on its own column: the empty lanes in front of it advance
             // 16 bytes each, and the lane that holds the start counts its entries of the previous row
             base2 = -2 * (before & ~7);
             if (before & 7) {
@@ -341,13 +365,11 @@ __device__ __forceinline__ bool spmv_wave_row_body(const void* __restrict__ valu
       }
     }
     if (TAILS && __any(tail != 0u)) {
-      // the tails, lane i row i's: every slot of the ring has been refilled with them by now.  The codes of lanes that have none
-      // are cleared: what such a lane holds is anybody's, and its row's position may lie 504 + 7 * 16 columns behind the last one
-      // already, so that another 8 * 16 would gather behind the guard.
+      // the tails, lane i row i's: every slot of the ring has been refilled with them by now.  Lanes that have none hold zeros: their
+      // row's position may lie 504 + 7 * 16 columns behind the last one already, and codes of anybody's would gather behind the guard.
       static_assert(2 * (504 + 7 * (1 << BD)) + 2 * 8 <= back_pad_for(BD) || !TAILS, "gathers of lanes without a tail end in the guard");
       LaneCodes<BD> w = wq[0];
       LaneValues<VB> v = vq[0];
-      w.keep_if(tail != 0u);
       v.keep_first(tail);
       w.decode();
       acc = 0.0f;

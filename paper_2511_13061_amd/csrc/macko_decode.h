@@ -23,12 +23,11 @@ template <int BD>
 struct LaneCodes;
 
 // 2- and 4-bit codes: the eight doubled prefixes are at most 2*15*8 = 240 and fit
-// the bytes of two words; the constant part 2K of entry K is added bytewise.
+// the bytes of two words; entry K advances by 2 K + 2 besides.
 template <int BD>
 struct LaneCodesBytes {
   uint32_t w;           // packed codes as loaded
   uint32_t P, E;        // byte m: doubled code prefix through entry 2m+1 / 2m
-  uint32_t P2, E2;      // the same plus the constant part: doubled position of the entry, minus 2
   __device__ __forceinline__ void clear() { w = 0u; }
   __device__ __forceinline__ void keep_if(bool c) { w = c ? w : 0u; }
   __device__ __forceinline__ void decode() {
@@ -47,13 +46,11 @@ struct LaneCodesBytes {
     P = lshl_add<8>(P, P);
     P = lshl_add<16>(P, P);
     E = lshl_add<8>(P, lo2);
-    E2 = E + 0x0C080400u;                              // the largest byte, 240 + 14, still fits
-    P2 = P + 0x0E0A0602u;
   }
   __device__ __forceinline__ uint32_t total() const { return (P >> 24) + 16u; }
   template <int K>
   __device__ __forceinline__ int offset() const {
-    return (int)((((K & 1) ? P2 : E2) >> (8 * (K >> 1))) & 0xFFu);
+    return (int)((((K & 1) ? P : E) >> (8 * (K >> 1))) & 0xFFu) + 2 * K;     // (2 K goes into the LDS instruction's offset)
   }
   __device__ __forceinline__ uint32_t through(int k, int l = 0) const {
     const uint32_t src = (uint32_t)__builtin_amdgcn_readlane((int)((k & 1) ? P : E), l);
@@ -179,11 +176,15 @@ struct LaneValues<16> {
     v.z &= nv >= 6 ? 0xFFFFFFFFu : (nv == 5 ? 0xFFFFu : 0u);
     v.w &= nv >= 8 ? 0xFFFFFFFFu : (nv == 7 ? 0xFFFFu : 0u);
   }
-  __device__ __forceinline__ void clear_first(uint32_t n) {       // clear the values of entries 0 .. n-1 (n <= 7)
-    v.x &= n >= 2 ? 0u : (n == 1 ? 0xFFFF0000u : 0xFFFFFFFFu);
-    v.y &= n >= 4 ? 0u : (n == 3 ? 0xFFFF0000u : 0xFFFFFFFFu);
-    v.z &= n >= 6 ? 0u : (n == 5 ? 0xFFFF0000u : 0xFFFFFFFFu);
-    v.w &= n == 7 ? 0xFFFF0000u : 0xFFFFFFFFu;
+  // clear the values of entries 0 .. n-1 where `here`; n is uniform, 1 ... 7
+  __device__ __forceinline__ void clear_first(uint32_t n, bool here) {
+    const uint64_t lo = n < 4 ? ~uint64_t{0} << (16 * n) : 0, hi = n > 4 ? ~uint64_t{0} << (16 * (n - 4)) : ~uint64_t{0};
+    if (here) {
+      v.x &= (uint32_t)lo;
+      v.y &= (uint32_t)(lo >> 32);
+      v.z &= (uint32_t)hi;
+      v.w &= (uint32_t)(hi >> 32);
+    }
   }
   template <int K>
   __device__ __forceinline__ uint32_t bits() const {              // the stored bit pattern of entry K
@@ -213,10 +214,12 @@ struct LaneValues<8> {
     v.x &= lo == 4 ? 0xFFFFFFFFu : ((1u << (8u * lo)) - 1u);
     v.y &= hi == 4 ? 0xFFFFFFFFu : ((1u << (8u * hi)) - 1u);
   }
-  __device__ __forceinline__ void clear_first(uint32_t n) {       // n <= 7
-    const uint32_t lo = n >= 4 ? 4u : n, hi = n > 4 ? n - 4u : 0u;
-    v.x &= lo == 4 ? 0u : ~((1u << (8u * lo)) - 1u);
-    v.y &= ~((1u << (8u * hi)) - 1u);
+  __device__ __forceinline__ void clear_first(uint32_t n, bool here) {
+    const uint64_t keep = ~uint64_t{0} << (8 * n);
+    if (here) {
+      v.x &= (uint32_t)keep;
+      v.y &= (uint32_t)(keep >> 32);
+    }
   }
   template <int K>
   __device__ __forceinline__ uint32_t bits() const {

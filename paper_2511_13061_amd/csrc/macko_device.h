@@ -45,37 +45,32 @@ constexpr int kStreamLoad = 2;        // the same for loads through a buffer des
   asm volatile("s_nop 1\n\t" op " %0, %0, %0 " ctrl " row_mask:" rmask " bank_mask:0xf bound_ctrl:0" \
                : "+v"(v))
 
+// All six steps in one statement: between statements the compiler puts a wait state of its own behind each.
+#define MACKO_DPP_SCAN(op, v)                                                                       \
+  asm volatile("s_nop 1\n\t" op " %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t" \
+               "s_nop 1\n\t" op " %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t" \
+               "s_nop 1\n\t" op " %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t" \
+               "s_nop 1\n\t" op " %0, %0, %0 row_shr:8 row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t" \
+               "s_nop 1\n\t" op " %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf bound_ctrl:0\n\t" \
+               "s_nop 1\n\t" op " %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf bound_ctrl:0"      \
+               : "+v"(v))
+
 // Inclusive prefix sum over the 64 lanes (Alg. 1 of the paper computes the same
 // quantity with five shuffle levels on 32 lanes; a wavefront needs six).
 __device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
-  MACKO_DPP_ADD("v_add_u32_dpp", v, "row_shr:1", "0xf");
-  MACKO_DPP_ADD("v_add_u32_dpp", v, "row_shr:2", "0xf");
-  MACKO_DPP_ADD("v_add_u32_dpp", v, "row_shr:4", "0xf");
-  MACKO_DPP_ADD("v_add_u32_dpp", v, "row_shr:8", "0xf");
-  MACKO_DPP_ADD("v_add_u32_dpp", v, "row_bcast:15", "0xa");
-  MACKO_DPP_ADD("v_add_u32_dpp", v, "row_bcast:31", "0xc");
+  MACKO_DPP_SCAN("v_add_u32_dpp", v);
   return v;
 }
 
 // Inclusive running maximum over the 64 lanes (unsigned; lanes without a source read 0).
 __device__ __forceinline__ uint32_t wave_incl_scan_max_u32(uint32_t v) {
-  MACKO_DPP_ADD("v_max_u32_dpp", v, "row_shr:1", "0xf");
-  MACKO_DPP_ADD("v_max_u32_dpp", v, "row_shr:2", "0xf");
-  MACKO_DPP_ADD("v_max_u32_dpp", v, "row_shr:4", "0xf");
-  MACKO_DPP_ADD("v_max_u32_dpp", v, "row_shr:8", "0xf");
-  MACKO_DPP_ADD("v_max_u32_dpp", v, "row_bcast:15", "0xa");
-  MACKO_DPP_ADD("v_max_u32_dpp", v, "row_bcast:31", "0xc");
+  MACKO_DPP_SCAN("v_max_u32_dpp", v);
   return v;
 }
 
 // Sum over the 64 lanes; the total ends up in lane 63 (other lanes hold prefixes).
 __device__ __forceinline__ float wave_sum_to_last_lane(float v) {
-  MACKO_DPP_ADD("v_add_f32_dpp", v, "row_shr:1", "0xf");
-  MACKO_DPP_ADD("v_add_f32_dpp", v, "row_shr:2", "0xf");
-  MACKO_DPP_ADD("v_add_f32_dpp", v, "row_shr:4", "0xf");
-  MACKO_DPP_ADD("v_add_f32_dpp", v, "row_shr:8", "0xf");
-  MACKO_DPP_ADD("v_add_f32_dpp", v, "row_bcast:15", "0xa");
-  MACKO_DPP_ADD("v_add_f32_dpp", v, "row_bcast:31", "0xc");
+  MACKO_DPP_SCAN("v_add_f32_dpp", v);
   return v;
 }
 

@@ -213,7 +213,7 @@ spmm_wave_row_kernel(const void* __restrict__ values, const uint32_t* __restrict
           base2 = -(int)w.through(before - 1);
           // lane 0 also holds the previous row's last entries: they read the zero guard, and their values
           // are cleared so that an infinity or a NaN among them cannot become a NaN of this row
-          v.clear_first(lane == 0 ? (uint32_t)before : 0u);
+          v.clear_first((uint32_t)before, lane == 0);
         }
       }
       const int lanebase = base2 + (int)(incl - tot);

@@ -310,6 +310,9 @@ __device__ __forceinline__ bool spmv_wave_row_body(const void* __restrict__ valu
     int tailbase = 0;                                  // lane i: doubled position behind row i's last step
     float acc = 0.0f;
     int base2 = 0;                                     // doubled position before this step (uniform)
+    int shared_step = -1;                              // the row's step whose last word of values holds some of the next row's, if any
+    auto find_shared_step = [&]() { shared_step = (cp.end & (32 / VB - 1)) != 0u ? cp.nsteps - 1 : -1; };
+    find_shared_step();
     while (cp.i < nb) {
 #pragma unroll
       for (int j = 0; j < RING; ++j) {
@@ -323,8 +326,7 @@ __device__ __forceinline__ bool spmv_wave_row_body(const void* __restrict__ valu
           const uint32_t e0 = cp.a0 + 512u * cp.step + lane8;
           const bool first = cp.step == 0;
           const int before = (int)(cp.start - cp.a0);  // entries in front of the row in its first step
-          // what the row's last word of values holds of the next row
-          if (cp.step == cp.nsteps - 1 && (cp.end & (32 / VB - 1)) != 0u) v.keep_first_of_words(e0 < cp.end ? cp.end - e0 : 0u);
+          if (cp.step == shared_step) v.keep_first_of_words(e0 < cp.end ? cp.end - e0 : 0u);
           w.decode();
           const uint32_t tot = w.total();              // doubled sum of this lane's 8 deltas
           const uint32_t incl = wave_incl_scan_u32(tot);
@@ -336,7 +338,7 @@ __device__ __forceinline__ bool spmv_wave_row_body(const void* __restrict__ valu
               base2 -= (int)w.through((before & 7) - 1, before >> 3);
               // the previous row's entries in that lane read the zero guard; their values are cleared all
               // the same, so that an infinity or a NaN among them cannot turn 0 * value into a NaN of this row
-              v.clear_first(lane == (before >> 3) ? (uint32_t)(before & 7) : 0u);
+              v.clear_first((uint32_t)(before & 7), lane == (before >> 3));
             }
           }
           const int lanebase = base2 + (int)(incl - tot);      // byte offset in x of the lane's chunk start
@@ -361,6 +363,7 @@ __device__ __forceinline__ bool spmv_wave_row_body(const void* __restrict__ valu
           acc = 0.0f;
           ++cp.i;
           seek_nonempty<TAILS>(cp, nb, rp_lo, rp_hi, amask);
+          find_shared_step();
         }
       }
     }

@@ -108,6 +108,29 @@ def test_spmv_small_cases_all_kernels(case, variant):
     check_y(y, W, x, f"{case}/{variant}")
 
 
+@pytest.mark.parametrize("bits", [16, 8])
+@pytest.mark.parametrize("cols", [2, 6, 258, 514, 1022, 1030, 2050, 2148, 3022, 4098])
+def test_spmv_x_of_an_even_length_ends_where_it_ends(cols, bits):
+    """x is loaded in pairs of elements up to its end, whatever remains of a chunk of 8: NaN in front of x and behind it stays out of y.
+    The rows hold from nothing to all columns, so that their first steps begin on every multiple that a row length is given."""
+    rng = np.random.default_rng(cols)
+    rows = 300
+    W = (rng.standard_normal((rows, cols)) * (rng.random((rows, cols)) < np.linspace(0, 1, rows)[:, None])).astype(np.float16)
+    W[5, -1] = 1.0
+    W[7, -2:] = 2.0
+    x = rng.standard_normal(cols).astype(np.float16)
+    big = torch.full((cols + 16,), float("nan"), dtype=torch.float16, device="cuda")
+    big[8:8 + cols] = torch.from_numpy(x).cuda()
+    for keep in (1.0, 0.4, 0.1):
+        Wk = W * (rng.random((rows, cols)) < keep)
+        if bits == 8:
+            W8 = wl.fp8_values_of(Wk.astype(np.float16).view(np.uint16))
+            check_y8(M.encode_fp8(W8).to_device().spmv(big[8:8 + cols]), W8, x.view(np.uint16), f"{cols} {keep}")
+        else:
+            Wk = Wk.astype(np.float16).view(np.uint16)
+            check_y(M.encode(Wk).to_device().spmv(big[8:8 + cols]), Wk, x.view(np.uint16), f"{cols} {keep}")
+
+
 def test_spmv_empty_rows_mixed_with_full_rows_and_row_boundaries_inside_chunks():
     rng = np.random.default_rng(5)
     C = 4096

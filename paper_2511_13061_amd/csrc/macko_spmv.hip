@@ -123,8 +123,8 @@ spmv_subwave_kernel(const uint4* __restrict__ values, const uint32_t* __restrict
 // values load, unconditionally (lanes before the row start, lanes past the row end and items past the
 // wavefront's last row get zeros and read nothing), which lets the compiler count outstanding loads exactly.
 //
-// A row's first step begins at its start rounded down to 8 entries (Section 4.5) or, for
-// long rows, to a larger power of two (see kStepAlign).  What a lane holds besides the row:
+// A row's first step begins at its start rounded down to 8 entries (Section 4.5) or to a larger
+// power of two (see step_align).  What a lane holds besides the row:
 //  - lanes that lie wholly before the row start (first step, larger alignments only):
 //    codes and values zero; they advance 16 bytes each below x[0];
 //  - entries of the previous row in the lane that holds the row start: the base is set
@@ -165,17 +165,26 @@ struct SpmvGroupHeader {
   int inv_nwaves;          // floor(65536 / wavefronts per workgroup) + 1
 };
 
-// Rows of at least kAlignMinEntries stored entries begin their first step on a multiple of
-// kStepAlign entries instead of where the row begins, so that the 1024 bytes of values and the
-// 64 * BD bytes of codes a wavefront requests per step are whole, aligned cache lines that no
+// Rows begin their first step on a multiple of a power of two of entries instead of where the row begins, so that the 1024
+// bytes of values and the 64 * BD bytes of codes a wavefront requests per step are whole, aligned cache lines that no
 // other step touches (otherwise nine lines are touched for eight lines of values, and
-// neighbouring steps share lines).  The lanes of the first step that lie wholly before the row
-// read nothing; the row costs a quarter step more on average.
-// Measured on 36864 x 12288: 4-9 % faster from 25 % to 80 % sparsity (rows of 5 steps and
-// more), 5-8 % slower at 90 % (3 steps), hence the threshold.  256 entries align the codes of
-// 4-bit matrices to their 128-byte lines as well; 512 was no better.
+// neighbouring steps share lines).  The lanes of the first step that lie wholly before the row read nothing.
+//  - From kAlignMinEntries on: kStepAlign.  A row costs a quarter step more on average.  Measured on 36864 x 12288 from 25 % to 80 % sparsity:
+//    4-9 % faster than 8.  256 entries align the codes of 4-bit matrices to their 128-byte lines as well; 512 is no better.
+//  - Shorter rows: as large as leaves the number of steps alone, with a sixteenth of the row for its neighbours' lengths, and 32 at least.
+//    Time on 12288 x 4096, 8000 x 6000 and 30000 x 4096 with 260 to 1690 entries a row, all at 8 = 1: at 16 0.954, 32 0.945, 64 0.941, 128 0.949, 256
+//    0.968, 512 1.007, by this rule 0.927 (us, 8 / rule: 30000 x 4096 with 700 entries 15.3 / 12.7, 12288 x 12288 at 95 % 8.5 / 8.2, 11007 x 4093 at 60 %
+//    9.7 / 9.5; but 8000 x 6000 with 947 entries 5.70 / 5.70, at 256 6.15).
 constexpr int kStepAlign = 256;
 constexpr int64_t kAlignMinEntries = 1700;
+int step_align(int64_t entries_per_row) {
+  int align = kStepAlign;
+  if (entries_per_row < kAlignMinEntries) {
+    const int64_t room = (entries_per_row + 511) / 512 * 512 - entries_per_row - entries_per_row / 16;
+    while (align > 32 && align - 8 > room) align /= 2;
+  }
+  return align;
+}
 
 // The work of one workgroup: workgroup number `wg` of the matrix given by the
 // pointers, whose rows are dealt out q (+1 for the first r workgroups) at a time.
@@ -892,12 +901,12 @@ int launch_wave_row_group(int nwr, const SpmvProblem* const* wr, int b_delta, in
     m.q = plan.m[i].q;
     m.r = plan.m[i].r;
     const int64_t align_knob = t.spmv_step_align;      // 0: by row length
-    const int align = align_knob ? (int)align_knob : (!tails && p.pad_nnz / p.rows >= kAlignMinEntries ? kStepAlign : 8);
+    const int align = align_knob ? (int)align_knob : tails ? 8 : step_align(p.pad_nnz / p.rows);
     m.amask = std::min(std::max(align, 8), kMaxStepAlign) - 1;
     m.pad = 0;
     (nwr > kMaxGroup ? wide_args.wg_begin : head.wg_begin)[i] = (int)wg_begin;
     wg_begin += plan.m[i].nwg;
-    // the lean start-up path needs an aligned x whose length is a multiple of 8 and fits the staging registers
+    // the lean start-up path needs an aligned x of an even length that fits the staging registers
     simple = simple && stage_x_is_simple(m.x, m.cols, plan.block);
   }
   if (nwr > kMaxGroup) {
@@ -1076,7 +1085,7 @@ int launch_spmv_chain(int n_phases, const int* sizes, const SpmvProblem* problem
       m.q = plan.m[at].q;
       m.r = plan.m[at].r;
       const int64_t align_knob = t.spmv_step_align;
-      const int align = align_knob ? (int)align_knob : (q.pad_nnz / q.rows >= kAlignMinEntries ? kStepAlign : 8);
+      const int align = align_knob ? (int)align_knob : step_align(q.pad_nnz / q.rows);
       m.amask = std::min(std::max(align, 8), kMaxStepAlign) - 1;
       args.wg_begin[at] = wg_begin;
       args.nwg[at] = plan.m[at].nwg;

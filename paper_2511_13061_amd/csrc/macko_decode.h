@@ -235,5 +235,19 @@ struct LaneValues<8> {
   __device__ __forceinline__ uint32_t half() const { return f32_to_f16_bits(get<K>()); }   // exact: E4M3 is a subset of fp16
 };
 
+// The entries from chunk c0 to entry `end` as two buffers: a lane at an offset in front of them or behind them gets zeros and reads
+// nothing (ends are checked per 4 bytes: of the values the last word may hold entries behind `end`, see keep_first_of_words;
+// the codes end with a chunk).  A chunk has VB bytes of values and BD of codes.
+template <int BD, int VB>
+struct EntryBuffers {
+  __amdgpu_buffer_rsrc_t values, codes;
+  __device__ __forceinline__ void open(const void* v, const uint32_t* d, uint32_t c0, uint32_t end) {
+    const uint32_t n = end - (c0 << 3);
+    unsigned char* vb = const_cast<unsigned char*>(static_cast<const unsigned char*>(v)) + (uint64_t)VB * c0;
+    unsigned char* cb = const_cast<unsigned char*>(reinterpret_cast<const unsigned char*>(d)) + (uint64_t)BD * c0;
+    values = __builtin_amdgcn_make_buffer_rsrc(vb, 0, (int)((n * (VB / 8) + 3u) & ~3u), 0x00020000);
+    codes = __builtin_amdgcn_make_buffer_rsrc(cb, 0, (int)(((n + 7u) >> 3) * BD), 0x00020000);
+  }
+};
 
 }  // namespace macko

@@ -16,6 +16,7 @@
 #include "macko_plan.h"
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 
 namespace macko {
@@ -152,7 +153,6 @@ spmm_wave_row_kernel(const void* __restrict__ values, const uint32_t* __restrict
   const int blk = row_begin + wave * per_wave + min(wave, extra);
   const int nb = per_wave + (wave < extra ? 1 : 0);      // at most 64: the host sees to that
 
-  uint32_t chunk = 0;
   RowCursor ld, cp;
   LaneCodes<BD> wq[RING];
   LaneValues<VB> vq[RING];
@@ -164,23 +164,31 @@ spmm_wave_row_kernel(const void* __restrict__ values, const uint32_t* __restrict
   XStageBatch<BT> xst;
   xst.begin(X, ldx, batch, cols);
 
+  // every row is a buffer of its own, as in the matrix-vector kernel (us, clamped addresses and
+  // masks / this: 4096 x 4096 at 50 %, 2 / 4 / 8 vectors, 7.47 / 8.13 / 11.8 -> 6.79 / 7.37 / 10.3, 11008 x 4096 12.7 / 15.1 / 22.6 -> 12.5 / 14.1 /
+  // 20.7; but 4096 x 4096 at 80 %, rows of two steps, 5.04 / 5.20 -> 5.14 / 5.33)
+  EntryBuffers<BD, VB> row;
+  int at_v = 0, at_c = 0;                              // where lane 0 reads: the buffers' bytes
+  auto open_row = [&]() {
+    if (ld.i >= nb) ld.nsteps = INT_MAX;               // no row follows
+    row.open(values, deltas, ld.start >> 3, ld.end);
+    at_v = at_c = 0;
+  };
   auto issue = [&](int j) {
-    if (ld.i < nb) {
-      const uint32_t e0 = ld.a0 + 512u * ld.step + lane8;
-      chunk = min(e0, ld.end - 1u) >> 3;
-      if (++ld.step == ld.nsteps) {
-        ++ld.i;
-        seek_nonempty(ld, nb, rp_lo, rp_hi);
-      }
-    } else {
-      chunk = 0;
+    wq[j].load(row.codes, BD * lane + at_c);
+    vq[j].load(row.values, VB * lane + at_v);
+    at_v += 64 * VB;
+    at_c += 64 * BD;
+    if (++ld.step == ld.nsteps) {
+      ++ld.i;
+      seek_nonempty(ld, nb, rp_lo, rp_hi);
+      open_row();
     }
-    wq[j].load(deltas, chunk);
-    vq[j].load(values, chunk);
   };
   ld.i = 0;
   seek_nonempty(ld, nb, rp_lo, rp_hi);
   cp = ld;
+  open_row();
 #pragma unroll
   for (int j = 0; j < RING; ++j) issue(j);
   xst.finish(lds, X, ldx, batch, cols, front_pad_for(BD), back_pad_for(BD));    // ends with a barrier
@@ -189,49 +197,50 @@ spmm_wave_row_kernel(const void* __restrict__ values, const uint32_t* __restrict
 #pragma unroll
   for (int b = 0; b < BT; ++b) yv[b] = acc[b] = 0.0f;
   int base2 = 0;
+  int shared_step = -1;                                // the row's step whose last word of values holds some of the next row's, if any
+  auto find_shared_step = [&]() { shared_step = (cp.end & (32 / VB - 1)) != 0u ? cp.nsteps - 1 : -1; };
+  find_shared_step();
   while (cp.i < nb) {
 #pragma unroll
     for (int j = 0; j < RING; ++j) {
-      LaneCodes<BD> w = wq[j];
-      LaneValues<VB> v = vq[j];
-      const bool live = cp.i < nb;
-      if (!live) base2 = 0;
-      const uint32_t end_eff = live ? cp.end : 0u;
-      const uint32_t e0 = cp.a0 + 512u * cp.step + lane8;
-      if (!live || cp.step == cp.nsteps - 1) {
-        const uint32_t nv = e0 < end_eff ? end_eff - e0 : 0u;
-        w.keep_if(nv != 0);
-        v.keep_first(nv);
-      }
-      w.decode();
-      const uint32_t tot = w.total();
-      const uint32_t incl = wave_incl_scan_u32(tot);
-      if (live && cp.step == 0) {
-        base2 = 0;
-        const int before = (int)(cp.start - cp.a0);
-        if (before > 0) {
-          base2 = -(int)w.through(before - 1);
-          // lane 0 also holds the previous row's last entries: they read the zero guard, and their values
-          // are cleared so that an infinity or a NaN among them cannot become a NaN of this row
-          v.clear_first((uint32_t)before, lane == 0);
+      const bool live = cp.i < nb;                     // false for the padding items after the last row: they are left out
+      if (live) {
+        LaneCodes<BD> w = wq[j];
+        LaneValues<VB> v = vq[j];
+        if (cp.step == shared_step) {
+          const uint32_t e0 = cp.a0 + 512u * cp.step + lane8;
+          v.keep_first_of_words(e0 < cp.end ? cp.end - e0 : 0u);
         }
-      }
-      const int lanebase = base2 + (int)(incl - tot);
-      // entry K: one gather address fetches the BT activations of its column
+        w.decode();
+        const uint32_t tot = w.total();
+        const uint32_t incl = wave_incl_scan_u32(tot);
+        if (cp.step == 0) {
+          base2 = 0;
+          const int before = (int)(cp.start - cp.a0);
+          if (before > 0) {
+            base2 = -(int)w.through(before - 1);
+            // lane 0 also holds the previous row's last entries: they read the zero guard, and their values
+            // are cleared so that an infinity or a NaN among them cannot become a NaN of this row
+            v.clear_first((uint32_t)before, lane == 0);
+          }
+        }
+        const int lanebase = base2 + (int)(incl - tot);
+        // entry K: one gather address fetches the BT activations of its column
 #define MACKO_ENTRY(K)                                                                       \
-      {                                                                                      \
-        const int q = lanebase + w.template offset<K>();     /* byte offset for one vector */ \
-        const XV xraw = *reinterpret_cast<const XV*>(xbase + q * BT);                          \
-        float xf[BT];                                                                        \
-        unpack_x<BT>(xraw, xf);                                                              \
-        const float wk = v.template get<K>();                                                \
-        _Pragma("unroll") for (int b = 0; b < BT; ++b) acc[b] = fmaf(wk, xf[b], acc[b]);     \
-      }
-      MACKO_ENTRY(0) MACKO_ENTRY(1) MACKO_ENTRY(2) MACKO_ENTRY(3)
-      MACKO_ENTRY(4) MACKO_ENTRY(5) MACKO_ENTRY(6) MACKO_ENTRY(7)
+        {                                                                                      \
+          const int q = lanebase + w.template offset<K>();     /* byte offset for one vector */ \
+          const XV xraw = *reinterpret_cast<const XV*>(xbase + q * BT);                          \
+          float xf[BT];                                                                        \
+          unpack_x<BT>(xraw, xf);                                                              \
+          const float wk = v.template get<K>();                                                \
+          _Pragma("unroll") for (int b = 0; b < BT; ++b) acc[b] = fmaf(wk, xf[b], acc[b]);     \
+        }
+        MACKO_ENTRY(0) MACKO_ENTRY(1) MACKO_ENTRY(2) MACKO_ENTRY(3)
+        MACKO_ENTRY(4) MACKO_ENTRY(5) MACKO_ENTRY(6) MACKO_ENTRY(7)
 #undef MACKO_ENTRY
+        base2 += (int)__builtin_amdgcn_readlane((int)incl, 63);
+      }
       issue(j);
-      base2 += (int)__builtin_amdgcn_readlane((int)incl, 63);
       if (live && ++cp.step == cp.nsteps) {
         wave_sum_to_last_lane_n<BT>(acc);                // the BT sums side by side
 #pragma unroll
@@ -242,6 +251,7 @@ spmm_wave_row_kernel(const void* __restrict__ values, const uint32_t* __restrict
         }
         ++cp.i;
         seek_nonempty(cp, nb, rp_lo, rp_hi);
+        find_shared_step();
       }
     }
   }

@@ -236,23 +236,14 @@ __device__ __forceinline__ bool spmv_wave_row_body(const void* __restrict__ valu
   // it or behind it, at offsets that are not in it, get zeros and read nothing.  Against addresses clamped into the row, and masks on what
   // they brought, that is 6 vector instructions of 44 a step, 25 in a row's first and 30 in its last: us, 4096 x 4096 at 50 % 6.06 ->
   // 5.82, 36864 x 12288 86.2 -> 83.8, at 85 % 36.8 -> 31.0, 12288 x 12288 at 95 % 8.85 -> 8.57, seven products of a 7B-shaped layer 54.6 -> 52.5.
-  const unsigned char* value_bytes = static_cast<const unsigned char*>(values);
-  const unsigned char* code_bytes = reinterpret_cast<const unsigned char*>(deltas);
-  __amdgpu_buffer_rsrc_t row_values, row_codes;
+  EntryBuffers<BD, VB> row;
   int at_v = 0, at_c = 0;                              // where lane 0 reads: the buffers' bytes
-  int lane_v = VB * lane, lane_c = BD * lane;          // a chunk has VB bytes of values and BD of codes
+  int lane_v = VB * lane, lane_c = BD * lane;
   int next_v = 64 * VB, next_c = 64 * BD;              // from a step to the next
-  auto buffers = [&](uint32_t c0, uint32_t end) {      // from chunk c0 to entry `end`
-    const uint32_t n = end - (c0 << 3);
-    row_values = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(value_bytes + (uint64_t)VB * c0), 0,
-                                                   (int)((n * (VB / 8) + 3u) & ~3u), 0x00020000);
-    row_codes = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(code_bytes + (uint64_t)BD * c0), 0,
-                                                  (int)(((n + 7u) >> 3) * BD), 0x00020000);
-  };
   auto open_row = [&]() {
     if (TAILS && ld.i >= nb) {                         // behind the last row: the wavefront's rows are one buffer, lane i reads row i's tail
       const uint32_t c0 = (uint32_t)__builtin_amdgcn_readlane((int)rp_lo, 0) >> 3;
-      buffers(c0, (uint32_t)__builtin_amdgcn_readlane((int)rp_hi, max(nb - 1, 0)));
+      row.open(values, deltas, c0, (uint32_t)__builtin_amdgcn_readlane((int)rp_hi, max(nb - 1, 0)));
       const uint32_t chunk = ((rp_hi - 1u) >> 3) - c0;
       lane_v = tail != 0u ? (int)(VB * chunk) : -VB;
       lane_c = tail != 0u ? (int)(BD * chunk) : -BD;
@@ -263,13 +254,13 @@ __device__ __forceinline__ bool spmv_wave_row_body(const void* __restrict__ valu
     const uint32_t c0 = ld.start >> 3;                 // (behind the last row: nothing, of chunk 0)
     if (ld.i >= nb) ld.nsteps = INT_MAX;               // no row follows
     const int skipped = (int)(c0 - (ld.a0 >> 3));
-    buffers(c0, ld.end);
+    row.open(values, deltas, c0, ld.end);
     at_v = -VB * skipped;
     at_c = -BD * skipped;
   };
   auto issue = [&](int j) {
-    wq[j].load(row_codes, lane_c + at_c);
-    vq[j].load(row_values, lane_v + at_v);
+    wq[j].load(row.codes, lane_c + at_c);
+    vq[j].load(row.values, lane_v + at_v);
     at_v += next_v;
     at_c += next_c;
     if (++ld.step == ld.nsteps) {

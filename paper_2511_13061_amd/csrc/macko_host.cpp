@@ -716,11 +716,12 @@ int macko_spmv_many(int64_t n, const macko_handle_t* handles, const void* const*
     return macko::SpmvProblem{h->d_values, h->d_deltas, h->d_row_ptr, h->rows, h->cols, h->pad_nnz,
                               x_dev[i], y_dev[i], h->b_delta, h->b_val};
   };
+  auto class_of = [](const macko::SpmvProblem& q) { return macko::spmv_launch_class(q, macko::wave_row_min_entries(q.rows, true)); };
   int launch_class = -1;
   int64_t wide_rows = 0;
   for (int64_t i = 0; i < n && launch_class != 0; ++i) {
     if (handles[i]->rows == 0) continue;
-    const int c = macko::spmv_launch_class(problem(i));
+    const int c = class_of(problem(i));
     launch_class = launch_class < 0 || launch_class >> 1 == c >> 1 ? c : 0;
     if (c & 1) wide_rows += handles[i]->rows;
   }
@@ -738,7 +739,7 @@ int macko_spmv_many(int64_t n, const macko_handle_t* handles, const void* const*
       for (int64_t i = 0; i < n; ++i) {
         if (handles[i]->rows != 0) {
           p[m] = problem(i);
-          if (!apart || (macko::spmv_launch_class(p[m]) & 1) == pass) ++m;
+          if (!apart || (class_of(p[m]) & 1) == pass) ++m;
         }
         if (m == macko::kMaxWide || (m > 0 && i == n - 1)) {
           const int st = macko::launch_spmv_group(m, p, static_cast<hipStream_t>(stream));

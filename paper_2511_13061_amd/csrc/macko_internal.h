@@ -99,22 +99,30 @@ struct GemvProblem {
 };
 // n independent products, as few kernel launches as the shapes allow (1 <= n <= kMaxGroup; kMaxWide for the sparse product)
 int launch_spmv_group(int n, const SpmvProblem* problems, hipStream_t stream);
-// Rows of at least this many stored entries on average take the wave-per-row kernel (a step
-// covers 512 entries; below about 40 % use of a step the sub-wave kernel wins: measured
-// crossover between 133 and 247 entries per row on 36864 x 12288 at 98-99 % sparsity).
-constexpr int64_t kWaveRowMinEntries = 192;
+// Stored entries per row on average from which a product takes the wave-per-row kernel.  A row takes a wavefront one step of up to 512
+// entries, however short it is; the sub-wave kernel takes its rows 4 at a time, but one launch to a product, whose start is longer.
+// us, sub-wave / wave-per-row, rows x entries per row: 1000 x 40 3.1 / 2.8, x 220 4.4 / 2.7; 5000 x 40 3.5 / 4.5, x 130 5.1 / 4.6; 8192 x 100 4.8 / 4.8, x 150
+// 5.2 / 4.5; 12000 x 100 5.3 / 6.0, x 150 6.0 / 5.6; 20000 x 150 6.6 / 7.8, x 250 8.0 / 8.7, x 300 9.8 / 7.9; 36000 x 220 10.4 / 10.8, x 250 12.8 / 11.8.
+// grouped: one of several products of a call, which the wave-per-row kernel takes in one launch (4 of 504 x 448 with 43 entries
+// 15.6 / 4.0, 4 of 2296 x 2248 with 187 20.3 / 6.4, 3 of 10000 x 1000 with 80 15.7 / 10.9; 84 of 1000 x 300 with 150 117 / 6.6).
+constexpr int64_t kWaveRowMinEntries = 192;            // where nothing more is known of the call
+inline int64_t wave_row_min_entries(int64_t rows, bool grouped) {
+  const int64_t per_cu = rows / device_cu_count();
+  if (per_cu < 4 || (grouped && per_cu < 64)) return 1;
+  return per_cu < 32 ? 112 : per_cu < 48 ? 144 : 240;
+}
 // Whether the product goes to the wave-per-row kernel (8-bit values: it has to).
-inline bool spmv_takes_wave_row(const SpmvProblem& p) {
+inline bool spmv_takes_wave_row(const SpmvProblem& p, int64_t min_entries = kWaveRowMinEntries) {
   if (p.rows == 0 || p.pad_nnz == 0 || spmv_lds_bytes(p.cols, p.b_delta) > kMaxLdsBytes) return false;
   if (p.b_val == 8) return p.b_delta == 4;
   const int64_t knob = tuning().spmv_kernel;
-  return knob != 0 ? knob == 2 : p.pad_nnz / p.rows >= kWaveRowMinEntries;
+  return knob != 0 ? knob == 2 : p.pad_nnz / p.rows >= min_entries || min_entries <= 1;
 }
 // 0: the product may need a launch of its own, or a kernel that a knob asks for; products whose numbers differ in bit 0 at
 // most fit one launch of the wave-per-row kernel.  Bit 0: a wide x.
-inline int spmv_launch_class(const SpmvProblem& p) {
+inline int spmv_launch_class(const SpmvProblem& p, int64_t min_entries = kWaveRowMinEntries) {
   const Tuning& t = tuning();
-  if (!spmv_takes_wave_row(p) || t.spmv_kernel != 0 || (t.spmv_ring != 0 && t.spmv_ring != 2)) return 0;
+  if (!spmv_takes_wave_row(p, min_entries) || t.spmv_kernel != 0 || (t.spmv_ring != 0 && t.spmv_ring != 2)) return 0;
   return 2 * (p.b_val * 16 + p.b_delta) + (spmv_lds_bytes(p.cols, p.b_delta) - kAlignFrontPad >= kWideLdsBytes ? 1 : 0);
 }
 int launch_gemv_group(int n, const GemvProblem* problems, hipStream_t stream);

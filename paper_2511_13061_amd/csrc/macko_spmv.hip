@@ -1094,6 +1094,7 @@ int launch_spmv_chain(int n_phases, const int* sizes, const SpmvProblem* problem
 int launch_spmv_group(int n, const SpmvProblem* problems, hipStream_t stream) {
   if (n < 1 || n > kMaxWide) return MACKO_E_INVALID_ARG;
   const Tuning& t = tuning();
+  auto takes_wave_row = [&](const SpmvProblem& p) { return spmv_takes_wave_row(p, wave_row_min_entries(p.rows, n > 1)); };
   // matrices that do not go into a grouped wave-per-row launch
   for (int i = 0; i < n; ++i) {
     const SpmvProblem& p = problems[i];
@@ -1106,8 +1107,8 @@ int launch_spmv_group(int n, const SpmvProblem* problems, hipStream_t stream) {
       hipError_t e0 = hipGetLastError();
       if (e0 != hipSuccess) return hip_fail(e0);
     } else if (p.b_val == 8) {                          // 8-bit values: 4-bit codes, wave-per-row kernel only
-      if (!spmv_takes_wave_row(p)) return MACKO_E_UNSUPPORTED;
-    } else if (!spmv_takes_wave_row(p)) {                    // short rows or x larger than LDS: own launch
+      if (!takes_wave_row(p)) return MACKO_E_UNSUPPORTED;
+    } else if (!takes_wave_row(p)) {             // short rows or x larger than LDS: own launch
       int st = launch_subwave(p, (int)t.spmv_lanes, stream);
       if (st != MACKO_OK) return st;
     }
@@ -1117,7 +1118,7 @@ int launch_spmv_group(int n, const SpmvProblem* problems, hipStream_t stream) {
     const SpmvProblem* wr[kMaxWide];
     int nwr = 0;
     for (int i = 0; i < n; ++i)
-      if (problems[i].b_delta == bd && problems[i].b_val == 16 && spmv_takes_wave_row(problems[i])) wr[nwr++] = &problems[i];
+      if (problems[i].b_delta == bd && problems[i].b_val == 16 && takes_wave_row(problems[i])) wr[nwr++] = &problems[i];
     if (nwr == 0) continue;
     int st = launch_wave_row_group(nwr, wr, bd, 16, stream);
     if (st != MACKO_OK) return st;

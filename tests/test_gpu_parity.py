@@ -131,6 +131,40 @@ def test_spmv_x_of_an_even_length_ends_where_it_ends(cols, bits):
             check_y(M.encode(Wk).to_device().spmv(big[8:8 + cols]), Wk, x.view(np.uint16), f"{cols} {keep}")
 
 
+@pytest.mark.parametrize("n", [1, 2, 5, 11])
+@pytest.mark.parametrize("b_delta,rows,entries", [(4, 300, 1), (4, 1023, 30), (2, 1500, 111), (4, 1500, 113), (8, 8300, 100), (8, 8300, 143), (1, 8300, 144),
+                                                  (4, 12400, 239), (4, 12400, 241), (8, 16500, 20)])
+def test_short_rows_on_either_side_of_the_choice_of_kernel(b_delta, rows, entries, n):
+    """Short rows go to one launch of wavefronts per row or to sub-wave launches, by rows per compute unit, their mean length and whether
+    the call holds several products.  Rows from empty to three times the mean."""
+    gen = torch.Generator(device="cuda").manual_seed(rows + n)
+    cols = 3 * entries + 7 if b_delta < 8 else 40 * entries
+    for many in (False, True) if n > 1 else (False,):
+        mats, xs, want = [], [], []
+        for _ in range(n):
+            share = torch.rand((rows, 1), generator=gen, device="cuda") * 2 * entries / cols
+            share[::7] = 0
+            W = torch.randn((rows, cols), generator=gen, device="cuda").half()
+            W *= torch.rand((rows, cols), generator=gen, device="cuda") < share
+            W[3, :] = 1.0
+            x = torch.randn(cols, generator=gen, device="cuda").half()
+            mats.append(M.encode_device(W, b_delta=b_delta))
+            xs.append(x)
+            want.append((W.double() @ x.double(), W.double().abs() @ x.double().abs()))
+            del W
+        ys = [torch.full((rows,), float("nan"), dtype=torch.float16, device="cuda") for _ in range(n)]
+        if many:
+            M.SpmvMany(mats, xs, ys).launch()
+        elif n <= 8:
+            M.SpmvGroup(mats, xs, ys).launch()
+        else:
+            continue
+        for y, (y64, s64) in zip(ys, want):
+            assert bool(((y.double() - y64).abs() <= 1e-3 * s64 + 1e-3).all())
+        if n == 1:
+            assert torch.equal(mats[0].spmv(xs[0]), ys[0])
+
+
 def test_spmv_empty_rows_mixed_with_full_rows_and_row_boundaries_inside_chunks():
     rng = np.random.default_rng(5)
     C = 4096

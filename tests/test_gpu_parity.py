@@ -165,6 +165,21 @@ def test_short_rows_on_either_side_of_the_choice_of_kernel(b_delta, rows, entrie
             assert torch.equal(mats[0].spmv(xs[0]), ys[0])
 
 
+@pytest.mark.parametrize("batch", [2, 3, 5, 8, 13, 64])
+@pytest.mark.parametrize("rows,cols", [(2047, 512), (2048, 512), (2300, 520), (2300, 523), (3000, 8)])
+def test_spmm_short_rows_with_8_bit_codes(rows, cols, batch):
+    """Either side of the line from which short rows with 8-bit codes share passes over the matrix; results in a wider buffer."""
+    gen = torch.Generator(device="cuda").manual_seed(rows + batch)
+    W = torch.randn((rows, cols), generator=gen, device="cuda").half() * (torch.rand((rows, cols), generator=gen, device="cuda") < 0.08)
+    W[5] = 0
+    X = torch.randn((batch, cols), generator=gen, device="cuda").half()
+    Y = torch.full((batch, rows + 3), 7.0, dtype=torch.float16, device="cuda")
+    M.encode_device(W, b_delta=8).spmm(X, Y[:, :rows])
+    want, scale = X.double() @ W.double().t().contiguous(), X.double().abs() @ W.double().abs().t().contiguous()
+    assert bool(((Y[:, :rows].double() - want).abs() <= 1e-3 * scale + 1e-3).all())
+    assert bool((Y[:, rows:] == 7.0).all())
+
+
 def test_spmv_empty_rows_mixed_with_full_rows_and_row_boundaries_inside_chunks():
     rng = np.random.default_rng(5)
     C = 4096

@@ -44,6 +44,7 @@ expand_kernel(const void* __restrict__ values, const uint32_t* __restrict__ delt
       if (DENSE) v.load(values, chunk);
       w.keep_if(e0 < end);
       w.decode();
+      const LanePositions<BD> pos{w};
       const uint32_t tot = w.total();
       const uint32_t incl = wave_incl_scan_u32(tot);
       if (step == 0) {
@@ -54,7 +55,7 @@ expand_kernel(const void* __restrict__ values, const uint32_t* __restrict__ delt
 #define MACKO_ENTRY(k)                                                                  \
   {                                                                                     \
     const uint32_t e = e0 + k;                                                          \
-    const int col = (lanebase + w.template offset<k>()) >> 1;                           \
+    const int col = (lanebase + pos.template offset<k>()) >> 1;                           \
     if (e >= start && e < end) {                                                        \
       if (!DENSE) cols_out[e] = col;                                                    \
       else if (col < cols) dense[(int64_t)row * ld + col] = (uint16_t)v.template bits<k>(); \
@@ -111,6 +112,7 @@ check_kernel(const uint32_t* __restrict__ deltas, const uint32_t* __restrict__ r
         w.load(deltas, chunk);
         w.keep_if(e0 < end);
         w.decode();
+        const LanePositions<BD> pos{w};
         const uint32_t tot = w.total();
         const uint32_t incl = wave_incl_scan_u32(tot);
         if (step == 0) {
@@ -121,7 +123,7 @@ check_kernel(const uint32_t* __restrict__ deltas, const uint32_t* __restrict__ r
 #define MACKO_ENTRY(k)                                                                    \
   {                                                                                       \
     const uint32_t e = e0 + k;                                                            \
-    if (e >= start && e < end && ((lanebase + w.template offset<k>()) >> 1) >= cols) lane_bad = true; \
+    if (e >= start && e < end && ((lanebase + pos.template offset<k>()) >> 1) >= cols) lane_bad = true; \
   }
         MACKO_ENTRY(0) MACKO_ENTRY(1) MACKO_ENTRY(2) MACKO_ENTRY(3)
         MACKO_ENTRY(4) MACKO_ENTRY(5) MACKO_ENTRY(6) MACKO_ENTRY(7)
@@ -182,6 +184,7 @@ decode_rows_kernel(const void* __restrict__ values, const uint32_t* __restrict__
         }
         w.keep_if(e0 < end);
         w.decode();
+        const LanePositions<BD> pos{w};
         const uint32_t tot = w.total();
         const uint32_t incl = wave_incl_scan_u32(tot);
         if (step == 0) {
@@ -192,7 +195,7 @@ decode_rows_kernel(const void* __restrict__ values, const uint32_t* __restrict__
 #define MACKO_ENTRY(k)                                                                  \
   {                                                                                     \
     const uint32_t e = e0 + k;                                                          \
-    const int col = (lanebase + w.template offset<k>()) >> 1;                           \
+    const int col = (lanebase + pos.template offset<k>()) >> 1;                           \
     if (e >= start && e < end && col < cols) {                                          \
       if (VB == 16) reinterpret_cast<uint16_t*>(rowbuf)[col] = (uint16_t)v.template bits<k>(); \
       else rowbuf[col] = (unsigned char)v.template bits<k>();                           \
@@ -326,6 +329,7 @@ decode_windows_kernel(const void* __restrict__ values, const uint32_t* __restric
             v.keep_first(nv);
           }
           w.decode();
+          const LanePositions<BD> pos{w};
           const uint32_t tot = w.total();
           const uint32_t incl = wave_incl_scan_u32(tot);
           if (step == 0) {                                   // entries of the previous row land in front of column 0
@@ -341,14 +345,14 @@ decode_windows_kernel(const void* __restrict__ values, const uint32_t* __restric
               // previous row's entries put in front of a row that does not start on 16 bytes is not written out.
               unsigned char* p = win + ((uint32_t)(rel + kMargin) < (uint32_t)(kWindowBytes + kMargin) ? rel : -kMargin);
 #define MACKO_PUT(K)                                                                                          \
-  if (VB == 16) *reinterpret_cast<uint16_t*>(p + w.template offset<K>()) = (uint16_t)v.template bits<K>();      \
-  else p[w.template offset<K>() >> 1] = (unsigned char)v.template bits<K>();
+  if (VB == 16) *reinterpret_cast<uint16_t*>(p + pos.template offset<K>()) = (uint16_t)v.template bits<K>();      \
+  else p[pos.template offset<K>() >> 1] = (unsigned char)v.template bits<K>();
               MACKO_PUT(0) MACKO_PUT(1) MACKO_PUT(2) MACKO_PUT(3) MACKO_PUT(4) MACKO_PUT(5) MACKO_PUT(6) MACKO_PUT(7)
 #undef MACKO_PUT
             } else {
 #define MACKO_PUT(K)                                                                                          \
   {                                                                                                           \
-    const int q = rel + w.template offset<K>();                                                                \
+    const int q = rel + pos.template offset<K>();                                                                \
     if (e0 + K >= start && e0 + K < end && q >= 0 && q < kWindowBytes)                                         \
       *reinterpret_cast<uint16_t*>(win + q) = (uint16_t)v.template bits<K>();                                  \
   }

@@ -81,12 +81,13 @@ void block_trim(int device) {
 }
 
 hipError_t block_acquire(void** block, size_t bytes) {
+  const bool kept = block_is_kept(bytes);
   bytes = block_bytes(bytes);
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
-  const bool stored = bytes >= kStoredBlockMin && dev >= 0 && dev < 64;
-  if (stored) {
+  const bool counted = dev >= 0 && dev < 64;
+  if (kept && counted) {
     std::lock_guard<std::mutex> lock(g_store_mutex);
     BlockStore& s = g_store[dev];
     for (int i = s.n - 1; i >= 0; --i)
@@ -96,7 +97,7 @@ hipError_t block_acquire(void** block, size_t bytes) {
       }
   }
   e = hipMalloc(block, bytes);
-  if (e != hipSuccess && stored) {                      // what is kept may be what is missing
+  if (e != hipSuccess && counted) {                      // what is kept may be what is missing
     (void)hipGetLastError();
     block_trim(dev);
     e = hipMalloc(block, bytes);
@@ -105,9 +106,10 @@ hipError_t block_acquire(void** block, size_t bytes) {
 }
 
 void block_release(void* block, size_t bytes, int device, void* idle_probe) {
+  const bool kept = block_is_kept(bytes);
   bytes = block_bytes(bytes);
   const bool idle = idle_probe && hipFree(idle_probe) == hipSuccess;       // waits until the device is idle
-  if (!idle || bytes < kStoredBlockMin || bytes > kStoredBytes || device < 0 || device >= 64) {
+  if (!idle || !kept || device < 0 || device >= 64) {
     (void)hipFree(block);
     return;
   }
@@ -425,7 +427,11 @@ static int encode_device_any(const void* dense_dev, int64_t rows, int64_t cols, 
   m->owns_device = true;
   m->d_block = block;
   if (hipGetDevice(&m->d_block_device) != hipSuccess) m->d_block_device = -1;
-  if (hipMalloc(&m->d_idle_probe, 16) != hipSuccess) m->d_idle_probe = nullptr;      // the block is not kept then
+  if (macko::block_is_kept(macko::encoded_layout(rows, alloc, b_delta, b_val).total) &&
+      hipMalloc(&m->d_idle_probe, 16) != hipSuccess) {
+    (void)hipGetLastError();
+    m->d_idle_probe = nullptr;                          // the block is not kept then
+  }
   macko::fill_report(&m->report, rows, cols, nnz, pad, alloc, empty, longest, b_delta, b_val);
   if (report) *report = m->report;
   *out = m;

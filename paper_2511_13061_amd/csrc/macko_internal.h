@@ -172,6 +172,7 @@ constexpr size_t block_bytes(size_t bytes) {
   while (granule * 128 <= bytes) granule *= 2;
   return (bytes + granule - 1) / granule * granule;
 }
+constexpr bool block_is_kept(size_t bytes) { return block_bytes(bytes) >= kStoredBlockMin && block_bytes(bytes) <= kStoredBytes; }
 // A block of block_bytes(bytes) on the current device.  It is kept only with an idle_probe, a small allocation on its device, which goes with it.
 hipError_t block_acquire(void** block, size_t bytes);
 void block_release(void* block, size_t bytes, int device, void* idle_probe);

@@ -722,7 +722,7 @@ int macko_spmv_many(int64_t n, const macko_handle_t* handles, const void* const*
     return macko::SpmvProblem{h->d_values, h->d_deltas, h->d_row_ptr, h->rows, h->cols, h->pad_nnz,
                               x_dev[i], y_dev[i], h->b_delta, h->b_val};
   };
-  auto class_of = [](const macko::SpmvProblem& q) { return macko::spmv_launch_class(q, macko::wave_row_min_entries(q.rows, true)); };
+  auto class_of = [](const macko::SpmvProblem& q) { return macko::spmv_launch_class(q, macko::wave_row_min_entries(q, true)); };
   int launch_class = -1;
   int64_t wide_rows = 0;
   for (int64_t i = 0; i < n && launch_class != 0; ++i) {

@@ -106,10 +106,12 @@ int launch_spmv_group(int n, const SpmvProblem* problems, hipStream_t stream);
 // grouped: one of several products of a call, which the wave-per-row kernel takes in one launch (4 of 504 x 448 with 43 entries
 // 15.6 / 4.0, 4 of 2296 x 2248 with 187 20.3 / 6.4, 3 of 10000 x 1000 with 80 15.7 / 10.9; 84 of 1000 x 300 with 150 117 / 6.6).
 constexpr int64_t kWaveRowMinEntries = 192;            // where nothing more is known of the call
-inline int64_t wave_row_min_entries(int64_t rows, bool grouped) {
-  const int64_t per_cu = rows / device_cu_count();
+inline int64_t wave_row_min_entries(const SpmvProblem& p, bool grouped) {
+  constexpr int64_t kLargest = 240;
+  if (p.pad_nnz >= kLargest * p.rows) return kLargest;   // no need to ask which device it is (0.08 us of a small call's 3.4)
+  const int64_t per_cu = p.rows / device_cu_count();
   if (per_cu < 4 || (grouped && per_cu < 64)) return 1;
-  return per_cu < 32 ? 112 : per_cu < 48 ? 144 : 240;
+  return per_cu < 32 ? 112 : per_cu < 48 ? 144 : kLargest;
 }
 // Whether the product goes to the wave-per-row kernel (8-bit values: it has to).
 inline bool spmv_takes_wave_row(const SpmvProblem& p, int64_t min_entries = kWaveRowMinEntries) {

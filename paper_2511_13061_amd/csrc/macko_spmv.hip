@@ -171,17 +171,18 @@ struct SpmvGroupHeader {
 // neighbouring steps share lines).  The lanes of the first step that lie wholly before the row read nothing.
 //  - From kAlignMinEntries on: kStepAlign.  A row costs a quarter step more on average.  Measured on 36864 x 12288 from 25 % to 80 % sparsity:
 //    4-9 % faster than 8.  256 entries align the codes of 4-bit matrices to their 128-byte lines as well; 512 is no better.
-//  - Shorter rows: as large as leaves the number of steps alone, with a sixteenth of the row for its neighbours' lengths, and 32 at least.
-//    Time on 12288 x 4096, 8000 x 6000 and 30000 x 4096 with 260 to 1690 entries a row, all at 8 = 1: at 16 0.954, 32 0.945, 64 0.941, 128 0.949, 256
-//    0.968, 512 1.007, by this rule 0.927 (us, 8 / rule: 30000 x 4096 with 700 entries 15.3 / 12.7, 12288 x 12288 at 95 % 8.5 / 8.2, 11007 x 4093 at 60 %
-//    9.7 / 9.5; but 8000 x 6000 with 947 entries 5.70 / 5.70, at 256 6.15).
+//  - Shorter rows: as large as leaves the number of steps alone, with a sixteenth of the row for its neighbours' lengths.  Time on 12288 x 4096,
+//    8000 x 6000 and 30000 x 4096 with 260 to 1690 entries a row, all at 8 = 1: at 16 0.954, 32 0.945, 64 0.941, 128 0.949, 256 0.968, 512 1.007, by this
+//    rule 0.927 (us, 8 / rule: 30000 x 4096 with 700 entries 15.3 / 12.7, 12288 x 12288 at 95 % 8.5 / 8.2, 11007 x 4093 at 60 % 9.7 / 9.5).  Where the row
+//    fills its steps, any alignment makes one more of them: 14000 rows of 490, 990, 1490 entries at 8 / 16 / 32: 6.92 / 7.09 / 7.31, 8.31 / 8.36 / 8.69,
+//    10.32 / 10.38 / 10.41.
 constexpr int kStepAlign = 256;
 constexpr int64_t kAlignMinEntries = 1700;
 int step_align(int64_t entries_per_row) {
   int align = kStepAlign;
   if (entries_per_row < kAlignMinEntries) {
     const int64_t room = (entries_per_row + 511) / 512 * 512 - entries_per_row - entries_per_row / 16;
-    while (align > 32 && align - 8 > room) align /= 2;
+    while (align > 8 && align > room) align /= 2;
   }
   return align;
 }
@@ -1094,10 +1095,11 @@ int launch_spmv_chain(int n_phases, const int* sizes, const SpmvProblem* problem
 int launch_spmv_group(int n, const SpmvProblem* problems, hipStream_t stream) {
   if (n < 1 || n > kMaxWide) return MACKO_E_INVALID_ARG;
   const Tuning& t = tuning();
-  auto takes_wave_row = [&](const SpmvProblem& p) { return spmv_takes_wave_row(p, wave_row_min_entries(p.rows, n > 1)); };
+  bool wave_row[kMaxWide];
   // matrices that do not go into a grouped wave-per-row launch
   for (int i = 0; i < n; ++i) {
     const SpmvProblem& p = problems[i];
+    wave_row[i] = spmv_takes_wave_row(p, wave_row_min_entries(p, n > 1));
     if (p.rows == 0) continue;
     // the kernels index entries with 32 bits and look up to two steps past a row's end
     if (p.pad_nnz > (int64_t{1} << 32) - 4096) return MACKO_E_UNSUPPORTED;
@@ -1107,8 +1109,8 @@ int launch_spmv_group(int n, const SpmvProblem* problems, hipStream_t stream) {
       hipError_t e0 = hipGetLastError();
       if (e0 != hipSuccess) return hip_fail(e0);
     } else if (p.b_val == 8) {                          // 8-bit values: 4-bit codes, wave-per-row kernel only
-      if (!takes_wave_row(p)) return MACKO_E_UNSUPPORTED;
-    } else if (!takes_wave_row(p)) {             // short rows or x larger than LDS: own launch
+      if (!wave_row[i]) return MACKO_E_UNSUPPORTED;
+    } else if (!wave_row[i]) {                          // short rows or x larger than LDS: own launch
       int st = launch_subwave(p, (int)t.spmv_lanes, stream);
       if (st != MACKO_OK) return st;
     }
@@ -1118,7 +1120,7 @@ int launch_spmv_group(int n, const SpmvProblem* problems, hipStream_t stream) {
     const SpmvProblem* wr[kMaxWide];
     int nwr = 0;
     for (int i = 0; i < n; ++i)
-      if (problems[i].b_delta == bd && problems[i].b_val == 16 && takes_wave_row(problems[i])) wr[nwr++] = &problems[i];
+      if (problems[i].b_delta == bd && problems[i].b_val == 16 && wave_row[i]) wr[nwr++] = &problems[i];
     if (nwr == 0) continue;
     int st = launch_wave_row_group(nwr, wr, bd, 16, stream);
     if (st != MACKO_OK) return st;

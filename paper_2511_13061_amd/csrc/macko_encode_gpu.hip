@@ -28,15 +28,11 @@ struct EncodeStats {
   unsigned int empty_rows;
   unsigned int max_row_entries;
 };
-// The host's view of an encoding, in pinned memory: the totals, and the number of the last step that is over.
+// The host's view of an encoding, in pinned memory: the counting pass's totals, and the number of the last encoding that is over.
 struct EncodeReport {
   EncodeStats stats;
-  uint32_t step;
+  uint32_t done;
 };
-// Everything before it on the stream is over when the host reads `step`.
-__device__ __forceinline__ void report_step(EncodeReport* report, uint32_t step) {
-  __hip_atomic_store(&report->step, step, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
 
 // 8 consecutive columns of one row as loaded: fp16 values, or bytes (8-bit values).
 template <bool IN8>
@@ -297,7 +293,7 @@ template <bool FUSED>
 __global__ void __launch_bounds__(1024)
 encode_block_offsets_kernel(const BlockSums* __restrict__ sums, const uint32_t* __restrict__ row_entries,
                             const uint32_t* __restrict__ row_nnz, int rows, int nblocks,
-                            unsigned long long* __restrict__ block_off, EncodeReport* report, uint32_t step) {
+                            unsigned long long* __restrict__ block_off, EncodeReport* __restrict__ report) {
   __shared__ BlockSums fused[FUSED ? kFusedBlocks : 1];
   if (FUSED) {
     const int lane = threadIdx.x & 63;
@@ -377,12 +373,12 @@ encode_block_offsets_kernel(const BlockSums* __restrict__ sums, const uint32_t* 
       mx = max(mx, s_long[i]);
     }
     report->stats = EncodeStats{nn, carry_s, em, mx};
-    report_step(report, step);
   }
 }
 
-__global__ void __launch_bounds__(64) encode_done_kernel(EncodeReport* report, uint32_t step) {
-  if (threadIdx.x == 0) report_step(report, step);
+// Everything before it on the stream is over when the host reads `number`.
+__global__ void __launch_bounds__(64) encode_done_kernel(EncodeReport* report, uint32_t number) {
+  if (threadIdx.x == 0) __hip_atomic_store(&report->done, number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 __global__ void __launch_bounds__(1024)
@@ -595,7 +591,7 @@ struct Workspace {
   void* p = nullptr;
   size_t cap = 0;
   EncodeReport* report = nullptr;   // host, pinned: the kernels report through it
-  uint32_t steps = 0;
+  uint32_t encodings = 0;
 };
 std::mutex g_ws_mutex;
 Workspace g_ws[64];
@@ -624,14 +620,18 @@ auto count_kernel(bool in8, int b_delta) {
                                                                              : encode_count_kernel<false, WIDE, 1>;
 }
 
-// Waits until the stream has come to the report of step `step`.  Looked at by the host itself the report is seen 5.9 us after a launch,
+// Waits until the stream has come to the end of encoding `number`.  Looked at by the host itself it is seen 5.9 us after a launch,
 // hipStreamSynchronize returns after 11.4.  The look ends after 2 ms, then the runtime waits (and says what is wrong, if the
-// report never comes).
-hipError_t wait_for_step(const EncodeReport* report, uint32_t step, hipStream_t stream) {
+// number never comes).  Only the last wait of an encoding is of this kind: the runtime does not learn from it that the launches are over, and
+// where more than about 8 of them pile up a program's next synchronization takes it 16 us longer and the launches after it 1 to 2 us each
+// (512 x 512, us: 4 kernels of the caller, encoding, 1 kernel, synchronization, product and synchronization: both waits by the runtime 21 + 43
+// + 7 + 12 + 18, both by the host 25 + 34 + 7 + 28 + 20, the first by the runtime and the last by the host 21 + 39 + 7 + 12 + 18; the encoding of 4096 x
+// 4096 158 / 122 / 128, most of that from the kept blocks).
+hipError_t wait_for_encoding(const EncodeReport* report, uint32_t number, hipStream_t stream) {
   const auto begin = std::chrono::steady_clock::now();
   do {
     for (int i = 0; i < 64; ++i) {
-      if (__atomic_load_n(&report->step, __ATOMIC_ACQUIRE) == step) return hipSuccess;
+      if (__atomic_load_n(&report->done, __ATOMIC_ACQUIRE) == number) return hipSuccess;
       __builtin_ia32_pause();
     }
   } while (std::chrono::steady_clock::now() - begin < std::chrono::milliseconds(2));
@@ -702,9 +702,9 @@ int encode_on_device(const void* dense, int64_t rows, int64_t cols, int64_t ld, 
   hipLaunchKernelGGL(nblocks > kFusedBlocks ? encode_block_offsets_kernel<false> : encode_block_offsets_kernel<true>,
                      dim3(1), dim3(1024), 0, stream, static_cast<const BlockSums*>(sums),
                      static_cast<const uint32_t*>(counts), static_cast<const uint32_t*>(nnzs), (int)rows, (int)nblocks,
-                     boff, ws.report, ++ws.steps);
+                     boff, ws.report);
   MACKO_HIP_TRY(hipGetLastError());
-  MACKO_HIP_TRY(wait_for_step(ws.report, ws.steps, stream));
+  MACKO_HIP_TRY(hipStreamSynchronize(stream));
   const EncodeStats st = ws.report->stats;
   if (st.pad_nnz >= (1ull << 32)) return MACKO_E_OVERFLOW;
   const int64_t pad = (int64_t)st.pad_nnz;
@@ -740,9 +740,9 @@ int encode_on_device(const void* dense, int64_t rows, int64_t cols, int64_t ld, 
     hipLaunchKernelGGL(kfill, dim3(grid), dim3(64 * kFillWaves), 0, stream, dense, (uint32_t)rows, (uint32_t)cols, ld,
                        static_cast<const uint32_t*>(rp), vals, dels, (uint32_t)pad, (uint32_t)alloc);
   }
-  hipLaunchKernelGGL(encode_done_kernel, dim3(1), dim3(64), 0, stream, ws.report, ++ws.steps);
+  hipLaunchKernelGGL(encode_done_kernel, dim3(1), dim3(64), 0, stream, ws.report, ++ws.encodings);
   MACKO_HIP_TRY(hipGetLastError());
-  MACKO_HIP_TRY(wait_for_step(ws.report, ws.steps, stream));
+  MACKO_HIP_TRY(wait_for_encoding(ws.report, ws.encodings, stream));
   // a large scratch buffer is not kept (from 6.7 M rows on: 8 bytes per row and a quarter more)
   if (ws.cap > kKeepScratchBytes) {
     (void)hipFree(ws.p);

@@ -43,7 +43,7 @@ int device_cu_count() {
 
 // ---- blocks of the encoder's handles ----------------------------------------
 // hipMalloc and hipFree of a large block take about 25 and 30 us around kernels of 90 (11008 x 4096 at 50 %, encoded, expanded and
-// destroyed: 159 us, with kept blocks 117).  A released block is kept once the device is idle: a handle may be in use on streams that
+// destroyed: 159 us, with kept blocks 117, with the encoder's waits as they are now 122 to 127).  A released block is kept once the device is idle: a handle may be in use on streams that
 // the library does not know, and whoever takes the block next, on whatever stream, has to have it alone.  The wait is that of hipFree,
 // on a small allocation that came with the block: 0.4 us where there is nothing to wait for, and allowed wherever destroying a handle
 // always was (hipDeviceSynchronize invalidates a relaxed capture, hipFree does not).

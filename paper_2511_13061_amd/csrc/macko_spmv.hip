@@ -862,10 +862,11 @@ int launch_wave_row_group(int nwr, const SpmvProblem* const* wr, int b_delta, in
   // they need no further step but for the chunk that a start inside a chunk pushes behind the last one.  Lane i of the
   // wavefront takes row i's chunk, all of them at once behind the last row (TAILS).  Time against steps on kStepAlign over 399 launches of
   // 1500 to 22016 rows, by the entries per row, the same number in each: 2048 - 15 ... 2048 - 1 0.92, 2048 0.96, 2049 0.97, 2050 and
-  // 2051 1.01, 2053 to 2064 1.02; 4096 - 15 ... 4096 0.94, 4099 to 4107 1.02; 6144 - 15 ... - 2 0.97, 6144 1.01 (11008 x 4096: 11.5 ->
-  // 10.7 us, 22016 x 4096 17.2 -> 16.4).  So not above one entry more than whole steps.  iid masks, which the average does not tell apart,
-  // 1.00 to 1.02.  With 16-bit values steps on whole lines are worth more (11008 x 4096: 12.7, with tails 13.5), and where there are
-  // hardly any tails the code for them costs up to 3 %.
+  // 2051 1.01, 2053 to 2064 1.02; 4096 - 15 ... 4096 0.94, 4099 to 4107 1.02; 6144 - 15 ... - 2 0.97, 6144 1.01 (measured with rows read by
+  // clamped addresses; read as buffers 11008 x 4096 10.0 -> 9.25 us).  So not above one entry more than whole steps.  iid masks, which the
+  // average does not tell apart, 1.00 to 1.02.  With 16-bit values steps on whole lines are worth more but for the smallest (us without /
+  // with tails: 4096 x 4096 5.74 / 5.53, 11008 x 4096 11.48 / 11.75, 28672 x 8192 45.6 / 48.8), and where there are hardly any tails the code for
+  // them costs up to 3 %.
   const bool tails = in_step && whole_steps && b_val == 8 && nwr <= kMaxGroup;
 
   SpmvWideArgs wide_args;                              // filled in for more than kMaxGroup matrices only

@@ -259,11 +259,11 @@ template <int BD, int VB>
 struct EntryBuffers {
   __amdgpu_buffer_rsrc_t values, codes;
   __device__ __forceinline__ void open(const void* v, const uint32_t* d, uint32_t c0, uint32_t end) {
-    const uint32_t n = end - (c0 << 3);
+    const uint32_t n = buffer_entries(c0, end);
     unsigned char* vb = const_cast<unsigned char*>(static_cast<const unsigned char*>(v)) + (uint64_t)VB * c0;
     unsigned char* cb = const_cast<unsigned char*>(reinterpret_cast<const unsigned char*>(d)) + (uint64_t)BD * c0;
-    values = __builtin_amdgcn_make_buffer_rsrc(vb, 0, (int)((n * (VB / 8) + 3u) & ~3u), 0x00020000);
-    codes = __builtin_amdgcn_make_buffer_rsrc(cb, 0, (int)(((n + 7u) >> 3) * BD), 0x00020000);
+    values = __builtin_amdgcn_make_buffer_rsrc(vb, 0, (int)buffer_value_bytes(n, VB), 0x00020000);
+    codes = __builtin_amdgcn_make_buffer_rsrc(cb, 0, (int)buffer_code_bytes(n, BD), 0x00020000);
   }
 };
 

@@ -122,34 +122,14 @@ __device__ __forceinline__ float f16_bits_to_f32(uint16_t b) {
 
 // ---- row cursor of the wavefront-per-row kernels ------------------------------
 // A wavefront keeps the pointers of its (at most 64) rows in two registers, lane i
-// holding row i's; the scalar bounds of the current row are read out of them.
-struct RowCursor {
-  int i;               // row index within the block (== nb when exhausted)
-  uint32_t start, end; // its entry range
-  uint32_t a0;         // start rounded down to ALIGN entries: where the row's first step begins
-  int nsteps, step;
-};
-
-// Move the cursor to the first non-empty row at or after cur.i.  Only lanes
-// below nb hold pointers of the wavefront's rows; others are never selected.
-// amask + 1 is the alignment of the row's first step in entries: 8 is the reverse-offset
-// alignment of the paper (a lane's 16-byte chunk never straddles the row start); larger powers
-// of two up to 512 make every step of the row begin on a multiple of that many entries.
-// TAILS: a last step of one chunk (behind at least one other step) is left out, see row_tail.
+// holding row i's; the scalar bounds of the current row are read out of them (RowCursor and seek_row stand in macko_internal.h,
+// where the host can run them too).  Only lanes below nb hold pointers of the wavefront's rows; others are never selected.
 template <bool TAILS = false>
 __device__ __forceinline__ void seek_nonempty(RowCursor& cur, int nb, uint32_t rp_lo, uint32_t rp_hi,
                                               uint32_t amask = 7u) {
-  cur.start = cur.end = 0;
-  while (cur.i < nb) {
-    cur.start = (uint32_t)__builtin_amdgcn_readlane((int)rp_lo, cur.i);
-    cur.end = (uint32_t)__builtin_amdgcn_readlane((int)rp_hi, cur.i);
-    if (cur.end > cur.start) break;
-    ++cur.i;
-  }
-  cur.a0 = cur.start & ~amask;
-  const uint32_t len = cur.end - cur.a0;
-  cur.nsteps = (int)((len + 511u - (TAILS && len > 512u ? 8u : 0u)) >> 9);
-  cur.step = 0;
+  seek_row<TAILS>(
+      cur, nb, [=](int i) { return (uint32_t)__builtin_amdgcn_readlane((int)rp_lo, i); },
+      [=](int i) { return (uint32_t)__builtin_amdgcn_readlane((int)rp_hi, i); }, amask);
 }
 
 // Entries of a row that lie in the one chunk of a step that seek_nonempty<true> has left out (0: there is no such step).

@@ -148,6 +148,46 @@ bool spmm_tile_pairs_groups(const SpmvProblem& p, int batch);      // two groups
 constexpr uint32_t panel_row_units(uint32_t start, uint32_t end, uint32_t per_unit) {
   return end > start ? (end - (start & ~7u) + per_unit - 1u) / per_unit : 1u;
 }
+// ---- rows of the vector kernels ------------------------------------------------
+struct RowCursor {
+  int i;               // row index within the wavefront's rows (== nb when exhausted)
+  uint32_t start, end; // its entry range
+  uint32_t a0;         // start rounded down to the alignment: where the row's first step begins
+  int nsteps, step;
+};
+// Move the cursor to the first non-empty row at or after cur.i of nb, whose pointers lo(i) and hi(i) give.
+// amask + 1 is the alignment of the row's first step in entries: 8 is the reverse-offset
+// alignment of the paper (a lane's 16-byte chunk never straddles the row start); larger powers
+// of two up to 512 make every step of the row begin on a multiple of that many entries.
+// TAILS: a last step of one chunk (behind at least one other step) is left out, see row_tail.
+// Behind the last row the range is empty, at entry 0, whatever the last pointers are: the buffer opened on it (buffer_entries) holds nothing.
+// Left as they are, pointers that decrease there (no encoding's) made one of 2^32 entries.
+template <bool TAILS, class Lo, class Hi>
+__attribute__((always_inline)) constexpr void seek_row(RowCursor& cur, int nb, const Lo& lo, const Hi& hi, uint32_t amask) {
+  cur.start = cur.end = 0;
+  while (cur.i < nb) {
+    cur.start = lo(cur.i);
+    cur.end = hi(cur.i);
+    if (cur.end > cur.start) break;
+    ++cur.i;
+    cur.start = cur.end = 0;
+  }
+  cur.a0 = cur.start & ~amask;
+  const uint32_t len = cur.end - cur.a0;
+  cur.nsteps = (int)((len + 511u - (TAILS && len > 512u ? 8u : 0u)) >> 9);
+  cur.step = 0;
+}
+// What the buffers hold that these kernels read a row through, from chunk c0 (8 entries, the row's first or an earlier one) to entry `end`:
+// entries, and their bytes (ends are checked per 4 bytes, and codes are read by chunks).
+constexpr uint32_t buffer_entries(uint32_t c0, uint32_t end) { return end - (c0 << 3); }
+constexpr uint32_t buffer_value_bytes(uint32_t entries, int b_val) { return (entries * (uint32_t)(b_val / 8) + 3u) & ~3u; }
+constexpr uint32_t buffer_code_bytes(uint32_t entries, int b_delta) { return ((entries + 7u) >> 3) * (uint32_t)b_delta; }
+// The tails of 8-bit rows are read through the arrays as a whole: a lane that has one reads the last chunk of its own row, wherever that is;
+// the others, at the last chunk below 2^32 bytes, are behind the end (the launchers take fewer than 2^32 - 4096 entries).
+struct TailBuffer {
+  uint32_t c0, end;
+};
+constexpr TailBuffer tail_buffer() { return {0u, 0xFFFFFFE0u}; }
 int launch_spmm_tile(const SpmvProblem& p, const uint16_t* X, int64_t ldx, uint16_t* Y, int64_t ldy, int batch,
                      hipStream_t stream);
 // bytes of the encoder's block: values, codes and row pointers, each from a multiple of 256 bytes on

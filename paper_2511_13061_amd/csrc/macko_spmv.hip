@@ -242,10 +242,10 @@ __device__ __forceinline__ bool spmv_wave_row_body(const void* __restrict__ valu
   int lane_v = VB * lane, lane_c = BD * lane;
   int next_v = 64 * VB, next_c = 64 * BD;              // from a step to the next
   auto open_row = [&]() {
-    if (TAILS && ld.i >= nb) {                         // behind the last row: the wavefront's rows are one buffer, lane i reads row i's tail
-      const uint32_t c0 = (uint32_t)__builtin_amdgcn_readlane((int)rp_lo, 0) >> 3;
-      row.open(values, deltas, c0, (uint32_t)__builtin_amdgcn_readlane((int)rp_hi, max(nb - 1, 0)));
-      const uint32_t chunk = ((rp_hi - 1u) >> 3) - c0;
+    if (TAILS && ld.i >= nb) {                         // behind the last row: lane i reads row i's tail
+      static_assert(!TAILS || VB == 8, "a byte to a value: the arrays as a whole are one buffer");
+      row.open(values, deltas, tail_buffer().c0, tail_buffer().end);
+      const uint32_t chunk = (rp_hi - 1u) >> 3;
       lane_v = tail != 0u ? (int)(VB * chunk) : -VB;
       lane_c = tail != 0u ? (int)(BD * chunk) : -BD;
       at_v = at_c = next_v = next_c = 0;

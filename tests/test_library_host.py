@@ -347,6 +347,100 @@ int main() {
     assert out.returncode == 0 and out.stdout == "ok\n", out.stdout
 
 
+def test_row_buffers_stay_inside_the_arrays(tmp_path):
+    """The product kernels read a row through buffers whose ends come from its pointers.  Replayed here for a wavefront's rows, empty ones among
+    them and (trusted input, but no reason to read outside the arrays) pointers that decrease: what a lane requests, in a step, behind
+    the last row or for a row's tail, is behind the buffer's end or inside the arrays."""
+    import shutil
+    import subprocess
+    from paper_2511_13061_amd import build as B
+    if not shutil.which("g++") or not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"):
+        pytest.skip("needs g++ and the HIP headers")
+    src, exe = tmp_path / "rows.cpp", tmp_path / "rows"
+    src.write_text(r"""
+#include <cstdio>
+#include <cstdlib>
+#include <algorithm>
+#include <random>
+#include <vector>
+#include "macko_internal.h"
+using namespace macko;
+static int64_t pad_nnz;
+static const char* what;
+// one lane's load of `size` bytes at `at` of a buffer of `records` bytes that begins `base` bytes into an array of `bytes`
+static void load(uint64_t base, uint32_t at, uint32_t records, int size, uint64_t bytes) {
+  for (int k = 0; k < size; k += 4) {
+    const uint64_t end = (uint64_t)at + k + std::min(size, 4);
+    if (end > records) continue;                              // reads as zero
+    if (base + end > bytes) std::printf("%s: %llu + %u of %llu\n", what, (unsigned long long)base, at, (unsigned long long)bytes), std::exit(1);
+  }
+}
+struct Row { uint32_t start, end; };
+template <bool TAILS>
+static void wavefront(const std::vector<Row>& rows, uint32_t amask, int b_delta, int b_val, int ahead) {
+  const int64_t alloc = (pad_nnz + alloc_granule(b_delta) - 1) / alloc_granule(b_delta) * alloc_granule(b_delta);
+  const uint64_t vbytes = (uint64_t)alloc * (b_val / 8), cbytes = (uint64_t)alloc * b_delta / 8;
+  auto lo = [&](int i) { return rows[i].start; };
+  auto hi = [&](int i) { return rows[i].end; };
+  const int nb = (int)rows.size();
+  RowCursor cur{};
+  seek_row<TAILS>(cur, nb, lo, hi, amask);
+  for (int behind = 0; behind < ahead;) {                     // every step, and as many items behind the last row as a wavefront requests
+    if (TAILS && cur.i >= nb) break;
+    const uint32_t c0 = cur.start >> 3, n = buffer_entries(c0, cur.end), skipped = c0 - (cur.a0 >> 3);
+    const uint32_t step = cur.i < nb ? (uint32_t)cur.step : (uint32_t)behind++;
+    for (uint32_t lane = 0; lane < 64; ++lane) {
+      load((uint64_t)b_val * c0, (uint32_t)b_val * (64 * step + lane - skipped), buffer_value_bytes(n, b_val), b_val, vbytes);
+      load((uint64_t)b_delta * c0, (uint32_t)b_delta * (64 * step + lane - skipped), buffer_code_bytes(n, b_delta), b_delta, cbytes);
+    }
+    if (cur.i < nb && ++cur.step == cur.nsteps) {
+      ++cur.i;
+      seek_row<TAILS>(cur, nb, lo, hi, amask);
+    }
+  }
+  if (!TAILS) return;
+  const uint32_t n = buffer_entries(tail_buffer().c0, tail_buffer().end);
+  for (const Row& r : rows) {                                 // behind the last row: every lane its row's last chunk, or nothing
+    const uint32_t chunk = (r.end - 1u) >> 3;
+    const bool has = r.end > r.start;
+    load(0, has ? b_val * chunk : 0u - b_val, buffer_value_bytes(n, b_val), b_val, vbytes);
+    load(0, has ? b_delta * chunk : 0u - b_delta, buffer_code_bytes(n, b_delta), b_delta, cbytes);
+  }
+}
+int main() {
+  std::mt19937_64 rng(7);
+  for (int trial = 0; trial < 4000; ++trial) {
+    std::vector<uint32_t> rp(2 + rng() % 64);
+    const bool far = trial % 3 == 0;                          // entries from 2^32 - 20000 on, as far as the launchers go
+    const uint32_t first = far ? 4294947300u : 0u;
+    pad_nnz = far ? 4294963200ll : 16000 - (int64_t)(rng() % 40);
+    const uint32_t room = (uint32_t)(pad_nnz - first);
+    for (uint32_t& p : rp) p = first + (uint32_t)(rng() % (room + 1));
+    if (trial % 2) std::sort(rp.begin(), rp.end());
+    for (size_t i = 1; i < rp.size(); ++i)
+      if (rng() % 3 == 0) rp[i] = rp[i - 1];
+    if (rng() % 2) rp.back() = first + room;
+    if (rng() % 4 == 0) rp.back() = first + (uint32_t)(rng() % 200);
+    std::vector<Row> rows;
+    for (size_t i = 0; i + 1 < rp.size(); ++i) rows.push_back({rp[i], rp[i + 1]});
+    for (uint32_t amask : {7u, 31u, 255u, 511u})
+      for (int b_delta : {1, 2, 4, 8})
+        for (int b_val : {16, 8}) {
+          what = b_val == 8 ? "8-bit values" : "16-bit values";
+          if (b_val == 8 && b_delta != 4) continue;
+          wavefront<false>(rows, amask, b_delta, b_val, 4);
+          if (b_val == 8) wavefront<true>(rows, amask, b_delta, b_val, 4);
+        }
+  }
+  std::puts("ok");
+}
+""")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-w", "-I/opt/rocm/include", "-I", os.path.join(ROOT, "include"),
+                           "-I", B.CSRC, str(src), "-o", str(exe)])
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert out.returncode == 0 and out.stdout == "ok\n", out.stdout
+
+
 def test_host_code_under_address_and_undefined_behaviour_sanitizers(tmp_path):
     """The library's host translation unit (encoders for every code and value width, decoders, storage
     report, argument checks) linked with stand-ins for the GPU launchers and run under ASan + UBSan on

@@ -648,13 +648,9 @@ int macko_decode_device(macko_handle_t h, void* dense_dev, int64_t ld, void* str
   return macko::launch_decode(p, dense_dev, ld, static_cast<hipStream_t>(stream));
 }
 
-int macko_spmv(macko_handle_t h, const void* x_dev, void* y_dev, void* stream) {
-  return macko_spmv_group(1, &h, &x_dev, &y_dev, stream);
-}
-
-int macko_spmv_group(int n, const macko_handle_t* handles, const void* const* x_dev, void* const* y_dev,
-                     void* stream) {
-  if (n < 1 || n > MACKO_MAX_GROUP || !handles || !x_dev || !y_dev) return MACKO_E_INVALID_ARG;
+// one grouped launch of a call of `in_call` products
+static int spmv_group_of(int n, const macko_handle_t* handles, const void* const* x_dev, void* const* y_dev, int64_t in_call,
+                         void* stream) {
   macko::SpmvProblem p[MACKO_MAX_GROUP];
   int m = 0;
   for (int i = 0; i < n; ++i) {
@@ -668,7 +664,17 @@ int macko_spmv_group(int n, const macko_handle_t* handles, const void* const* x_
                                 x_dev[i], y_dev[i], h->b_delta, h->b_val};
   }
   if (m == 0) return MACKO_OK;
-  return macko::launch_spmv_group(m, p, static_cast<hipStream_t>(stream));
+  return macko::launch_spmv_group(m, p, in_call, static_cast<hipStream_t>(stream));
+}
+
+int macko_spmv(macko_handle_t h, const void* x_dev, void* y_dev, void* stream) {
+  return spmv_group_of(1, &h, &x_dev, &y_dev, 1, stream);
+}
+
+int macko_spmv_group(int n, const macko_handle_t* handles, const void* const* x_dev, void* const* y_dev,
+                     void* stream) {
+  if (n < 1 || n > MACKO_MAX_GROUP || !handles || !x_dev || !y_dev) return MACKO_E_INVALID_ARG;
+  return spmv_group_of(n, handles, x_dev, y_dev, n, stream);
 }
 
 namespace {
@@ -722,7 +728,7 @@ int macko_spmv_many(int64_t n, const macko_handle_t* handles, const void* const*
     return macko::SpmvProblem{h->d_values, h->d_deltas, h->d_row_ptr, h->rows, h->cols, h->pad_nnz,
                               x_dev[i], y_dev[i], h->b_delta, h->b_val};
   };
-  auto class_of = [](const macko::SpmvProblem& q) { return macko::spmv_launch_class(q, macko::wave_row_min_entries(q, true)); };
+  auto class_of = [n](const macko::SpmvProblem& q) { return macko::spmv_launch_class(q, macko::wave_row_min_entries(q, n)); };
   int launch_class = -1;
   int64_t wide_rows = 0;
   for (int64_t i = 0; i < n && launch_class != 0; ++i) {
@@ -748,7 +754,7 @@ int macko_spmv_many(int64_t n, const macko_handle_t* handles, const void* const*
           if (!apart || (class_of(p[m]) & 1) == pass) ++m;
         }
         if (m == macko::kMaxWide || (m > 0 && i == n - 1)) {
-          const int st = macko::launch_spmv_group(m, p, static_cast<hipStream_t>(stream));
+          const int st = macko::launch_spmv_group(m, p, n, static_cast<hipStream_t>(stream));
           if (st != MACKO_OK) return st;
           m = 0;
         }
@@ -770,7 +776,7 @@ int macko_spmv_many(int64_t n, const macko_handle_t* handles, const void* const*
   int turn = 0;
   for (int64_t at = 0; at < n && result == MACKO_OK; at += MACKO_MAX_GROUP, ++turn) {
     const int count = (int)std::min<int64_t>(MACKO_MAX_GROUP, n - at);
-    result = macko_spmv_group(count, handles + at, x_dev + at, y_dev + at, ms->side[turn % kManyStreams]);
+    result = spmv_group_of(count, handles + at, x_dev + at, y_dev + at, n, ms->side[turn % kManyStreams]);
   }
   // join, also after a failed launch: the caller's stream continues once every side stream is done
   for (int i = 0; i < kManyStreams; ++i) {

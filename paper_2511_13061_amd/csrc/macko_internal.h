@@ -97,20 +97,22 @@ struct GemvProblem {
   const void* x;
   void* y;
 };
-// n independent products, as few kernel launches as the shapes allow (1 <= n <= kMaxGroup; kMaxWide for the sparse product)
-int launch_spmv_group(int n, const SpmvProblem* problems, hipStream_t stream);
+// n independent products, as few kernel launches as the shapes allow (1 <= n <= kMaxGroup; kMaxWide for the sparse product).
+// in_call: products of the caller's call, which may take several launches (n <= in_call).  The kernel is chosen by it and not by n, so that
+// a product takes the same one in whichever launch of the call it lands.
+int launch_spmv_group(int n, const SpmvProblem* problems, int64_t in_call, hipStream_t stream);
 // Stored entries per row on average from which a product takes the wave-per-row kernel.  A row takes a wavefront one step of up to 512
 // entries, however short it is; the sub-wave kernel takes its rows 4 at a time, but one launch to a product, whose start is longer.
 // us, sub-wave / wave-per-row, rows x entries per row: 1000 x 40 3.1 / 2.8, x 220 4.4 / 2.7; 5000 x 40 3.5 / 4.5, x 130 5.1 / 4.6; 8192 x 100 4.8 / 4.8, x 150
 // 5.2 / 4.5; 12000 x 100 5.3 / 6.0, x 150 6.0 / 5.6; 20000 x 150 6.6 / 7.8, x 250 8.0 / 8.7, x 300 9.8 / 7.9; 36000 x 220 10.4 / 10.8, x 250 12.8 / 11.8.
-// grouped: one of several products of a call, which the wave-per-row kernel takes in one launch (4 of 504 x 448 with 43 entries
+// in_call > 1: one of several products of a call, which the wave-per-row kernel takes in one launch (4 of 504 x 448 with 43 entries
 // 15.6 / 4.0, 4 of 2296 x 2248 with 187 20.3 / 6.4, 3 of 10000 x 1000 with 80 15.7 / 10.9; 84 of 1000 x 300 with 150 117 / 6.6).
 constexpr int64_t kWaveRowMinEntries = 192;            // where nothing more is known of the call
-inline int64_t wave_row_min_entries(const SpmvProblem& p, bool grouped) {
+inline int64_t wave_row_min_entries(const SpmvProblem& p, int64_t in_call) {
   constexpr int64_t kLargest = 240;
   if (p.pad_nnz >= kLargest * p.rows) return kLargest;   // no need to ask which device it is (0.08 us of a small call's 3.4)
   const int64_t per_cu = p.rows / device_cu_count();
-  if (per_cu < 4 || (grouped && per_cu < 64)) return 1;
+  if (per_cu < 4 || (in_call > 1 && per_cu < 64)) return 1;
   return per_cu < 32 ? 112 : per_cu < 48 ? 144 : kLargest;
 }
 // Whether the product goes to the wave-per-row kernel (8-bit values: it has to).

@@ -448,7 +448,7 @@ int launch_spmm(const SpmvProblem& p, const void* X, int64_t ldx, void* Y, int64
         q[i].x = Xb + (int64_t)i * ldx;
         q[i].y = Yb + (int64_t)i * ldy;
       }
-      st = launch_spmv_group(take, q, stream);
+      st = launch_spmv_group(take, q, batch, stream);
     }
     if (st != MACKO_OK) return st;
     done += take;

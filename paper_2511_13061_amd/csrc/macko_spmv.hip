@@ -1093,14 +1093,14 @@ int launch_spmv_chain(int n_phases, const int* sizes, const SpmvProblem* problem
   return e == hipSuccess ? MACKO_OK : hip_fail(e);
 }
 
-int launch_spmv_group(int n, const SpmvProblem* problems, hipStream_t stream) {
-  if (n < 1 || n > kMaxWide) return MACKO_E_INVALID_ARG;
+int launch_spmv_group(int n, const SpmvProblem* problems, int64_t in_call, hipStream_t stream) {
+  if (n < 1 || n > kMaxWide || n > in_call) return MACKO_E_INVALID_ARG;
   const Tuning& t = tuning();
   bool wave_row[kMaxWide];
   // matrices that do not go into a grouped wave-per-row launch
   for (int i = 0; i < n; ++i) {
     const SpmvProblem& p = problems[i];
-    wave_row[i] = spmv_takes_wave_row(p, wave_row_min_entries(p, n > 1));
+    wave_row[i] = spmv_takes_wave_row(p, wave_row_min_entries(p, in_call));
     if (p.rows == 0) continue;
     // the kernels index entries with 32 bits and look up to two steps past a row's end
     if (p.pad_nnz > (int64_t{1} << 32) - 4096) return MACKO_E_UNSUPPORTED;

@@ -12,7 +12,7 @@ namespace macko {
   std::fprintf(stderr, "host sanitizer check reached the GPU launcher %s\n", what);
   std::abort();
 }
-int launch_spmv_group(int, const SpmvProblem*, hipStream_t) { unreachable("launch_spmv_group"); }
+int launch_spmv_group(int, const SpmvProblem*, int64_t, hipStream_t) { unreachable("launch_spmv_group"); }
 int launch_gemv_group(int, const GemvProblem*, hipStream_t) { unreachable("launch_gemv_group"); }
 int launch_spmv_chain(int, const int*, const SpmvProblem*, uint32_t*, uint32_t, hipStream_t) {
   unreachable("launch_spmv_chain");

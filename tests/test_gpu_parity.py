@@ -165,6 +165,34 @@ def test_short_rows_on_either_side_of_the_choice_of_kernel(b_delta, rows, entrie
             assert torch.equal(mats[0].spmv(xs[0]), ys[0])
 
 
+@pytest.mark.parametrize("kind", ["all alike", "two kinds", "batch"])
+@pytest.mark.parametrize("rows,entries", [(2000, 60), (300, 30), (9000, 90), (20000, 150)])
+def test_short_rows_give_equal_bits_in_every_launch_of_a_call(rows, entries, kind):
+    """One matrix and one vector, 33 times in a call: a launch of 32 and one of 1, or (with a second kind of matrix among them) launches of 8
+    and one of 1 on side streams; nine equal vectors of a batch: products in groups of 8 and 1.  All results are the same bit for bit."""
+    gen = torch.Generator(device="cuda").manual_seed(rows)
+    cols = 8 * entries
+    W = torch.randn((rows, cols), generator=gen, device="cuda").half() * (torch.rand((rows, cols), generator=gen, device="cuda") < 0.125)
+    x = torch.randn(cols, generator=gen, device="cuda").half()
+    m = M.encode_device(W)
+    want, scale = W.double() @ x.double(), W.double().abs() @ x.double().abs()
+    if kind == "batch":
+        M.set_tuning("spmm_kernel", 1)
+        try:
+            ys = list(m.spmm(x.expand(9, cols).contiguous()))
+        finally:
+            M.set_tuning("spmm_kernel", 0)
+    else:
+        other = M.encode_device(W, b_delta=8)
+        mats = [other if kind == "two kinds" and i % 5 == 4 else m for i in range(33)]
+        ys = [torch.full((rows,), float("nan"), dtype=torch.float16, device="cuda") for _ in mats]
+        M.SpmvMany(mats, [x] * 33, ys).launch()
+        ys = [y for y, o in zip(ys, mats) if o is m]
+    for i, y in enumerate(ys):
+        assert torch.equal(y, ys[0]), i
+    assert bool(((ys[0].double() - want).abs() <= 1e-3 * scale + 1e-3).all())
+
+
 @pytest.mark.parametrize("batch", [2, 3, 5, 8, 13, 64])
 @pytest.mark.parametrize("rows,cols", [(2047, 512), (2048, 512), (2300, 520), (2300, 523), (3000, 8)])
 def test_spmm_short_rows_with_8_bit_codes(rows, cols, batch):

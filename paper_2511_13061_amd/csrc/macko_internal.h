@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <vector>
 
@@ -103,17 +104,24 @@ struct GemvProblem {
 int launch_spmv_group(int n, const SpmvProblem* problems, int64_t in_call, hipStream_t stream);
 // Stored entries per row on average from which a product takes the wave-per-row kernel.  A row takes a wavefront one step of up to 512
 // entries, however short it is; the sub-wave kernel takes its rows 4 at a time, but one launch to a product, whose start is longer.
-// us, sub-wave / wave-per-row, rows x entries per row: 1000 x 40 3.1 / 2.8, x 220 4.4 / 2.7; 5000 x 40 3.5 / 4.5, x 130 5.1 / 4.6; 8192 x 100 4.8 / 4.8, x 150
-// 5.2 / 4.5; 12000 x 100 5.3 / 6.0, x 150 6.0 / 5.6; 20000 x 150 6.6 / 7.8, x 250 8.0 / 8.7, x 300 9.8 / 7.9; 36000 x 220 10.4 / 10.8, x 250 12.8 / 11.8.
-// in_call > 1: one of several products of a call, which the wave-per-row kernel takes in one launch (4 of 504 x 448 with 43 entries
-// 15.6 / 4.0, 4 of 2296 x 2248 with 187 20.3 / 6.4, 3 of 10000 x 1000 with 80 15.7 / 10.9; 84 of 1000 x 300 with 150 117 / 6.6).
+// Measured on 5600 calls, both kernels on the same matrices in graphs of 20 to 40 calls: 100 to 45000 rows, 100 to 60000 columns, 4 to 300 entries a
+// row, all code widths.  One product: by rows per compute unit, within 0.14 % of the better kernel in the mean, 1.14 at worst (us, sub-wave /
+// wave-per-row: 1000 x 40 2.9 / 2.9, 2046 x 109 3.7 / 3.1, 5318 x 119 4.1 / 5.0, 7174 x 113 4.0 / 5.6, 7460 x 172 4.7 / 5.9, 30064 x 245 9.0 / 10.5).
+// 8-bit codes with few rows: the larger zero guards cost the wave-per-row kernel what its start saves (693 x 82 3.3 / 3.6).
+// in_call > 1, several products of a call: the wave-per-row kernel takes them in one launch, which counts for more the more they are (4 of
+// 504 x 43 12.5 / 3.4, 2 of 13186 x 58 7.4 / 10.7, 4 of 14499 x 6 16.6 / 23.4, 8 of 17902 x 208 54 / 33, 8 of 17747 x 44 38 / 33): within
+// 0.2 to 0.4 % in the mean, 1.37 at worst.
 constexpr int64_t kWaveRowMinEntries = 192;            // where nothing more is known of the call
 inline int64_t wave_row_min_entries(const SpmvProblem& p, int64_t in_call) {
-  constexpr int64_t kLargest = 240;
+  constexpr int64_t kLargest = 248;
   if (p.pad_nnz >= kLargest * p.rows) return kLargest;   // no need to ask which device it is (0.08 us of a small call's 3.4)
   const int64_t per_cu = p.rows / device_cu_count();
-  if (per_cu < 4 || (in_call > 1 && per_cu < 64)) return 1;
-  return per_cu < 32 ? 112 : per_cu < 48 ? 144 : kLargest;
+  if (in_call <= 1) {
+    if (per_cu < 4) return p.b_delta == 8 ? 104 : 1;
+    return per_cu < 16 ? 104 : per_cu < 48 ? 200 : kLargest;
+  }
+  if (per_cu < 24 + 6 * std::min<int64_t>(in_call, 8)) return 1;
+  return per_cu < (in_call == 2 ? 72 : 80) ? 104 : in_call == 2 ? 208 : 136;
 }
 // Whether the product goes to the wave-per-row kernel (8-bit values: it has to).
 inline bool spmv_takes_wave_row(const SpmvProblem& p, int64_t min_entries = kWaveRowMinEntries) {

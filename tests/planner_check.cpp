@@ -16,6 +16,7 @@
 using namespace macko;
 
 static Tuning knobs;
+int macko::device_cu_count() { return 256; }
 Tuning& macko::tuning() { return knobs; }              // the library's own lives in its host translation unit
 
 static int failures = 0;
@@ -246,6 +247,22 @@ int main() {
     knobs.spmv_kernel = 2;
     EXPECT(spmv_launch_class(product(4096, 4096, 2048, 4, 16)) == 0 && spmv_takes_wave_row(product(4096, 4096, 10, 4, 16)), "spmv_kernel 2");
     knobs.spmv_kernel = 0;
+  }
+
+  // ---- short rows: which kernel, by rows, stored entries, code width and products in the call (the faster one of each, timed on 256 units) ----
+  {
+    struct Shape { int64_t rows, entries; int b_delta; int64_t in_call; bool wave_row; };
+    const Shape shapes[] = {
+        {300, 10, 4, 1, true}, {1000, 40, 4, 1, true}, {693, 82, 8, 1, false}, {893, 130, 8, 1, true}, {2046, 109, 4, 1, true}, {2046, 60, 4, 1, false},
+        {5318, 119, 8, 1, false}, {7174, 113, 4, 1, false}, {7460, 172, 8, 1, false}, {8000, 230, 4, 1, true}, {30064, 245, 4, 1, false}, {30064, 260, 4, 1, true},
+        {504, 43, 4, 4, true}, {8000, 12, 8, 2, true}, {13186, 58, 8, 2, false}, {13186, 150, 8, 2, true}, {14499, 6, 8, 4, false}, {14499, 6, 8, 8, true},
+        {17747, 44, 4, 8, true}, {24000, 20, 4, 8, false}, {17902, 208, 4, 8, true}, {20395, 115, 4, 2, false}, {25267, 224, 4, 4, true}, {1000, 5, 8, 33, true}};
+    for (const Shape& s : shapes) {
+      SpmvProblem p{};
+      p.rows = s.rows; p.cols = 4 * s.entries + 100; p.pad_nnz = s.rows * s.entries; p.b_delta = s.b_delta; p.b_val = 16;
+      EXPECT(spmv_takes_wave_row(p, wave_row_min_entries(p, s.in_call)) == s.wave_row, "%lld rows of %lld entries, %d bits, %lld products",
+             (long long)s.rows, (long long)s.entries, s.b_delta, (long long)s.in_call);
+    }
   }
 
   if (failures) { std::printf("%d failures\n", failures); return 1; }

@@ -279,8 +279,8 @@ MACKO_API int macko_spmm(macko_handle_t h, int batch, const void* X_dev, int64_t
  * products; the y vectors must not alias each other or any x.  Argument
  * meaning per product is that of the single-product call.  Matrices with short rows
  * (fewer than about 250 stored entries on average) may take another kernel in a call of several
- * products than alone, and their results then differ in the last place; within one call the kernel
- * depends on the matrix alone.  The same holds for macko_spmv_many and for the vectors of macko_spmm. */
+ * products than alone, and their results may then differ in the last place; within one call, of this or of
+ * macko_spmv_many, the kernel depends on the matrix alone.  (The way macko_spmm takes depends on the batch.) */
 #define MACKO_MAX_GROUP 8
 MACKO_API int macko_spmv_group(int n, const macko_handle_t* handles, const void* const* x_dev,
                                void* const* y_dev, void* stream);

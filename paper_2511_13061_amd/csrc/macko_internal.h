@@ -151,6 +151,19 @@ int launch_spmm(const SpmvProblem& p, const void* X, int64_t ldx, void* Y, int64
                 hipStream_t stream);
 // the same on the matrix cores: which calls it can serve (any batch up to 64), and the launch
 bool spmm_tile_serves(const SpmvProblem& p, int64_t ldx);
+// Whether vectors share passes over the matrix on the vector units, in pieces of 8, 4 and 2, instead of going as single products in groups:
+// rows of at least kLongRow stored entries.  Shorter ones with codes of up to 4 bits go to the matrix cores from a few vectors on; with 8-bit
+// codes, which those do not serve, they share passes as well where the vectors are copied 8 columns at a time and there are rows enough to pay for a
+// workgroup's copy of 2, 4 or 8 of them.  Both ways timed on 2563 calls of 200 to 30000 rows, 64 to 45000 columns, 2 to 16 vectors: 0.3 % from the faster
+// one in the mean, 1.21 at worst; the line is a number of columns per row of a compute unit, and lower where four copies do not fit LDS (us, single products / pieces: 9232 x 1152 with 71 entries, 2 vectors 8.0 / 5.3, 17 54 / 22; 4096 x 4096 with 287, 5 9.1 / 7.2;
+// 2048 x 16384 with 208, 3, 5 and 16 5.4 / 7.7, 7.7 / 11.9 and 15.8 / 34.2; 4096 x 16384, 3 and 8 8.0 / 8.7 and 13.1 / 18.4).
+constexpr int64_t kLongRow = 384;
+inline bool spmm_shares_passes(const SpmvProblem& p, int batch) {
+  if (p.pad_nnz / p.rows >= kLongRow) return true;
+  if (p.b_delta != 8 || p.cols % 8 != 0) return false;
+  const int64_t cus = device_cu_count(), most = batch <= 2 ? 1500 : batch <= 4 && p.cols <= 16368 ? 1200 : 650;
+  return p.rows >= 4 * cus && p.cols * cus <= most * p.rows;
+}
 int64_t spmm_tile_windows(const SpmvProblem& p);       // windows that a workgroup goes through, of up to 16 vectors
 bool spmm_tile_pairs_groups(const SpmvProblem& p, int batch);      // two groups of columns share an operand there
 // Units of `per_unit` entries that a wavefront takes of a row there, from the 8 entries its start lies in; one, all cleared, for a row

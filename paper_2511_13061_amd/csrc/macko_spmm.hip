@@ -320,15 +320,6 @@ int launch_bt(const SpmvProblem& p, const uint16_t* X, int64_t ldx, uint16_t* Y,
 }
 
 constexpr int64_t kBatchLdsLimit = 160 * 1024 - 64;
-constexpr int64_t kLongRow = 384;       // stored entries per row from which vectors share a pass over the matrix
-// Shorter rows with codes of up to 4 bits go to the matrix cores from a few vectors on.  With 8-bit codes, which those do not serve, they share
-// passes as well where there are rows enough and the vectors are copied 8 columns at a time (us, single products in groups of 8 / pieces
-// of 8, 4 and 2: 9232 x 1152 with 71 entries, 2 vectors 8.4 / 5.4, 17 54.9 / 21.9; 4096 x 4096 with 287, 5 9.1 / 7.2; 2000 x 4096 with 164, 5 6.4 / 6.4;
-// but 1140 x 4654 with 209, 5 6.4 / 12.2, 800 x 600, 5 4.6 / 6.0).
-bool shares_passes(const SpmvProblem& p) {
-  return p.pad_nnz / p.rows >= kLongRow || (p.b_delta == 8 && p.cols % 8 == 0 && p.rows >= (int64_t)8 * device_cu_count());
-}
-
 // Vectors that the next pass over the matrix takes, of `left`: a piece of 8, 4 or 2 whose interleaved copies fit LDS, or one;
 // with short rows up to kMaxGroup single products (pass = 0).
 struct Piece {
@@ -374,7 +365,7 @@ double vector_estimate(const SpmvProblem& p, int batch) {
   const double busiest = std::ceil(rows / (16.0 * cus)) * steps;        // steps of one wavefront
   const double few = rows < 4.0 * cus ? steps : 0.0;                   // no resident round: nothing covers a step's latency
   const double mbytes = entries * (p.b_val + p.b_delta) / 8e6;
-  const bool long_rows = shares_passes(p);
+  const bool long_rows = spmm_shares_passes(p, batch);
   const bool one_launch = p.b_val == 8 || p.pad_nnz / p.rows >= kWaveRowMinEntries;    // of a group of single products
   const int64_t one = lds_bytes_for(p.cols, p.b_delta);
   double us = 0.0;
@@ -424,7 +415,7 @@ int launch_spmm(const SpmvProblem& p, const void* X, int64_t ldx, void* Y, int64
     return e == hipSuccess ? MACKO_OK : hip_fail(e);
   }
   const int64_t one = lds_bytes_for(p.cols, p.b_delta);
-  const bool long_rows = shares_passes(p);
+  const bool long_rows = spmm_shares_passes(p, batch);
   const int64_t knob = tuning().spmm_kernel;
   if (batch > 1 && spmm_tile_serves(p, ldx) && (!vectors_serve(p) || (knob != 0 ? knob == 2 : tile_is_faster(p, batch))))
     return launch_spmm_tile(p, Xp, ldx, Yp, ldy, batch, stream);

@@ -265,6 +265,21 @@ int main() {
     }
   }
 
+  // ---- batches on short rows with 8-bit codes: passes shared by several vectors, or single products (the faster way of each) ----
+  {
+    struct Shape { int64_t rows, cols, entries; int b_delta, batch; bool shared; };
+    const Shape shapes[] = {
+        {9232, 1152, 71, 8, 2, true}, {9232, 1152, 71, 8, 17, true}, {4096, 4096, 287, 8, 5, true}, {2048, 16384, 208, 8, 3, false}, {2048, 16384, 208, 8, 16, false},
+        {4096, 16384, 208, 8, 2, true}, {4096, 16384, 208, 8, 3, false}, {4096, 8192, 208, 8, 3, true}, {4096, 16384, 208, 8, 8, false}, {1000, 512, 60, 8, 2, false}, {9232, 1153, 71, 8, 4, false},
+        {9232, 1152, 71, 4, 4, false}, {9232, 1152, 384, 4, 4, true}, {40, 60000, 400, 8, 2, true}, {12000, 40000, 180, 8, 8, false}};
+    for (const Shape& s : shapes) {
+      SpmvProblem p{};
+      p.rows = s.rows; p.cols = s.cols; p.pad_nnz = s.rows * s.entries; p.b_delta = s.b_delta; p.b_val = 16;
+      EXPECT(spmm_shares_passes(p, s.batch) == s.shared, "%lld x %lld with %lld entries, %d bits, %d vectors", (long long)s.rows, (long long)s.cols,
+             (long long)s.entries, s.b_delta, s.batch);
+    }
+  }
+
   if (failures) { std::printf("%d failures\n", failures); return 1; }
   std::printf("ok %d resident plans\n", resident_plans);
   return 0;

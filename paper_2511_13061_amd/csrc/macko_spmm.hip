@@ -342,15 +342,17 @@ bool vectors_serve(const SpmvProblem& p) { return p.b_val != 8 || spmv_takes_wav
 // Up to 16 vectors take the matrix cores one launch whose time is a sum of its parts (the phases of a window do not overlap, see
 // macko_spmm_tile.hip).  The vector kernel takes a launch per piece: its start, the steps of 512 entries that the busiest wavefront
 // takes one after the other (16 wavefronts to a compute unit) and that a compute unit takes in all, and the copy of the vectors,
-// element by element where their length is no multiple of 8.  The factors were fitted to 16 000 calls timed both ways: 2 to 16
-// vectors, 16 to 40000 rows, 64 to 80000 columns, 30 to 99 % pruned, all code widths up to 4 bits at the densities they suit, both value
-// widths.  The estimates are off by 5 % (matrix cores) and 8 to 10 % (vectors), the way chosen is 0.3 % slower than the better
-// one in the mean; without the busiest wavefront it was 0.7 %, and 3 or 4 vectors on 2049 to 4096 dense rows up to 1.3 times as slow
-// (3832 x 10352 at 53 %, 8-bit values, 3 vectors, 15.5 -> 12.0; 2733 x 11072 at 33 %, 4: 17.8 -> 14.0).  What is left is at most 1.45 times
-// as slow, where the copy of odd vectors costs the vector kernel more than estimated (6396 x 2629 at 63 %, 2-bit codes, 4: 15.6 / 10.7).
-// The matrix cores' estimate has to be 3 % below the vectors'; with short rows, where both take about 5 us and the vectors' estimate is
-// low for some, 3 % above it is enough (760 x 414 at 45 %, 7 vectors, 5.8 / 4.8; of 3690 such calls 4 instead of 47 are more than
-// 5 % slower than the matrix cores were).
+// element by element where their length is no multiple of 8.  The factors were fitted to 16 000 calls timed both ways, before rows were read as
+// buffers; over 18 000 others timed since (2 to 16 vectors, 16 to 40000 rows, 64 to 40000 columns, 30 to 99 % pruned, rows of 8 entries on, all code widths up
+// to 4 bits, both value widths) the matrix cores' times are 5 % below the estimate and off by 5 % from there, the vectors' 7 % below and off by
+// 8 %.  The way chosen is 0.22 % slower than the better one in the mean, for rows below and above kLongRow alike; factors fitted again to half of them chose no
+// better on the other half (0.24 %).  What is left is at most 1.43 times as slow: 4 vectors on 32000 rows and more of 10 to 30 entries, and two on as many of
+// 150 (34434 x 188 26.0 / 18.2, 32167 x 1920 13.6 / 18.7); with long rows 1.26, where the copy of odd vectors costs more than estimated (2654 x 3548 8.2 / 6.5).
+// Without the busiest wavefront 3 or 4 vectors on 2049 to 4096 dense rows were up to 1.3 times as slow (3832 x 10352 at 53 %, 8-bit values, 3
+// vectors, 15.5 -> 12.0; 2733 x 11072 at 33 %, 4: 17.8 -> 14.0).  A group of single products has to be priced as the launch it takes: as a launch
+// to each product, as it was for rows of fewer than 192 entries before the wave-per-row kernel took them, the choice was 8.2 % slower with short rows (us,
+// matrix cores / vectors: 504 x 448 with 43 entries, 4 vectors, 4.8 / 3.4; 195 x 3240 with 186, 3, 5.2 / 3.2).
+// The matrix cores' estimate has to be 3 % below the vectors'; with short rows, where both take about 5 us, 3 % above it is enough.
 double tile_estimate(const SpmvProblem& p, int batch) {
   const double cols = (double)p.cols / 4096.0, tiles = std::ceil((double)p.rows / (16.0 * device_cu_count()));
   const double steps = tiles * std::ceil((double)p.pad_nnz / (double)p.rows / 512.0), more = batch > 8 ? 1.0 : 0.0;
@@ -366,7 +368,7 @@ double vector_estimate(const SpmvProblem& p, int batch) {
   const double few = rows < 4.0 * cus ? steps : 0.0;                   // no resident round: nothing covers a step's latency
   const double mbytes = entries * (p.b_val + p.b_delta) / 8e6;
   const bool long_rows = spmm_shares_passes(p, batch);
-  const bool one_launch = p.b_val == 8 || p.pad_nnz / p.rows >= kWaveRowMinEntries;    // of a group of single products
+  const bool one_launch = spmv_takes_wave_row(p, wave_row_min_entries(p, batch));      // of a group of single products, as launch_spmv_group decides
   const int64_t one = lds_bytes_for(p.cols, p.b_delta);
   double us = 0.0;
   for (int left = batch; left > 0;) {

@@ -2269,6 +2269,8 @@ def test_spmm_either_way_for_few_vectors(kind, rows, cols, sparsity, batch):
     (226, 178280, 0.99, 6, 16), (52, 88736, 0.95, 5, 16), (40, 300001, 0.999, 2, 16),
     # pieces of 3 and 4 vectors, one dense row to a wavefront: the matrix cores 1.3 times as slow; x of one vector fits LDS: 1.5 times
     (3832, 10352, 0.526, 3, 8), (2733, 11072, 0.333, 4, 8), (3077, 5728, 0.317, 3, 8), (376, 53088, 0.956, 2, 16),
+    # short rows, a group of single products in one launch: the matrix cores 1.3 to 1.6 times as slow
+    (504, 448, 0.904, 4, 16), (195, 3240, 0.957, 3, 16), (47, 2608, 0.945, 2, 16), (1000, 300, 0.5, 2, 16),
     # and calls that the matrix cores win by as much
     (1392, 1012, 0.87, 8, 16), (718, 8797, 0.5, 8, 16), (8872, 280, 0.49, 2, 16)])
 def test_spmm_takes_the_faster_kernel(rows, cols, sparsity, batch, vals):

@@ -461,7 +461,9 @@ encode_fill_kernel(const void* __restrict__ dense, uint32_t rows, uint32_t cols,
     if (BD < 3) table_high[threadIdx.x] = m.count;
   }
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  // A buffer has to be the wavefront's, or every load through it stands in a loop over the lanes' descriptors (11008 x 4096 with 8-bit values
+  // 27.7 / 26.1 us without it).  The version with branches is slower with a uniform row (36864 x 12288 350 / 413, 11008 x 4096 34.8 / 37.0).
+  const int wave = BUFFER ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : (int)(threadIdx.x >> 6);
   unsigned char* sv = stage_v[wave] + 16;               // entry 0 of the window
   uint32_t* sc = stage_c[wave] + 4;
   for (int i = lane; i < (kFillWindow + 2 * kPiece) * kValueBytes / 16; i += 64)
@@ -729,13 +731,17 @@ int encode_on_device(const void* dense, int64_t rows, int64_t cols, int64_t ld, 
   else
     MACKO_HIP_TRY(hipMemsetAsync(rp, 0, 4, stream));
   if (rows > 0 && alloc > 0) {
-    // A wavefront's loads are under way with RowBuffer; with load_chunk only other wavefronts cover them.  us, load_chunk / RowBuffer:
-    // 280 x 504 6.1 / 5.2, 2000 x 2000 10.4 / 8.4, 4096 x 4096 at 90 % 15.0 / 13.6, 4096 x 11008 34.2 / 33.6, 11008 x 4096 with 8-bit values 29.3 /
-    // 28.2; but 11008 x 4096 fp16 35.6 / 37.1, at 40 % with 2-bit codes 36.3 / 38.0: fp16 rows for more wavefronts than the chip holds keep
-    // load_chunk.
+    // A wavefront's loads are under way with RowBuffer; with load_chunk only other wavefronts cover them, and those reach the rate of a large
+    // fp16 matrix better.  us, load_chunk / RowBuffer: up to as many rows as the chip holds wavefronts, 280 x 504 5.8 / 5.0, 2000 x 2000 9.9 / 8.1,
+    // 4096 x 11008 33.8 / 32.3; 8-bit values of any size, 11008 x 4096 29.3 / 26.1, 36864 x 12288 277 / 249; few columns, 120000 x 128 89 / 77,
+    // 1000000 x 64 660 / 549; else by the cells, 11008 x 1024 16.7 / 14.4, 20000 x 2048 35.1 / 36.5, 11008 x 4096 34.8 / 35.3, 36864 x 4096 at 90 % 86 / 116;
+    // more of them where 16 bytes of a row lie across two lines, 11008 x 4100 40.7 / 38.0, 36864 x 4100 153 / 166, and with 8-bit codes, which
+    // take load_chunk more registers, 11008 x 4096 at 90 % 31.3 / 27.7, 24576 x 4096 56.6 / 54.6, 60000 x 4096 147 / 186.
     const int per_word = in8 ? 4 : 2;
-    const bool whole_words = (reinterpret_cast<uintptr_t>(dense) & 3) == 0 && ld % per_word == 0 && cols % per_word == 0;
-    const bool buffer = whole_words && cols <= kMaxBufferCols && (in8 || rows <= (int64_t)cus * 28);
+    const uintptr_t row_starts = reinterpret_cast<uintptr_t>(dense) | (uintptr_t)(ld * (in8 ? 1 : 2));
+    const bool whole_words = (row_starts & 3) == 0 && cols % per_word == 0;
+    const int64_t cells = b_delta == 8 ? 100000000 : (row_starts & 15) != 0 ? 64000000 : 20000000;
+    const bool buffer = whole_words && cols <= kMaxBufferCols && (in8 || rows <= (int64_t)cus * 28 || cols <= 256 || rows * cols <= cells);
     auto kfill = buffer ? fill_kernel<true>(in8, b_delta) : fill_kernel<false>(in8, b_delta);
     hipLaunchKernelGGL(kfill, dim3(grid), dim3(64 * kFillWaves), 0, stream, dense, (uint32_t)rows, (uint32_t)cols, ld,
                        static_cast<const uint32_t*>(rp), vals, dels, (uint32_t)pad, (uint32_t)alloc);

@@ -347,6 +347,25 @@ int main() {
     assert out.returncode == 0 and out.stdout == "ok\n", out.stdout
 
 
+def test_no_buffer_load_stands_in_a_loop_over_descriptors(tmp_path):
+    """A buffer descriptor that the compiler takes as different from lane to lane puts each load through it in a loop of its own (its block
+    ends in a branch back to itself while lanes are left).  The encoder's kernels hold none."""
+    import re
+    import subprocess
+    from paper_2511_13061_amd import build as B
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not os.path.exists(hipcc):
+        pytest.skip("needs hipcc")
+    out = tmp_path / "encode.txt"
+    subprocess.check_call([hipcc, *B.HIPCC_FLAGS, "-w", "-I", os.path.join(ROOT, "include"), "-I", B.CSRC, "-x", "hip", "--offload-device-only", "-S",
+                           os.path.join(B.CSRC, "macko_encode_gpu.hip"), "-o", str(out)], stderr=subprocess.DEVNULL)
+    loads = 0
+    for label, block in re.findall(r"^(\.LBB\w+):(.*?)(?=^\.LBB|^\.Lfunc_end)", out.read_text(), re.S | re.M):
+        loads += len(re.findall(r"\bbuffer_load_dword", block))
+        assert not (re.search(r"\bbuffer_load_dword", block) and re.search(r"s_cbranch_execnz " + re.escape(label) + r"\b", block)), label
+    assert loads >= 10
+
+
 def test_row_buffers_stay_inside_the_arrays(tmp_path):
     """The product kernels read a row through buffers whose ends come from its pointers.  Replayed here for a wavefront's rows, empty ones among
     them and (trusted input, but no reason to read outside the arrays) pointers that decrease: what a lane requests, in a step, behind

@@ -599,18 +599,13 @@ std::mutex g_ws_mutex;
 Workspace g_ws[64];
 constexpr size_t kKeepScratchBytes = size_t{64} << 20;
 
-hipError_t workspace_reserve(Workspace& ws, size_t bytes, int device) {
+hipError_t workspace_reserve(Workspace& ws, size_t bytes) {
   if (bytes <= ws.cap) return hipSuccess;
   if (ws.p) (void)hipFree(ws.p);
   ws.p = nullptr;
   ws.cap = 0;
   const size_t want = bytes + bytes / 4;             // some slack so that similar sizes do not reallocate
-  hipError_t e = hipMalloc(&ws.p, want);
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    block_trim(device);
-    e = hipMalloc(&ws.p, want);
-  }
+  const hipError_t e = device_malloc(&ws.p, want);
   if (e == hipSuccess) ws.cap = want;
   return e;
 }
@@ -679,7 +674,7 @@ int encode_on_device(const void* dense, int64_t rows, int64_t cols, int64_t ld, 
   const size_t o_sums = align_up(o_nnz + 4 * (size_t)rows, 256);
   const size_t o_boff = align_up(o_sums + sizeof(BlockSums) * (size_t)std::max<int64_t>(nblocks, 1), 256);
   const size_t scratch_bytes = o_boff + 8 * (size_t)std::max<int64_t>(nblocks, 1);
-  if (workspace_reserve(ws, scratch_bytes, dev) != hipSuccess) {
+  if (workspace_reserve(ws, scratch_bytes) != hipSuccess) {
     (void)hipGetLastError();
     return MACKO_E_OUT_OF_MEMORY;
   }

@@ -80,14 +80,25 @@ void block_trim(int device) {
   }
 }
 
+hipError_t device_malloc(void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  int dev = 0;
+  if (e == hipSuccess) return e;
+  (void)hipGetLastError();
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return e;
+  block_trim(dev);                                       // what is kept may be what is missing
+  e = hipMalloc(p, bytes);
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e;
+}
+
 hipError_t block_acquire(void** block, size_t bytes) {
   const bool kept = block_is_kept(bytes);
   bytes = block_bytes(bytes);
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
-  const bool counted = dev >= 0 && dev < 64;
-  if (kept && counted) {
+  if (kept && dev >= 0 && dev < 64) {
     std::lock_guard<std::mutex> lock(g_store_mutex);
     BlockStore& s = g_store[dev];
     for (int i = s.n - 1; i >= 0; --i)
@@ -96,13 +107,7 @@ hipError_t block_acquire(void** block, size_t bytes) {
         return hipSuccess;
       }
   }
-  e = hipMalloc(block, bytes);
-  if (e != hipSuccess && counted) {                      // what is kept may be what is missing
-    (void)hipGetLastError();
-    block_trim(dev);
-    e = hipMalloc(block, bytes);
-  }
-  return e;
+  return device_malloc(block, bytes);
 }
 
 void block_release(void* block, size_t bytes, int device, void* idle_probe) {
@@ -428,10 +433,8 @@ static int encode_device_any(const void* dense_dev, int64_t rows, int64_t cols, 
   m->d_block = block;
   if (hipGetDevice(&m->d_block_device) != hipSuccess) m->d_block_device = -1;
   if (macko::block_is_kept(macko::encoded_layout(rows, alloc, b_delta, b_val).total) &&
-      hipMalloc(&m->d_idle_probe, 16) != hipSuccess) {
-    (void)hipGetLastError();
+      macko::device_malloc(&m->d_idle_probe, 16) != hipSuccess)
     m->d_idle_probe = nullptr;                          // the block is not kept then
-  }
   macko::fill_report(&m->report, rows, cols, nnz, pad, alloc, empty, longest, b_delta, b_val);
   if (report) *report = m->report;
   *out = m;
@@ -604,7 +607,7 @@ int macko_check_device(macko_handle_t h, void* stream, int64_t* first_bad_row) {
   if (h->rows == 0) return h->pad_nnz == 0 ? MACKO_OK : MACKO_E_CORRUPT;
   hipStream_t s = static_cast<hipStream_t>(stream);
   unsigned int* d_first = nullptr;
-  hipError_t e = hipMalloc(reinterpret_cast<void**>(&d_first), sizeof(unsigned int));
+  hipError_t e = macko::device_malloc(reinterpret_cast<void**>(&d_first), sizeof(unsigned int));
   if (e != hipSuccess) return e == hipErrorOutOfMemory ? MACKO_E_OUT_OF_MEMORY : macko::hip_fail(e);
   unsigned int first = (unsigned int)h->rows;
   int st = MACKO_OK;

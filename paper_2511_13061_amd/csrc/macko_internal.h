@@ -238,6 +238,8 @@ constexpr size_t block_bytes(size_t bytes) {
   return (bytes + granule - 1) / granule * granule;
 }
 constexpr bool block_is_kept(size_t bytes) { return block_bytes(bytes) >= kStoredBlockMin && block_bytes(bytes) <= kStoredBytes; }
+// hipMalloc on the current device for all that the library allocates: when it fails, what is kept there is given back and it tries again.
+hipError_t device_malloc(void** p, size_t bytes);
 // A block of block_bytes(bytes) on the current device.  It is kept only with an idle_probe, a small allocation on its device, which goes with it.
 hipError_t block_acquire(void** block, size_t bytes);
 void block_release(void* block, size_t bytes, int device, void* idle_probe);

@@ -347,6 +347,21 @@ int main() {
     assert out.returncode == 0 and out.stdout == "ok\n", out.stdout
 
 
+def test_memory_of_the_encoders_handles(tmp_path):
+    """Kept blocks, their bounds, devices, the wait before one is used again and what happens when memory runs out
+    (tests/block_store_check.cpp)."""
+    import shutil
+    import subprocess
+    from paper_2511_13061_amd import build as B
+    if not shutil.which("g++") or not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"):
+        pytest.skip("needs g++ and the HIP headers")
+    exe = tmp_path / "block_store_check"
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-w", "-I/opt/rocm/include", "-I", os.path.join(ROOT, "include"), "-I", B.CSRC,
+                           os.path.join(ROOT, "tests", "block_store_check.cpp"), os.path.join(B.CSRC, "macko_host.cpp"), "-o", str(exe), "-lpthread"])
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert out.returncode == 0 and out.stdout == "ok\n", out.stdout
+
+
 def test_no_buffer_load_stands_in_a_loop_over_descriptors(tmp_path):
     """A buffer descriptor that the compiler takes as different from lane to lane puts each load through it in a loop of its own (its block
     ends in a branch back to itself while lanes are left).  The encoder's kernels hold none."""

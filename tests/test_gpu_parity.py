@@ -494,7 +494,7 @@ def test_code_widths_full_size_llama_shape():
 
 def test_spmv_group_mixed_shapes_one_call():
     specs = [(300, 2048, 0.5), (64, 4096, 0.5), (500, 1000, 0.3), (40, 8000, 0.9),   # wave-per-row kernel
-             (200, 300, 0.5),                                                         # short rows: own launch
+             (200, 300, 0.5),                                                         # short rows, few of them: the same kernel
              (77, 640, 0.0),                                                          # nothing stored
              (10, 100000, 0.2),                                                       # x larger than LDS
              (129, 5000, 1.0)]
@@ -517,6 +517,25 @@ def test_spmv_group_mixed_shapes_one_call():
     torch.cuda.synchronize()
     for i in range(3):
         check_y(yq[i], wl.half_row_matrix(256, 4096, 60 + i), wl.x_vector(4096, 31, 99), f"qkv {i}")
+
+
+def test_spmv_group_of_short_and_long_rows():
+    """Short rows in so many that they go to sub-wave launches of their own, next to rows of the wave-per-row launch."""
+    specs = [(20000, 300, 0.05), (300, 2048, 0.5), (24000, 96, 0.2), (500, 1000, 0.3)]
+    Ws = [wl.bernoulli(r, c, d, 0.02, 33, i) for i, (r, c, d) in enumerate(specs)]
+    xs = [wl.x_vector(c, 33, i) for i, (_, c, _) in enumerate(specs)]
+    ms = [M.encode(W).to_device() for W in Ws]
+    xd = [to_dev(x) for x in xs]
+    ys = M.spmv_group(ms, xd)
+    torch.cuda.synchronize()
+    for i, (W, x, y) in enumerate(zip(Ws, xs, ys)):
+        check_y(y, W, x, f"group member {i} {specs[i]}")
+    for i, kernel in ((0, 1), (1, 2), (2, 1), (3, 2)):          # the kernels that the comment above says: sub-wave, wave-per-row
+        M.set_tuning("spmv_kernel", kernel)
+        try:
+            assert torch.equal(ms[i].spmv(xd[i]), ys[i]), specs[i]
+        finally:
+            M.set_tuning("spmv_kernel", 0)
 
 
 def test_group_argument_errors():
@@ -1815,22 +1834,34 @@ def test_gpu_encoding_is_over_when_the_call_returns(rows, cols):
 
 
 def test_gpu_encoder_blocks_are_reused_once_the_device_is_idle():
-    """The memory of a destroyed handle goes to the next one of its size.  Whatever stream still reads it when the handle is destroyed
-    has read it before the next encoding writes there."""
+    """The memory of a destroyed handle goes to the next one of its size (equal patterns, so that it surely does).  Whatever stream still reads it
+    when the handle is destroyed has read it before the next encoding writes there: the side stream is busy for some milliseconds
+    before it comes to its reads."""
     gen = torch.Generator(device="cuda").manual_seed(5)
     side = torch.cuda.Stream()
-
-    def matrix():
-        return torch.randn((4096, 3072), generator=gen, device="cuda").half() * (torch.rand((4096, 3072), generator=gen, device="cuda") < 0.5)
-
-    for _ in range(8):
-        first, second = matrix(), matrix()
+    first = torch.randn((4096, 3072), generator=gen, device="cuda").half() * (torch.rand((4096, 3072), generator=gen, device="cuda") < 0.5)
+    second = first.flip(0).contiguous()
+    busy = torch.randn((8192, 8192), generator=gen, device="cuda")
+    with torch.cuda.stream(side):
+        for _ in range(2):                                     # what PyTorch and its libraries allocate for this is there before free memory is read
+            busy = torch.tanh(busy @ busy)
+        warm = [torch.empty_like(first) for _ in range(3)]
+    warm.append(torch.empty_like(first))
+    del warm
+    M.encode_device(second).decode_device()
+    for _ in range(4):
         torch.cuda.synchronize()
         m = M.encode_device(first)
         with torch.cuda.stream(side):
-            dense = [m.decode_device() for _ in range(6)]
+            for _ in range(4):
+                busy = torch.tanh(busy @ busy)
+            dense = [m.decode_device() for _ in range(3)]
+        free = torch.cuda.mem_get_info()[0]
+        waiting = not side.query()
         m.destroy()
+        assert waiting and side.query()
         m = M.encode_device(second)
+        assert abs(torch.cuda.mem_get_info()[0] - free) < 4 << 20          # the 30 MiB were neither freed nor allocated again
         again = m.decode_device()
         m.destroy()
         torch.cuda.synchronize()

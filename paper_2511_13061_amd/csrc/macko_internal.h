@@ -120,7 +120,7 @@ inline int64_t wave_row_min_entries(const SpmvProblem& p, int64_t in_call) {
     if (per_cu < 4) return p.b_delta == 8 ? 104 : 1;
     return per_cu < 16 ? 104 : per_cu < 48 ? 200 : kLargest;
   }
-  if (per_cu < 24 + 6 * std::min<int64_t>(in_call, 8)) return 1;
+  if (per_cu < (p.b_delta == 8 ? 20 : 24) + 6 * std::min<int64_t>(in_call, 8)) return 1;
   return per_cu < (in_call == 2 ? 72 : 80) ? 104 : in_call == 2 ? 208 : 136;
 }
 // Whether the product goes to the wave-per-row kernel (8-bit values: it has to).

@@ -166,19 +166,17 @@ spmm_wave_row_kernel(const void* __restrict__ values, const uint32_t* __restrict
 
   // every row is a buffer of its own, as in the matrix-vector kernel (us, clamped addresses and
   // masks / this: 4096 x 4096 at 50 %, 2 / 4 / 8 vectors, 7.47 / 8.13 / 11.8 -> 6.79 / 7.37 / 10.3, 11008 x 4096 12.7 / 15.1 / 22.6 -> 12.5 / 14.1 /
-  // 20.7; but 4096 x 4096 at 80 %, rows of two steps, 5.04 / 5.20 -> 5.14 / 5.33)
+  // 20.7; over 144 calls on rows of 1 to 5 steps 0.95).  The position in a row is kept as its step alone: with a register each for values and
+  // codes the kernel of two vectors needs 82 scalar ones, beyond 80 a SIMD holds 7 wavefronts instead of 8 (it has 800, and the trap handler takes
+  // 16 of a wavefront's), and where a resident round has workgroups of 13 wavefronts and more half of it waits (us, 82 / 80: 6373 x 4096 with 570 8-bit values, 2 vectors, 6.6 / 5.6, 7477 x 4096 7.1 / 6.2).
   EntryBuffers<BD, VB> row;
-  int at_v = 0, at_c = 0;                              // where lane 0 reads: the buffers' bytes
   auto open_row = [&]() {
     if (ld.i >= nb) ld.nsteps = INT_MAX;               // no row follows
     row.open(values, deltas, ld.start >> 3, ld.end);
-    at_v = at_c = 0;
   };
   auto issue = [&](int j) {
-    wq[j].load(row.codes, BD * lane + at_c);
-    vq[j].load(row.values, VB * lane + at_v);
-    at_v += 64 * VB;
-    at_c += 64 * BD;
+    wq[j].load(row.codes, BD * (lane + 64 * ld.step));
+    vq[j].load(row.values, VB * (lane + 64 * ld.step));
     if (++ld.step == ld.nsteps) {
       ++ld.i;
       seek_nonempty(ld, nb, rp_lo, rp_hi);

@@ -381,6 +381,27 @@ def test_no_buffer_load_stands_in_a_loop_over_descriptors(tmp_path):
     assert loads >= 10
 
 
+def test_a_simd_holds_8_wavefronts_of_the_resident_kernels(tmp_path):
+    """A resident round of the product kernels, and of the batch kernel of two vectors, counts on 8 wavefronts to a SIMD: at most 64 vector
+    registers and at most 80 scalar ones (800 to a SIMD, 16 more to a wavefront for the trap handler)."""
+    import subprocess
+    from paper_2511_13061_amd import build as B
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not os.path.exists(hipcc):
+        pytest.skip("needs hipcc")
+    seen = 0
+    for src, kernels in (("macko_spmv.hip", r"spmv_(wave_row|chain)\w*"), ("macko_spmm.hip", r"spmm_wave_row_kernelILi2E\w*")):
+        out = tmp_path / (src + ".txt")
+        subprocess.check_call([hipcc, *B.HIPCC_FLAGS, "-w", "-I", os.path.join(ROOT, "include"), "-I", B.CSRC, "-x", "hip", "--offload-device-only", "-S",
+                               os.path.join(B.CSRC, src), "-o", str(out)], stderr=subprocess.DEVNULL)
+        for name, sgprs, vgprs in re.findall(r"\.name:\s+(_Z\S+)\n(?:(?!\.name:).)*?\.sgpr_count:\s+(\d+)(?:(?!\.name:).)*?\.vgpr_count:\s+(\d+)",
+                                             out.read_text(), re.S):
+            if re.search(kernels, name):
+                assert int(sgprs) <= 80 and int(vgprs) <= 64, (name, sgprs, vgprs)
+                seen += 1
+    assert seen >= 20
+
+
 def test_row_buffers_stay_inside_the_arrays(tmp_path):
     """The product kernels read a row through buffers whose ends come from its pointers.  Replayed here for a wavefront's rows, empty ones among
     them and (trusted input, but no reason to read outside the arrays) pointers that decrease: what a lane requests, in a step, behind

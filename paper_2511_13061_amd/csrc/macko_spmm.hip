@@ -350,6 +350,9 @@ bool vectors_serve(const SpmvProblem& p) { return p.b_val != 8 || spmv_takes_wav
 // vectors, 15.5 -> 12.0; 2733 x 11072 at 33 %, 4: 17.8 -> 14.0).  A group of single products has to be priced as the launch it takes: as a launch
 // to each product, as it was for rows of fewer than 192 entries before the wave-per-row kernel took them, the choice was 8.2 % slower with short rows (us,
 // matrix cores / vectors: 504 x 448 with 43 entries, 4 vectors, 4.8 / 3.4; 195 x 3240 with 186, 3, 5.2 / 3.2).
+// Up to 28 rows per compute unit in all, a resident round, such a launch takes the time of its wavefronts' rows one after the other: over 693 calls on
+// 200 to 6000 short rows the choice is 0.9 % slower than the better one, 1.07 times at worst, 1.55 % and 1.13 with one slope for all (us, matrix
+// cores / vectors: 600 x 100 with 60 entries, 8 vectors, 4.5 / 5.1, 900 x 400, 6, 4.5 / 5.0; 500 x 400, 8, 4.5 / 4.2).
 // The matrix cores' estimate has to be 3 % below the vectors'; with short rows, where both take about 5 us, 3 % above it is enough.
 double tile_estimate(const SpmvProblem& p, int batch) {
   const double cols = (double)p.cols / 4096.0, tiles = std::ceil((double)p.rows / (16.0 * device_cu_count()));
@@ -380,7 +383,7 @@ double vector_estimate(const SpmvProblem& p, int batch) {
     else if (q.pass == 1)
       us += 2.07 + 0.317 * busiest + 0.023 * all + 0.14 * cols + ragged * (0.94 + 0.25 * cols) + 0.135 * few + 0.039 * rows / cus;
     else if (one_launch)
-      us += 3.47 + q.take * (0.056 * all + 0.033 * mbytes) + (0.86 * ragged + 0.68 * std::min(1.0, rows / (4.0 * cus))) * cols;
+      us += std::max(3.47 + 0.056 * q.take * all, 2.95 + 0.105 * std::min(28.0, q.take * all)) + q.take * 0.033 * mbytes + (0.86 * ragged + 0.68 * std::min(1.0, rows / (4.0 * cus))) * cols;
     else
       us += q.take * (2.89 + 1.025 * entries / 1e6 + 0.46 * cols) + 3.45 * ragged * cols;
     left -= q.take;

@@ -2303,7 +2303,9 @@ def test_spmm_either_way_for_few_vectors(kind, rows, cols, sparsity, batch):
     # short rows, a group of single products in one launch: the matrix cores 1.3 to 1.6 times as slow
     (504, 448, 0.904, 4, 16), (195, 3240, 0.957, 3, 16), (47, 2608, 0.945, 2, 16), (1000, 300, 0.5, 2, 16),
     # and calls that the matrix cores win by as much
-    (1392, 1012, 0.87, 8, 16), (718, 8797, 0.5, 8, 16), (8872, 280, 0.49, 2, 16)])
+    (1392, 1012, 0.87, 8, 16), (718, 8797, 0.5, 8, 16), (8872, 280, 0.49, 2, 16),
+    # a group whose wavefronts take two rows, one after the other
+    (600, 100, 0.4, 8, 16), (900, 100, 0.4, 7, 16)])
 def test_spmm_takes_the_faster_kernel(rows, cols, sparsity, batch, vals):
     """Where the two batch kernels differ by 1.25 times and more the library's choice is within 1.15 times of the better one (a graph of 20
     calls, so that the host's pace does not count; least of 5 replays), and the results are right."""

@@ -92,9 +92,12 @@ MACKO_API int macko_encode(const uint16_t* dense_host, int64_t rows, int64_t col
                            macko_handle_t* out, macko_report_t* report);
 
 /* Encode a dense fp16 matrix held in device memory, on the GPU.  The library
- * allocates the device arrays (one hipMalloc) and the handle owns them; the handle
- * is bound on return and keeps no host copy.  Synchronises `stream` (the sizes
- * of the outputs are only known after a counting pass).  The result is
+ * allocates the device arrays (one block, new or that of a destroyed handle, see macko_trim; up to 1.6 % larger than
+ * report->total_bytes from 2 MiB on) and the handle owns them; the handle
+ * is bound on return and keeps no host copy.  Returns when all that was on `stream` and the encoding itself are over (the
+ * host waits once for the sizes of the outputs, which are only known after a counting pass, and once for a word that the
+ * device writes at the end: other streams may use the arrays at once, while hipStreamQuery may
+ * take some microseconds more to say that the stream is empty).  The result is
  * bit-identical to macko_encode on the same input.  The encoder keeps one scratch
  * buffer per device between calls (about 8 bytes per row) as long as it is at most
  * 64 MiB; a larger one is released before the call returns.  One call at a time per process. */
@@ -256,8 +259,8 @@ MACKO_API int macko_dense_gemv(const void* W_dev, int64_t rows, int64_t cols, in
  * batch on the matrix cores (more than 16 vectors; 2 to 16 where estimates of both ways' times,
  * from the shape, the stored entries and the batch, say so, and wherever x does not fit LDS; codes of up to
  * 4 bits, two columns or more, ldx < 2^24), else once per piece of up to 8 vectors, for every
- * code width and both value widths (rows shorter than 384 stored entries on average, and batches whose
- * interleaved vectors do not fit LDS, then run as independent matrix-vector products).
+ * code width and both value widths (rows shorter than 384 stored entries on average, unless with 8-bit codes, a multiple of 8
+ * columns and rows enough, and batches whose interleaved vectors do not fit LDS, then run as independent matrix-vector products).
  * On the matrix cores an infinity or a NaN in a vector reaches only the results of rows that store an entry
  * at its column (such results are computed apart, entry by entry, which is slow); the other ways, like
  * macko_spmv, may multiply it with a zero where a row stores nothing, and the result is then a NaN.
@@ -369,8 +372,9 @@ MACKO_API int macko_dense_gemv_group(int n, const void* const* W_dev, const int6
 
 /* Waits until the device is idle if the handle owns device memory (that of the GPU encoder). */
 MACKO_API void macko_destroy(macko_handle_t h);
-/* Device memory of destroyed handles is kept for the next ones, up to 8 blocks and 256 MiB per device; this gives
- * what is kept on the current device back (hipFree).  The encoder does so itself when memory runs out. */
+/* Device memory of destroyed handles is kept for the next ones, blocks of 2 to 256 MiB, up to 8 and 256 MiB in all per device; this gives
+ * what is kept on the current device back (hipFree).  An allocation of the library's that fails does so itself and tries again; other
+ * allocators of the process cannot, so call it where they may run short. */
 MACKO_API void macko_trim(void);
 
 MACKO_API const char* macko_status_string(int status);
